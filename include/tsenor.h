@@ -92,10 +92,9 @@ enum {
    * runs on the small tiles (below) iterates in double whatever this flag says: such a launch is bound by latency,
    * not by instruction issue, and single precision would buy nothing. */
   TSENOR_FLAG_FP32_ITERATIONS = 1u << 2,
-  /* Which kernel runs the greedy selection (Algorithm 2 lines 1-6).  Both give the same mask.  One takes
-   * one lane per block (fewest instructions: best when tens of thousands of blocks fill the chip), the other
-   * M lanes per block and decides M scan entries per step (shortest dependent chain: best for the small
-   * calls of a column-by-column pruning loop).  Default: chosen by the number of blocks in the launch.
+  /* Which kernel runs the greedy selection (Algorithm 2 lines 1-6) for M <= 8 on the large tiles.  Both give the same
+   * mask.  One takes one lane per block (the default: never slower), the other M lanes per block and decides M scan
+   * entries per step.  For M >= 16 the selection is part of the one rounding kernel and the flags change nothing.
    * Setting both is an error. */
   TSENOR_FLAG_GREEDY_ONE_LANE = 1u << 3,
   TSENOR_FLAG_GREEDY_M_LANES = 1u << 4,
@@ -171,8 +170,8 @@ enum { TSENOR_IMPORTANCE_ABS = 0, TSENOR_IMPORTANCE_SQUARE = 1 };
 
 /* Bytes of device scratch that tsenor_mask_ex / tsenor_mask_batched need for these problems
  * (the sum over the batch).  0 on invalid arguments.  The scratch holds what passes between the kernels of
- * the path: the scan order of Algorithm 2 line 1 (two bytes per weight), the mask greedy selection leaves
- * (Algorithm 2 line 6) and per-block objective values of Eq. 1. */
+ * the path: the potentials of every block or the scan order of Algorithm 2 line 1 (two bytes per weight are set aside), the
+ * mask greedy selection leaves (Algorithm 2 line 6) and per-block objective values of Eq. 1. */
 size_t tsenor_workspace_bytes(const tsenor_problem* problems, int count);
 
 /* The whole path (tile load -> Algorithm 1 -> Algorithm 2 -> mask write) for one matrix: Eq. 1 solved block

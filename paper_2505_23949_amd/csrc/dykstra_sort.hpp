@@ -1,4 +1,5 @@
-// Tile load, Algorithm 1 (Dykstra iterations) and the sort that feeds Algorithm 2, one kernel.
+// Tile load and Algorithm 1 (Dykstra iterations), one kernel.  For M >= 16 on the large tiles it leaves the potentials of
+// every block for round_kernel; for M <= 8 and on the small tiles the sort that feeds Algorithm 2 follows here.
 //
 // How Algorithm 1 is evaluated.  With A = log S + log Q, the cap step (lines 5-6) gives
 // log S = min(A, 0) and log Q = max(A, 0) after every iteration, and one iteration adds a row term
@@ -41,7 +42,6 @@
 namespace tsenor_dev {
 
 constexpr double kMinLogKernel = -700.0;  // exp(-700) is still a normal double
-constexpr int kIdxBits = 12;              // flat index within a block: up to 64*64 entries
 constexpr int kWarmIters = 4;             // FAST: iterations done in double before switching to fp32
 constexpr int kRowChunks64 = 2;           // M = 64: the 8 x 8 tile is loaded in this many pieces (loads in flight cost registers)
 constexpr int kChunk = 8;                 // FAST: iterations between range checks of the fp32 scalings
@@ -444,12 +444,6 @@ __device__ __forceinline__ float dykstra_iteration_f32(const float (&kap)[TH][TW
   return worst;
 }
 
-__device__ __forceinline__ void compare_exchange(double& lo, double& hi) {
-  const double a = fmin(lo, hi), b = fmax(lo, hi);
-  lo = a;
-  hi = b;
-}
-
 // min(a, -b) as one instruction (fmin() would first quiet possible signalling NaNs in operands the compiler
 // has not computed itself, one more instruction each)
 __device__ __forceinline__ double min_with_negated(double a, double b) {
@@ -581,7 +575,8 @@ __global__ __launch_bounds__((DykstraLaunch<M, FAST, ADAPT, SMALL>::kThreads), (
   int64_t blk = wave * BPW + lane / LPB;
   const bool active = blk < p.nblocks;
   if (!active) blk = p.nblocks - 1;  // idle lanes shadow the last block and write nothing
-  const int64_t r0 = (blk / p.bc) * M, c0 = (blk % p.bc) * M;
+  const BlockAt at = block_at(p, blk, M);
+  const int64_t r0 = at.r0, c0 = at.c0;
   const double tau_eff = tau_eff_of(batch.e[which]);
   if (tau_eff_out && group == 0 && threadIdx.x == 0) *tau_eff_out = tau_eff;
 
@@ -611,7 +606,9 @@ __global__ __launch_bounds__((DykstraLaunch<M, FAST, ADAPT, SMALL>::kThreads), (
   // tiles of M = 64 would keep 64 loads with their addresses in flight and spill
   constexpr int NA = M == 64 ? TH / kRowChunks64 : (FAST && TH >= 8) ? TH / 2 : TH;
 
-  double c[E];  // sort keys
+  // Blocks of 16 and more on the large tiles leave their potentials to round_kernel; the others are sorted here
+  constexpr bool kPotentials = M >= 16 && !SMALL;
+  [[maybe_unused]] double c[kPotentials ? 1 : E];  // sort keys
   int iters_done = 0;
   double kap[ZERO_T ? 1 : TH][ZERO_T ? 1 : TW];
   // Normaliser of every in-kernel row: kappa = exp(K - mrow) <= ~1.  Any per-row constant gives the same
@@ -642,6 +639,7 @@ __global__ __launch_bounds__((DykstraLaunch<M, FAST, ADAPT, SMALL>::kThreads), (
         };
         row_chunks<0, NA, TH>(plan_rows);
       }
+      if constexpr (kPotentials) return;  // (launched for the plan alone: round_kernel forms the keys itself)
     }
     auto rows = [&](auto first) {
       constexpr int A0 = decltype(first)::value;
@@ -653,14 +651,9 @@ __global__ __launch_bounds__((DykstraLaunch<M, FAST, ADAPT, SMALL>::kThreads), (
         for (int b = 0; b < TW; ++b) {
           const double K = tau_eff * (double)imp[a][b];  // K of Algorithm 1 line 1
           if constexpr (ZERO_T) {
-            // no iterations: the greedy order is descending K itself.  Bit patterns of non-negative doubles
-            // order like the doubles: pattern(2^1023) - pattern(K) reverses the order for every finite
-            // K >= 0 and is again the pattern of a positive double
+            // no iterations: the greedy order is descending K itself
             const int ri = gy * TH + ((A0 + a) ^ rx0), cj = gx * TW + (b ^ ry0);
-            const unsigned long long idx = (unsigned long long)(mat_row(ri, cj) * M + mat_col(ri, cj));
-            const unsigned long long bits = (unsigned long long)__double_as_longlong(K);
-            const unsigned long long key = (0x7FE0000000000000ull - bits) & ~((1ull << kIdxBits) - 1);
-            c[(A0 + a) * TW + b] = __longlong_as_double((long long)(key | idx));
+            if constexpr (!kPotentials) c[(A0 + a) * TW + b] = scan_key_of_k(K, mat_row(ri, cj) * M + mat_col(ri, cj));
           } else {
             kap[A0 + a][b] = K;
             const float up = __double2float_ru(K);
@@ -854,6 +847,20 @@ __global__ __launch_bounds__((DykstraLaunch<M, FAST, ADAPT, SMALL>::kThreads), (
     }
 
     const int rx2 = fresh(rx), ry2 = fresh(ry);
+    if constexpr (kPotentials) {
+      if (group == 0 && threadIdx.x == 0) batch.e[which].hdr->tau_eff = tau_eff;
+      if (active) {
+        // every row and column of the block has one owner among its lanes
+        static_assert(TH >= GX && TW >= GY, "one owner");
+        BlockPotentials<M>* out = reinterpret_cast<BlockPotentials<M>*>(order) + blk;
+#pragma unroll
+        for (int a = 0; a < OWN_R; ++a) out->u[gy * TH + (a ^ rx2)] = lu_own[a] - (double)mrow[a];
+#pragma unroll
+        for (int b = 0; b < OWN_C; ++b) out->v[gx * TW + (b ^ ry2)] = lv_own[b];
+        if (q == 0 && batch.e[which].iters_done_out) batch.e[which].iters_done_out[blk] = iters_done;
+      }
+      if (!plan_out) return;
+    }
     double lu[TH], lv[TW];
 #pragma unroll
     for (int a = 0; a < OWN_R; ++a) lu[a] = lu_own[a];
@@ -862,12 +869,12 @@ __global__ __launch_bounds__((DykstraLaunch<M, FAST, ADAPT, SMALL>::kThreads), (
     all_gather_x<T, double, TH>(lu);
     all_gather_y<T, double, TW>(lv);
     const auto addr = addr_of(rx2, ry2);
-    // log S^(T) = min(K + f_i + g_j, 0)
+    // K + f_i + g_j, of which log S^(T) is the minimum with 0
     // (K is not floored here as it is for kappa: entries too small for the iterations to see keep
     // their own order in the scan)
     auto log_plan = [&](float importance, int a, int b) {
       const double K = tau_eff * (double)importance;
-      return fmin((K - (double)mrow[a]) + (lu[a] + lv[b]), 0.0);
+      return (K - (double)mrow[a]) + (lu[a] + lv[b]);
     };
     // the plan (a diagnostic output) in a pass of its own, with its own loads: an exp() inside the key pass
     // costs it registers (spills for M = 64)
@@ -881,62 +888,60 @@ __global__ __launch_bounds__((DykstraLaunch<M, FAST, ADAPT, SMALL>::kThreads), (
 #pragma unroll
           for (int b = 0; b < TW; ++b) {
             const int ri = gy * TH + ((A0 + a) ^ rx2), cj = gx * TW + (b ^ ry2);
-            plan_out[(r0 + mat_row(ri, cj)) * p.cols + c0 + mat_col(ri, cj)] = exp(log_plan(imp[a][b], A0 + a, b));
+            plan_out[(r0 + mat_row(ri, cj)) * p.cols + c0 + mat_col(ri, cj)] = exp(fmin(log_plan(imp[a][b], A0 + a, b), 0.0));
             __builtin_amdgcn_sched_barrier(0);
           }
       };
       row_chunks<0, NA, TH>(plan_rows);
     }
-    auto rows = [&](auto first) {
-      constexpr int A0 = decltype(first)::value;
-      float imp[NA][TW];
-      tile_importance<A0, NA>(p, addr, imp);
+    if constexpr (!kPotentials) {
+      auto rows = [&](auto first) {
+        constexpr int A0 = decltype(first)::value;
+        float imp[NA][TW];
+        tile_importance<A0, NA>(p, addr, imp);
 #pragma unroll
-      for (int a = 0; a < NA; ++a)
+        for (int a = 0; a < NA; ++a)
 #pragma unroll
-        for (int b = 0; b < TW; ++b) {
-          const int ri = gy * TH + ((A0 + a) ^ rx2), cj = gx * TW + (b ^ ry2);
-          const double key = log_plan(imp[a][b], A0 + a, b);
-          const unsigned long long idx = (unsigned long long)(mat_row(ri, cj) * M + mat_col(ri, cj));
-          const unsigned long long bits = (unsigned long long)__double_as_longlong(fabs(key));
-          // descending key, ties by ascending flat index; + 2^52 keeps the pattern a normal double
-          c[(A0 + a) * TW + b] =
-              __longlong_as_double((long long)(((bits & ~((1ull << kIdxBits) - 1)) | idx) + (1ull << 52)));
-        }
-    };
-    row_chunks<0, NA, TH>(rows);
-  }
-
-  sort_ascending<E, LPB>(c, q);
-  // The stores below sit under `active`, and only the index bits of a key are stored: the compiler would move
-  // the last stage's selects into that branch but has to leave its cross-lane moves outside, all of them
-  // alive at once (spills for M = 64).  Using the keys here keeps every select next to its moves.
-#pragma unroll
-  for (int r = 0; r < E; ++r) asm volatile("" : "+v"(c[r]));
-
-  if (active && q == 0 && batch.e[which].iters_done_out) batch.e[which].iters_done_out[blk] = iters_done;
-  if constexpr (SMALL) {
-    // Algorithm 2 behind the sort, in the same wave: the scan order of the wave's blocks through LDS
-    static_assert(WPG == 1, "the rounding steps synchronise single-wave workgroups");
-    __shared__ unsigned short scan[BPW][M * M];
-    __shared__ RoundingLds<M, BPW> lds;
-    unsigned short* mine = &scan[lane / LPB][0];
-#pragma unroll
-    for (int r = 0; r < E; ++r)
-      mine[q * E + r] = (unsigned short)((unsigned long long)__double_as_longlong(c[r]) & ((1ull << kIdxBits) - 1));
-    __syncthreads();
-    const int placed = greedy_wide_scan<M, LPB>([&](int pos) { return (unsigned int)mine[pos]; }, p.N, lane, lds);
-    if (batch.e[which].stats_out) {
-      int missing = (active && q == 0) ? p.N * M - placed : 0;
-      for (int s = 1; s < kWave; s <<= 1) missing += __shfl_xor(missing, s, kWave);
-      if (lane == 0 && missing) atomicAdd(&batch.e[which].hdr->stats[0], (unsigned long long)missing);
+          for (int b = 0; b < TW; ++b) {
+            const int ri = gy * TH + ((A0 + a) ^ rx2), cj = gx * TW + (b ^ ry2);
+            c[(A0 + a) * TW + b] = scan_key(log_plan(imp[a][b], A0 + a, b), mat_row(ri, cj) * M + mat_col(ri, cj));
+          }
+      };
+      row_chunks<0, NA, TH>(rows);
     }
-    local_search_and_write<M, LPB>(p, batch.e[which], blk, active, lane, lds);
-  } else if (active) {
-    unsigned short* dst = order + blk * (int64_t)(M * M) + q * E;
+  }
+  if constexpr (!kPotentials) {
+    sort_ascending<E, LPB>(c, q);
+    // The stores below sit under `active`, and only the index bits of a key are stored: the compiler would move
+    // the last stage's selects into that branch but has to leave its cross-lane moves outside, all of them
+    // alive at once (spills for M = 64).  Using the keys here keeps every select next to its moves.
 #pragma unroll
-    for (int r = 0; r < E; ++r)
-      dst[r] = (unsigned short)((unsigned long long)__double_as_longlong(c[r]) & ((1ull << kIdxBits) - 1));
+    for (int r = 0; r < E; ++r) asm volatile("" : "+v"(c[r]));
+
+    if (active && q == 0 && batch.e[which].iters_done_out) batch.e[which].iters_done_out[blk] = iters_done;
+    if constexpr (SMALL) {
+      // Algorithm 2 behind the sort, in the same wave: the scan order of the wave's blocks through LDS
+      static_assert(WPG == 1, "the rounding steps synchronise single-wave workgroups");
+      __shared__ unsigned short scan[BPW][M * M];
+      __shared__ RoundingLds<M, BPW> lds;
+      unsigned short* mine = &scan[lane / LPB][0];
+#pragma unroll
+      for (int r = 0; r < E; ++r)
+        mine[q * E + r] = (unsigned short)((unsigned long long)__double_as_longlong(c[r]) & ((1ull << kIdxBits) - 1));
+      __syncthreads();
+      const int placed = greedy_wide_scan<M, LPB>([&](int pos) { return (unsigned int)mine[pos]; }, p.N, lane, lds);
+      if (batch.e[which].stats_out) {
+        int missing = (active && q == 0) ? p.N * M - placed : 0;
+        for (int s = 1; s < kWave; s <<= 1) missing += __shfl_xor(missing, s, kWave);
+        if (lane == 0 && missing) atomicAdd(&batch.e[which].hdr->stats[0], (unsigned long long)missing);
+      }
+      local_search_and_write<M, LPB>(p, batch.e[which], blk, active, r0, c0, lane, lds);
+    } else if (active) {
+      unsigned short* dst = order + blk * (int64_t)(M * M) + q * E;
+#pragma unroll
+      for (int r = 0; r < E; ++r)
+        dst[r] = (unsigned short)((unsigned long long)__double_as_longlong(c[r]) & ((1ull << kIdxBits) - 1));
+    }
   }
 }
 

@@ -13,7 +13,7 @@ namespace tsenor_dev {
 struct Variant {
   int M;
   bool fast, zero_t;
-  uint32_t greedy;  // 0: chosen by size, else the TSENOR_FLAG_GREEDY_* asked for
+  uint32_t greedy;  // the TSENOR_FLAG_GREEDY_* asked for (M <= 8)
   bool small;       // the Dykstra kernel's small tiles (decided per problem, so that fusing never changes results)
   bool simple;      // TSENOR_FLAG_SIMPLE_ROUNDING
   bool adaptive;    // tol > 0: the early-exit instantiation of the Dykstra kernel
@@ -37,18 +37,10 @@ constexpr int64_t small_tiles_below_blocks(int M, bool fp32) {
        : M == 32 ? (fp32 ? 2100 : 3200) : 0;
 }
 
-// Below this many blocks in a launch the greedy selection runs with M lanes per block: the one-lane kernel
-// takes the time of M*M dependent steps of a single wave however few blocks there are (22 / 70 / 310 us for
-// M = 16 / 32 / 64), the M-lane kernel issues several times the instructions but its chain is M steps, so it
-// wins while it does not fill the chip.  Measured crossovers (us, one lane / M lanes, T = 300): M = 32: 8192
-// blocks 70 / 52, 12 288 blocks 70 / 69, 16 384 blocks 70 / 84; M = 16: 12 288 blocks 22 / 20, 16 384 blocks
-// 23 / 25; M = 64: 8192 blocks 308 / 214, 12 288 blocks 317 / 315, 16 384 blocks 314 / 396.  For M <= 8 the
-// one-lane kernel is never slower.
-constexpr int64_t greedy_wide_below_blocks(int M) { return M == 16 ? 14000 : M == 32 ? 12000 : M == 64 ? 12000 : 0; }
-
-// Enqueues the kernels of one fused launch that depend on M: tile load + Algorithm 1 + sort, greedy selection
-// (or the simple rounding arm), local search + mask write.  `b.count` non-degenerate problems of variant v.
-// ev (optional): events recorded after the first and the second of the three.
+// Enqueues the kernels of one fused launch that depend on M: tile load + Algorithm 1 (+ sort for M <= 8), greedy selection
+// (or the simple rounding arm), local search + mask write; the last two are one kernel for M >= 16.  `b.count`
+// non-degenerate problems of variant v.  ev (optional): events recorded after the iterations and after the greedy selection
+// (M >= 16: after the whole of Algorithm 2).
 // Returns false if a launch could not be described (more workgroups than a grid holds).
 template <int M>
 bool launch_block_kernels(Batch& b, const Variant& v, hipStream_t stream, hipEvent_t ev_sorted, hipEvent_t ev_greedy);

@@ -21,8 +21,6 @@ inline bool assign_groups(Batch& b, int64_t per_group) {
 template <int M>
 bool launch_block_kernels(Batch& b, const Variant& v, hipStream_t stream, hipEvent_t ev_sorted, hipEvent_t ev_greedy) {
   constexpr int BPW = kWave >> (Tiling<M>::NX + Tiling<M>::NY);
-  int64_t total_blocks = 0;
-  for (int k = 0; k < b.count; ++k) total_blocks += b.e[k].p.nblocks;
   constexpr bool kHasSmall = M <= 32;
   const bool small = kHasSmall && !v.fast && !v.zero_t && v.small;
   if (small) {
@@ -52,29 +50,42 @@ bool launch_block_kernels(Batch& b, const Variant& v, hipStream_t stream, hipEve
     using L = DykstraLaunch<M, false>;
     using LA = DykstraLaunch<M, false, true>;
     if (!assign_groups(b, (int64_t)BPW * (v.adaptive ? LA::kWavesPerGroup : L::kWavesPerGroup))) return false;
-    if (v.zero_t)
-      dykstra_sort_kernel<M, false, true><<<b.first[b.count], L::kThreads, 0, stream>>>(b);
-    else if (v.adaptive)
+    if (v.zero_t) {
+      // (M >= 16: the rounding kernel starts from the importance itself, this one only writes a plan that is asked for)
+      bool any_plan = M < 16;
+      for (int k = 0; k < b.count; ++k) any_plan |= b.e[k].plan_out != nullptr;
+      if (any_plan) dykstra_sort_kernel<M, false, true><<<b.first[b.count], L::kThreads, 0, stream>>>(b);
+    } else if (v.adaptive)
       dykstra_sort_kernel<M, false, false, false, true><<<b.first[b.count], LA::kThreads, 0, stream>>>(b);
     else
       dykstra_sort_kernel<M, false><<<b.first[b.count], L::kThreads, 0, stream>>>(b);
   }
   if (ev_sorted) (void)hipEventRecord(ev_sorted, stream);
-  const bool wide = v.greedy ? v.greedy == TSENOR_FLAG_GREEDY_M_LANES : total_blocks < greedy_wide_below_blocks(M);
-  if (v.simple) {
-    if (!assign_groups(b, kWave)) return false;
-    simple_round_kernel<M><<<b.first[b.count], kWave, 0, stream>>>(b);
-  } else if (wide) {
+  if constexpr (M >= 16) {
+    // the whole of Algorithm 2 in one kernel
     if (!assign_groups(b, kWave / M)) return false;
-    greedy_wide_kernel<M><<<b.first[b.count], kWave, 0, stream>>>(b);
+    if (v.zero_t)
+      round_kernel<M, true><<<b.first[b.count], kWave, 0, stream>>>(b, v.simple);
+    else
+      round_kernel<M, false><<<b.first[b.count], kWave, 0, stream>>>(b, v.simple);
+    if (ev_greedy) (void)hipEventRecord(ev_greedy, stream);
   } else {
-    if (!assign_groups(b, kWave)) return false;
-    constexpr int GW = kGreedyWaves<M>;
-    greedy_kernel<M><<<(b.first[b.count] + GW - 1) / GW, kWave * GW, 0, stream>>>(b);
+    const bool wide = v.greedy == TSENOR_FLAG_GREEDY_M_LANES;
+    if (v.simple) {
+      if (!assign_groups(b, kWave)) return false;
+      simple_round_kernel<M><<<b.first[b.count], kWave, 0, stream>>>(b);
+    } else if (wide) {
+      if (!assign_groups(b, kWave / M)) return false;
+      greedy_wide_kernel<M><<<b.first[b.count], kWave, 0, stream>>>(b);
+    } else {
+      if (!assign_groups(b, kWave)) return false;
+      constexpr int GW = kGreedyWaves;
+      greedy_kernel<M><<<(b.first[b.count] + GW - 1) / GW, kWave * GW, 0, stream>>>(b);
+    }
+    if (ev_greedy) (void)hipEventRecord(ev_greedy, stream);
+    if (!assign_groups(b, kWave / M)) return false;
+    finalize_kernel<M><<<b.first[b.count], kWave, 0, stream>>>(b);
   }
-  if (ev_greedy) (void)hipEventRecord(ev_greedy, stream);
-  if (!assign_groups(b, kWave / M)) return false;
-  finalize_kernel<M><<<b.first[b.count], kWave, 0, stream>>>(b);
   return true;
 }
 

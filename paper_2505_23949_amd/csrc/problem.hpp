@@ -12,6 +12,7 @@ struct WsHeader {
   unsigned int use_prev;  // safeguard verdict: 1 = the caller's previous mask scores higher and is returned
   unsigned long long stats[4];  // the four rounding counters (accumulated only when the caller asks for them)
   double objective[2];    // sum S*importance of the mask found / of the previous mask
+  double tau_eff;         // multiplier of the importance, left by the iterations for the rounding (M >= 16, T > 0)
   // measurement aid: shader-clock cycles and constant-rate timer ticks that the first wave of the Dykstra kernel
   // spent in its iteration loop (their ratio is the clock the chip held under that load)
   unsigned long long loop_cycles, loop_ticks;
@@ -75,6 +76,15 @@ __device__ __forceinline__ int find_problem(const Batch& b, unsigned int workgro
   int k = 0;
   while (k + 1 < b.count && workgroup >= b.first[k + 1]) ++k;
   return k;
+}
+
+// matrix position of a block.  A launch holds fewer than 2^31 blocks: a 32-bit division, a fraction of a 64-bit one
+struct BlockAt {
+  int64_t r0, c0;
+};
+__device__ __forceinline__ BlockAt block_at(const DevProblem& p, int64_t blk, int M) {
+  const unsigned int b = (unsigned int)blk, bc = (unsigned int)p.bc, row = b / bc;
+  return {(int64_t)row * M, (int64_t)(b - row * bc) * M};
 }
 
 __device__ __forceinline__ float load_element(const void* base, int dtype, int64_t index) {
@@ -228,10 +238,10 @@ __device__ __forceinline__ void block_column_importance(const DevProblem& p, int
   }
   const float cs = p.col_scale ? p.col_scale[c] : 1.0f;
 #pragma unroll
-  for (int k = 0; k < M; ++k) {
-    float m = __fmul_rn(fabsf(imp[k]), cs);  // times exactly 1 where there is no scale
-    if (p.square) m = __fmul_rn(m, m);
-    imp[k] = m;
+  for (int k = 0; k < M; ++k) imp[k] = __fmul_rn(fabsf(imp[k]), cs);  // times exactly 1 where there is no scale
+  if (p.square) {
+#pragma unroll
+    for (int k = 0; k < M; ++k) imp[k] = __fmul_rn(imp[k], imp[k]);
   }
 }
 

@@ -1,4 +1,4 @@
-// Algorithm 2: greedy selection (one lane per block) and local search plus the mask write.
+// Algorithm 2: greedy selection, local search and the mask write.
 #pragma once
 #include <limits>
 #include <type_traits>
@@ -20,30 +20,26 @@ __device__ __forceinline__ int mask_popc(mask_t v) {
     return __popc((unsigned int)v);
 }
 
-// Waves per workgroup of greedy_kernel.  A full matrix gives the kernel about one wave per SIMD (57 344 blocks: 896
-// waves for 1024 SIMDs), and a wave's pace is its own dependent chain: it must not share a SIMD while others
-// idle.  One-wave workgroups were placed unevenly (0.096 ms for the headline matrix); workgroups of four waves, one
-// per SIMD of a CU, take 0.077 ms.  (M = 64 keeps one wave: its 36 KB of LDS per wave already spread the
-// workgroups, and four waves measured the same.)  The waves of a workgroup do not interact.
-template <int M>
-constexpr int kGreedyWaves = M <= 32 ? 4 : 1;
+// Waves per workgroup of greedy_kernel: one per SIMD of a CU.  A wave's pace is its own dependent chain: it must not share a
+// SIMD while others idle, and one-wave workgroups were placed unevenly (57 344 blocks: 0.096 ms against 0.077 ms).
+constexpr int kGreedyWaves = 4;
 
 // Algorithm 2 lines 1-6: scan the entries of a block in sorted order and keep an entry while its row
 // and its column hold fewer than N.  The chain of M*M dependent steps runs with ONE LANE PER BLOCK, so
 // every lane of the wave does useful work; the state of a lane (M row masks, M column counters) lives in
 // LDS.  The kernel is bound by the instruction issue of its single wave per SIMD (~27 instructions per
 // entry), not by memory: the scan order is prefetched a cache line ahead and the LDS state of four entries
-// is fetched per round trip.  Output: the mask as M row bit masks per block (bit c of word r = S[r][c]).
+// is fetched per round trip.  Serves M <= 8 (larger blocks: round_kernel).  Output: the mask as M row bit masks per block (bit c of word r = S[r][c]).
 template <int M>
-__global__ __launch_bounds__(kWave * kGreedyWaves<M>) void greedy_kernel(Batch batch) {
+__global__ __launch_bounds__(kWave * kGreedyWaves) void greedy_kernel(Batch batch) {
   using mask_t = block_mask_t<M>;
   constexpr int MM = M * M;
-  __shared__ mask_t rowbits_[kGreedyWaves<M>][M][kWave];
-  __shared__ unsigned char colcnt_[kGreedyWaves<M>][M][kWave];
+  __shared__ mask_t rowbits_[kGreedyWaves][M][kWave];
+  __shared__ unsigned char colcnt_[kGreedyWaves][M][kWave];
   auto& rowbits = rowbits_[threadIdx.x / kWave];
   auto& colcnt = colcnt_[threadIdx.x / kWave];
   // `vgroup` counts 64-block groups across the launch, as the group prefix of the batch does
-  const unsigned int vgroup = blockIdx.x * kGreedyWaves<M> + threadIdx.x / kWave;
+  const unsigned int vgroup = blockIdx.x * kGreedyWaves + threadIdx.x / kWave;
   if (vgroup >= batch.first[batch.count]) return;  // (a whole wave; the kernel has no barrier)
   const int which = find_problem(batch, vgroup);
   const unsigned short* order = batch.e[which].order;
@@ -336,10 +332,10 @@ __device__ __forceinline__ double group_sum(double v) {
 // Algorithm 2 lines 7-13 and the mask write for the blocks of one wave.  A block owns LPB >= M consecutive lanes,
 // of which the first M take part: lane r owns row r and column r of the block as bit masks.  On entry lds.rowm
 // holds the mask greedy selection left.  blk: the lane's block (a valid one also for idle lanes, which write
-// nothing: `active`).  To be called by whole single-wave workgroups.
+// nothing: `active`), at matrix position (r0, c0).  To be called by whole single-wave workgroups.
 template <int M, int LPB>
 __device__ __forceinline__ void local_search_and_write(const DevProblem& p, const BatchEntry& e, int64_t blk, bool active,
-                                                       int lane, RoundingLds<M, kWave / LPB>& lds) {
+                                                       int64_t r0, int64_t c0, int lane, RoundingLds<M, kWave / LPB>& lds) {
   using mask_t = block_mask_t<M>;
   constexpr int MM = M * M, LD = RoundingLds<M, kWave / LPB>::kImpLd;
   uint8_t* mask = e.mask;
@@ -351,7 +347,6 @@ __device__ __forceinline__ void local_search_and_write(const DevProblem& p, cons
   const int g = lane / LPB, ql = lane % LPB;
   const bool part = ql < M;
   const int qm = ql % M;  // (an index that stays inside the block's LDS rows also for the lanes that only tag along)
-  const int64_t r0 = (blk / p.bc) * M, c0 = (blk % p.bc) * M;
   const mask_t one = 1;
 
   // the transpose of the mask greedy selection left
@@ -391,17 +386,18 @@ __device__ __forceinline__ void local_search_and_write(const DevProblem& p, cons
     if (!open || !part || ((lds.colm[g][j] >> qm) & 1)) cand = 0;
     const double base = (double)lds.imp[g][qm * LD + j];
     SwapBest best = {-std::numeric_limits<double>::infinity(), MM};
-    while (__any(cand != 0)) {
-      if (cand != 0) {
+    while (cand != 0) {
+      {
         const int jp = sizeof(mask_t) == 8 ? __ffsll((long long)cand) - 1 : __ffs((int)cand) - 1;
         cand &= cand - 1;
         const double sc = ((double)lds.imp[g][i * LD + jp] + base) - (double)lds.imp[g][qm * LD + jp];
-        if (best.arg == MM || sc > best.score) {
+        if (sc > best.score) {
           best.score = sc;
-          best.arg = qm * M + jp;
+          best.arg = jp;
         }
       }
     }
+    best.arg = best.arg == MM ? MM : qm * M + best.arg;
     best = group_best<M>(best);
     if (open) ++rounds;
     bool apply = open && best.arg != MM;
@@ -496,7 +492,256 @@ __global__ __launch_bounds__(kWave) void finalize_kernel(Batch batch) {
   const bool active = blk < p.nblocks;
   if (!active) blk = p.nblocks - 1;  // idle groups shadow the last block and write nothing
   lds.rowm[g][ql] = rowmask[blk * M + ql];
-  local_search_and_write<M, M>(p, batch.e[which], blk, active, lane, lds);
+  const BlockAt at = block_at(p, blk, M);
+  local_search_and_write<M, M>(p, batch.e[which], blk, active, at.r0, at.c0, lane, lds);
+}
+
+// ------------------------------------------------------------------------------------------------------------------
+// The whole of Algorithm 2 in one kernel for M >= 16, from the potentials the iterations leave.
+//
+// The greedy selection needs no sort of the M*M entries.  It scans them in one common order (descending plan, ties by
+// index) and keeps an entry while its row and its column have room; its result is the one stable assignment in which
+// every row and every column prefers entries in that order and holds at most N of them (the first entry of the order is
+// in every stable assignment, and what follows is the same problem with one place less; Gale and Shapley 1962, the
+// common order makes the stable assignment unique).  So deferred acceptance finds it from the order INSIDE every row and
+// every column alone: a row proposes to the columns of its first N entries; a column keeps the best N of its proposals
+// and turns the others away; a row that was turned away proposes its next entries, until nobody proposes any more (about
+// four rounds).  Two sorts of M keys in the registers of a lane (one lane per row, then one lane per column) replace a
+// sort of M*M keys across the lanes of a block, and the M*M dependent steps of the scan are gone.
+// ------------------------------------------------------------------------------------------------------------------
+
+// What the iterations hand to the rounding, per block: log S = min(K + (u + v), 0) with u per in-kernel row and v per
+// in-kernel column (in-kernel rows are matrix columns under TSENOR_FLAG_COLS_FIRST).
+template <int M>
+struct BlockPotentials {
+  double u[M], v[M];
+};
+
+// Scan key of an entry: positive doubles whose order is descending plan, ties by ascending flat index.
+constexpr int kIdxBits = 12;  // flat index within a block: up to 64*64 entries
+// log_plan: K + (u + v), to be capped at 0.
+__device__ __forceinline__ double scan_key(double log_plan, unsigned int flat) {
+  const double x = fmax(-log_plan, 0.0);
+  // + 2^52 keeps the pattern a normal double
+  return __hiloint2double((__double2hiint(x) & 0x7FFFFFFF) + (1 << 20), (__double2loint(x) & ~((1 << kIdxBits) - 1)) | (int)flat);
+}
+// T = 0: the order is descending K itself.  Bit patterns of non-negative doubles order like the doubles:
+// pattern(2^1023) - pattern(K) reverses the order for every finite K >= 0 and is again the pattern of a positive double
+__device__ __forceinline__ double scan_key_of_k(double K, unsigned int flat) {
+  const unsigned long long bits = (unsigned long long)__double_as_longlong(K);
+  return __longlong_as_double((long long)(((0x7FE0000000000000ull - bits) & ~((1ull << kIdxBits) - 1)) | flat));
+}
+
+__device__ __forceinline__ void compare_exchange(double& lo, double& hi) {
+  const double a = fmin(lo, hi), b = fmax(lo, hi);
+  lo = a;
+  hi = b;
+}
+
+// the same as the two bare instructions: fmin() and fmax() first quiet possible signalling NaNs in keys that were put
+// together from words
+__device__ __forceinline__ void compare_exchange_as_is(double& lo, double& hi) {
+  double a;
+  asm("v_min_f64 %0, %1, %2" : "=v"(a) : "v"(lo), "v"(hi));
+  asm("v_max_f64 %0, %0, %1" : "+v"(hi) : "v"(lo));
+  lo = a;
+}
+
+// Ascending sort of the E keys of a lane: Batcher's odd-even merge sort (191 comparators for 32 keys, 543 for 64; the
+// bitonic network has 240 and 672), no data movement between lanes.
+template <int E, int P = 1, int K = 1>
+__device__ __forceinline__ void sort_in_lane(double (&c)[E]) {
+  if constexpr (P < E) {
+#pragma unroll
+    for (int x = 0; x + K < E; ++x) {
+      const int y = x - K % P;
+      if (y >= 0 && y % (2 * K) < K && x / (2 * P) == (x + K) / (2 * P)) compare_exchange_as_is(c[x], c[x + K]);
+    }
+    if constexpr (E >= 32) __builtin_amdgcn_sched_barrier(0);  // stage by stage: stages that overlap need registers
+    if constexpr (K > 1)
+      sort_in_lane<E, P, K / 2>(c);
+    else
+      sort_in_lane<E, P * 2, P * 2>(c);
+  }
+}
+
+// position of the N-th set bit (N >= 1) of a mask that has at least N
+template <int M, class mask_t>
+__device__ __forceinline__ int nth_set_bit(mask_t h, int N) {
+  int pos = 0;
+#pragma unroll
+  for (int s = M / 2; s >= 1; s >>= 1) {
+    const int below = mask_popc((mask_t)((h >> pos) & (((mask_t)1 << s) - 1)));
+    if (below < N) {
+      N -= below;
+      pos += s;
+    }
+  }
+  return pos;
+}
+
+// M lanes per block, 64/M blocks per wave, one wave per workgroup; lane r of a block is its row r and its column r.
+// Bound by instruction issue: of ~2 500 vector instructions per wave before the swaps (M = 32) the two sorts are 764 and
+// the keys 512.  57 344 blocks of 16:32: 0.206 ms with the swaps, where the sort across lanes (0.20 ms of the iteration
+// kernel), the scan kernel (0.077 ms) and the swap kernel (0.104 ms) took 0.38 ms; 16 384 blocks of 32:64: 0.34 ms for 0.78.
+template <int M, bool ZERO_T>
+__global__ __launch_bounds__(kWave, M <= 32 ? 4 : 2) void round_kernel(Batch batch, int simple) {
+  using mask_t = block_mask_t<M>;
+  constexpr int G = kWave / M, LOGM = M == 16 ? 4 : M == 32 ? 5 : 6, LD = RoundingLds<M, G>::kImpLd;
+  __shared__ RoundingLds<M, G> lds;
+  __shared__ double row_pot[ZERO_T ? 1 : G][M], col_pot[ZERO_T ? 1 : G][M];  // potentials of the matrix rows and columns
+  const int which = find_problem(batch, blockIdx.x);
+  const BatchEntry& e = batch.e[which];
+  const DevProblem p = e.p;
+  const int lane = threadIdx.x, g = lane / M, ql = lane % M, N = p.N;
+  const unsigned int group = blockIdx.x - batch.first[which];
+  int64_t blk = (int64_t)group * G + g;
+  const bool active = blk < p.nblocks;
+  if (!active) blk = p.nblocks - 1;  // idle groups shadow the last block and write nothing
+  const BlockAt at = block_at(p, blk, M);
+  const int64_t r0 = at.r0, c0 = at.c0;
+
+  // the importance of the block, a column per lane (coalesced), and the potentials: into LDS
+  {
+    float col[M];
+    block_column_importance<M>(p, r0, c0 + ql, col);
+#pragma unroll
+    for (int k = 0; k < M; ++k) lds.imp[g][k * LD + ql] = col[k];
+  }
+  double tau_eff;
+  if constexpr (ZERO_T) {
+    tau_eff = tau_eff_of(e);
+    if (e.tau_eff_out && group == 0 && lane == 0) *e.tau_eff_out = tau_eff;
+    if (active && ql == 0 && e.iters_done_out) e.iters_done_out[blk] = 0;
+  } else {
+    tau_eff = e.hdr->tau_eff;
+    const BlockPotentials<M>* src = reinterpret_cast<const BlockPotentials<M>*>(e.order) + blk;
+    const double of_row = src->u[ql], of_col = src->v[ql];
+    row_pot[g][ql] = p.transpose ? of_col : of_row;
+    col_pot[g][ql] = p.transpose ? of_row : of_col;
+  }
+  __syncthreads();
+
+  // keys of the entries of this lane's row (ROWS) or column
+  double c[M];
+  auto keys = [&](auto rows_tag) {
+    constexpr bool ROWS = decltype(rows_tag)::value;
+    double own = 0.0;
+    if constexpr (!ZERO_T) own = ROWS ? row_pot[g][ql] : col_pot[g][ql];
+#pragma unroll
+    for (int k = 0; k < M; ++k) {
+      const double imp = (double)lds.imp[g][ROWS ? ql * LD + k : k * LD + ql];
+      const unsigned int flat = ROWS ? ql * M + k : k * M + ql;
+      if constexpr (ZERO_T) {
+        c[k] = scan_key_of_k(tau_eff * imp, flat);
+      } else {
+        // (the same operations in both passes: an entry has one key)
+        const double other = ROWS ? col_pot[g][k] : row_pot[g][k];
+        c[k] = scan_key(fma(tau_eff, imp, own + other), flat);
+      }
+      // a few entries at a time: with all their LDS reads in flight the keys no longer fit the registers
+      if (k % 8 == 7) __builtin_amdgcn_sched_barrier(0);
+    }
+  };
+  using yes = std::integral_constant<bool, true>;
+  using no = std::integral_constant<bool, false>;
+
+  // this lane's row in scan order: the column of every place, four to a register
+  unsigned int row_list[M / 4];
+  keys(yes{});
+  sort_in_lane(c);
+#pragma unroll
+  for (int r = 0; r < M; ++r) {
+    const unsigned int j = (unsigned int)__double2loint(c[r]) & (M - 1);
+    row_list[r / 4] = r % 4 ? row_list[r / 4] | j << (8 * (r % 4)) : j;
+  }
+  // this lane's column in scan order
+  keys(no{});
+  sort_in_lane(c);
+  __syncthreads();
+
+  // From here the space of the importance holds three byte tables per block (rows padded by a word so that a lane per
+  // row meets no other in a bank): rank of entry (i, j) within column j, the columns of row i in scan order, the rows
+  // of column j in scan order.
+  constexpr int LDB = M + 4;
+  static_assert(3 * M * LDB <= (int)sizeof(lds.imp[0]), "the tables fit where the importance was");
+  unsigned char* rank = reinterpret_cast<unsigned char*>(&lds.imp[g][0]);
+  unsigned char* columns_of = rank + M * LDB;
+  unsigned char* rows_of = columns_of + M * LDB;
+  {
+    unsigned int packed = 0;
+#pragma unroll
+    for (int r = 0; r < M; ++r) {
+      const unsigned int i = ((unsigned int)__double2loint(c[r]) >> LOGM) & (M - 1);
+      rank[i * LDB + ql] = (unsigned char)r;
+      packed = r % 4 ? packed | i << (8 * (r % 4)) : i;
+      if (r % 4 == 3) {
+        *reinterpret_cast<unsigned int*>(rows_of + ql * LDB + r - 3) = packed;
+        *reinterpret_cast<unsigned int*>(columns_of + ql * LDB + r - 3) = row_list[r / 4];
+      }
+    }
+  }
+  // lds.rowm[i]: the columns row i holds; lds.colm[j]: the ranks (within column j) of the entries column j holds;
+  // lds.colcnt[j]: entries of a higher rank than this one it would turn away
+  const mask_t one = 1;
+  lds.colm[g][ql] = 0;
+  __syncthreads();
+  mask_t held = 0;
+  {
+    unsigned int cr[M];
+#pragma unroll
+    for (int r = 0; r < M; ++r) cr[r] = rank[ql * LDB + ((row_list[r / 4] >> (8 * (r % 4))) & 0xFFu)] & (unsigned)(M - 1);
+#pragma unroll
+    for (int r = 0; r < M; ++r)
+      if (r < N) {
+        const unsigned int j = (row_list[r / 4] >> (8 * (r % 4))) & 0xFFu;
+        atomicOr(&lds.colm[g][j], one << cr[r]);
+        held |= one << j;
+      }
+  }
+  lds.rowm[g][ql] = held;
+  int next = N;  // the first place of its order this row has not proposed
+  for (;;) {
+    __syncthreads();
+    const mask_t h = lds.colm[g][ql];
+    mask_t surplus = 0;
+    int limit = M;
+    if (mask_popc(h) >= N) {
+      limit = nth_set_bit<M>(h, N);
+      surplus = h & ~(((one << limit) << 1) - 1);
+      lds.colm[g][ql] = h ^ surplus;
+    }
+    lds.colcnt[g][ql] = (unsigned)limit;
+    while (surplus != 0) {
+      const int at = sizeof(mask_t) == 8 ? __ffsll((long long)surplus) - 1 : __ffs((int)surplus) - 1;
+      surplus &= surplus - 1;
+      atomicAnd(&lds.rowm[g][rows_of[ql * LDB + at]], ~(one << ql));
+    }
+    __syncthreads();
+    held = lds.rowm[g][ql];
+    int lacks = simple ? 0 : N - mask_popc(held);
+    bool proposed = false;
+    while (lacks > 0 && next < M) {
+      const unsigned int j = columns_of[ql * LDB + next];
+      const unsigned int at = rank[ql * LDB + j];
+      ++next;
+      if (at < lds.colcnt[g][j]) {
+        atomicOr(&lds.colm[g][j], one << at);
+        held |= one << j;
+        --lacks;
+        proposed = true;
+      }
+    }
+    lds.rowm[g][ql] = held;
+    if (!__any(proposed)) break;
+  }
+  if (e.stats_out) {
+    int missing = active ? N - mask_popc(held) : 0;
+    for (int s = 1; s < kWave; s <<= 1) missing += __shfl_xor(missing, s, kWave);
+    if (lane == 0 && missing) atomicAdd(&e.hdr->stats[0], (unsigned long long)missing);
+  }
+  __syncthreads();
+  local_search_and_write<M, M>(p, e, blk, active, r0, c0, lane, lds);
 }
 
 }  // namespace tsenor_dev

@@ -3,15 +3,14 @@
 // One call enqueues, on the caller's stream, for every group of matrices that share a block size and a
 // kernel variant (a single matrix is a group of one):
 //   1. init_kernel / absmax_kernel      workspace reset; importance maximum of every matrix (relative tau only)
-//   2. dykstra_sort_kernel              tile load, all T Dykstra iterations of Algorithm 1 on chip, sort of
-//                                       the M*M plan entries of every block; writes the greedy scan order
-//                                       (and the plan if asked for)                       [dykstra_sort.hpp]
-//   3. greedy_kernel                    Algorithm 2 lines 1-6, one lane per block (greedy_wide_kernel: M lanes
-//                                       per block, for small launches; simple_round_kernel: the ablation arm)
-//                                                                                         [rounding.hpp]
-//   4. finalize_kernel                  Algorithm 2 lines 7-13 (local search), mask write [rounding.hpp]
-//   5. objective_kernel, emit_kernel, stats_kernel   optional outputs                     [outputs.hpp]
-// Steps 2-4 depend on the block size and are compiled per M (launch.hpp).  Every kernel takes the table of
+//   2. dykstra_sort_kernel              tile load, all T Dykstra iterations of Algorithm 1 on chip (and the plan if
+//                                       asked for); leaves the potentials of every block (M >= 16) or the greedy scan
+//                                       order (M <= 8)                                    [dykstra_sort.hpp]
+//   3. round_kernel                     M >= 16: the whole of Algorithm 2                 [rounding.hpp]
+//      greedy_kernel, finalize_kernel   M <= 8: Algorithm 2 lines 1-6, one lane per block, then lines 7-13 and the mask
+//                                       write (simple_round_kernel: the ablation arm)     [rounding.hpp]
+//   4. objective_kernel, emit_kernel, stats_kernel   optional outputs                     [outputs.hpp]
+// Steps 2-3 depend on the block size and are compiled per M (launch.hpp).  Every kernel takes the table of
 // the group by value and finds the matrix of a workgroup from a prefix of workgroup counts.
 #include <hip/hip_runtime.h>
 #include <stdint.h>

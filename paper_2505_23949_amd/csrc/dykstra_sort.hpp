@@ -539,16 +539,15 @@ struct DykstraLaunch {
   // The small tiles carry the rounding behind the iterations, whose steps synchronise one wave at a time.
   static constexpr int kWavesPerGroup = (ADAPT || SMALL) ? 1 : 4;
   static constexpr int kThreads = kWavesPerGroup * kWave;
-  // waves per SIMD the register budget is set for.  The fp32 loop wants more than two (one wave issues at
-  // most every ~5 cycles, an fp32 instruction occupies the SIMD for 2-3): three waves of 168 registers.  For
-  // M <= 32 the whole kernel fits them without spills (four waves, 128 registers and a few spills outside the
-  // loop, measured the same).  For M = 64 the loop fits (64 + 64 registers for the tile and the capped entries)
-  // but the double-precision phases around it do not (the warm-up iterations on a tile of 64 doubles, the sort
-  // of 64 keys): they spill ~90 registers to scratch, none inside the loop, and the kernel is 5.5 % faster than
-  // with two waves (not with the early exit, where a block may run a dozen iterations and the code around the loop
-  // is most of the work: two waves there).  The double-precision loop holds twice the state: two waves of up to
-  // 256 registers.
-  static constexpr int kWavesPerSimd = FAST && !(M == 64 && ADAPT) ? 3 : 2;
+  // Waves per SIMD the register budget is set for.  Double: the loop holds twice the state of the fp32 one, two waves of up
+  // to 256 registers.  FAST: the more waves, the nearer the issue of plain fp32 instructions comes to its limit (1.13 ns
+  // per instruction and SIMD with two waves, 1.05 with four).  M = 32: four waves of 128 registers, the loop fits and ~30
+  // registers of the double-precision code around it spill (4096x14336: iteration kernel 1425 us, 1470 with three waves).
+  // M = 16: three (four the same to 0.4 % slower), M <= 8: under 120 registers whatever is asked for (five spill: 1 %
+  // slower).  M = 64: three, ~90 registers spill outside the loop (8192x28672, T = 500: 10.5 ms, two waves 11.0, four 31);
+  // with the early exit, where a block may run a dozen iterations and the code around the loop is most of the work, two
+  // (8192x8192: 0.85 ms, three 1.05).
+  static constexpr int kWavesPerSimd = FAST && !(M == 64 && ADAPT) ? (M == 32 ? 4 : 3) : 2;
 };
 
 // ZERO_T: the instantiation for T = 0 (no iterations, keys are K itself).  It is a template parameter

@@ -9,9 +9,7 @@ namespace tsenor_dev {
 
 // Head of a matrix's workspace slice: what the kernels of a call pass to each other besides the scan order.
 struct WsHeader {
-  unsigned int use_prev;  // safeguard verdict: 1 = the caller's previous mask scores higher and is returned
   unsigned long long stats[4];  // the four rounding counters (accumulated only when the caller asks for them)
-  double objective[2];    // sum S*importance of the mask found / of the previous mask
   double tau_eff;         // multiplier of the importance, left by the iterations for the rounding (M >= 16, T > 0)
   // measurement aid: shader-clock cycles and constant-rate timer ticks that the first wave of the Dykstra kernel
   // spent in its iteration loop (their ratio is the clock the chip held under that load)
@@ -23,6 +21,10 @@ static_assert(sizeof(WsHeader) <= 256, "header must fit its slot");
 // pre-pass, in the workspace right after the header; the kernel that needs the maximum reduces them itself.
 // No atomic, so nothing has to be cleared before a call.
 constexpr int kMaxAbsmaxPartials = 1024;
+// Once the iterations have read them, their place holds the partial sums of the objectives: a pair (mask found, previous
+// mask) per workgroup of objective_kernel.
+constexpr int kObjectiveGroups = 64;
+static_assert(kObjectiveGroups * 2 * sizeof(double) <= kMaxAbsmaxPartials * sizeof(float), "the partial sums fit");
 
 struct DevProblem {
   const void* W;
@@ -61,8 +63,11 @@ struct BatchEntry {
   double* objective_out;
   const uint8_t* prev_mask;
   int* iters_done_out;
-  int wide_store;               // mask rows can be written with 16-byte stores
-  int absmax_vec;               // rows can be read with 16-byte loads by the maximum pre-pass
+  // alignment of the caller's buffers
+  uint8_t wide_store;           // mask rows can be written with 16-byte stores
+  uint8_t wide_prev;            // the previous mask can be read with loads as wide as a block row (at most 16 bytes)
+  uint8_t absmax_vec;           // rows of W (and of the additive term) can be read with 16-byte loads by the pre-pass
+  uint8_t emit_vec;             // everything the derived outputs read and write can be moved 8 weights at a time
 };
 
 struct Batch {

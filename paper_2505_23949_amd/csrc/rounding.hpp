@@ -447,11 +447,29 @@ __device__ __forceinline__ void local_search_and_write(const DevProblem& p, cons
       if (prev_mask) {
         // the previous mask's row as bits: the byte loads are independent of each other
         const uint8_t* prev = prev_mask + (r0 + qm) * p.cols + c0;
-        uint8_t pm[M];
+        if (e.wide_prev) {
+          unsigned int w[M / 4];
+          if constexpr (M == 4) {
+            w[0] = *reinterpret_cast<const unsigned int*>(prev);
+          } else if constexpr (M == 8) {
+            const uint2 v = *reinterpret_cast<const uint2*>(prev);
+            w[0] = v.x, w[1] = v.y;
+          } else {
 #pragma unroll
-        for (int k = 0; k < M; ++k) pm[k] = prev[k];
+            for (int k = 0; k < M / 16; ++k) {
+              const uint4 v = reinterpret_cast<const uint4*>(prev)[k];
+              w[4 * k] = v.x, w[4 * k + 1] = v.y, w[4 * k + 2] = v.z, w[4 * k + 3] = v.w;
+            }
+          }
 #pragma unroll
-        for (int k = 0; k < M; ++k) prev_bits |= (mask_t)(pm[k] != 0) << k;
+          for (int k = 0; k < M; ++k) prev_bits |= (mask_t)((w[k / 4] & (0xFFu << (8 * (k % 4)))) != 0) << k;
+        } else {
+          uint8_t pm[M];
+#pragma unroll
+          for (int k = 0; k < M; ++k) pm[k] = prev[k];
+#pragma unroll
+          for (int k = 0; k < M; ++k) prev_bits |= (mask_t)(pm[k] != 0) << k;
+        }
       }
 #pragma unroll
       for (int k = 0; k < M; ++k) {

@@ -47,10 +47,33 @@ __host__ __device__ inline int absmax_threads_per_row(int64_t vectors_per_row, i
   return tpr;
 }
 
+// m and the largest |x| * scale of 8 weights (from column col) in each of kAbsmaxInFlight rows (from r, none past r_end)
+template <bool BF16, bool ADD>
+__device__ __forceinline__ float absmax_rows(const DevProblem& p, int64_t r, int64_t r_end, int64_t col,
+                                             const float (&scale)[8], float m) {
+  float x[kAbsmaxInFlight][8], add[ADD ? kAbsmaxInFlight : 1][8];
+#pragma unroll
+  for (int u = 0; u < kAbsmaxInFlight; ++u) {
+    const int64_t at = (r + u < r_end ? r + u : r) * p.ld + col;
+    load_8<BF16>(p.W, at, x[u]);
+    if constexpr (ADD) load_8<BF16>(p.add, at, add[u]);
+  }
+#pragma unroll
+  for (int u = 0; u < kAbsmaxInFlight; ++u)
+#pragma unroll
+    for (int k = 0; k < 8; ++k) {
+      float v = x[u][k];
+      if constexpr (ADD) v = __fadd_rn(v, __fmul_rn(p.add_scale, add[u][k]));
+      m = fmaxf(m, __fmul_rn(fabsf(v), scale[k]));
+    }
+  return m;
+}
+
 // Largest importance of every matrix of the batch that uses the relative tau (App. B.1 parameter choice).
 // blockIdx.z: matrix; x and y stride over its columns and rows.  With absmax_vec every thread reads 8
-// consecutive weights of a row with 16-byte loads (needs cols % 8 == 0 and 16-byte aligned rows and column
-// scale); otherwise one weight at a time.  A matrix with fewer than 256 such vectors per row shares the
+// consecutive weights of a row (and of the additive term) with 16-byte loads (needs cols % 8 == 0 and 16-byte aligned
+// rows and column scale); otherwise one weight at a time.  Squaring rounds monotonically, so a squared importance has its
+// maximum where the plain one has: it is squared once, at the end.  A matrix with fewer than 256 such vectors per row shares the
 // workgroup between rows.
 __global__ __launch_bounds__(256) void absmax_kernel(Batch batch) {
   const BatchEntry& e = batch.e[blockIdx.z];
@@ -75,39 +98,19 @@ __global__ __launch_bounds__(256) void absmax_kernel(Batch batch) {
       const int64_t r_end = (blockIdx.y + 1) * band < rows ? (blockIdx.y + 1) * band : rows;
       for (int64_t r = blockIdx.y * band + (int64_t)tr * kAbsmaxInFlight; r < r_end; r += (int64_t)rpp * kAbsmaxInFlight) {
         if (p.dtype == TSENOR_BF16) {
-          uint4 raw[kAbsmaxInFlight];
-#pragma unroll
-          for (int u = 0; u < kAbsmaxInFlight; ++u) {
-            const int64_t ru = r + u < r_end ? r + u : r;
-            raw[u] = *reinterpret_cast<const uint4*>(reinterpret_cast<const unsigned short*>(p.W) + ru * p.ld + v * 8);
-          }
-#pragma unroll
-          for (int u = 0; u < kAbsmaxInFlight; ++u) {
-            const unsigned int w[4] = {raw[u].x, raw[u].y, raw[u].z, raw[u].w};
-#pragma unroll
-            for (int k = 0; k < 4; ++k) {
-              m = fmaxf(m, fabsf(__uint_as_float(w[k] << 16)) * c[2 * k]);
-              m = fmaxf(m, fabsf(__uint_as_float(w[k] & 0xFFFF0000u)) * c[2 * k + 1]);
-            }
-          }
+          if (p.add)
+            m = absmax_rows<true, true>(p, r, r_end, v * 8, c, m);
+          else
+            m = absmax_rows<true, false>(p, r, r_end, v * 8, c, m);
         } else {
-          float4 lo[kAbsmaxInFlight], hi[kAbsmaxInFlight];
-#pragma unroll
-          for (int u = 0; u < kAbsmaxInFlight; ++u) {
-            const int64_t ru = r + u < r_end ? r + u : r;
-            const float4* src = reinterpret_cast<const float4*>(reinterpret_cast<const float*>(p.W) + ru * p.ld + v * 8);
-            lo[u] = src[0];
-            hi[u] = src[1];
-          }
-#pragma unroll
-          for (int u = 0; u < kAbsmaxInFlight; ++u) {
-            const float w[8] = {lo[u].x, lo[u].y, lo[u].z, lo[u].w, hi[u].x, hi[u].y, hi[u].z, hi[u].w};
-#pragma unroll
-            for (int k = 0; k < 8; ++k) m = fmaxf(m, fabsf(w[k]) * c[k]);
-          }
+          if (p.add)
+            m = absmax_rows<false, true>(p, r, r_end, v * 8, c, m);
+          else
+            m = absmax_rows<false, false>(p, r, r_end, v * 8, c, m);
         }
       }
     }
+    if (p.square) m = __fmul_rn(m, m);
   } else {
     for (int64_t r = blockIdx.y; r < rows; r += gridDim.y)
       for (int64_t c = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; c < p.cols; c += (int64_t)gridDim.x * blockDim.x)
@@ -258,10 +261,15 @@ BatchEntry entry_of(const tsenor_problem& p, char* ws) {
   e.objective_out = p.objective_out;
   e.prev_mask = p.prev_mask;
   e.iters_done_out = p.iters_done_out;
-  e.wide_store = reinterpret_cast<uintptr_t>(p.mask) % 16 == 0;
+  const auto aligned = [](const void* ptr, size_t to) { return reinterpret_cast<uintptr_t>(ptr) % to == 0; };
   const size_t esize = p.dtype == TSENOR_BF16 ? 2 : 4;
-  e.absmax_vec = p.cols % 8 == 0 && reinterpret_cast<uintptr_t>(p.W) % 16 == 0 && ((size_t)p.ld * esize) % 16 == 0 &&
-                 reinterpret_cast<uintptr_t>(p.col_scale) % 16 == 0 && !p.add && !dp.square;
+  const bool rows_aligned =
+      p.cols % 8 == 0 && aligned(p.W, 16) && ((size_t)p.ld * esize) % 16 == 0 && aligned(p.add, 16);
+  e.wide_store = aligned(p.mask, 16);
+  e.wide_prev = aligned(p.prev_mask, 16);
+  e.absmax_vec = rows_aligned && aligned(p.col_scale, 16);
+  // (a row of the outputs is `cols` long, a multiple of 8: 8 mask bytes and 8 weights stay aligned in every row)
+  e.emit_vec = rows_aligned && aligned(p.mask, 8) && aligned(p.prev_mask, 8) && aligned(p.pruned_out, 16);
   return e;
 }
 
@@ -325,8 +333,11 @@ int run_group(Batch& b, const Variant& v, hipStream_t stream, hipEvent_t* ev = n
     case 64: ok = launch_block_kernels<64>(b, v, stream, ev_sorted, ev_greedy); break;
   }
   if (!ok) return TSENOR_ERR_SHAPE;  // (ruled out by the checks before the first launch)
-  if (any_objective) objective_kernel<<<b.count, 1024, 0, stream>>>(b);
-  if (any_emit) emit_kernel<<<strided_grid(b, true, 2048, false), 256, 0, stream>>>(b);
+  if (any_objective) objective_kernel<<<dim3(kObjectiveGroups, (unsigned)b.count), 256, 0, stream>>>(b);
+  if (any_emit)
+    emit_kernel<<<strided_grid(b, true, 2048, false), 256, 0, stream>>>(b);
+  else if (any_objective)  // (only the sums are wanted)
+    emit_kernel<<<dim3(1, 1, (unsigned)b.count), 256, 0, stream>>>(b);
   if (any_stats) stats_kernel<<<1, 4 * kMaxBatch, 0, stream>>>(b);
   mark(4);
   return hip_status_of_launches();

@@ -1,0 +1,57 @@
+"""The outputs derived from the final mask, on buffers that allow 8-weight accesses and on ones that do not."""
+import numpy as np
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+
+def _at(torch, dev, shape, dtype, offset):
+    """A contiguous tensor `offset` elements into a buffer that is itself 256-byte aligned."""
+    n = int(np.prod(shape))
+    return torch.zeros(n + offset, dtype=dtype, device=dev)[offset:].view(shape)
+
+
+@pytest.mark.parametrize("offset", [0, 1])
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("M", [4, 8, 16, 32])
+def test_derived_outputs_at_every_alignment(M, dtype, offset):
+    # offset 1: no buffer is aligned for a wide access.  The previous mask is once worse than any found one (it keeps the
+    # lightest weights) and once better (the mask found under its own importance, scored against a found mask of T = 0 with
+    # the printed swap rule, which may leave rows short).
+    import torch
+
+    from paper_2505_23949_amd import binding as b
+
+    dev = torch.device("cuda:0")
+    N, rows, cols = M // 2, 5 * M, 24 * M
+    rng = np.random.Generator(np.random.Philox(40 + M))
+    tdt = torch.float32 if dtype == "f32" else torch.bfloat16
+    W, V = (_at(torch, dev, (rows, cols), tdt, offset) for _ in range(2))
+    W.copy_(torch.from_numpy(rng.standard_normal((rows, cols), dtype=np.float32)))
+    V.copy_(torch.from_numpy(0.3 * rng.standard_normal((rows, cols), dtype=np.float32)))
+    x = W.float().cpu().numpy() + np.float32(0.5) * V.float().cpu().numpy()
+    imp = (np.abs(x) * np.abs(x)).astype(np.float32)
+    kw = dict(add=V, add_scale=0.5, importance=b.TSENOR_IMPORTANCE_SQUARE, tau_mode=b.TSENOR_TAU_REL_MATRIX_MAX)
+    good = b.solve(W, N, M, 0.01, 200, **kw)["mask"]
+    for prev_better in (False, True):
+        print(f"[case] outputs {M} {dtype} offset={offset} prev_better={prev_better}", flush=True)
+        mask, prev, packed, pruned, plain = (_at(torch, dev, (rows, c), t, offset) for c, t in (
+            (cols, torch.uint8), (cols, torch.uint8), (cols // 8, torch.uint8), (cols, tdt), (cols, torch.uint8)))
+        objective = torch.zeros(2, dtype=torch.float64, device=dev)
+        T, flags = (0, b.TSENOR_FLAG_STRICT_PAPER) if prev_better else (200, 0)
+        prev.copy_(good if prev_better else torch.from_numpy((imp < np.median(imp)).astype(np.uint8)))
+        for prev_mask, out, extra in ((None, plain, {}), (prev, mask, dict(packed_out=packed, pruned_out=pruned, objective_out=objective))):
+            p = b.make_problem(W, N, M, 0.01, T, mask=out, prev_mask=prev_mask, flags=flags, **kw, **extra)
+            b.tsenor_mask_ex(p, torch.empty(b.tsenor_workspace_bytes([p]), dtype=torch.uint8, device=dev))
+        torch.cuda.synchronize()
+        mine, theirs = (float((imp.astype(np.float64) * m.cpu().numpy()).sum()) for m in (plain, prev))
+        assert (theirs > mine) == prev_better, "the case should decide as it says"
+        want = (prev if prev_better else plain).cpu().numpy()
+        assert np.array_equal(mask.cpu().numpy(), want)
+        assert np.array_equal(packed.cpu().numpy(), np.packbits(want, axis=1, bitorder="little"))
+        kept = torch.from_numpy(np.where(want != 0, x, np.float32(0))).to(tdt)
+        assert torch.equal(pruned.cpu(), kept)
+        # the importance terms are the same numbers on both sides; the two sums of `size` of them differ by their order
+        bar = imp.size * 2.0 ** -53
+        got = objective.cpu().numpy()
+        assert abs(got[0] - max(mine, theirs)) <= bar * got[0] and abs(got[1] - theirs) <= bar * theirs

@@ -101,7 +101,7 @@ enum {
   /* How the Dykstra kernel spreads a block over lanes.  Same arithmetic, same results up to the order of
    * the additions inside a row or column sum (~1e-15).  LARGE tiles: 32 entries per lane (16 for M <= 8),
    * fewest instructions per entry: best for full matrices.  SMALL tiles (M <= 32, iters > 0, not with
-   * TSENOR_FLAG_SIMPLE_ROUNDING; ignored otherwise): 16 entries per lane (4 for M <= 8),
+   * TSENOR_FLAG_SIMPLE_ROUNDING; ignored otherwise): 16 entries per lane (4 for M <= 8, and for M = 16 in small matrices),
    * more lanes per block, a shorter dependent chain per iteration: best while the launch cannot fill the
    * chip anyway; on them the whole path, Algorithm 2 included, runs in one kernel (the TSENOR_FLAG_GREEDY_* choice
    * does not apply).  Default: chosen by the number of blocks of the matrix (and earlier for the large tiles when

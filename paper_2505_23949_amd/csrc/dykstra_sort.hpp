@@ -36,6 +36,7 @@
 #include <type_traits>
 
 #include "lanes.hpp"
+#include "launch.hpp"
 #include "problem.hpp"
 #include "rounding.hpp"
 
@@ -55,62 +56,69 @@ constexpr int ilog2(int x) { return x <= 1 ? 0 : 1 + ilog2(x / 2); }
 // Per-M tiling.  XM[s] / YM[s]: lane masks of the exchange steps along a lane-row / lane-column.
 // The top bit of XM[s] is lane bit NX-1-s (mirror masks keep the exchanges on DPP); YM[s] is a single
 // lane bit, listed cheapest mechanism first because the first step moves the most registers.
-// SMALL: a finer tiling (more lanes per block, fewer entries per lane) for launches that cannot fill the
+// Small tiles: a finer tiling (more lanes per block, fewer entries per lane) for launches that cannot fill the
 // chip anyway: the dependent chain of an iteration is shorter.  Where a tile has fewer rows than the
 // lane-row has lanes, the last exchange steps of a reduction have no registers left to split: they add the
 // partner's value into the same register instead (both lanes end up owning the same sum).
-template <int M, bool SMALL = false>
+// kFinestTiles: a 16 x 16 block on a whole wave, for launches that leave SIMDs without a wave even so.
+template <int M, int TILES = kLargeTiles>
 struct Tiling;
 template <>
-struct Tiling<4, false> {
+struct Tiling<4, kLargeTiles> {
   static constexpr int NX = 0, NY = 0;
   static constexpr int XM[1] = {1}, YM[1] = {1};
   static constexpr bool STORE_E = true;
 };
 template <>
-struct Tiling<8, false> {
+struct Tiling<8, kLargeTiles> {
   static constexpr int NX = 1, NY = 1;
   static constexpr int XM[1] = {1}, YM[1] = {2};
   static constexpr bool STORE_E = true;
 };
 template <>
-struct Tiling<16, false> {
+struct Tiling<16, kLargeTiles> {
   static constexpr int NX = 2, NY = 1;  // 8 lanes per block, 8 x 4 tiles
   static constexpr int XM[2] = {3, 1}, YM[1] = {4};
   static constexpr bool STORE_E = true;
 };
 template <>
-struct Tiling<32, false> {
+struct Tiling<32, kLargeTiles> {
   static constexpr int NX = 3, NY = 2;  // 32 lanes per block, 8 x 4 tiles
   static constexpr int XM[3] = {7, 3, 1}, YM[2] = {8, 16};
   static constexpr bool STORE_E = true;
 };
 template <>
-struct Tiling<64, false> {
+struct Tiling<64, kLargeTiles> {
   static constexpr int NX = 3, NY = 3;  // 64 lanes per block, 8 x 8 tiles; too large to hold e as doubles
   static constexpr int XM[3] = {7, 3, 1}, YM[3] = {8, 16, 32};
   static constexpr bool STORE_E = false;
 };
 template <>
-struct Tiling<4, true> {
+struct Tiling<4, kSmallTiles> {
   static constexpr int NX = 1, NY = 1;  // 4 lanes per block, 2 x 2 tiles
   static constexpr int XM[1] = {1}, YM[1] = {2};
   static constexpr bool STORE_E = true;
 };
 template <>
-struct Tiling<8, true> {
+struct Tiling<8, kSmallTiles> {
   static constexpr int NX = 2, NY = 2;  // 16 lanes per block, 2 x 2 tiles
   static constexpr int XM[2] = {3, 1}, YM[2] = {8, 4};
   static constexpr bool STORE_E = true;
 };
 template <>
-struct Tiling<16, true> {
+struct Tiling<16, kSmallTiles> {
   static constexpr int NX = 2, NY = 2;  // 16 lanes per block, 4 x 4 tiles
   static constexpr int XM[2] = {3, 1}, YM[2] = {8, 4};
   static constexpr bool STORE_E = true;
 };
 template <>
-struct Tiling<32, true> {
+struct Tiling<16, kFinestTiles> {
+  static constexpr int NX = 3, NY = 3;  // 64 lanes per block, 2 x 2 tiles
+  static constexpr int XM[3] = {7, 3, 1}, YM[3] = {8, 16, 32};
+  static constexpr bool STORE_E = true;
+};
+template <>
+struct Tiling<32, kSmallTiles> {
   static constexpr int NX = 3, NY = 3;  // 64 lanes per block, 4 x 4 tiles
   static constexpr int XM[3] = {7, 3, 1}, YM[3] = {8, 16, 32};
   static constexpr bool STORE_E = true;
@@ -487,8 +495,6 @@ __device__ __forceinline__ void sort_half_cleaners(double (&c)[E], int q) {
       sort_resign<SB, lm>(c, q);
 #pragma unroll
       for (int r = 0; r < E; ++r) c[r] = min_with_negated(c[r], lane_xor<lm>(c[r]));
-      // with 64 keys per lane the scheduler otherwise starts the next stage's exchanges early and spills them
-      if constexpr (E >= 64) __builtin_amdgcn_sched_barrier(0);
       sort_half_cleaners<E, LPB, J / 2, lm>(c, q);
     }
   } else {
@@ -516,7 +522,6 @@ __device__ __forceinline__ void sort_ascending(double (&c)[E], int q) {
         c[r] = min_with_negated(c[r], o_lo);
         c[E - 1 - r] = min_with_negated(c[E - 1 - r], o_hi);
       }
-      if constexpr (E >= 64) __builtin_amdgcn_sched_barrier(0);
       sort_half_cleaners<E, LPB, K / 4, bit>(c, q);
     }
     sort_ascending<E, LPB, K * 2>(c, q);
@@ -532,12 +537,12 @@ __device__ __forceinline__ void row_chunks(F& f) {
   }
 }
 
-template <int M, bool FAST, bool ADAPT = false, bool SMALL = false>
+template <int M, bool FAST, bool ADAPT = false, int TILES = kLargeTiles>
 struct DykstraLaunch {
   // with the early exit the waves of a launch run for very different times; one-wave workgroups let the
   // dispatcher refill every wave slot as it frees (a four-wave workgroup holds its slots until its slowest wave).
   // The small tiles carry the rounding behind the iterations, whose steps synchronise one wave at a time.
-  static constexpr int kWavesPerGroup = (ADAPT || SMALL) ? 1 : 4;
+  static constexpr int kWavesPerGroup = (ADAPT || TILES != kLargeTiles) ? 1 : 4;
   static constexpr int kThreads = kWavesPerGroup * kWave;
   // Waves per SIMD the register budget is set for.  Double: the loop holds twice the state of the fp32 one, two waves of up
   // to 256 registers.  FAST: the more waves, the nearer the issue of plain fp32 instructions comes to its limit (1.13 ns
@@ -552,14 +557,15 @@ struct DykstraLaunch {
 
 // ZERO_T: the instantiation for T = 0 (no iterations, keys are K itself).  It is a template parameter
 // rather than a branch because keeping both paths in one kernel costs the iterating path ~40 registers.
-// SMALL: the finer tiling, for launches that cannot fill the chip.  There the whole path stays in this kernel:
-// a block lives in one wave from its tile load to its mask, so the sorted scan order goes to LDS instead of the
-// workspace and Algorithm 2 (greedy selection with M lanes per block, local search, mask write) runs behind the
-// sort; no further kernel follows.
-template <int M, bool FAST, bool ZERO_T = false, bool SMALL = false, bool ADAPT = false>
-__global__ __launch_bounds__((DykstraLaunch<M, FAST, ADAPT, SMALL>::kThreads), (DykstraLaunch<M, FAST, ADAPT, SMALL>::kWavesPerSimd)) void dykstra_sort_kernel(
+// TILES: the finer tilings are for launches that cannot fill the chip.  There the whole path stays in this kernel: a block
+// lives in one wave from its tile load to its mask, what Algorithm 2 starts from (the potentials for M >= 16, the sorted scan
+// order below) goes to LDS instead of the workspace, and Algorithm 2 runs behind; no further kernel follows.  (4096 x 32,
+// 16:32, T = 300: 120 us a call with a sort across the lanes and the scan of its result, 106 with round_blocks.)
+template <int M, bool FAST, bool ZERO_T = false, int TILES = kLargeTiles, bool ADAPT = false>
+__global__ __launch_bounds__((DykstraLaunch<M, FAST, ADAPT, TILES>::kThreads), (DykstraLaunch<M, FAST, ADAPT, TILES>::kWavesPerSimd)) void dykstra_sort_kernel(
     Batch batch) {
-  using T = Tiling<M, SMALL>;
+  using T = Tiling<M, TILES>;
+  constexpr bool SMALL = TILES != kLargeTiles;
   const int which = find_problem(batch, blockIdx.x);
   const DevProblem p = batch.e[which].p;
   unsigned short* order = batch.e[which].order;
@@ -567,7 +573,7 @@ __global__ __launch_bounds__((DykstraLaunch<M, FAST, ADAPT, SMALL>::kThreads), (
   double* tau_eff_out = batch.e[which].tau_eff_out;
   const unsigned int group = blockIdx.x - batch.first[which];  // workgroup index within the matrix
   constexpr int GX = 1 << T::NX, GY = 1 << T::NY, TH = M / GY, TW = M / GX, LPB = GX * GY, BPW = kWave / LPB,
-                E = TH * TW, SHX = ilog2(TH) - T::NX, WPG = DykstraLaunch<M, FAST, ADAPT, SMALL>::kWavesPerGroup;
+                E = TH * TW, SHX = ilog2(TH) - T::NX, WPG = DykstraLaunch<M, FAST, ADAPT, TILES>::kWavesPerGroup;
   const int lane = threadIdx.x & (kWave - 1), wave_in_group = threadIdx.x / kWave;
   const int64_t wave = (int64_t)group * WPG + wave_in_group;
   const int q = lane % LPB, gx = q % GX, gy = q / GX;
@@ -605,9 +611,11 @@ __global__ __launch_bounds__((DykstraLaunch<M, FAST, ADAPT, SMALL>::kThreads), (
   // tiles of M = 64 would keep 64 loads with their addresses in flight and spill
   constexpr int NA = M == 64 ? TH / kRowChunks64 : (FAST && TH >= 8) ? TH / 2 : TH;
 
-  // Blocks of 16 and more on the large tiles leave their potentials to round_kernel; the others are sorted here
-  constexpr bool kPotentials = M >= 16 && !SMALL;
+  // Blocks of 16 and more are rounded from their potentials (in a kernel of their own for the large tiles), smaller ones
+  // from the order of their entries, which are sorted here
+  constexpr bool kPotentials = M >= 16;
   [[maybe_unused]] double c[kPotentials ? 1 : E];  // sort keys
+  __shared__ double pot[2][kPotentials && SMALL ? BPW : 1][M];  // small tiles: potentials of the matrix rows and columns
   int iters_done = 0;
   double kap[ZERO_T ? 1 : TH][ZERO_T ? 1 : TW];
   // Normaliser of every in-kernel row: kappa = exp(K - mrow) <= ~1.  Any per-row constant gives the same
@@ -847,73 +855,87 @@ __global__ __launch_bounds__((DykstraLaunch<M, FAST, ADAPT, SMALL>::kThreads), (
 
     const int rx2 = fresh(rx), ry2 = fresh(ry);
     if constexpr (kPotentials) {
-      if (group == 0 && threadIdx.x == 0) batch.e[which].hdr->tau_eff = tau_eff;
-      if (active) {
-        // every row and column of the block has one owner among its lanes
-        static_assert(TH >= GX && TW >= GY, "one owner");
-        BlockPotentials<M>* out = reinterpret_cast<BlockPotentials<M>*>(order) + blk;
+      // every row and column of the block has an owner among its lanes (on fine tiles several, with the same values)
+      if constexpr (SMALL) {
 #pragma unroll
-        for (int a = 0; a < OWN_R; ++a) out->u[gy * TH + (a ^ rx2)] = lu_own[a] - (double)mrow[a];
+        for (int a = 0; a < OWN_R; ++a)
+          pot[p.transpose ? 1 : 0][lane / LPB][gy * TH + (a ^ rx2)] = lu_own[a] - (double)mrow[a];
 #pragma unroll
-        for (int b = 0; b < OWN_C; ++b) out->v[gx * TW + (b ^ ry2)] = lv_own[b];
-        if (q == 0 && batch.e[which].iters_done_out) batch.e[which].iters_done_out[blk] = iters_done;
+        for (int b = 0; b < OWN_C; ++b) pot[p.transpose ? 0 : 1][lane / LPB][gx * TW + (b ^ ry2)] = lv_own[b];
+      } else {
+        if (group == 0 && threadIdx.x == 0) batch.e[which].hdr->tau_eff = tau_eff;
+        if (active) {
+          BlockPotentials<M>* out = reinterpret_cast<BlockPotentials<M>*>(order) + blk;
+#pragma unroll
+          for (int a = 0; a < OWN_R; ++a) out->u[gy * TH + (a ^ rx2)] = lu_own[a] - (double)mrow[a];
+#pragma unroll
+          for (int b = 0; b < OWN_C; ++b) out->v[gx * TW + (b ^ ry2)] = lv_own[b];
+        }
       }
-      if (!plan_out) return;
+      if (active && q == 0 && batch.e[which].iters_done_out) batch.e[which].iters_done_out[blk] = iters_done;
     }
-    double lu[TH], lv[TW];
+    if (!kPotentials || plan_out) {
+      double lu[TH], lv[TW];
 #pragma unroll
-    for (int a = 0; a < OWN_R; ++a) lu[a] = lu_own[a];
+      for (int a = 0; a < OWN_R; ++a) lu[a] = lu_own[a];
 #pragma unroll
-    for (int b = 0; b < OWN_C; ++b) lv[b] = lv_own[b];
-    all_gather_x<T, double, TH>(lu);
-    all_gather_y<T, double, TW>(lv);
-    const auto addr = addr_of(rx2, ry2);
-    // K + f_i + g_j, of which log S^(T) is the minimum with 0
-    // (K is not floored here as it is for kappa: entries too small for the iterations to see keep
-    // their own order in the scan)
-    auto log_plan = [&](float importance, int a, int b) {
-      const double K = tau_eff * (double)importance;
-      return (K - (double)mrow[a]) + (lu[a] + lv[b]);
-    };
-    // the plan (a diagnostic output) in a pass of its own, with its own loads: an exp() inside the key pass
-    // costs it registers (spills for M = 64)
-    if (plan_out && active) {
-      auto plan_rows = [&](auto first) {
-        constexpr int A0 = decltype(first)::value;
-        float imp[NA][TW];
-        tile_importance<A0, NA>(p, addr, imp);
-#pragma unroll
-        for (int a = 0; a < NA; ++a)
-#pragma unroll
-          for (int b = 0; b < TW; ++b) {
-            const int ri = gy * TH + ((A0 + a) ^ rx2), cj = gx * TW + (b ^ ry2);
-            plan_out[(r0 + mat_row(ri, cj)) * p.cols + c0 + mat_col(ri, cj)] = exp(fmin(log_plan(imp[a][b], A0 + a, b), 0.0));
-            __builtin_amdgcn_sched_barrier(0);
-          }
+      for (int b = 0; b < OWN_C; ++b) lv[b] = lv_own[b];
+      all_gather_x<T, double, TH>(lu);
+      all_gather_y<T, double, TW>(lv);
+      const auto addr = addr_of(rx2, ry2);
+      // K + f_i + g_j, of which log S^(T) is the minimum with 0
+      // (K is not floored here as it is for kappa: entries too small for the iterations to see keep
+      // their own order in the scan)
+      auto log_plan = [&](float importance, int a, int b) {
+        const double K = tau_eff * (double)importance;
+        return (K - (double)mrow[a]) + (lu[a] + lv[b]);
       };
-      row_chunks<0, NA, TH>(plan_rows);
-    }
-    if constexpr (!kPotentials) {
-      auto rows = [&](auto first) {
-        constexpr int A0 = decltype(first)::value;
-        float imp[NA][TW];
-        tile_importance<A0, NA>(p, addr, imp);
+      // the plan (a diagnostic output) in a pass of its own, with its own loads: an exp() inside the key pass
+      // costs it registers (spills for M = 64)
+      if (plan_out && active) {
+        auto plan_rows = [&](auto first) {
+          constexpr int A0 = decltype(first)::value;
+          float imp[NA][TW];
+          tile_importance<A0, NA>(p, addr, imp);
 #pragma unroll
-        for (int a = 0; a < NA; ++a)
+          for (int a = 0; a < NA; ++a)
 #pragma unroll
-          for (int b = 0; b < TW; ++b) {
-            const int ri = gy * TH + ((A0 + a) ^ rx2), cj = gx * TW + (b ^ ry2);
-            c[(A0 + a) * TW + b] = scan_key(log_plan(imp[a][b], A0 + a, b), mat_row(ri, cj) * M + mat_col(ri, cj));
-          }
-      };
-      row_chunks<0, NA, TH>(rows);
+            for (int b = 0; b < TW; ++b) {
+              const int ri = gy * TH + ((A0 + a) ^ rx2), cj = gx * TW + (b ^ ry2);
+              plan_out[(r0 + mat_row(ri, cj)) * p.cols + c0 + mat_col(ri, cj)] = exp(fmin(log_plan(imp[a][b], A0 + a, b), 0.0));
+              __builtin_amdgcn_sched_barrier(0);
+            }
+        };
+        row_chunks<0, NA, TH>(plan_rows);
+      }
+      if constexpr (!kPotentials) {
+        auto rows = [&](auto first) {
+          constexpr int A0 = decltype(first)::value;
+          float imp[NA][TW];
+          tile_importance<A0, NA>(p, addr, imp);
+#pragma unroll
+          for (int a = 0; a < NA; ++a)
+#pragma unroll
+            for (int b = 0; b < TW; ++b) {
+              const int ri = gy * TH + ((A0 + a) ^ rx2), cj = gx * TW + (b ^ ry2);
+              c[(A0 + a) * TW + b] = scan_key(log_plan(imp[a][b], A0 + a, b), mat_row(ri, cj) * M + mat_col(ri, cj));
+            }
+        };
+        row_chunks<0, NA, TH>(rows);
+      }
     }
   }
-  if constexpr (!kPotentials) {
+  if constexpr (kPotentials) {
+    if constexpr (SMALL) {
+      __shared__ RoundingLds<M, BPW> lds;
+      wave_sync();
+      round_blocks<M, LPB, false>(p, batch.e[which], blk, active, r0, c0, lane, tau_eff, pot[0], pot[1], lds, false);
+    }
+  } else {
     sort_ascending<E, LPB>(c, q);
     // The stores below sit under `active`, and only the index bits of a key are stored: the compiler would move
     // the last stage's selects into that branch but has to leave its cross-lane moves outside, all of them
-    // alive at once (spills for M = 64).  Using the keys here keeps every select next to its moves.
+    // alive at once.  Using the keys here keeps every select next to its moves.
 #pragma unroll
     for (int r = 0; r < E; ++r) asm volatile("" : "+v"(c[r]));
 
@@ -927,7 +949,7 @@ __global__ __launch_bounds__((DykstraLaunch<M, FAST, ADAPT, SMALL>::kThreads), (
 #pragma unroll
       for (int r = 0; r < E; ++r)
         mine[q * E + r] = (unsigned short)((unsigned long long)__double_as_longlong(c[r]) & ((1ull << kIdxBits) - 1));
-      __syncthreads();
+      wave_sync();
       const int placed = greedy_wide_scan<M, LPB>([&](int pos) { return (unsigned int)mine[pos]; }, p.N, lane, lds);
       if (batch.e[which].stats_out) {
         int missing = (active && q == 0) ? p.N * M - placed : 0;

@@ -9,16 +9,19 @@
 
 namespace tsenor_dev {
 
+// how the Dykstra kernel spreads a block over lanes (see Tiling in dykstra_sort.hpp)
+enum { kLargeTiles, kSmallTiles, kFinestTiles };
+
 // kernel variant of a problem: problems with the same variant can share one fused launch
 struct Variant {
   int M;
   bool fast, zero_t;
   uint32_t greedy;  // the TSENOR_FLAG_GREEDY_* asked for (M <= 8)
-  bool small;       // the Dykstra kernel's small tiles (decided per problem, so that fusing never changes results)
+  int tiles;        // the Dykstra kernel's tiling (decided per problem, so that fusing never changes results)
   bool simple;      // TSENOR_FLAG_SIMPLE_ROUNDING
   bool adaptive;    // tol > 0: the early-exit instantiation of the Dykstra kernel
   bool operator==(const Variant& o) const {
-    return M == o.M && fast == o.fast && zero_t == o.zero_t && greedy == o.greedy && small == o.small &&
+    return M == o.M && fast == o.fast && zero_t == o.zero_t && greedy == o.greedy && tiles == o.tiles &&
            simple == o.simple && adaptive == o.adaptive;
   }
 };
@@ -36,6 +39,11 @@ constexpr int64_t small_tiles_below_blocks(int M, bool fp32) {
   return M == 4 ? (fp32 ? 55000 : 100000) : M == 8 ? (fp32 ? 12000 : 13000) : M == 16 ? (fp32 ? 9000 : 40000)
        : M == 32 ? (fp32 ? 2100 : 3200) : 0;
 }
+
+// Below this many blocks a 16 x 16 block has a wave of its own: 51 instead of 98 vector instructions in the chain of an
+// iteration, four times the waves.  Whole calls, T = 300 (us, finest / small tiles): 256 blocks 67 / 88, 1024 blocks
+// 73 / 89, 1536 blocks 81 / 90, 2304 blocks 104 / 90 (from three waves on a SIMD on, issue decides).
+constexpr int64_t finest_tiles_below_blocks(int M) { return M == 16 ? 1800 : 0; }
 
 // Enqueues the kernels of one fused launch that depend on M: tile load + Algorithm 1 (+ sort for M <= 8), greedy selection
 // (or the simple rounding arm), local search + mask write; the last two are one kernel for M >= 16.  `b.count`

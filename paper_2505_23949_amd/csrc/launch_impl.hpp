@@ -21,20 +21,28 @@ inline bool assign_groups(Batch& b, int64_t per_group) {
 template <int M>
 bool launch_block_kernels(Batch& b, const Variant& v, hipStream_t stream, hipEvent_t ev_sorted, hipEvent_t ev_greedy) {
   constexpr int BPW = kWave >> (Tiling<M>::NX + Tiling<M>::NY);
-  constexpr bool kHasSmall = M <= 32;
-  const bool small = kHasSmall && !v.fast && !v.zero_t && v.small;
-  if (small) {
+  if (v.tiles != kLargeTiles) {
     // the small tiles carry Algorithm 2 behind the iterations: this one kernel is the whole path
-    if constexpr (kHasSmall) {
-      constexpr int BPWS = kWave >> (Tiling<M, true>::NX + Tiling<M, true>::NY);
-      using L = DykstraLaunch<M, false, false, true>;
-      static_assert(L::kWavesPerGroup == 1 && DykstraLaunch<M, false, true, true>::kWavesPerGroup == 1, "");
+    const auto launch = [&](auto tiles) {
+      constexpr int TILES = decltype(tiles)::value;
+      constexpr int BPWS = kWave >> (Tiling<M, TILES>::NX + Tiling<M, TILES>::NY);
+      using L = DykstraLaunch<M, false, false, TILES>;
+      static_assert(L::kWavesPerGroup == 1 && DykstraLaunch<M, false, true, TILES>::kWavesPerGroup == 1, "");
       if (!assign_groups(b, (int64_t)BPWS)) return false;
       if (v.adaptive)
-        dykstra_sort_kernel<M, false, false, true, true><<<b.first[b.count], L::kThreads, 0, stream>>>(b);
+        dykstra_sort_kernel<M, false, false, TILES, true><<<b.first[b.count], L::kThreads, 0, stream>>>(b);
       else
-        dykstra_sort_kernel<M, false, false, true><<<b.first[b.count], L::kThreads, 0, stream>>>(b);
+        dykstra_sort_kernel<M, false, false, TILES><<<b.first[b.count], L::kThreads, 0, stream>>>(b);
+      return true;
+    };
+    bool ok = false;
+    if constexpr (M <= 32) {
+      if (v.tiles == kSmallTiles) ok = launch(std::integral_constant<int, kSmallTiles>{});
     }
+    if constexpr (finest_tiles_below_blocks(M) > 0) {
+      if (v.tiles == kFinestTiles) ok = launch(std::integral_constant<int, kFinestTiles>{});
+    }
+    if (!ok) return false;
     if (ev_sorted) (void)hipEventRecord(ev_sorted, stream);
     if (ev_greedy) (void)hipEventRecord(ev_greedy, stream);
     return true;

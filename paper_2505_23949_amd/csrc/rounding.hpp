@@ -8,6 +8,13 @@
 
 namespace tsenor_dev {
 
+// The rounding steps below belong to one wave each (whatever the size of its workgroup).  Its LDS accesses take effect in
+// the order they are issued; what is needed between them is that the compiler keeps that order.
+__device__ __forceinline__ void wave_sync() {
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+}
+
 // Bit masks over the M columns (or rows) of a block.
 template <int M>
 using block_mask_t = typename std::conditional<(M > 32), unsigned long long, unsigned int>::type;
@@ -190,7 +197,7 @@ struct RoundingLds {
 // few rounds instead of M*M steps.
 // A block owns LPB >= M consecutive lanes of the wave (LPB a power of two), of which the first M take part;
 // fetch(pos) returns the flat index at scan position pos of this lane's block.  Leaves the mask in lds.rowm and
-// returns the number of entries the lane's block holds.  To be called by whole single-wave workgroups.
+// returns the number of entries the lane's block holds.  To be called by whole waves.
 template <int M, int LPB, class Fetch>
 __device__ __forceinline__ int greedy_wide_scan(Fetch&& fetch, int N, int lane, RoundingLds<M, kWave / LPB>& lds) {
   using mask_t = block_mask_t<M>;
@@ -202,7 +209,7 @@ __device__ __forceinline__ int greedy_wide_scan(Fetch&& fetch, int N, int lane, 
     lds.rowm[g][ql] = 0;
     lds.colcnt[g][ql] = 0;
   }
-  __syncthreads();
+  wave_sync();
   const unsigned long long gmask = (M == 64 ? ~0ull : ((1ull << M) - 1)) << (g * LPB);
   const unsigned long long earlier = gmask & ((1ull << lane) - 1);  // lanes of this block before this one
   const int need = N * M;
@@ -244,7 +251,7 @@ __device__ __forceinline__ int greedy_wide_scan(Fetch&& fetch, int N, int lane, 
       atomicAdd(&lds.colcnt[g][j], 1u);
     }
     placed += __popcll(taken & gmask);
-    __syncthreads();
+    wave_sync();
     if (!__any(placed < need)) break;  // every block of the wave is full
   }
   return placed;
@@ -332,7 +339,7 @@ __device__ __forceinline__ double group_sum(double v) {
 // Algorithm 2 lines 7-13 and the mask write for the blocks of one wave.  A block owns LPB >= M consecutive lanes,
 // of which the first M take part: lane r owns row r and column r of the block as bit masks.  On entry lds.rowm
 // holds the mask greedy selection left.  blk: the lane's block (a valid one also for idle lanes, which write
-// nothing: `active`), at matrix position (r0, c0).  To be called by whole single-wave workgroups.
+// nothing: `active`), at matrix position (r0, c0).  To be called by whole waves.
 template <int M, int LPB>
 __device__ __forceinline__ void local_search_and_write(const DevProblem& p, const BatchEntry& e, int64_t blk, bool active,
                                                        int64_t r0, int64_t c0, int lane, RoundingLds<M, kWave / LPB>& lds) {
@@ -355,7 +362,7 @@ __device__ __forceinline__ void local_search_and_write(const DevProblem& p, cons
     const mask_t c = bit_transpose<M>(r, qm);
     if (part) lds.colm[g][qm] = c;
   }
-  __syncthreads();
+  wave_sync();
   const auto popc = [](mask_t v) { return mask_popc(v); };
   const unsigned long long gmask = (M == 64 ? ~0ull : ((1ull << M) - 1)) << (g * LPB);
   const bool any_short = __any(part && popc(lds.rowm[g][qm]) < p.N);
@@ -367,7 +374,7 @@ __device__ __forceinline__ void local_search_and_write(const DevProblem& p, cons
 #pragma unroll
     for (int k = 0; k < M; ++k) lds.imp[g][k * LD + qm] = col[k];
   }
-  __syncthreads();
+  wave_sync();
 
   int rounds = 0, nonpos = 0;
   bool open = any_short;  // this block may still take swaps
@@ -403,7 +410,7 @@ __device__ __forceinline__ void local_search_and_write(const DevProblem& p, cons
     bool apply = open && best.arg != MM;
     if (p.strict && !(best.score > 0.0)) apply = false;
     if (open && !apply) open = false;  // nothing changes any more for this block
-    __syncthreads();
+    wave_sync();
     if (apply && ql == 0) {
       // line 13: remove (i', j'), insert (i', j) and (i, j')
       const int ip = best.arg / M, jp = best.arg % M;
@@ -413,7 +420,7 @@ __device__ __forceinline__ void local_search_and_write(const DevProblem& p, cons
       lds.colm[g][j] |= one << ip;
       if (!(best.score > 0.0)) ++nonpos;
     }
-    __syncthreads();
+    wave_sync();
   }
 
   if (active && part) {
@@ -598,47 +605,25 @@ __device__ __forceinline__ int nth_set_bit(mask_t h, int N) {
   return pos;
 }
 
-// M lanes per block, 64/M blocks per wave, one wave per workgroup; lane r of a block is its row r and its column r.
-// Bound by instruction issue: of ~2 500 vector instructions per wave before the swaps (M = 32) the two sorts are 764 and
-// the keys 512.  57 344 blocks of 16:32: 0.206 ms with the swaps, where the sort across lanes (0.20 ms of the iteration
-// kernel), the scan kernel (0.077 ms) and the swap kernel (0.104 ms) took 0.38 ms; 16 384 blocks of 32:64: 0.34 ms for 0.78.
-template <int M, bool ZERO_T>
-__global__ __launch_bounds__(kWave, M <= 32 ? 4 : 2) void round_kernel(Batch batch, int simple) {
+// Algorithm 2 for the blocks of one wave.  A block owns LPB >= M consecutive lanes; lane r of the first M is its row r and
+// its column r, further ones repeat what lane r % M does.  blk: the lane's block (a valid one also for idle lanes, which
+// write nothing: `active`), at matrix position (r0, c0).  row_pot, col_pot (LDS, T > 0): the potentials of the matrix rows
+// and columns of the wave's blocks.  To be called by whole waves.
+template <int M, int LPB, bool ZERO_T>
+__device__ __forceinline__ void round_blocks(const DevProblem& p, const BatchEntry& e, int64_t blk, bool active, int64_t r0,
+                                             int64_t c0, int lane, double tau_eff, const double (*row_pot)[M],
+                                             const double (*col_pot)[M], RoundingLds<M, kWave / LPB>& lds, bool simple) {
   using mask_t = block_mask_t<M>;
-  constexpr int G = kWave / M, LOGM = M == 16 ? 4 : M == 32 ? 5 : 6, LD = RoundingLds<M, G>::kImpLd;
-  __shared__ RoundingLds<M, G> lds;
-  __shared__ double row_pot[ZERO_T ? 1 : G][M], col_pot[ZERO_T ? 1 : G][M];  // potentials of the matrix rows and columns
-  const int which = find_problem(batch, blockIdx.x);
-  const BatchEntry& e = batch.e[which];
-  const DevProblem p = e.p;
-  const int lane = threadIdx.x, g = lane / M, ql = lane % M, N = p.N;
-  const unsigned int group = blockIdx.x - batch.first[which];
-  int64_t blk = (int64_t)group * G + g;
-  const bool active = blk < p.nblocks;
-  if (!active) blk = p.nblocks - 1;  // idle groups shadow the last block and write nothing
-  const BlockAt at = block_at(p, blk, M);
-  const int64_t r0 = at.r0, c0 = at.c0;
-
-  // the importance of the block, a column per lane (coalesced), and the potentials: into LDS
+  constexpr int LOGM = M == 16 ? 4 : M == 32 ? 5 : 6, LD = RoundingLds<M, kWave / LPB>::kImpLd;
+  const int g = lane / LPB, ql = lane % M, N = p.N;
+  // the importance of the block, a column per lane (coalesced), into LDS
   {
     float col[M];
     block_column_importance<M>(p, r0, c0 + ql, col);
 #pragma unroll
     for (int k = 0; k < M; ++k) lds.imp[g][k * LD + ql] = col[k];
   }
-  double tau_eff;
-  if constexpr (ZERO_T) {
-    tau_eff = tau_eff_of(e);
-    if (e.tau_eff_out && group == 0 && lane == 0) *e.tau_eff_out = tau_eff;
-    if (active && ql == 0 && e.iters_done_out) e.iters_done_out[blk] = 0;
-  } else {
-    tau_eff = e.hdr->tau_eff;
-    const BlockPotentials<M>* src = reinterpret_cast<const BlockPotentials<M>*>(e.order) + blk;
-    const double of_row = src->u[ql], of_col = src->v[ql];
-    row_pot[g][ql] = p.transpose ? of_col : of_row;
-    col_pot[g][ql] = p.transpose ? of_row : of_col;
-  }
-  __syncthreads();
+  wave_sync();
 
   // keys of the entries of this lane's row (ROWS) or column
   double c[M];
@@ -676,7 +661,7 @@ __global__ __launch_bounds__(kWave, M <= 32 ? 4 : 2) void round_kernel(Batch bat
   // this lane's column in scan order
   keys(no{});
   sort_in_lane(c);
-  __syncthreads();
+  wave_sync();
 
   // From here the space of the importance holds three byte tables per block (rows padded by a word so that a lane per
   // row meets no other in a bank): rank of entry (i, j) within column j, the columns of row i in scan order, the rows
@@ -703,7 +688,7 @@ __global__ __launch_bounds__(kWave, M <= 32 ? 4 : 2) void round_kernel(Batch bat
   // lds.colcnt[j]: entries of a higher rank than this one it would turn away
   const mask_t one = 1;
   lds.colm[g][ql] = 0;
-  __syncthreads();
+  wave_sync();
   mask_t held = 0;
   {
     unsigned int cr[M];
@@ -720,7 +705,7 @@ __global__ __launch_bounds__(kWave, M <= 32 ? 4 : 2) void round_kernel(Batch bat
   lds.rowm[g][ql] = held;
   int next = N;  // the first place of its order this row has not proposed
   for (;;) {
-    __syncthreads();
+    wave_sync();
     const mask_t h = lds.colm[g][ql];
     mask_t surplus = 0;
     int limit = M;
@@ -735,7 +720,7 @@ __global__ __launch_bounds__(kWave, M <= 32 ? 4 : 2) void round_kernel(Batch bat
       surplus &= surplus - 1;
       atomicAnd(&lds.rowm[g][rows_of[ql * LDB + at]], ~(one << ql));
     }
-    __syncthreads();
+    wave_sync();
     held = lds.rowm[g][ql];
     int lacks = simple ? 0 : N - mask_popc(held);
     bool proposed = false;
@@ -754,12 +739,45 @@ __global__ __launch_bounds__(kWave, M <= 32 ? 4 : 2) void round_kernel(Batch bat
     if (!__any(proposed)) break;
   }
   if (e.stats_out) {
-    int missing = active ? N - mask_popc(held) : 0;
+    int missing = active && lane % LPB < M ? N - mask_popc(held) : 0;
     for (int s = 1; s < kWave; s <<= 1) missing += __shfl_xor(missing, s, kWave);
     if (lane == 0 && missing) atomicAdd(&e.hdr->stats[0], (unsigned long long)missing);
   }
-  __syncthreads();
-  local_search_and_write<M, M>(p, e, blk, active, r0, c0, lane, lds);
+  wave_sync();
+  local_search_and_write<M, LPB>(p, e, blk, active, r0, c0, lane, lds);
+}
+
+// The stand-alone kernel: 64/M blocks per wave, one wave per workgroup; the potentials come from the workspace.
+// Bound by instruction issue: of ~2 500 vector instructions per wave before the swaps (M = 32) the two sorts are 764 and
+// the keys 512.  57 344 blocks of 16:32: 0.206 ms with the swaps, where the sort across lanes (0.20 ms of the iteration
+// kernel), the scan kernel (0.077 ms) and the swap kernel (0.104 ms) took 0.38 ms; 16 384 blocks of 32:64: 0.34 ms for 0.78.
+template <int M, bool ZERO_T>
+__global__ __launch_bounds__(kWave, M <= 32 ? 4 : 2) void round_kernel(Batch batch, int simple) {
+  constexpr int G = kWave / M;
+  __shared__ RoundingLds<M, G> lds;
+  __shared__ double row_pot[ZERO_T ? 1 : G][M], col_pot[ZERO_T ? 1 : G][M];
+  const int which = find_problem(batch, blockIdx.x);
+  const BatchEntry& e = batch.e[which];
+  const DevProblem p = e.p;
+  const int lane = threadIdx.x, g = lane / M, ql = lane % M;
+  const unsigned int group = blockIdx.x - batch.first[which];
+  int64_t blk = (int64_t)group * G + g;
+  const bool active = blk < p.nblocks;
+  if (!active) blk = p.nblocks - 1;  // idle groups shadow the last block and write nothing
+  const BlockAt at = block_at(p, blk, M);
+  double tau_eff;
+  if constexpr (ZERO_T) {
+    tau_eff = tau_eff_of(e);
+    if (e.tau_eff_out && group == 0 && lane == 0) *e.tau_eff_out = tau_eff;
+    if (active && ql == 0 && e.iters_done_out) e.iters_done_out[blk] = 0;
+  } else {
+    tau_eff = e.hdr->tau_eff;
+    const BlockPotentials<M>* src = reinterpret_cast<const BlockPotentials<M>*>(e.order) + blk;
+    const double of_row = src->u[ql], of_col = src->v[ql];
+    row_pot[g][ql] = p.transpose ? of_col : of_row;
+    col_pot[g][ql] = p.transpose ? of_row : of_col;
+  }
+  round_blocks<M, M, ZERO_T>(p, e, blk, active, at.r0, at.c0, lane, tau_eff, row_pot, col_pot, lds, simple != 0);
 }
 
 }  // namespace tsenor_dev

@@ -36,3 +36,24 @@ def test_rounding_of_whole_blocks(M, share):
                               cols_first=flags == b.TSENOR_FLAG_COLS_FIRST, strict_paper=flags == b.TSENOR_FLAG_STRICT_PAPER)
             assert np.array_equal(res["mask"].cpu().numpy(), ref["mask"])
             assert np.array_equal(res["stats"].cpu().numpy(), ref["stats"])
+
+
+@pytest.mark.parametrize("blocks", [(1, 1), (30, 59), (30, 61)])
+def test_fine_tilings_of_16_wide_blocks(blocks):
+    # one block, and the two sides of the line (1800 blocks) below which a block has a wave of its own
+    import torch
+
+    from paper_2505_23949_amd import binding as b
+
+    dev = torch.device("cuda:0")
+    W = np.random.Generator(np.random.Philox(5)).standard_normal((blocks[0] * 16, blocks[1] * 16), dtype=np.float32)
+    for cols_first in (False, True):
+        print(f"[case] fine tiles {blocks} cols_first={cols_first}", flush=True)
+        res = b.solve(torch.from_numpy(W).to(dev), 7, 16, 0.01, 60, tau_mode=b.TSENOR_TAU_REL_MATRIX_MAX, want_plan=True, want_stats=True,
+                      flags=b.TSENOR_FLAG_COLS_FIRST if cols_first else 0)
+        torch.cuda.synchronize()
+        ref = oracle.mask(W, 7, 16, 0.01, 60, tau_mode=synth.TAU_REL_MATRIX_MAX, cols_first=cols_first, return_plan=True)
+        # 1e-9: what the parity tests ask of a plan computed in double on both sides
+        assert np.abs(res["plan"].cpu().numpy() - np.exp(ref["log_S"])).max() <= 1e-9
+        assert np.array_equal(res["mask"].cpu().numpy(), ref["mask"])
+        assert np.array_equal(res["stats"].cpu().numpy(), ref["stats"])

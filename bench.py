@@ -60,8 +60,8 @@ LOOP_VALU_PER_WAVE_ITER = {
 }
 # a matrix with fewer blocks than this runs the small-tile instantiation (the library's own choice, mirrored here
 # only to pick the row of the table above)
-SMALL_TILES_BELOW_BLOCKS = {False: {4: 100000, 8: 13000, 16: 40000, 32: 3200, 64: 0},     # default mode
-                            True: {4: 55000, 8: 12000, 16: 9000, 32: 2100, 64: 0}}         # with the fp32 flag
+SMALL_TILES_BELOW_BLOCKS = {False: {4: 100000, 8: 13000, 16: 40000, 32: 3200, 64: 257},     # default mode
+                            True: {4: 55000, 8: 12000, 16: 9000, 32: 2100, 64: 257}}         # with the fp32 flag
 
 
 def recorded_traffic(workload: str, fp32: bool):

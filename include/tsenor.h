@@ -89,12 +89,12 @@ enum {
    * double-precision evaluation to ~1e-5 instead of ~1e-13, and the greedy order - hence the mask - can
    * differ from it in a block where two plan entries are closer than that (none in 8192 blocks of the
    * 16:32 test workload).  Sort keys, swap scores and all results stay in double.  Off by default.  A matrix that
-   * runs on the small tiles (below) iterates in double whatever this flag says: such a launch is bound by latency,
+   * runs on the small tiles or on a workgroup per block (below) iterates in double whatever this flag says: such a launch is bound by latency,
    * not by instruction issue, and single precision would buy nothing. */
   TSENOR_FLAG_FP32_ITERATIONS = 1u << 2,
-  /* Which kernel runs the greedy selection (Algorithm 2 lines 1-6) for M <= 8 on the large tiles.  Both give the same
+  /* Which kernel runs the greedy selection (Algorithm 2 lines 1-6) for M = 4 on the large tiles.  Both give the same
    * mask.  One takes one lane per block (the default: never slower), the other M lanes per block and decides M scan
-   * entries per step.  For M >= 16 the selection is part of the one rounding kernel and the flags change nothing.
+   * entries per step.  For M >= 8 the selection is part of the one rounding kernel and the flags change nothing.
    * Setting both is an error. */
   TSENOR_FLAG_GREEDY_ONE_LANE = 1u << 3,
   TSENOR_FLAG_GREEDY_M_LANES = 1u << 4,
@@ -104,7 +104,8 @@ enum {
    * TSENOR_FLAG_SIMPLE_ROUNDING; ignored otherwise): 16 entries per lane (4 for M <= 8, and for M = 16 in small matrices),
    * more lanes per block, a shorter dependent chain per iteration: best while the launch cannot fill the
    * chip anyway; on them the whole path, Algorithm 2 included, runs in one kernel (the TSENOR_FLAG_GREEDY_* choice
-   * does not apply).  Default: chosen by the number of blocks of the matrix (and earlier for the large tiles when
+   * does not apply).  A few 64 x 64 blocks (fewer than 257) get a workgroup each, in one kernel as well, unless LARGE is
+   * asked for.  Default: chosen by the number of blocks of the matrix (and earlier for the large tiles when
    * TSENOR_FLAG_FP32_ITERATIONS is set, which only they honour).  Setting both is an error. */
   TSENOR_FLAG_TILES_LARGE = 1u << 5,
   TSENOR_FLAG_TILES_SMALL = 1u << 6,

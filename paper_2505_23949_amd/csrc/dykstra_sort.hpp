@@ -1,5 +1,6 @@
-// Tile load and Algorithm 1 (Dykstra iterations), one kernel.  For M >= 16 on the large tiles it leaves the potentials of
-// every block for round_kernel; for M <= 8 and on the small tiles the sort that feeds Algorithm 2 follows here.
+// Tile load and Algorithm 1 (Dykstra iterations), one kernel.  For M >= 8 on the large tiles it leaves the potentials of
+// every block for round_kernel; for M = 4 there the sort that feeds Algorithm 2 follows; on the small tiles the whole of
+// Algorithm 2 does.
 //
 // How Algorithm 1 is evaluated.  With A = log S + log Q, the cap step (lines 5-6) gives
 // log S = min(A, 0) and log Q = max(A, 0) after every iteration, and one iteration adds a row term
@@ -558,9 +559,9 @@ struct DykstraLaunch {
 // ZERO_T: the instantiation for T = 0 (no iterations, keys are K itself).  It is a template parameter
 // rather than a branch because keeping both paths in one kernel costs the iterating path ~40 registers.
 // TILES: the finer tilings are for launches that cannot fill the chip.  There the whole path stays in this kernel: a block
-// lives in one wave from its tile load to its mask, what Algorithm 2 starts from (the potentials for M >= 16, the sorted scan
-// order below) goes to LDS instead of the workspace, and Algorithm 2 runs behind; no further kernel follows.  (4096 x 32,
-// 16:32, T = 300: 120 us a call with a sort across the lanes and the scan of its result, 106 with round_blocks.)
+// lives in one wave from its tile load to its mask, the potentials that Algorithm 2 starts from go to LDS instead of the
+// workspace, and Algorithm 2 runs behind; no further kernel follows.  (4096 x 32, 16:32, T = 300: 120 us a call with a sort
+// across the lanes and the scan of its result, 106 with round_blocks.)
 template <int M, bool FAST, bool ZERO_T = false, int TILES = kLargeTiles, bool ADAPT = false>
 __global__ __launch_bounds__((DykstraLaunch<M, FAST, ADAPT, TILES>::kThreads), (DykstraLaunch<M, FAST, ADAPT, TILES>::kWavesPerSimd)) void dykstra_sort_kernel(
     Batch batch) {
@@ -611,9 +612,10 @@ __global__ __launch_bounds__((DykstraLaunch<M, FAST, ADAPT, TILES>::kThreads), (
   // tiles of M = 64 would keep 64 loads with their addresses in flight and spill
   constexpr int NA = M == 64 ? TH / kRowChunks64 : (FAST && TH >= 8) ? TH / 2 : TH;
 
-  // Blocks of 16 and more are rounded from their potentials (in a kernel of their own for the large tiles), smaller ones
-  // from the order of their entries, which are sorted here
-  constexpr bool kPotentials = M >= 16;
+  // Blocks are rounded from their potentials (in a kernel of their own for the large tiles); only 4 x 4 blocks on the large
+  // tiles, a lane each, are sorted here and scanned with one lane per block (round_kernel would give them four lanes, and
+  // their potentials take more room than their order)
+  constexpr bool kPotentials = M >= 8 || SMALL;
   [[maybe_unused]] double c[kPotentials ? 1 : E];  // sort keys
   __shared__ double pot[2][kPotentials && SMALL ? BPW : 1][M];  // small tiles: potentials of the matrix rows and columns
   int iters_done = 0;
@@ -940,24 +942,7 @@ __global__ __launch_bounds__((DykstraLaunch<M, FAST, ADAPT, TILES>::kThreads), (
     for (int r = 0; r < E; ++r) asm volatile("" : "+v"(c[r]));
 
     if (active && q == 0 && batch.e[which].iters_done_out) batch.e[which].iters_done_out[blk] = iters_done;
-    if constexpr (SMALL) {
-      // Algorithm 2 behind the sort, in the same wave: the scan order of the wave's blocks through LDS
-      static_assert(WPG == 1, "the rounding steps synchronise single-wave workgroups");
-      __shared__ unsigned short scan[BPW][M * M];
-      __shared__ RoundingLds<M, BPW> lds;
-      unsigned short* mine = &scan[lane / LPB][0];
-#pragma unroll
-      for (int r = 0; r < E; ++r)
-        mine[q * E + r] = (unsigned short)((unsigned long long)__double_as_longlong(c[r]) & ((1ull << kIdxBits) - 1));
-      wave_sync();
-      const int placed = greedy_wide_scan<M, LPB>([&](int pos) { return (unsigned int)mine[pos]; }, p.N, lane, lds);
-      if (batch.e[which].stats_out) {
-        int missing = (active && q == 0) ? p.N * M - placed : 0;
-        for (int s = 1; s < kWave; s <<= 1) missing += __shfl_xor(missing, s, kWave);
-        if (lane == 0 && missing) atomicAdd(&batch.e[which].hdr->stats[0], (unsigned long long)missing);
-      }
-      local_search_and_write<M, LPB>(p, batch.e[which], blk, active, r0, c0, lane, lds);
-    } else if (active) {
+    if (active) {
       unsigned short* dst = order + blk * (int64_t)(M * M) + q * E;
 #pragma unroll
       for (int r = 0; r < E; ++r)

@@ -10,13 +10,13 @@
 namespace tsenor_dev {
 
 // how the Dykstra kernel spreads a block over lanes (see Tiling in dykstra_sort.hpp)
-enum { kLargeTiles, kSmallTiles, kFinestTiles };
+enum { kLargeTiles, kSmallTiles, kFinestTiles, kTeam };
 
 // kernel variant of a problem: problems with the same variant can share one fused launch
 struct Variant {
   int M;
   bool fast, zero_t;
-  uint32_t greedy;  // the TSENOR_FLAG_GREEDY_* asked for (M <= 8)
+  uint32_t greedy;  // the TSENOR_FLAG_GREEDY_* asked for (M = 4)
   int tiles;        // the Dykstra kernel's tiling (decided per problem, so that fusing never changes results)
   bool simple;      // TSENOR_FLAG_SIMPLE_ROUNDING
   bool adaptive;    // tol > 0: the early-exit instantiation of the Dykstra kernel
@@ -45,10 +45,15 @@ constexpr int64_t small_tiles_below_blocks(int M, bool fp32) {
 // 73 / 89, 1536 blocks 81 / 90, 2304 blocks 104 / 90 (from three waves on a SIMD on, issue decides).
 constexpr int64_t finest_tiles_below_blocks(int M) { return M == 16 ? 1800 : 0; }
 
-// Enqueues the kernels of one fused launch that depend on M: tile load + Algorithm 1 (+ sort for M <= 8), greedy selection
-// (or the simple rounding arm), local search + mask write; the last two are one kernel for M >= 16.  `b.count`
+// Below this many blocks a 64 x 64 block has a workgroup of its own (team.hpp), which iterates in double: one workgroup per
+// CU.  Whole calls, T = 300 (us, team / large tiles in double / with fp32 iterations): 64 blocks 185 / 292 / 369, 256 blocks
+// 189 / 299 / 377, 300 blocks 354 / 300.
+constexpr int64_t team_below_blocks(int M) { return M == 64 ? 257 : 0; }
+
+// Enqueues the kernels of one fused launch that depend on M: tile load + Algorithm 1 (+ sort for M = 4), greedy selection
+// (or the simple rounding arm), local search + mask write; the last two are one kernel for M >= 8.  `b.count`
 // non-degenerate problems of variant v.  ev (optional): events recorded after the iterations and after the greedy selection
-// (M >= 16: after the whole of Algorithm 2).
+// (M >= 8: after the whole of Algorithm 2).
 // Returns false if a launch could not be described (more workgroups than a grid holds).
 template <int M>
 bool launch_block_kernels(Batch& b, const Variant& v, hipStream_t stream, hipEvent_t ev_sorted, hipEvent_t ev_greedy);

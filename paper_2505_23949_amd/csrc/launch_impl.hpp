@@ -3,6 +3,7 @@
 #pragma once
 #include "dykstra_sort.hpp"
 #include "launch.hpp"
+#include "team.hpp"
 
 namespace tsenor_dev {
 
@@ -42,6 +43,16 @@ bool launch_block_kernels(Batch& b, const Variant& v, hipStream_t stream, hipEve
     if constexpr (finest_tiles_below_blocks(M) > 0) {
       if (v.tiles == kFinestTiles) ok = launch(std::integral_constant<int, kFinestTiles>{});
     }
+    if constexpr (M == Team::M) {
+      if (v.tiles == kTeam) {
+        if (!assign_groups(b, 1)) return false;
+        if (v.adaptive)
+          team_kernel<true><<<b.first[b.count], Team::W * kWave, 0, stream>>>(b);
+        else
+          team_kernel<false><<<b.first[b.count], Team::W * kWave, 0, stream>>>(b);
+        ok = true;
+      }
+    }
     if (!ok) return false;
     if (ev_sorted) (void)hipEventRecord(ev_sorted, stream);
     if (ev_greedy) (void)hipEventRecord(ev_greedy, stream);
@@ -59,8 +70,8 @@ bool launch_block_kernels(Batch& b, const Variant& v, hipStream_t stream, hipEve
     using LA = DykstraLaunch<M, false, true>;
     if (!assign_groups(b, (int64_t)BPW * (v.adaptive ? LA::kWavesPerGroup : L::kWavesPerGroup))) return false;
     if (v.zero_t) {
-      // (M >= 16: the rounding kernel starts from the importance itself, this one only writes a plan that is asked for)
-      bool any_plan = M < 16;
+      // (M >= 8: the rounding kernel starts from the importance itself, this one only writes a plan that is asked for)
+      bool any_plan = M < 8;
       for (int k = 0; k < b.count; ++k) any_plan |= b.e[k].plan_out != nullptr;
       if (any_plan) dykstra_sort_kernel<M, false, true><<<b.first[b.count], L::kThreads, 0, stream>>>(b);
     } else if (v.adaptive)
@@ -69,7 +80,7 @@ bool launch_block_kernels(Batch& b, const Variant& v, hipStream_t stream, hipEve
       dykstra_sort_kernel<M, false><<<b.first[b.count], L::kThreads, 0, stream>>>(b);
   }
   if (ev_sorted) (void)hipEventRecord(ev_sorted, stream);
-  if constexpr (M >= 16) {
+  if constexpr (M >= 8) {
     // the whole of Algorithm 2 in one kernel
     if (!assign_groups(b, kWave / M)) return false;
     if (v.zero_t)

@@ -9,8 +9,7 @@ namespace tsenor_dev {
 
 // Head of a matrix's workspace slice: what the kernels of a call pass to each other besides the scan order.
 struct WsHeader {
-  unsigned long long stats[4];  // the four rounding counters (accumulated only when the caller asks for them)
-  double tau_eff;         // multiplier of the importance, left by the iterations for the rounding (M >= 16, T > 0)
+  double tau_eff;         // multiplier of the importance, left by the iterations for the rounding (M >= 8, T > 0)
   // measurement aid: shader-clock cycles and constant-rate timer ticks that the first wave of the Dykstra kernel
   // spent in its iteration loop (their ratio is the clock the chip held under that load)
   unsigned long long loop_cycles, loop_ticks;
@@ -52,7 +51,7 @@ struct BatchEntry {
   float* absmax_partial;        // partial maxima of the importance, absmax_count of them (relative tau only)
   int absmax_count;
   unsigned short* order;
-  void* rowmask;
+  void* rowmask;                // greedy's mask (M = 4), then the blocks' counters
   double* block_objective;      // NULL: no objective asked for
   uint8_t* mask;                // outputs of the caller (NULL where optional and not asked for)
   double* plan_out;

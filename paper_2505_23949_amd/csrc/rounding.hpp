@@ -36,7 +36,7 @@ constexpr int kGreedyWaves = 4;
 // every lane of the wave does useful work; the state of a lane (M row masks, M column counters) lives in
 // LDS.  The kernel is bound by the instruction issue of its single wave per SIMD (~27 instructions per
 // entry), not by memory: the scan order is prefetched a cache line ahead and the LDS state of four entries
-// is fetched per round trip.  Serves M <= 8 (larger blocks: round_kernel).  Output: the mask as M row bit masks per block (bit c of word r = S[r][c]).
+// is fetched per round trip.  Serves M = 4 (larger blocks: round_kernel).  Output: the mask as M row bit masks per block (bit c of word r = S[r][c]).
 template <int M>
 __global__ __launch_bounds__(kWave * kGreedyWaves) void greedy_kernel(Batch batch) {
   using mask_t = block_mask_t<M>;
@@ -53,14 +53,12 @@ __global__ __launch_bounds__(kWave * kGreedyWaves) void greedy_kernel(Batch batc
   const int64_t nblocks = batch.e[which].p.nblocks;
   const int N = batch.e[which].p.N;
   mask_t* rowmask = static_cast<mask_t*>(batch.e[which].rowmask);
-  WsHeader* hdr = batch.e[which].hdr;
   const int lane = threadIdx.x % kWave;
   const int64_t blk = (int64_t)(vgroup - batch.first[which]) * kWave + lane;
   for (int k = 0; k < M; ++k) {
     rowbits[k][lane] = 0;
     colcnt[k][lane] = 0;
   }
-  int missing = 0;
   if (blk < nblocks) {
     const unsigned short* src = order + blk * MM;
     int placed = 0;
@@ -119,11 +117,6 @@ __global__ __launch_bounds__(kWave * kGreedyWaves) void greedy_kernel(Batch batc
       for (int d = 0; d < D; ++d) cur[d] = nxt[d];
     }
     for (int k = 0; k < M; ++k) rowmask[blk * M + k] = rowbits[k][lane];
-    missing = need - placed;
-  }
-  if (batch.e[which].stats_out) {
-    for (int s = 1; s < kWave; s <<= 1) missing += __shfl_xor(missing, s, kWave);
-    if (lane == 0 && missing) atomicAdd(&hdr->stats[0], (unsigned long long)missing);
   }
 }
 
@@ -142,7 +135,6 @@ __global__ __launch_bounds__(kWave) void simple_round_kernel(Batch batch) {
   const int64_t nblocks = batch.e[which].p.nblocks;
   const int N = batch.e[which].p.N;
   mask_t* rowmask = static_cast<mask_t*>(batch.e[which].rowmask);
-  WsHeader* hdr = batch.e[which].hdr;
   const int lane = threadIdx.x;
   const int64_t blk = (int64_t)(blockIdx.x - batch.first[which]) * kWave + lane;
   for (int k = 0; k < M; ++k) {
@@ -150,10 +142,8 @@ __global__ __launch_bounds__(kWave) void simple_round_kernel(Batch batch) {
     passed[k][lane] = 0;
     colcnt[k][lane] = 0;
   }
-  int missing = 0;
   if (blk < nblocks) {
     const unsigned short* src = order + blk * MM;
-    int placed = 0;
     for (int h = 0; h < MM; ++h) {
       const unsigned int idx = src[h] & (unsigned)(MM - 1);
       const unsigned int i = idx / M, j = idx % M;
@@ -164,16 +154,10 @@ __global__ __launch_bounds__(kWave) void simple_round_kernel(Batch batch) {
         if (cj < (unsigned)N) {
           colcnt[j][lane] = (unsigned char)(cj + 1);
           rowbits[i][lane] |= (mask_t)1 << j;
-          ++placed;
         }
       }
     }
     for (int k = 0; k < M; ++k) rowmask[blk * M + k] = rowbits[k][lane];
-    missing = N * M - placed;
-  }
-  if (batch.e[which].stats_out) {
-    for (int s = 1; s < kWave; s <<= 1) missing += __shfl_xor(missing, s, kWave);
-    if (lane == 0 && missing) atomicAdd(&hdr->stats[0], (unsigned long long)missing);
   }
 }
 
@@ -196,10 +180,10 @@ struct RoundingLds {
 // induction along the scan order every decision equals the sequential one.  Dependent chain: M chunks of a
 // few rounds instead of M*M steps.
 // A block owns LPB >= M consecutive lanes of the wave (LPB a power of two), of which the first M take part;
-// fetch(pos) returns the flat index at scan position pos of this lane's block.  Leaves the mask in lds.rowm and
-// returns the number of entries the lane's block holds.  To be called by whole waves.
+// fetch(pos) returns the flat index at scan position pos of this lane's block.  Leaves the mask in lds.rowm.  To be called by
+// whole waves.
 template <int M, int LPB, class Fetch>
-__device__ __forceinline__ int greedy_wide_scan(Fetch&& fetch, int N, int lane, RoundingLds<M, kWave / LPB>& lds) {
+__device__ __forceinline__ void greedy_wide_scan(Fetch&& fetch, int N, int lane, RoundingLds<M, kWave / LPB>& lds) {
   using mask_t = block_mask_t<M>;
   constexpr int MM = M * M;
   constexpr int LOGM = M == 4 ? 2 : M == 8 ? 3 : M == 16 ? 4 : M == 32 ? 5 : 6;
@@ -254,7 +238,6 @@ __device__ __forceinline__ int greedy_wide_scan(Fetch&& fetch, int N, int lane, 
     wave_sync();
     if (!__any(placed < need)) break;  // every block of the wave is full
   }
-  return placed;
 }
 
 template <int M>
@@ -267,19 +250,13 @@ __global__ __launch_bounds__(kWave) void greedy_wide_kernel(Batch batch) {
   const int64_t nblocks = batch.e[which].p.nblocks;
   const int N = batch.e[which].p.N;
   mask_t* rowmask = static_cast<mask_t*>(batch.e[which].rowmask);
-  WsHeader* hdr = batch.e[which].hdr;
   const int lane = threadIdx.x, g = lane / M, ql = lane % M;
   int64_t blk = (int64_t)(blockIdx.x - batch.first[which]) * G + g;
   const bool active = blk < nblocks;
   if (!active) blk = nblocks - 1;  // idle groups shadow the last block and write nothing
   const unsigned short* src = order + blk * MM;
-  const int placed = greedy_wide_scan<M, M>([&](int pos) { return (unsigned int)src[pos]; }, N, lane, lds);
+  greedy_wide_scan<M, M>([&](int pos) { return (unsigned int)src[pos]; }, N, lane, lds);
   if (active) rowmask[blk * M + ql] = lds.rowm[g][ql];
-  if (batch.e[which].stats_out) {
-    int missing = (active && ql == 0) ? N * M - placed : 0;
-    for (int s = 1; s < kWave; s <<= 1) missing += __shfl_xor(missing, s, kWave);
-    if (lane == 0 && missing) atomicAdd(&hdr->stats[0], (unsigned long long)missing);
-  }
 }
 
 // Transpose of an M x M bit matrix held as one M-bit row per lane (M consecutive lanes): afterwards the
@@ -336,6 +313,16 @@ __device__ __forceinline__ double group_sum(double v) {
   }
 }
 
+template <int M, int STEP = 1>
+__device__ __forceinline__ int group_sum(int v) {
+  if constexpr (STEP < M) {
+    v += lane_xor_i32<STEP>(v);
+    return group_sum<M, STEP * 2>(v);
+  } else {
+    return v;
+  }
+}
+
 // Algorithm 2 lines 7-13 and the mask write for the blocks of one wave.  A block owns LPB >= M consecutive lanes,
 // of which the first M take part: lane r owns row r and column r of the block as bit masks.  On entry lds.rowm
 // holds the mask greedy selection left.  blk: the lane's block (a valid one also for idle lanes, which write
@@ -346,7 +333,6 @@ __device__ __forceinline__ void local_search_and_write(const DevProblem& p, cons
   using mask_t = block_mask_t<M>;
   constexpr int MM = M * M, LD = RoundingLds<M, kWave / LPB>::kImpLd;
   uint8_t* mask = e.mask;
-  WsHeader* hdr = e.hdr;
   const int wide_store = e.wide_store;
   double* block_objective = e.block_objective;
   const uint8_t* prev_mask = e.prev_mask;
@@ -364,6 +350,7 @@ __device__ __forceinline__ void local_search_and_write(const DevProblem& p, cons
   }
   wave_sync();
   const auto popc = [](mask_t v) { return mask_popc(v); };
+  const int missing = want_stats ? group_sum<M>(part ? p.N - popc(lds.rowm[g][qm]) : 0) : 0;
   const unsigned long long gmask = (M == 64 ? ~0ull : ((1ull << M) - 1)) << (g * LPB);
   const bool any_short = __any(part && popc(lds.rowm[g][qm]) < p.N);
   if ((any_short || block_objective) && part) {
@@ -492,13 +479,13 @@ __device__ __forceinline__ void local_search_and_write(const DevProblem& p, cons
       block_objective[2 * blk + 1] = theirs;
     }
   }
-  if (want_stats && active && part) {
-    const int left = p.N - popc(lds.rowm[g][qm]);
-    if (left) atomicAdd(&hdr->stats[3], (unsigned long long)left);
-    if (ql == 0) {
-      if (nonpos) atomicAdd(&hdr->stats[1], (unsigned long long)nonpos);
-      if (!p.strict && rounds > p.L) atomicAdd(&hdr->stats[2], 1ull);
-    }
+  if (want_stats) {
+    // a record per block where its mask from the greedy selection was (this wave has read it); stats_kernel adds them up.
+    // (Atomic additions of every wave to the four counters took 0.24 ms for 24 000 waves.)
+    const int left = group_sum<M>(part ? p.N - popc(lds.rowm[g][qm]) : 0);
+    if (active && ql == 0)
+      reinterpret_cast<uint4*>(static_cast<char*>(e.rowmask) + blk * (int64_t)(M * sizeof(mask_t)))[0] =
+          make_uint4((unsigned)missing, (unsigned)nonpos, !p.strict && rounds > p.L ? 1u : 0u, (unsigned)left);
   }
 }
 
@@ -522,7 +509,7 @@ __global__ __launch_bounds__(kWave) void finalize_kernel(Batch batch) {
 }
 
 // ------------------------------------------------------------------------------------------------------------------
-// The whole of Algorithm 2 in one kernel for M >= 16, from the potentials the iterations leave.
+// The whole of Algorithm 2 from the potentials the iterations leave (M >= 8, and M = 4 on the small tiles).
 //
 // The greedy selection needs no sort of the M*M entries.  It scans them in one common order (descending plan, ties by
 // index) and keeps an entry while its row and its column have room; its result is the one stable assignment in which
@@ -614,7 +601,7 @@ __device__ __forceinline__ void round_blocks(const DevProblem& p, const BatchEnt
                                              int64_t c0, int lane, double tau_eff, const double (*row_pot)[M],
                                              const double (*col_pot)[M], RoundingLds<M, kWave / LPB>& lds, bool simple) {
   using mask_t = block_mask_t<M>;
-  constexpr int LOGM = M == 16 ? 4 : M == 32 ? 5 : 6, LD = RoundingLds<M, kWave / LPB>::kImpLd;
+  constexpr int LOGM = M == 4 ? 2 : M == 8 ? 3 : M == 16 ? 4 : M == 32 ? 5 : 6, LD = RoundingLds<M, kWave / LPB>::kImpLd;
   const int g = lane / LPB, ql = lane % M, N = p.N;
   // the importance of the block, a column per lane (coalesced), into LDS
   {
@@ -666,7 +653,7 @@ __device__ __forceinline__ void round_blocks(const DevProblem& p, const BatchEnt
   // From here the space of the importance holds three byte tables per block (rows padded by a word so that a lane per
   // row meets no other in a bank): rank of entry (i, j) within column j, the columns of row i in scan order, the rows
   // of column j in scan order.
-  constexpr int LDB = M + 4;
+  constexpr int LDB = M == 4 ? 4 : M + 4;
   static_assert(3 * M * LDB <= (int)sizeof(lds.imp[0]), "the tables fit where the importance was");
   unsigned char* rank = reinterpret_cast<unsigned char*>(&lds.imp[g][0]);
   unsigned char* columns_of = rank + M * LDB;
@@ -737,11 +724,6 @@ __device__ __forceinline__ void round_blocks(const DevProblem& p, const BatchEnt
     }
     lds.rowm[g][ql] = held;
     if (!__any(proposed)) break;
-  }
-  if (e.stats_out) {
-    int missing = active && lane % LPB < M ? N - mask_popc(held) : 0;
-    for (int s = 1; s < kWave; s <<= 1) missing += __shfl_xor(missing, s, kWave);
-    if (lane == 0 && missing) atomicAdd(&e.hdr->stats[0], (unsigned long long)missing);
   }
   wave_sync();
   local_search_and_write<M, LPB>(p, e, blk, active, r0, c0, lane, lds);

@@ -4,10 +4,10 @@
 // kernel variant (a single matrix is a group of one):
 //   1. init_kernel / absmax_kernel      workspace reset; importance maximum of every matrix (relative tau only)
 //   2. dykstra_sort_kernel              tile load, all T Dykstra iterations of Algorithm 1 on chip (and the plan if
-//                                       asked for); leaves the potentials of every block (M >= 16) or the greedy scan
-//                                       order (M <= 8)                                    [dykstra_sort.hpp]
-//   3. round_kernel                     M >= 16: the whole of Algorithm 2                 [rounding.hpp]
-//      greedy_kernel, finalize_kernel   M <= 8: Algorithm 2 lines 1-6, one lane per block, then lines 7-13 and the mask
+//                                       asked for); leaves the potentials of every block (M >= 8) or the greedy scan
+//                                       order (M = 4)                                     [dykstra_sort.hpp]
+//   3. round_kernel                     M >= 8: the whole of Algorithm 2                  [rounding.hpp]
+//      greedy_kernel, finalize_kernel   M = 4: Algorithm 2 lines 1-6, one lane per block, then lines 7-13 and the mask
 //                                       write (simple_round_kernel: the ablation arm)     [rounding.hpp]
 //   4. objective_kernel, emit_kernel, stats_kernel   optional outputs                     [outputs.hpp]
 // Steps 2-3 depend on the block size and are compiled per M (launch.hpp).  Every kernel takes the table of
@@ -32,11 +32,10 @@ namespace {
 
 using namespace tsenor_dev;
 
-// clears the rounding counters of every matrix of the batch (launched only when a caller asks for them)
+// clears the caller's counters (launched only when a caller asks for them)
 __global__ void init_kernel(Batch batch) {
-  if ((int)threadIdx.x >= batch.count) return;
-  WsHeader* hdr = batch.e[threadIdx.x].hdr;
-  for (int k = 0; k < 4; ++k) hdr->stats[k] = 0ull;
+  const int which = threadIdx.x / 4, k = threadIdx.x % 4;
+  if (which < batch.count && batch.e[which].stats_out) batch.e[which].stats_out[k] = 0;
 }
 
 constexpr int kAbsmaxInFlight = 4;  // rows read per thread before any is used
@@ -132,9 +131,20 @@ __global__ void fill_kernel(uint8_t* mask, int64_t total, uint8_t value) {
     mask[k] = value;
 }
 
-__global__ void stats_kernel(Batch batch) {
-  const int which = threadIdx.x / 4, k = threadIdx.x % 4;
-  if (which < batch.count && batch.e[which].stats_out) batch.e[which].stats_out[k] = (int64_t)batch.e[which].hdr->stats[k];
+// adds the blocks' counters to the caller's (blockIdx.y: matrix); `stride`: bytes between the records of two blocks
+constexpr int kStatsGroups = 64;
+__global__ __launch_bounds__(256) void stats_kernel(Batch batch, int stride) {
+  const BatchEntry& e = batch.e[blockIdx.y];
+  if (!e.stats_out) return;
+  unsigned long long sum[4] = {};
+  for (int64_t k = (int64_t)blockIdx.x * 256 + threadIdx.x; k < e.p.nblocks; k += kStatsGroups * 256) {
+    const uint4 v = *reinterpret_cast<const uint4*>(static_cast<const char*>(e.rowmask) + k * stride);
+    sum[0] += v.x, sum[1] += v.y, sum[2] += v.z, sum[3] += v.w;
+  }
+  for (int k = 0; k < 4; ++k) {
+    for (int s = 1; s < kWave; s <<= 1) sum[k] += __shfl_xor(sum[k], s, kWave);
+    if (threadIdx.x % kWave == 0 && sum[k]) atomicAdd(reinterpret_cast<unsigned long long*>(e.stats_out) + k, sum[k]);
+  }
 }
 
 // ------------------------------------------------------------------------------------------------
@@ -210,10 +220,11 @@ inline Variant variant_of(const tsenor_problem& p) {
   // tilings differ in the order of the additions inside a row or column sum
   const int64_t nblocks = (p.rows / p.M) * (p.cols / p.M);
   const bool fp32 = (p.flags & TSENOR_FLAG_FP32_ITERATIONS) != 0;
-  const bool small = p.M <= 32 && !v.zero_t && !v.simple &&
-                     ((p.flags & TSENOR_FLAG_TILES_SMALL) != 0 ||
-                      (!(p.flags & TSENOR_FLAG_TILES_LARGE) && nblocks < small_tiles_below_blocks(p.M, fp32)));
-  v.tiles = !small ? kLargeTiles : nblocks < finest_tiles_below_blocks(p.M) ? kFinestTiles : kSmallTiles;
+  const bool tiled = !v.zero_t && !v.simple && !(p.flags & TSENOR_FLAG_TILES_LARGE);
+  const bool team = tiled && nblocks < team_below_blocks(p.M);
+  const bool small = team || (p.M <= 32 && tiled &&
+                              ((p.flags & TSENOR_FLAG_TILES_SMALL) != 0 || nblocks < small_tiles_below_blocks(p.M, fp32)));
+  v.tiles = !small ? kLargeTiles : team ? kTeam : nblocks < finest_tiles_below_blocks(p.M) ? kFinestTiles : kSmallTiles;
   // the small tiles (launches that cannot fill the chip: bound by latency, not by issue) iterate in double only
   v.fast = p.iters > 0 && fp32 && !small;
   v.adaptive = p.tol > 0.0 && p.iters > 0;
@@ -317,7 +328,7 @@ int run_group(Batch& b, const Variant& v, hipStream_t stream, hipEvent_t* ev = n
     any_stats |= e.stats_out != nullptr;
   }
   mark(0);
-  if (any_stats) init_kernel<<<1, kMaxBatch, 0, stream>>>(b);
+  if (any_stats) init_kernel<<<1, 4 * kMaxBatch, 0, stream>>>(b);
   if (any_rel) {
     const dim3 grid = strided_grid(b, false, 512, true);
     for (int k = 0; k < b.count; ++k) b.e[k].absmax_count = (int)(grid.x * grid.y);
@@ -339,7 +350,8 @@ int run_group(Batch& b, const Variant& v, hipStream_t stream, hipEvent_t* ev = n
     emit_kernel<<<strided_grid(b, true, 2048, false), 256, 0, stream>>>(b);
   else if (any_objective)  // (only the sums are wanted)
     emit_kernel<<<dim3(1, 1, (unsigned)b.count), 256, 0, stream>>>(b);
-  if (any_stats) stats_kernel<<<1, 4 * kMaxBatch, 0, stream>>>(b);
+  if (any_stats)
+    stats_kernel<<<dim3(kStatsGroups, (unsigned)b.count), 256, 0, stream>>>(b, (int)rowmask_bytes_per_block(v.M));
   mark(4);
   return hip_status_of_launches();
 }
@@ -354,10 +366,7 @@ int run_degenerate(const tsenor_problem& p, char* ws, hipStream_t stream, hipEve
   Batch b = {};
   b.count = 1;
   b.e[0] = entry_of(p, ws);
-  if (p.stats_out) {
-    init_kernel<<<1, kMaxBatch, 0, stream>>>(b);
-    stats_kernel<<<1, 4 * kMaxBatch, 0, stream>>>(b);
-  }
+  if (p.stats_out) init_kernel<<<1, 4 * kMaxBatch, 0, stream>>>(b);
   if (p.packed_out || p.pruned_out) emit_kernel<<<strided_grid(b, true, 2048, false), 256, 0, stream>>>(b);
   if (ev) (void)hipEventRecord(ev[4], stream);
   return hip_status_of_launches();

@@ -1,4 +1,4 @@
-"""round_kernel (Algorithm 2 for M >= 16 by deferred acceptance) against the oracle's sequential selection and swaps."""
+"""round_kernel (Algorithm 2 for M >= 8 by deferred acceptance) against the oracle's sequential selection and swaps."""
 import numpy as np
 import pytest
 
@@ -8,7 +8,7 @@ from paper_2505_23949_amd import synth
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("M", [16, 32, 64])
+@pytest.mark.parametrize("M", [8, 16, 32, 64])
 @pytest.mark.parametrize("share", ["one", "half", "all but one"])
 def test_rounding_of_whole_blocks(M, share):
     # N from the smallest to the largest that is solved; numbers of blocks that fill, overfill and leave idle parts of a
@@ -57,3 +57,28 @@ def test_fine_tilings_of_16_wide_blocks(blocks):
         assert np.abs(res["plan"].cpu().numpy() - np.exp(ref["log_S"])).max() <= 1e-9
         assert np.array_equal(res["mask"].cpu().numpy(), ref["mask"])
         assert np.array_equal(res["stats"].cpu().numpy(), ref["stats"])
+
+
+@pytest.mark.parametrize("blocks", [(1, 1), (16, 16), (1, 257)])
+def test_workgroup_per_64_wide_block(blocks):
+    # one block, and the two sides of the line (257 blocks) below which a block has a workgroup of its own
+    import torch
+
+    from paper_2505_23949_amd import binding as b
+
+    dev = torch.device("cuda:0")
+    W = np.random.Generator(np.random.Philox(6)).standard_normal((blocks[0] * 64, blocks[1] * 64), dtype=np.float32)
+    for cols_first, tol in ((False, 0.0), (True, 0.0), (False, 1e-2)):
+        print(f"[case] team {blocks} cols_first={cols_first} tol={tol}", flush=True)
+        res = b.solve(torch.from_numpy(W).to(dev), 29, 64, 0.02, 24, tau_mode=b.TSENOR_TAU_REL_MATRIX_MAX, want_plan=True, want_stats=True,
+                      tol=tol, want_iters_done=True, flags=b.TSENOR_FLAG_COLS_FIRST if cols_first else 0)
+        torch.cuda.synchronize()
+        imp = oracle.importance(W)
+        te = oracle.tau_eff(imp, 0.02, synth.TAU_REL_MATRIX_MAX)
+        log_S, done = oracle.dykstra_adaptive(imp, 29, 64, te, 24, tol, cols_first=cols_first)
+        mask, stats = oracle.round_plan(log_S, imp, 29, 64)
+        assert np.array_equal(res["iters_done"].cpu().numpy(), done)
+        # 1e-9: what the parity tests ask of a plan computed in double on both sides
+        assert np.abs(res["plan"].cpu().numpy() - np.exp(log_S)).max() <= 1e-9
+        assert np.array_equal(res["mask"].cpu().numpy(), mask)
+        assert np.array_equal(res["stats"].cpu().numpy(), stats)

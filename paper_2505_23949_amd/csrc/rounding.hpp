@@ -529,19 +529,28 @@ struct BlockPotentials {
   double u[M], v[M];
 };
 
-// Scan key of an entry: positive doubles whose order is descending plan, ties by ascending flat index.
-constexpr int kIdxBits = 12;  // flat index within a block: up to 64*64 entries
-// log_plan: K + (u + v), to be capped at 0.
-__device__ __forceinline__ double scan_key(double log_plan, unsigned int flat) {
-  const double x = fmax(-log_plan, 0.0);
-  // + 2^52 keeps the pattern a normal double
-  return __hiloint2double((__double2hiint(x) & 0x7FFFFFFF) + (1 << 20), (__double2loint(x) & ~((1 << kIdxBits) - 1)) | (int)flat);
+// Scan key of an entry: positive doubles whose order is descending plan, ties by ascending index.  `index` (below 2^12) is the
+// entry's place in what is being sorted: a block, a row or a column.
+constexpr int kIdxBits = 12;  // index bits: up to 64*64 entries
+__device__ __forceinline__ double with_index(double key, unsigned int index) {
+  return __hiloint2double(__double2hiint(key), (__double2loint(key) & ~((1 << kIdxBits) - 1)) | (int)index);
+}
+// log_plan: K + (u + v), to be capped at 0 (at -2^-1021: with the index bits in place the key is a normal double, and all
+// capped entries tie)
+__device__ __forceinline__ double scan_key(double log_plan, unsigned int index) {
+  return with_index(fmax(-log_plan, 0x1p-1021), index);
 }
 // T = 0: the order is descending K itself.  Bit patterns of non-negative doubles order like the doubles:
 // pattern(2^1023) - pattern(K) reverses the order for every finite K >= 0 and is again the pattern of a positive double
-__device__ __forceinline__ double scan_key_of_k(double K, unsigned int flat) {
+__device__ __forceinline__ double scan_key_of_k(double K, unsigned int index) {
   const unsigned long long bits = (unsigned long long)__double_as_longlong(K);
-  return __longlong_as_double((long long)(((0x7FE0000000000000ull - bits) & ~((1ull << kIdxBits) - 1)) | flat));
+  return with_index(__longlong_as_double((long long)(0x7FE0000000000000ull - bits)), index);
+}
+// the index bytes of four keys whose index is below 2^8, next to each other
+__device__ __forceinline__ unsigned int index_bytes(double a, double b, double c, double d) {
+  const unsigned int ab = __builtin_amdgcn_perm((unsigned)__double2loint(b), (unsigned)__double2loint(a), 0x0c0c0400u);
+  const unsigned int cd = __builtin_amdgcn_perm((unsigned)__double2loint(d), (unsigned)__double2loint(c), 0x0c0c0400u);
+  return ab | cd << 16;
 }
 
 __device__ __forceinline__ void compare_exchange(double& lo, double& hi) {
@@ -601,7 +610,7 @@ __device__ __forceinline__ void round_blocks(const DevProblem& p, const BatchEnt
                                              int64_t c0, int lane, double tau_eff, const double (*row_pot)[M],
                                              const double (*col_pot)[M], RoundingLds<M, kWave / LPB>& lds, bool simple) {
   using mask_t = block_mask_t<M>;
-  constexpr int LOGM = M == 4 ? 2 : M == 8 ? 3 : M == 16 ? 4 : M == 32 ? 5 : 6, LD = RoundingLds<M, kWave / LPB>::kImpLd;
+  constexpr int LD = RoundingLds<M, kWave / LPB>::kImpLd;
   const int g = lane / LPB, ql = lane % M, N = p.N;
   // the importance of the block, a column per lane (coalesced), into LDS
   {
@@ -621,13 +630,12 @@ __device__ __forceinline__ void round_blocks(const DevProblem& p, const BatchEnt
 #pragma unroll
     for (int k = 0; k < M; ++k) {
       const double imp = (double)lds.imp[g][ROWS ? ql * LD + k : k * LD + ql];
-      const unsigned int flat = ROWS ? ql * M + k : k * M + ql;
       if constexpr (ZERO_T) {
-        c[k] = scan_key_of_k(tau_eff * imp, flat);
+        c[k] = scan_key_of_k(tau_eff * imp, k);
       } else {
         // (the same operations in both passes: an entry has one key)
         const double other = ROWS ? col_pot[g][k] : row_pot[g][k];
-        c[k] = scan_key(fma(tau_eff, imp, own + other), flat);
+        c[k] = scan_key(fma(tau_eff, imp, own + other), k);
       }
       // a few entries at a time: with all their LDS reads in flight the keys no longer fit the registers
       if (k % 8 == 7) __builtin_amdgcn_sched_barrier(0);
@@ -641,10 +649,7 @@ __device__ __forceinline__ void round_blocks(const DevProblem& p, const BatchEnt
   keys(yes{});
   sort_in_lane(c);
 #pragma unroll
-  for (int r = 0; r < M; ++r) {
-    const unsigned int j = (unsigned int)__double2loint(c[r]) & (M - 1);
-    row_list[r / 4] = r % 4 ? row_list[r / 4] | j << (8 * (r % 4)) : j;
-  }
+  for (int r = 0; r < M; r += 4) row_list[r / 4] = index_bytes(c[r], c[r + 1], c[r + 2], c[r + 3]);
   // this lane's column in scan order
   keys(no{});
   sort_in_lane(c);
@@ -658,17 +663,13 @@ __device__ __forceinline__ void round_blocks(const DevProblem& p, const BatchEnt
   unsigned char* rank = reinterpret_cast<unsigned char*>(&lds.imp[g][0]);
   unsigned char* columns_of = rank + M * LDB;
   unsigned char* rows_of = columns_of + M * LDB;
-  {
-    unsigned int packed = 0;
 #pragma unroll
-    for (int r = 0; r < M; ++r) {
-      const unsigned int i = ((unsigned int)__double2loint(c[r]) >> LOGM) & (M - 1);
-      rank[i * LDB + ql] = (unsigned char)r;
-      packed = r % 4 ? packed | i << (8 * (r % 4)) : i;
-      if (r % 4 == 3) {
-        *reinterpret_cast<unsigned int*>(rows_of + ql * LDB + r - 3) = packed;
-        *reinterpret_cast<unsigned int*>(columns_of + ql * LDB + r - 3) = row_list[r / 4];
-      }
+  for (int r = 0; r < M; ++r) {
+    const unsigned int i = (unsigned int)__double2loint(c[r]) & (M - 1);
+    rank[i * LDB + ql] = (unsigned char)r;
+    if (r % 4 == 3) {
+      *reinterpret_cast<unsigned int*>(rows_of + ql * LDB + r - 3) = index_bytes(c[r - 3], c[r - 2], c[r - 1], c[r]);
+      *reinterpret_cast<unsigned int*>(columns_of + ql * LDB + r - 3) = row_list[r / 4];
     }
   }
   // lds.rowm[i]: the columns row i holds; lds.colm[j]: the ranks (within column j) of the entries column j holds;

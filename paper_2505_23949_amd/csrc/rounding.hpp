@@ -280,27 +280,32 @@ __device__ __forceinline__ mask_t bit_transpose(mask_t x, int ql) {
   }
 }
 
-// Best candidate of Eq. (5) held by a lane: score, flat index i'*M+j' (MM = none).  Higher score wins,
-// equal scores go to the lower flat index.
+// The best of the swaps (i', j') of Eq. (5) that a lane i' may take part in: `cand` are its columns j', row_i and row_q the
+// importance of row i and of its own.  Higher score wins, equal scores go to the lower column.
 struct SwapBest {
   double score;
-  int arg;
+  int column;
 };
-template <int MM>
-__device__ __forceinline__ SwapBest better_of(SwapBest a, SwapBest b) {
-  const bool take_b = b.arg != MM && (a.arg == MM || b.score > a.score || (b.score == a.score && b.arg < a.arg));
-  return take_b ? b : a;
-}
-template <int M, int STEP = 1>
-__device__ __forceinline__ SwapBest group_best(SwapBest v) {
-  if constexpr (STEP < M) {
-    SwapBest o;
-    o.score = lane_xor<STEP>(v.score);
-    o.arg = lane_xor_i32<STEP>(v.arg);
-    return group_best<M, STEP * 2>(better_of<M * M>(v, o));
-  } else {
-    return v;
+__device__ __forceinline__ void scan_candidate(unsigned int& word, int first, const float* row_i, const float* row_q, double base,
+                                               SwapBest& best) {
+  const int j = first + __ffs((int)word) - 1;
+  word &= word - 1;
+  const double score = ((double)row_i[j] + base) - (double)row_q[j];
+  if (score > best.score) {
+    best.score = score;
+    best.column = j;
   }
+}
+template <class mask_t>
+__device__ __forceinline__ SwapBest best_candidate(mask_t cand, const float* row_i, const float* row_q, double base) {
+  SwapBest best = {-std::numeric_limits<double>::infinity(), 0};
+  unsigned int word = (unsigned int)cand;
+  while (word != 0) scan_candidate(word, 0, row_i, row_q, base, best);
+  if constexpr (sizeof(mask_t) == 8) {
+    word = (unsigned int)(cand >> 32);
+    while (word != 0) scan_candidate(word, 32, row_i, row_q, base, best);
+  }
+  return best;
 }
 
 template <int M, int STEP = 1>
@@ -331,7 +336,7 @@ template <int M, int LPB>
 __device__ __forceinline__ void local_search_and_write(const DevProblem& p, const BatchEntry& e, int64_t blk, bool active,
                                                        int64_t r0, int64_t c0, int lane, RoundingLds<M, kWave / LPB>& lds) {
   using mask_t = block_mask_t<M>;
-  constexpr int MM = M * M, LD = RoundingLds<M, kWave / LPB>::kImpLd;
+  constexpr int LD = RoundingLds<M, kWave / LPB>::kImpLd;
   uint8_t* mask = e.mask;
   const int wide_store = e.wide_store;
   double* block_objective = e.block_objective;
@@ -378,34 +383,24 @@ __device__ __forceinline__ void local_search_and_write(const DevProblem& p, cons
     // line 11 for i' = this lane: columns j' with S[i'][j'] = 1 and S[i][j'] = 0, provided S[i'][j] = 0
     mask_t cand = Srow & ~lds.rowm[g][i];
     if (!open || !part || ((lds.colm[g][j] >> qm) & 1)) cand = 0;
-    const double base = (double)lds.imp[g][qm * LD + j];
-    SwapBest best = {-std::numeric_limits<double>::infinity(), MM};
-    while (cand != 0) {
-      {
-        const int jp = sizeof(mask_t) == 8 ? __ffsll((long long)cand) - 1 : __ffs((int)cand) - 1;
-        cand &= cand - 1;
-        const double sc = ((double)lds.imp[g][i * LD + jp] + base) - (double)lds.imp[g][qm * LD + jp];
-        if (sc > best.score) {
-          best.score = sc;
-          best.arg = jp;
-        }
-      }
-    }
-    best.arg = best.arg == MM ? MM : qm * M + best.arg;
-    best = group_best<M>(best);
+    const SwapBest best =
+        best_candidate(cand, &lds.imp[g][i * LD], &lds.imp[g][qm * LD], (double)lds.imp[g][qm * LD + j]);
+    // the best of the block: lanes are rows i', so among equal scores the first lane has the lowest flat index
+    const double top = block_max<M>(best.score);
+    const unsigned long long winners = __ballot(part && best.score == top) & gmask;
+    const int winner = winners ? __ffsll((long long)winners) - 1 : 0;
+    const int ip = winner - g * LPB, jp = __shfl(best.column, winner, kWave);
     if (open) ++rounds;
-    bool apply = open && best.arg != MM;
-    if (p.strict && !(best.score > 0.0)) apply = false;
+    const bool apply = open && top > (p.strict ? 0.0 : -std::numeric_limits<double>::infinity());
     if (open && !apply) open = false;  // nothing changes any more for this block
     wave_sync();
     if (apply && ql == 0) {
       // line 13: remove (i', j'), insert (i', j) and (i, j')
-      const int ip = best.arg / M, jp = best.arg % M;
       lds.rowm[g][ip] = (lds.rowm[g][ip] & ~(one << jp)) | (one << j);
       lds.rowm[g][i] |= one << jp;
       lds.colm[g][jp] = (lds.colm[g][jp] & ~(one << ip)) | (one << i);
       lds.colm[g][j] |= one << ip;
-      if (!(best.score > 0.0)) ++nonpos;
+      if (!(top > 0.0)) ++nonpos;
     }
     wave_sync();
   }
@@ -713,15 +708,28 @@ __device__ __forceinline__ void round_blocks(const DevProblem& p, const BatchEnt
     int lacks = simple ? 0 : N - mask_popc(held);
     bool proposed = false;
     while (lacks > 0 && next < M) {
-      const unsigned int j = columns_of[ql * LDB + next];
-      const unsigned int at = rank[ql * LDB + j];
-      ++next;
-      if (at < lds.colcnt[g][j]) {
-        atomicOr(&lds.colm[g][j], one << at);
-        held |= one << j;
-        --lacks;
-        proposed = true;
+      // four places of the row's order per LDS round trip (a row that stays short looks at all that is left of it)
+      const int first = next & ~3;
+      const unsigned int four = *reinterpret_cast<const unsigned int*>(columns_of + ql * LDB + first);
+      unsigned int at[4], below[4];
+#pragma unroll
+      for (int k = 0; k < 4; ++k) {
+        const unsigned int j = (four >> (8 * k)) & 0xFFu;
+        at[k] = rank[ql * LDB + j];
+        below[k] = lds.colcnt[g][j];
       }
+#pragma unroll
+      for (int k = 0; k < 4; ++k)
+        if (first + k >= next && lacks > 0) {
+          next = first + k + 1;
+          if (at[k] < below[k]) {
+            const unsigned int j = (four >> (8 * k)) & 0xFFu;
+            atomicOr(&lds.colm[g][j], one << at[k]);
+            held |= one << j;
+            --lacks;
+            proposed = true;
+          }
+        }
     }
     lds.rowm[g][ql] = held;
     if (!__any(proposed)) break;

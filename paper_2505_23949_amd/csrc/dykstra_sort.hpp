@@ -177,6 +177,12 @@ __device__ __forceinline__ void all_gather_x(real (&v)[TH]) {
     all_gather_x<T, real, TH, S - 1>(v);
   }
 }
+// The float above x >= 0 (infinity stays).  The normaliser of a row is to be a float not below its largest K: the largest of
+// the K rounded to nearest, one step up, once per row.  (Every K rounded upwards: there is no such conversion, its 14
+// instructions per entry were a third of the 64-wide prologue; 32:64 8192x8192 with early exit: 796 -> 777 us a call.)
+__device__ __forceinline__ float next_up(float x) {
+  return x < __builtin_huge_valf() ? __uint_as_float(__float_as_uint(x) + 1u) : x;
+}
 // Maximum over the lanes of a lane-row of a value per tile row (all TH registers, butterfly): afterwards
 // every lane holds the maximum of each of its tile rows.
 template <class T, int TH, int S = 0>
@@ -665,8 +671,7 @@ __global__ __launch_bounds__((DykstraLaunch<M, FAST, ADAPT, TILES>::kThreads), (
             if constexpr (!kPotentials) c[(A0 + a) * TW + b] = scan_key_of_k(K, mat_row(ri, cj) * M + mat_col(ri, cj));
           } else {
             kap[A0 + a][b] = K;
-            const float up = __double2float_ru(K);
-            mrow[A0 + a] = b == 0 ? up : fmaxf(mrow[A0 + a], up);
+            mrow[A0 + a] = b == 0 ? (float)K : fmaxf(mrow[A0 + a], (float)K);
           }
         }
     };
@@ -674,6 +679,8 @@ __global__ __launch_bounds__((DykstraLaunch<M, FAST, ADAPT, TILES>::kThreads), (
   }
   if constexpr (!ZERO_T) {
     all_reduce_max_x<T, TH>(mrow);
+#pragma unroll
+    for (int a = 0; a < TH; ++a) mrow[a] = next_up(mrow[a]);
 #pragma unroll
     for (int a = 0; a < TH; ++a)
 #pragma unroll

@@ -70,14 +70,14 @@ __global__ __launch_bounds__(Team::W * kWave, 2) void team_kernel(Batch batch) {
 #pragma unroll
     for (int a = 0; a < TH; ++a) {
       kap[a] = tau_eff * (double)imp[a][0];
-      mrow[a] = __double2float_ru(kap[a]);
+      mrow[a] = (float)kap[a];
     }
   }
   all_reduce_max_x<T, TH>(mrow);
 #pragma unroll
   for (int a = 0; a < TH; ++a) {
     mrow[a] = fmaxf(mrow[a], lane_xor<16>(mrow[a]));
-    mrow[a] = fmaxf(mrow[a], lane_xor<32>(mrow[a]));
+    mrow[a] = next_up(fmaxf(mrow[a], lane_xor<32>(mrow[a])));
     kap[a] = exp(fmax(kap[a] - (double)mrow[a], kMinLogKernel));
   }
 

@@ -19,11 +19,11 @@
 // Precision.  Default: everything in double (MI355X issues fp64 vector operations at 16 lanes/clk/SIMD),
 // which reproduces a double-precision reference to ~1e-13.  FAST: the first kWarmIters iterations in
 // double, then the loop in fp32 (a shorter instruction, and half the registers: three waves per SIMD
-// instead of two) on kappa32 = fl32(kappa U V) with fp32 scalings relative to the double ones, which are
-// kept as logarithms.  fp32 has 8 exponent bits, so every kChunk iterations the relative scalings are
-// checked and, when one has drifted past 2^+-kDriftBits, their logarithms are added to the double ones and
-// kappa32 is rebuilt as fl32(exp(K - row max + log U + log V)) from a fresh read of the importance (kappa
-// itself is not kept: the kernel is budgeted the registers of three waves per SIMD).  Rebuilt entries are clamped to about
+// instead of two; four for M = 32) on kappa32 = fl32(kappa U V) with fp32 scalings relative to the double ones.  fp32 has 8
+// exponent bits, so every kChunk iterations the relative scalings are checked and, when one has drifted past
+// 2^+-kDriftBits, they are multiplied into the double ones and kappa32 is rebuilt as
+// fl32(exp(K - row max + log U + log V)) from a fresh read of the importance (kappa itself is not kept: the kernel is
+// budgeted the registers of the fp32 loop).  Rebuilt entries are clamped to about
 // [2^-120, 2^80]; within the drift bound (2^+-80 for a product of a row and a column scaling) a clamped
 // entry is still >= 1 (capped) or <= 2^-40 (nothing).
 //
@@ -692,10 +692,13 @@ __global__ __launch_bounds__((DykstraLaunch<M, FAST, ADAPT, TILES>::kThreads), (
     const double Nd = (double)p.N;
     iters_done = p.T;
     const long long cycles0 = clock64(), ticks0 = wall_clock64();
-    // logs of the scalings of the rows and columns this lane owns (the first registers after a
-    // reduce-scatter); the other lanes of the lane-row / lane-column hold the same values for theirs
+    // scalings of the rows and columns this lane owns (the first registers after a reduce-scatter); the other lanes of the
+    // lane-row / lane-column hold the same values for theirs.  FAST: in the form own * 2^exponent, so that the factors of
+    // any number of chunks can be multiplied in; their logarithms (76 instructions each) are only taken where they are used (2:4
+    // 4096x4096: 462 -> 450 us a call).
     constexpr int OWN_R = owned(TH, T::NX), OWN_C = owned(TW, T::NY);
-    double lu_own[OWN_R], lv_own[OWN_C];
+    double u_own[OWN_R], v_own[OWN_C];
+    [[maybe_unused]] int u_exp[OWN_R] = {}, v_exp[OWN_C] = {};
     // early exit: a block whose factors have passed the tolerance is frozen at that iteration
     bool frozen = false;
     auto freeze_if = [&](bool passed, int t_done) {
@@ -755,16 +758,26 @@ __global__ __launch_bounds__((DykstraLaunch<M, FAST, ADAPT, TILES>::kThreads), (
           for (int b = 0; b < TW; ++b) kap32[a][b] = (float)fmin(fmax(kap[a][b] * V[b], floor32), ceil32);
       }
 #pragma unroll
+      for (int a = 0; a < OWN_R; ++a) u_own[a] = Uown[a];
+#pragma unroll
+      for (int b = 0; b < OWN_C; ++b) v_own[b] = V[b];
+    }
+    double lu_own[OWN_R], lv_own[OWN_C];  // (set by take_logs)
+    auto take_logs = [&]() {
+      constexpr double kLn2 = 0x1.62e42fefa39efp-1;
+#pragma unroll
       for (int a = 0; a < OWN_R; ++a) {
-        lu_own[a] = log(Uown[a]);
+        lu_own[a] = log(u_own[a]);
+        if constexpr (FAST) lu_own[a] = fma((double)u_exp[a], kLn2, lu_own[a]);
         __builtin_amdgcn_sched_barrier(0);
       }
 #pragma unroll
       for (int b = 0; b < OWN_C; ++b) {
-        lv_own[b] = log(V[b]);
+        lv_own[b] = log(v_own[b]);
+        if constexpr (FAST) lv_own[b] = fma((double)v_exp[b], kLn2, lv_own[b]);
         __builtin_amdgcn_sched_barrier(0);
       }
-    }
+    };
 
     if constexpr (FAST) {
       if (p.T > kWarmIters && !(ADAPT && __all(frozen))) {
@@ -806,13 +819,15 @@ __global__ __launch_bounds__((DykstraLaunch<M, FAST, ADAPT, TILES>::kThreads), (
         auto fold = [&]() {
 #pragma unroll
           for (int a = 0; a < OWN_R; ++a) {
-            lu_own[a] += log((double)U32[a]);
-            __builtin_amdgcn_sched_barrier(0);
+            const double u = u_own[a] * (double)U32[a];
+            u_exp[a] += __builtin_amdgcn_frexp_exp(u);
+            u_own[a] = __builtin_amdgcn_frexp_mant(u);
           }
 #pragma unroll
           for (int b = 0; b < OWN_C; ++b) {
-            lv_own[b] += log((double)V32[b]);
-            __builtin_amdgcn_sched_barrier(0);
+            const double v = v_own[b] * (double)V32[b];
+            v_exp[b] += __builtin_amdgcn_frexp_exp(v);
+            v_own[b] = __builtin_amdgcn_frexp_mant(v);
           }
         };
 #pragma unroll
@@ -849,6 +864,7 @@ __global__ __launch_bounds__((DykstraLaunch<M, FAST, ADAPT, TILES>::kThreads), (
           // wave-uniform: fold the fp32 scalings into the double ones when any lane's have drifted
           if (t < p.T && __any(!(mxs < hi && mns > lo))) {
             fold();
+            take_logs();
             rebuild();
           }
         }
@@ -862,6 +878,7 @@ __global__ __launch_bounds__((DykstraLaunch<M, FAST, ADAPT, TILES>::kThreads), (
       h->loop_ticks = (unsigned long long)(wall_clock64() - ticks0);
     }
 
+    take_logs();
     const int rx2 = fresh(rx), ry2 = fresh(ry);
     if constexpr (kPotentials) {
       // every row and column of the block has an owner among its lanes (on fine tiles several, with the same values)

@@ -92,10 +92,8 @@ enum {
    * runs on the small tiles or on a workgroup per block (below) iterates in double whatever this flag says: such a launch is bound by latency,
    * not by instruction issue, and single precision would buy nothing. */
   TSENOR_FLAG_FP32_ITERATIONS = 1u << 2,
-  /* Which kernel runs the greedy selection (Algorithm 2 lines 1-6) for M = 4 on the large tiles.  Both give the same
-   * mask.  One takes one lane per block (the default: never slower), the other M lanes per block and decides M scan
-   * entries per step.  For M >= 8 the selection is part of the one rounding kernel and the flags change nothing.
-   * Setting both is an error. */
+  /* Accepted for callers that set them, and without effect: there is one way the greedy selection (Algorithm 2 lines 1-6) is
+   * found for each block size.  Setting both is an error. */
   TSENOR_FLAG_GREEDY_ONE_LANE = 1u << 3,
   TSENOR_FLAG_GREEDY_M_LANES = 1u << 4,
   /* How the Dykstra kernel spreads a block over lanes.  Same arithmetic, same results up to the order of
@@ -103,9 +101,8 @@ enum {
    * fewest instructions per entry: best for full matrices.  SMALL tiles (M <= 32, iters > 0, not with
    * TSENOR_FLAG_SIMPLE_ROUNDING; ignored otherwise): 16 entries per lane (4 for M <= 8, and for M = 16 in small matrices),
    * more lanes per block, a shorter dependent chain per iteration: best while the launch cannot fill the
-   * chip anyway; on them the whole path, Algorithm 2 included, runs in one kernel (the TSENOR_FLAG_GREEDY_* choice
-   * does not apply).  A few 64 x 64 blocks (fewer than 257) get a workgroup each, in one kernel as well, unless LARGE is
-   * asked for.  Default: chosen by the number of blocks of the matrix (and earlier for the large tiles when
+   * chip anyway; on them the whole path, Algorithm 2 included, runs in one kernel.  A few 64 x 64 blocks (fewer
+   * than 257) get a workgroup each, in one kernel as well, unless LARGE is asked for.  Default: chosen by the number of blocks of the matrix (and earlier for the large tiles when
    * TSENOR_FLAG_FP32_ITERATIONS is set, which only they honour).  Setting both is an error. */
   TSENOR_FLAG_TILES_LARGE = 1u << 5,
   TSENOR_FLAG_TILES_SMALL = 1u << 6,
@@ -171,8 +168,8 @@ enum { TSENOR_IMPORTANCE_ABS = 0, TSENOR_IMPORTANCE_SQUARE = 1 };
 
 /* Bytes of device scratch that tsenor_mask_ex / tsenor_mask_batched need for these problems
  * (the sum over the batch).  0 on invalid arguments.  The scratch holds what passes between the kernels of
- * the path: the potentials of every block or the scan order of Algorithm 2 line 1 (two bytes per weight are set aside), the
- * mask greedy selection leaves (Algorithm 2 line 6) and per-block objective values of Eq. 1. */
+ * the path: the potentials of every block (two bytes per weight are set aside), the mask greedy selection leaves (Algorithm 2
+ * line 6), per-block counters and per-block objective values of Eq. 1. */
 size_t tsenor_workspace_bytes(const tsenor_problem* problems, int count);
 
 /* The whole path (tile load -> Algorithm 1 -> Algorithm 2 -> mask write) for one matrix: Eq. 1 solved block

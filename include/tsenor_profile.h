@@ -18,8 +18,8 @@ extern "C" {
  * stage boundaries, synchronises the stream, and writes to the HOST array stage_ms[TSENOR_NUM_STAGES] the
  * mean duration in milliseconds of
  *   [0] workspace reset + matrix maximum (REL_MATRIX_MAX only)
- *   [1] tile load + Algorithm 1 (M = 4: + sort; small launches: the whole path)
- *   [2] M >= 8: the whole of Algorithm 2; M = 4: greedy selection (lines 1-6)
+ *   [1] tile load + Algorithm 1 (M = 4: + greedy selection; small launches: the whole path)
+ *   [2] M >= 8: Algorithm 2 and the mask write
  *   [3] M = 4: local search (lines 7-13) + mask write; and the optional outputs.
  * loop_clock_mhz (HOST, optional): the shader clock, in MHz, that the first wave of the Dykstra kernel saw over
  * its iteration loop in the last repeat (cycle counter against the constant-rate timer; 0 if not measured, as

@@ -1,6 +1,6 @@
 // Tile load and Algorithm 1 (Dykstra iterations), one kernel.  For M >= 8 on the large tiles it leaves the potentials of
-// every block for round_kernel; for M = 4 there the sort that feeds Algorithm 2 follows; on the small tiles the whole of
-// Algorithm 2 does.
+// every block for round_kernel; for M = 4 there the greedy selection follows; on the small tiles the whole of Algorithm 2
+// does.
 //
 // How Algorithm 1 is evaluated.  With A = log S + log Q, the cap step (lines 5-6) gives
 // log S = min(A, 0) and log Q = max(A, 0) after every iteration, and one iteration adds a row term
@@ -459,82 +459,6 @@ __device__ __forceinline__ float dykstra_iteration_f32(const float (&kap)[TH][TW
   return worst;
 }
 
-// min(a, -b) as one instruction (fmin() would first quiet possible signalling NaNs in operands the compiler
-// has not computed itself, one more instruction each)
-__device__ __forceinline__ double min_with_negated(double a, double b) {
-  double r;
-  asm("v_min_f64 %0, %1, -%2" : "=v"(r) : "v"(a), "v"(b));
-  return r;
-}
-
-// Sign convention of the keys between sort stages: the lanes whose bit SB is set hold their keys negated
-// (SB = 0: nobody).  Moves from convention SB to convention B: one xor per key in the lanes that change.
-template <int SB, int B, int E>
-__device__ __forceinline__ void sort_resign(double (&c)[E], int q) {
-  if constexpr (SB != B) {
-    const bool flip = ((q & SB) != 0) != ((q & B) != 0);
-    const int mask = flip ? (int)0x80000000 : 0;
-#pragma unroll
-    for (int r = 0; r < E; ++r) c[r] = __hiloint2double(__double2hiint(c[r]) ^ mask, __double2loint(c[r]));
-  }
-}
-
-// Ascending bitonic sort of E*LPB distinct positive doubles spread over LPB lanes (position q*E + r).
-// Every merge starts with the mirrored compare (position p against p ^ (k-1)), after which the smaller
-// key always belongs at the lower position, so no direction flags are needed.
-// A stage across lanes: the lane whose bit is clear keeps the smaller of its key and the partner's, the other
-// lane the larger.  With the keys of the second kind of lane held negated, both are min(own, -partner's):
-// two cross-lane moves and one instruction per key instead of a compare and two selects (the selects and the
-// moves issue at the double-precision rate on this chip), plus one xor per key where the convention changes.
-template <int E, int LPB, int J, int SB = 0>
-__device__ __forceinline__ void sort_half_cleaners(double (&c)[E], int q) {
-  if constexpr (J >= 1) {
-    if constexpr (J < E) {
-      sort_resign<SB, 0>(c, q);
-#pragma unroll
-      for (int r = 0; r < E; ++r) {
-        const int pr = r ^ J;
-        if (pr > r) compare_exchange(c[r], c[pr]);
-      }
-      sort_half_cleaners<E, LPB, J / 2, 0>(c, q);
-    } else {
-      constexpr int lm = J / E;
-      sort_resign<SB, lm>(c, q);
-#pragma unroll
-      for (int r = 0; r < E; ++r) c[r] = min_with_negated(c[r], lane_xor<lm>(c[r]));
-      sort_half_cleaners<E, LPB, J / 2, lm>(c, q);
-    }
-  } else {
-    sort_resign<SB, 0>(c, q);
-  }
-}
-
-template <int E, int LPB, int K = 2>
-__device__ __forceinline__ void sort_ascending(double (&c)[E], int q) {
-  if constexpr (K <= E * LPB) {
-    if constexpr (K <= E) {
-#pragma unroll
-      for (int r = 0; r < E; ++r) {
-        const int pr = r ^ (K - 1);
-        if (pr > r) compare_exchange(c[r], c[pr]);
-      }
-      sort_half_cleaners<E, LPB, K / 4, 0>(c, q);
-    } else {
-      constexpr int lm = K / E - 1, bit = K / E / 2;
-      sort_resign<0, bit>(c, q);
-      // position r meets the partner lane's position E-1-r; two registers at a time keeps this in place
-#pragma unroll
-      for (int r = 0; r < E / 2; ++r) {
-        const double o_lo = lane_xor<lm>(c[E - 1 - r]), o_hi = lane_xor<lm>(c[r]);
-        c[r] = min_with_negated(c[r], o_lo);
-        c[E - 1 - r] = min_with_negated(c[E - 1 - r], o_hi);
-      }
-      sort_half_cleaners<E, LPB, K / 4, bit>(c, q);
-    }
-    sort_ascending<E, LPB, K * 2>(c, q);
-  }
-}
-
 // calls f(integral_constant<A0>) for A0 = 0, NA, 2 NA, ... < TH: a tile is loaded NA rows at a time
 template <int A0, int NA, int TH, class F>
 __device__ __forceinline__ void row_chunks(F& f) {
@@ -575,7 +499,6 @@ __global__ __launch_bounds__((DykstraLaunch<M, FAST, ADAPT, TILES>::kThreads), (
   constexpr bool SMALL = TILES != kLargeTiles;
   const int which = find_problem(batch, blockIdx.x);
   const DevProblem p = batch.e[which].p;
-  unsigned short* order = batch.e[which].order;
   double* plan_out = batch.e[which].plan_out;
   double* tau_eff_out = batch.e[which].tau_eff_out;
   const unsigned int group = blockIdx.x - batch.first[which];  // workgroup index within the matrix
@@ -618,9 +541,8 @@ __global__ __launch_bounds__((DykstraLaunch<M, FAST, ADAPT, TILES>::kThreads), (
   // tiles of M = 64 would keep 64 loads with their addresses in flight and spill
   constexpr int NA = M == 64 ? TH / kRowChunks64 : (FAST && TH >= 8) ? TH / 2 : TH;
 
-  // Blocks are rounded from their potentials (in a kernel of their own for the large tiles); only 4 x 4 blocks on the large
-  // tiles, a lane each, are sorted here and scanned with one lane per block (round_kernel would give them four lanes, and
-  // their potentials take more room than their order)
+  // Blocks are rounded from their potentials (in a kernel of their own for the large tiles); only for 4 x 4 blocks on the
+  // large tiles, a lane each, the greedy selection is done here (round_kernel would give them four lanes)
   constexpr bool kPotentials = M >= 8 || SMALL;
   [[maybe_unused]] double c[kPotentials ? 1 : E];  // sort keys
   __shared__ double pot[2][kPotentials && SMALL ? BPW : 1][M];  // small tiles: potentials of the matrix rows and columns
@@ -891,7 +813,7 @@ __global__ __launch_bounds__((DykstraLaunch<M, FAST, ADAPT, TILES>::kThreads), (
       } else {
         if (group == 0 && threadIdx.x == 0) batch.e[which].hdr->tau_eff = tau_eff;
         if (active) {
-          BlockPotentials<M>* out = reinterpret_cast<BlockPotentials<M>*>(order) + blk;
+          BlockPotentials<M>* out = static_cast<BlockPotentials<M>*>(batch.e[which].potentials) + blk;
 #pragma unroll
           for (int a = 0; a < OWN_R; ++a) out->u[gy * TH + (a ^ rx2)] = lu_own[a] - (double)mrow[a];
 #pragma unroll
@@ -955,22 +877,16 @@ __global__ __launch_bounds__((DykstraLaunch<M, FAST, ADAPT, TILES>::kThreads), (
     if constexpr (SMALL) {
       __shared__ RoundingLds<M, BPW> lds;
       wave_sync();
-      round_blocks<M, LPB, false>(p, batch.e[which], blk, active, r0, c0, lane, tau_eff, pot[0], pot[1], lds, false);
+      round_blocks<M, LPB, false>(p, batch.e[which], blk, active, r0, c0, lane, tau_eff, pot[0], pot[1], lds);
     }
   } else {
-    sort_ascending<E, LPB>(c, q);
-    // The stores below sit under `active`, and only the index bits of a key are stored: the compiler would move
-    // the last stage's selects into that branch but has to leave its cross-lane moves outside, all of them
-    // alive at once.  Using the keys here keeps every select next to its moves.
-#pragma unroll
-    for (int r = 0; r < E; ++r) asm volatile("" : "+v"(c[r]));
-
-    if (active && q == 0 && batch.e[which].iters_done_out) batch.e[which].iters_done_out[blk] = iters_done;
+    // a lane has its whole block: the greedy selection follows in registers
+    static_assert(LPB == 1 && M == 4, "a lane per block");
+    sort_in_lane(c);
     if (active) {
-      unsigned short* dst = order + blk * (int64_t)(M * M) + q * E;
-#pragma unroll
-      for (int r = 0; r < E; ++r)
-        dst[r] = (unsigned short)((unsigned long long)__double_as_longlong(c[r]) & ((1ull << kIdxBits) - 1));
+      const unsigned int m = select_in_lane(c, p.N, p.simple != 0);
+      reinterpret_cast<uint4*>(batch.e[which].rowmask)[blk] = make_uint4(m & 15u, (m >> 4) & 15u, (m >> 8) & 15u, m >> 12);
+      if (batch.e[which].iters_done_out) batch.e[which].iters_done_out[blk] = iters_done;
     }
   }
 }

@@ -16,12 +16,11 @@ enum { kLargeTiles, kSmallTiles, kFinestTiles, kTeam };
 struct Variant {
   int M;
   bool fast, zero_t;
-  uint32_t greedy;  // the TSENOR_FLAG_GREEDY_* asked for (M = 4)
   int tiles;        // the Dykstra kernel's tiling (decided per problem, so that fusing never changes results)
   bool simple;      // TSENOR_FLAG_SIMPLE_ROUNDING
   bool adaptive;    // tol > 0: the early-exit instantiation of the Dykstra kernel
   bool operator==(const Variant& o) const {
-    return M == o.M && fast == o.fast && zero_t == o.zero_t && greedy == o.greedy && tiles == o.tiles &&
+    return M == o.M && fast == o.fast && zero_t == o.zero_t && tiles == o.tiles &&
            simple == o.simple && adaptive == o.adaptive;
   }
 };
@@ -50,10 +49,9 @@ constexpr int64_t finest_tiles_below_blocks(int M) { return M == 16 ? 1800 : 0; 
 // 189 / 299 / 377, 300 blocks 354 / 300.
 constexpr int64_t team_below_blocks(int M) { return M == 64 ? 257 : 0; }
 
-// Enqueues the kernels of one fused launch that depend on M: tile load + Algorithm 1 (+ sort for M = 4), greedy selection
-// (or the simple rounding arm), local search + mask write; the last two are one kernel for M >= 8.  `b.count`
-// non-degenerate problems of variant v.  ev (optional): events recorded after the iterations and after the greedy selection
-// (M >= 8: after the whole of Algorithm 2).
+// Enqueues the kernels of one fused launch that depend on M: tile load + Algorithm 1 (for M = 4 with the greedy selection, on
+// small launches the whole path), then Algorithm 2 + mask write.  `b.count` non-degenerate problems of variant v.
+// ev (optional): events recorded after the first, and after the second where that is the whole of Algorithm 2 (M >= 8).
 // Returns false if a launch could not be described (more workgroups than a grid holds).
 template <int M>
 bool launch_block_kernels(Batch& b, const Variant& v, hipStream_t stream, hipEvent_t ev_sorted, hipEvent_t ev_greedy);

@@ -84,23 +84,11 @@ bool launch_block_kernels(Batch& b, const Variant& v, hipStream_t stream, hipEve
     // the whole of Algorithm 2 in one kernel
     if (!assign_groups(b, kWave / M)) return false;
     if (v.zero_t)
-      round_kernel<M, true><<<b.first[b.count], kWave, 0, stream>>>(b, v.simple);
+      round_kernel<M, true><<<b.first[b.count], kWave, 0, stream>>>(b);
     else
-      round_kernel<M, false><<<b.first[b.count], kWave, 0, stream>>>(b, v.simple);
+      round_kernel<M, false><<<b.first[b.count], kWave, 0, stream>>>(b);
     if (ev_greedy) (void)hipEventRecord(ev_greedy, stream);
   } else {
-    const bool wide = v.greedy == TSENOR_FLAG_GREEDY_M_LANES;
-    if (v.simple) {
-      if (!assign_groups(b, kWave)) return false;
-      simple_round_kernel<M><<<b.first[b.count], kWave, 0, stream>>>(b);
-    } else if (wide) {
-      if (!assign_groups(b, kWave / M)) return false;
-      greedy_wide_kernel<M><<<b.first[b.count], kWave, 0, stream>>>(b);
-    } else {
-      if (!assign_groups(b, kWave)) return false;
-      constexpr int GW = kGreedyWaves;
-      greedy_kernel<M><<<(b.first[b.count] + GW - 1) / GW, kWave * GW, 0, stream>>>(b);
-    }
     if (ev_greedy) (void)hipEventRecord(ev_greedy, stream);
     if (!assign_groups(b, kWave / M)) return false;
     finalize_kernel<M><<<b.first[b.count], kWave, 0, stream>>>(b);

@@ -7,7 +7,7 @@
 
 namespace tsenor_dev {
 
-// Head of a matrix's workspace slice: what the kernels of a call pass to each other besides the scan order.
+// Head of a matrix's workspace slice: what the kernels of a call pass to each other besides the potentials and masks of the blocks.
 struct WsHeader {
   double tau_eff;         // multiplier of the importance, left by the iterations for the rounding (M >= 8, T > 0)
   // measurement aid: shader-clock cycles and constant-rate timer ticks that the first wave of the Dykstra kernel
@@ -31,7 +31,8 @@ struct DevProblem {
   const float* col_scale;
   int64_t ld, cols, nblocks, bc;  // bc: blocks per block-row
   int dtype, N, T, transpose;
-  int L, strict;
+  int L;
+  short strict, simple;  // simple: the ablation arm in place of Algorithm 2
   double tau;
   int tau_mode;
   float add_scale;
@@ -50,7 +51,7 @@ struct BatchEntry {
   WsHeader* hdr;                // workspace slices of this matrix
   float* absmax_partial;        // partial maxima of the importance, absmax_count of them (relative tau only)
   int absmax_count;
-  unsigned short* order;
+  void* potentials;             // BlockPotentials of every block (M >= 8)
   void* rowmask;                // greedy's mask (M = 4), then the blocks' counters
   double* block_objective;      // NULL: no objective asked for
   uint8_t* mask;                // outputs of the caller (NULL where optional and not asked for)

@@ -27,140 +27,6 @@ __device__ __forceinline__ int mask_popc(mask_t v) {
     return __popc((unsigned int)v);
 }
 
-// Waves per workgroup of greedy_kernel: one per SIMD of a CU.  A wave's pace is its own dependent chain: it must not share a
-// SIMD while others idle, and one-wave workgroups were placed unevenly (57 344 blocks: 0.096 ms against 0.077 ms).
-constexpr int kGreedyWaves = 4;
-
-// Algorithm 2 lines 1-6: scan the entries of a block in sorted order and keep an entry while its row
-// and its column hold fewer than N.  The chain of M*M dependent steps runs with ONE LANE PER BLOCK, so
-// every lane of the wave does useful work; the state of a lane (M row masks, M column counters) lives in
-// LDS.  The kernel is bound by the instruction issue of its single wave per SIMD (~27 instructions per
-// entry), not by memory: the scan order is prefetched a cache line ahead and the LDS state of four entries
-// is fetched per round trip.  Serves M = 4 (larger blocks: round_kernel).  Output: the mask as M row bit masks per block (bit c of word r = S[r][c]).
-template <int M>
-__global__ __launch_bounds__(kWave * kGreedyWaves) void greedy_kernel(Batch batch) {
-  using mask_t = block_mask_t<M>;
-  constexpr int MM = M * M;
-  __shared__ mask_t rowbits_[kGreedyWaves][M][kWave];
-  __shared__ unsigned char colcnt_[kGreedyWaves][M][kWave];
-  auto& rowbits = rowbits_[threadIdx.x / kWave];
-  auto& colcnt = colcnt_[threadIdx.x / kWave];
-  // `vgroup` counts 64-block groups across the launch, as the group prefix of the batch does
-  const unsigned int vgroup = blockIdx.x * kGreedyWaves + threadIdx.x / kWave;
-  if (vgroup >= batch.first[batch.count]) return;  // (a whole wave; the kernel has no barrier)
-  const int which = find_problem(batch, vgroup);
-  const unsigned short* order = batch.e[which].order;
-  const int64_t nblocks = batch.e[which].p.nblocks;
-  const int N = batch.e[which].p.N;
-  mask_t* rowmask = static_cast<mask_t*>(batch.e[which].rowmask);
-  const int lane = threadIdx.x % kWave;
-  const int64_t blk = (int64_t)(vgroup - batch.first[which]) * kWave + lane;
-  for (int k = 0; k < M; ++k) {
-    rowbits[k][lane] = 0;
-    colcnt[k][lane] = 0;
-  }
-  if (blk < nblocks) {
-    const unsigned short* src = order + blk * MM;
-    int placed = 0;
-    const int need = N * M;
-    // the scan order arrives 8 entries per 16-byte load; the D loads of the next 8*D entries (one 128-byte
-    // line of this lane's block for D = 8) are in flight while the current 8*D entries are decided
-    constexpr int D = MM / 8 < 8 ? MM / 8 : 8;
-    uint4 cur[D], nxt[D];
-#pragma unroll
-    for (int d = 0; d < D; ++d) nxt[d] = cur[d] = *reinterpret_cast<const uint4*>(src + 8 * d);
-    for (int h0 = 0; h0 < MM && placed < need; h0 += 8 * D) {
-      if (h0 + 8 * D < MM) {
-#pragma unroll
-        for (int d = 0; d < D; ++d) nxt[d] = *reinterpret_cast<const uint4*>(src + h0 + 8 * D + 8 * d);
-      }
-#pragma unroll
-      for (int d = 0; d < D; ++d) {
-      const uint4 v = cur[d];
-      const unsigned int pk[4] = {v.x, v.y, v.z, v.w};
-      // four entries per step: their rows' masks and columns' counters are read together (one LDS round trip
-      // instead of four), the decisions are then taken in order in registers, a later entry of the four
-      // inheriting the state of an earlier one in the same row or column
-#pragma unroll
-      for (int half = 0; half < 2; ++half) {
-        unsigned int i[4], j[4], cc[4];
-        mask_t rb[4];
-#pragma unroll
-        for (int k = 0; k < 4; ++k) {
-          const unsigned int idx = (pk[half * 2 + (k >> 1)] >> ((k & 1) * 16)) & (unsigned)(MM - 1);
-          i[k] = idx / M;
-          j[k] = idx % M;
-          rb[k] = rowbits[i[k]][lane];
-          cc[k] = colcnt[j[k]][lane];
-        }
-#pragma unroll
-        for (int k = 0; k < 4; ++k) {
-          const unsigned int take = (mask_popc(rb[k]) < N && cc[k] < (unsigned)N) ? 1u : 0u;
-          rb[k] |= (mask_t)take << j[k];
-          cc[k] += take;
-          placed += (int)take;
-#pragma unroll
-          for (int m = k + 1; m < 4; ++m) {
-            rb[m] = i[m] == i[k] ? rb[k] : rb[m];
-            cc[m] = j[m] == j[k] ? cc[k] : cc[m];
-          }
-        }
-        // written back in order: for a row or column that occurs twice the later, more complete value stays
-#pragma unroll
-        for (int k = 0; k < 4; ++k) {
-          rowbits[i[k]][lane] = rb[k];
-          colcnt[j[k]][lane] = (unsigned char)cc[k];
-        }
-      }
-      }
-#pragma unroll
-      for (int d = 0; d < D; ++d) cur[d] = nxt[d];
-    }
-    for (int k = 0; k < M; ++k) rowmask[blk * M + k] = rowbits[k][lane];
-  }
-}
-
-// Ablation arm "Simple" (App. B.2.1): row-wise then column-wise N:M rounding of the plan.  In scan order
-// (descending plan, ties by index) an entry survives the row stage while its row has passed fewer than N
-// entries, and a survivor is kept while its column holds fewer than N: the first N of every row, then the
-// first N survivors of every column.  One lane per block, same output as greedy_kernel.
-template <int M>
-__global__ __launch_bounds__(kWave) void simple_round_kernel(Batch batch) {
-  using mask_t = block_mask_t<M>;
-  constexpr int MM = M * M;
-  __shared__ mask_t rowbits[M][kWave];
-  __shared__ unsigned char passed[M][kWave], colcnt[M][kWave];
-  const int which = find_problem(batch, blockIdx.x);
-  const unsigned short* order = batch.e[which].order;
-  const int64_t nblocks = batch.e[which].p.nblocks;
-  const int N = batch.e[which].p.N;
-  mask_t* rowmask = static_cast<mask_t*>(batch.e[which].rowmask);
-  const int lane = threadIdx.x;
-  const int64_t blk = (int64_t)(blockIdx.x - batch.first[which]) * kWave + lane;
-  for (int k = 0; k < M; ++k) {
-    rowbits[k][lane] = 0;
-    passed[k][lane] = 0;
-    colcnt[k][lane] = 0;
-  }
-  if (blk < nblocks) {
-    const unsigned short* src = order + blk * MM;
-    for (int h = 0; h < MM; ++h) {
-      const unsigned int idx = src[h] & (unsigned)(MM - 1);
-      const unsigned int i = idx / M, j = idx % M;
-      const unsigned int through = passed[i][lane];
-      if (through < (unsigned)N) {
-        passed[i][lane] = (unsigned char)(through + 1);
-        const unsigned int cj = colcnt[j][lane];
-        if (cj < (unsigned)N) {
-          colcnt[j][lane] = (unsigned char)(cj + 1);
-          rowbits[i][lane] |= (mask_t)1 << j;
-        }
-      }
-    }
-    for (int k = 0; k < M; ++k) rowmask[blk * M + k] = rowbits[k][lane];
-  }
-}
-
 // LDS of the lane-parallel rounding steps for the G blocks a wave holds: the mask as row and column bit masks
 // (rowm[r] bit c == colm[c] bit r == S[r][c]), column counters of the greedy selection, the importance block.
 template <int M, int G>
@@ -171,93 +37,6 @@ struct RoundingLds {
   static constexpr int kImpLd = M + 1;
   float imp[G][M * kImpLd];
 };
-
-// The same selection with M lanes per block: the block's scan order is taken M entries at a time, one entry
-// per lane, and all M are decided together.  An entry is rejected for certain when the entries before it in
-// the chunk that are already accepted fill its row or its column, and accepted for certain when its row and
-// its column have room even if every undecided entry before it were accepted; what is left undecided waits
-// for the next round.  The earliest undecided entry of a block always resolves, so the rounds end, and by
-// induction along the scan order every decision equals the sequential one.  Dependent chain: M chunks of a
-// few rounds instead of M*M steps.
-// A block owns LPB >= M consecutive lanes of the wave (LPB a power of two), of which the first M take part;
-// fetch(pos) returns the flat index at scan position pos of this lane's block.  Leaves the mask in lds.rowm.  To be called by
-// whole waves.
-template <int M, int LPB, class Fetch>
-__device__ __forceinline__ void greedy_wide_scan(Fetch&& fetch, int N, int lane, RoundingLds<M, kWave / LPB>& lds) {
-  using mask_t = block_mask_t<M>;
-  constexpr int MM = M * M;
-  constexpr int LOGM = M == 4 ? 2 : M == 8 ? 3 : M == 16 ? 4 : M == 32 ? 5 : 6;
-  const int g = lane / LPB, ql = lane % LPB;
-  const bool part = ql < M;
-  if (part) {
-    lds.rowm[g][ql] = 0;
-    lds.colcnt[g][ql] = 0;
-  }
-  wave_sync();
-  const unsigned long long gmask = (M == 64 ? ~0ull : ((1ull << M) - 1)) << (g * LPB);
-  const unsigned long long earlier = gmask & ((1ull << lane) - 1);  // lanes of this block before this one
-  const int need = N * M;
-  int placed = 0;
-  unsigned int ahead = part ? fetch(ql) : 0u;
-  for (int ch = 0; ch < M; ++ch) {
-    const unsigned int idx = ahead & (unsigned)(MM - 1);
-    if (ch + 1 < M && part) ahead = fetch((ch + 1) * M + ql);
-    const unsigned int i = idx / M, j = idx % M;
-    // lanes of this block whose entry lies in the same row / the same column
-    unsigned long long same_row = gmask, same_col = gmask;
-#pragma unroll
-    for (int b = 0; b < LOGM; ++b) {
-      const bool ib = (i >> b) & 1, jb = (j >> b) & 1;
-      const unsigned long long rows_b = __ballot(ib), cols_b = __ballot(jb);
-      same_row &= ib ? rows_b : ~rows_b;
-      same_col &= jb ? cols_b : ~cols_b;
-    }
-    const unsigned long long before_row = same_row & earlier, before_col = same_col & earlier;
-    const int room_row = N - mask_popc(lds.rowm[g][i]), room_col = N - (int)lds.colcnt[g][j];
-    bool undecided = part && room_row > 0 && room_col > 0, take = false;
-    unsigned long long taken = 0, open = __ballot(undecided);
-    while (open) {
-      if (undecided) {
-        const int t_row = __popcll(taken & before_row), t_col = __popcll(taken & before_col);
-        const int o_row = __popcll(open & before_row), o_col = __popcll(open & before_col);
-        if (t_row >= room_row || t_col >= room_col) {
-          undecided = false;
-        } else if (t_row + o_row < room_row && t_col + o_col < room_col) {
-          undecided = false;
-          take = true;
-        }
-      }
-      taken = __ballot(take);
-      open = __ballot(undecided);
-    }
-    if (take) {
-      atomicOr(&lds.rowm[g][i], (mask_t)1 << j);
-      atomicAdd(&lds.colcnt[g][j], 1u);
-    }
-    placed += __popcll(taken & gmask);
-    wave_sync();
-    if (!__any(placed < need)) break;  // every block of the wave is full
-  }
-}
-
-template <int M>
-__global__ __launch_bounds__(kWave) void greedy_wide_kernel(Batch batch) {
-  using mask_t = block_mask_t<M>;
-  constexpr int MM = M * M, G = kWave / M;
-  __shared__ RoundingLds<M, G> lds;
-  const int which = find_problem(batch, blockIdx.x);
-  const unsigned short* order = batch.e[which].order;
-  const int64_t nblocks = batch.e[which].p.nblocks;
-  const int N = batch.e[which].p.N;
-  mask_t* rowmask = static_cast<mask_t*>(batch.e[which].rowmask);
-  const int lane = threadIdx.x, g = lane / M, ql = lane % M;
-  int64_t blk = (int64_t)(blockIdx.x - batch.first[which]) * G + g;
-  const bool active = blk < nblocks;
-  if (!active) blk = nblocks - 1;  // idle groups shadow the last block and write nothing
-  const unsigned short* src = order + blk * MM;
-  greedy_wide_scan<M, M>([&](int pos) { return (unsigned int)src[pos]; }, N, lane, lds);
-  if (active) rowmask[blk * M + ql] = lds.rowm[g][ql];
-}
 
 // Transpose of an M x M bit matrix held as one M-bit row per lane (M consecutive lanes): afterwards the
 // lane that held row r holds column r.  log2(M) block-swap steps.
@@ -484,8 +263,8 @@ __device__ __forceinline__ void local_search_and_write(const DevProblem& p, cons
   }
 }
 
-// The stand-alone kernel: M lanes per block, 64/M blocks per wave, one wave per workgroup; the mask greedy
-// selection left comes from the workspace.
+// The stand-alone kernel (M = 4 on the large tiles): M lanes per block, 64/M blocks per wave, one wave per workgroup; the
+// mask greedy selection left comes from the workspace.
 template <int M>
 __global__ __launch_bounds__(kWave) void finalize_kernel(Batch batch) {
   using mask_t = block_mask_t<M>;
@@ -523,6 +302,7 @@ template <int M>
 struct BlockPotentials {
   double u[M], v[M];
 };
+static_assert(sizeof(BlockPotentials<8>) <= 2 * 8 * 8, "fits the two bytes per weight the workspace has for it (M >= 8)");
 
 // Scan key of an entry: positive doubles whose order is descending plan, ties by ascending index.  `index` (below 2^12) is the
 // entry's place in what is being sorted: a block, a row or a column.
@@ -548,14 +328,7 @@ __device__ __forceinline__ unsigned int index_bytes(double a, double b, double c
   return ab | cd << 16;
 }
 
-__device__ __forceinline__ void compare_exchange(double& lo, double& hi) {
-  const double a = fmin(lo, hi), b = fmax(lo, hi);
-  lo = a;
-  hi = b;
-}
-
-// the same as the two bare instructions: fmin() and fmax() first quiet possible signalling NaNs in keys that were put
-// together from words
+// (bare instructions: fmin() and fmax() first quiet possible signalling NaNs in keys that were put together from words)
 __device__ __forceinline__ void compare_exchange_as_is(double& lo, double& hi) {
   double a;
   asm("v_min_f64 %0, %1, %2" : "=v"(a) : "v"(lo), "v"(hi));
@@ -581,6 +354,24 @@ __device__ __forceinline__ void sort_in_lane(double (&c)[E]) {
   }
 }
 
+// Algorithm 2 lines 1-6 for a 4 x 4 block in the registers of a lane, from its 16 keys in scan order (index = flat index):
+// an entry is kept while its row and its column hold fewer than N.  Bit i*4+j of the result = S[i][j].
+// `simple`: the ablation arm of App. B.2.1, row-wise then column-wise N:M rounding: an entry survives the row stage while its
+// row has passed fewer than N entries, and a survivor is kept while its column holds fewer than N.
+// ~250 instructions for 64 blocks behind the sort; as a kernel of its own the scan took 15 us of a 2:4 4096x4096 call, and its
+// input two bytes per weight through memory.
+__device__ __forceinline__ unsigned int select_in_lane(const double (&c)[16], int N, bool simple) {
+  unsigned int kept = 0, passed = 0;  // the entries kept; the entries their row counts
+#pragma unroll
+  for (int k = 0; k < 16; ++k) {
+    const unsigned int at = (unsigned int)__double2loint(c[k]) & 15u;
+    const bool pass = __popc((passed >> (at & 12u)) & 15u) < N, keep = pass && __popc((kept >> (at & 3u)) & 0x1111u) < N;
+    kept |= keep ? 1u << at : 0u;
+    passed |= (simple ? pass : keep) ? 1u << at : 0u;
+  }
+  return kept;
+}
+
 // position of the N-th set bit (N >= 1) of a mask that has at least N
 template <int M, class mask_t>
 __device__ __forceinline__ int nth_set_bit(mask_t h, int N) {
@@ -603,7 +394,7 @@ __device__ __forceinline__ int nth_set_bit(mask_t h, int N) {
 template <int M, int LPB, bool ZERO_T>
 __device__ __forceinline__ void round_blocks(const DevProblem& p, const BatchEntry& e, int64_t blk, bool active, int64_t r0,
                                              int64_t c0, int lane, double tau_eff, const double (*row_pot)[M],
-                                             const double (*col_pot)[M], RoundingLds<M, kWave / LPB>& lds, bool simple) {
+                                             const double (*col_pot)[M], RoundingLds<M, kWave / LPB>& lds) {
   using mask_t = block_mask_t<M>;
   constexpr int LD = RoundingLds<M, kWave / LPB>::kImpLd;
   const int g = lane / LPB, ql = lane % M, N = p.N;
@@ -705,7 +496,7 @@ __device__ __forceinline__ void round_blocks(const DevProblem& p, const BatchEnt
     }
     wave_sync();
     held = lds.rowm[g][ql];
-    int lacks = simple ? 0 : N - mask_popc(held);
+    int lacks = p.simple ? 0 : N - mask_popc(held);
     bool proposed = false;
     while (lacks > 0 && next < M) {
       // four places of the row's order per LDS round trip (a row that stays short looks at all that is left of it)
@@ -743,7 +534,7 @@ __device__ __forceinline__ void round_blocks(const DevProblem& p, const BatchEnt
 // the keys 512.  57 344 blocks of 16:32: 0.206 ms with the swaps, where the sort across lanes (0.20 ms of the iteration
 // kernel), the scan kernel (0.077 ms) and the swap kernel (0.104 ms) took 0.38 ms; 16 384 blocks of 32:64: 0.34 ms for 0.78.
 template <int M, bool ZERO_T>
-__global__ __launch_bounds__(kWave, M <= 32 ? 4 : 2) void round_kernel(Batch batch, int simple) {
+__global__ __launch_bounds__(kWave, M <= 32 ? 4 : 2) void round_kernel(Batch batch) {
   constexpr int G = kWave / M;
   __shared__ RoundingLds<M, G> lds;
   __shared__ double row_pot[ZERO_T ? 1 : G][M], col_pot[ZERO_T ? 1 : G][M];
@@ -763,12 +554,12 @@ __global__ __launch_bounds__(kWave, M <= 32 ? 4 : 2) void round_kernel(Batch bat
     if (active && ql == 0 && e.iters_done_out) e.iters_done_out[blk] = 0;
   } else {
     tau_eff = e.hdr->tau_eff;
-    const BlockPotentials<M>* src = reinterpret_cast<const BlockPotentials<M>*>(e.order) + blk;
+    const BlockPotentials<M>* src = static_cast<const BlockPotentials<M>*>(e.potentials) + blk;
     const double of_row = src->u[ql], of_col = src->v[ql];
     row_pot[g][ql] = p.transpose ? of_col : of_row;
     col_pot[g][ql] = p.transpose ? of_row : of_col;
   }
-  round_blocks<M, M, ZERO_T>(p, e, blk, active, at.r0, at.c0, lane, tau_eff, row_pot, col_pot, lds, simple != 0);
+  round_blocks<M, M, ZERO_T>(p, e, blk, active, at.r0, at.c0, lane, tau_eff, row_pot, col_pot, lds);
 }
 
 }  // namespace tsenor_dev

@@ -152,7 +152,7 @@ __global__ __launch_bounds__(Team::W * kWave, 2) void team_kernel(Batch batch) {
   }
   __syncthreads();
   if (wave == 0)
-    round_blocks<M, kWave, false>(p, e, blk, true, at.r0, at.c0, lane, tau_eff, pot[0], pot[1], lds, false);
+    round_blocks<M, kWave, false>(p, e, blk, true, at.r0, at.c0, lane, tau_eff, pot[0], pot[1], lds);
 }
 
 }  // namespace tsenor_dev

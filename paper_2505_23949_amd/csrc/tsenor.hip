@@ -4,11 +4,11 @@
 // kernel variant (a single matrix is a group of one):
 //   1. init_kernel / absmax_kernel      workspace reset; importance maximum of every matrix (relative tau only)
 //   2. dykstra_sort_kernel              tile load, all T Dykstra iterations of Algorithm 1 on chip (and the plan if
-//                                       asked for); leaves the potentials of every block (M >= 8) or the greedy scan
-//                                       order (M = 4)                                     [dykstra_sort.hpp]
+//                                       asked for); leaves the potentials of every block, for M = 4 the mask of the greedy
+//                                       selection; small launches: the whole path         [dykstra_sort.hpp]
+//      team_kernel                      the whole path for a few 64 x 64 blocks           [team.hpp]
 //   3. round_kernel                     M >= 8: the whole of Algorithm 2                  [rounding.hpp]
-//      greedy_kernel, finalize_kernel   M = 4: Algorithm 2 lines 1-6, one lane per block, then lines 7-13 and the mask
-//                                       write (simple_round_kernel: the ablation arm)     [rounding.hpp]
+//      finalize_kernel                  M = 4: Algorithm 2 lines 7-13 and the mask write  [rounding.hpp]
 //   4. objective_kernel, emit_kernel, stats_kernel   optional outputs                     [outputs.hpp]
 // Steps 2-3 depend on the block size and are compiled per M (launch.hpp).  Every kernel takes the table of
 // the group by value and finds the matrix of a workgroup from a prefix of workgroup counts.
@@ -164,10 +164,10 @@ constexpr size_t kAlign = 256;
 inline size_t align_up(size_t x) { return (x + kAlign - 1) / kAlign * kAlign; }
 
 struct WsLayout {
-  size_t header, partials, order, accept, objective, total;
+  size_t header, partials, potentials, accept, objective, total;
 };
 
-// greedy's output: M row bit masks per block, 32-bit words up to M = 32, 64-bit for M = 64
+// greedy's output (M row bit masks per block, 32-bit words up to M = 32, 64-bit for M = 64), then the block's counters
 inline size_t rowmask_bytes_per_block(int M) { return (size_t)M * (M > 32 ? 8 : 4); }
 
 WsLayout layout_of(const tsenor_problem& p) {
@@ -176,8 +176,8 @@ WsLayout layout_of(const tsenor_problem& p) {
   const size_t nblocks = elems / ((size_t)p.M * p.M);
   l.header = 0;
   l.partials = kAlign;
-  l.order = l.partials + align_up(kMaxAbsmaxPartials * sizeof(float));
-  l.accept = l.order + align_up(elems * sizeof(unsigned short));
+  l.potentials = l.partials + align_up(kMaxAbsmaxPartials * sizeof(float));
+  l.accept = l.potentials + align_up(elems * sizeof(unsigned short));
   l.objective = l.accept + align_up(nblocks * rowmask_bytes_per_block(p.M));
   l.total = l.objective + align_up(nblocks * 2 * sizeof(double));  // per-block objectives (new, previous mask)
   return l;
@@ -214,7 +214,6 @@ inline Variant variant_of(const tsenor_problem& p) {
   Variant v;
   v.M = p.M;
   v.zero_t = p.iters == 0;
-  v.greedy = p.flags & (uint32_t)(TSENOR_FLAG_GREEDY_ONE_LANE | TSENOR_FLAG_GREEDY_M_LANES);
   v.simple = (p.flags & TSENOR_FLAG_SIMPLE_ROUNDING) != 0;
   // the tiling is decided from the matrix's own number of blocks, never from what it is fused with: the two
   // tilings differ in the order of the additions inside a row or column sum
@@ -251,6 +250,7 @@ BatchEntry entry_of(const tsenor_problem& p, char* ws) {
   dp.L = p.local_search_steps;
   dp.strict = (p.flags & TSENOR_FLAG_STRICT_PAPER) ? 1 : 0;
   if (p.flags & TSENOR_FLAG_SIMPLE_ROUNDING) {
+    dp.simple = 1;
     dp.L = 0;  // the simple arm has no local search: the last kernel only writes the mask
     dp.strict = 1;
   }
@@ -261,7 +261,7 @@ BatchEntry entry_of(const tsenor_problem& p, char* ws) {
   e.hdr = reinterpret_cast<WsHeader*>(ws + l.header);
   e.absmax_partial = reinterpret_cast<float*>(ws + l.partials);
   e.absmax_count = 0;  // set with the grid of the pre-pass
-  e.order = reinterpret_cast<unsigned short*>(ws + l.order);
+  e.potentials = ws + l.potentials;
   e.rowmask = ws + l.accept;
   e.block_objective = (p.objective_out || p.prev_mask) ? reinterpret_cast<double*>(ws + l.objective) : nullptr;
   e.mask = p.mask;

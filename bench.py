@@ -58,10 +58,12 @@ LOOP_VALU_PER_WAVE_ITER = {
     (16, False): (176, 2048), (16, True): (98, 1024), (32, False): (164, 2048), (32, True): (110, 1024),
     (64, False): (384, 4096),
 }
-# a matrix with fewer blocks than this runs the small-tile instantiation (the library's own choice, mirrored here
-# only to pick the row of the table above)
-SMALL_TILES_BELOW_BLOCKS = {False: {4: 100000, 8: 13000, 16: 40000, 32: 3200, 64: 257},     # default mode
-                            True: {4: 55000, 8: 12000, 16: 9000, 32: 2100, 64: 257}}         # with the fp32 flag
+def small_launch_of(M: int, fp32: bool, nblocks: int) -> bool:
+    """The library's own choice of the small tiles (for M = 64 of a workgroup per block), mirrored here to pick the row
+    of the table above and to say which precision a call iterates in."""
+    if M == 4:
+        return nblocks <= 49152 or (not fp32 and 65536 < nblocks <= 114688)
+    return nblocks < {8: 8700, 16: 8193 if fp32 else 62001, 32: 2049 if fp32 else 3073, 64: 257}[M]
 
 
 def recorded_traffic(workload: str, fp32: bool):
@@ -239,7 +241,7 @@ def bench_matrix(args, name):
     steps = args.steps
     fp32_flag = binding.TSENOR_FLAG_FP32_ITERATIONS
     # a matrix this small runs on the small tiles, which iterate in double whatever the flag says
-    small_launch = nblocks < SMALL_TILES_BELOW_BLOCKS[True][w.M]
+    small_launch = small_launch_of(w.M, True, nblocks)
     headline_fp32 = args.precision == "fp32" and not small_launch
     no_cpu, no_modes = args.no_cpu_baseline, args.no_other_modes
     if args.tol > 0.0:
@@ -317,7 +319,7 @@ def bench_matrix(args, name):
             roofline["pass_traffic_over_algorithmic"] = round(
                 traffic["pass"] / roofline["algorithmic_bytes_per_pass"], 2)
         if not fp32 and w.iters > 0:
-            small = nblocks < SMALL_TILES_BELOW_BLOCKS[False][w.M]
+            small = small_launch_of(w.M, False, nblocks)
             counted = LOOP_VALU_PER_WAVE_ITER.get((w.M, small))
             if counted:
                 # second view of the same measurement: the vector instructions the loop issues against the issue

@@ -215,6 +215,8 @@ def tsenor_mask_ex_static(problem, stream=None) -> None:
 
 
 NUM_STAGES = 4
+# what a stage holds depends on the block size (tsenor_profile.h): for M >= 8 the third is the whole of Algorithm 2 and the
+# fourth the optional outputs
 STAGE_NAMES = ("reset+absmax", "dykstra+sort", "greedy", "local_search+write")
 
 

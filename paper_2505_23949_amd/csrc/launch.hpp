@@ -25,18 +25,23 @@ struct Variant {
   }
 };
 
-// Below this many blocks in a matrix the whole path runs in the one kernel with the small tiles (M <= 32, double
-// iterations): with few waves a SIMD holds one or two, whose iteration time is the dependent chain, and the
-// rounding needs no launches of its own.  `fp32`: the caller asked for single-precision iterations, which only
-// the large tiles have, so they win earlier.  Measured crossovers of a whole call, T = 300 (ms, small / large
-// fp64 / large fp32): M = 32: 3072 blocks 0.259 / 0.280 / 0.216, 3328 blocks 0.314 / 0.286 / 0.222, 2048 blocks
-// 0.189 / 0.198 / 0.188; M = 16: 8192 blocks 0.165 / 0.202 / 0.182, 9216 blocks 0.209 / 0.258 / 0.196, 32 768
-// blocks 0.484 / 0.492 / 0.367, 65 536 blocks 0.916 / 0.886 / 0.567; M = 8: 12 288 blocks 0.102 / 0.104 / 0.101,
-// 16 384 blocks 0.128 / 0.107 / 0.102; M = 4: 49 152 blocks 0.085 / 0.104 / 0.095, 57 344 blocks 0.107 / 0.106 /
-// 0.097, 81 920 blocks 0.133 / 0.174 / 0.113, 131 072 blocks 0.199 / 0.186 / 0.126.
-constexpr int64_t small_tiles_below_blocks(int M, bool fp32) {
-  return M == 4 ? (fp32 ? 55000 : 100000) : M == 8 ? (fp32 ? 12000 : 13000) : M == 16 ? (fp32 ? 9000 : 40000)
-       : M == 32 ? (fp32 ? 2100 : 3200) : 0;
+// Whether the whole path of a matrix runs in the one kernel with the small tiles (M <= 32, double iterations): with few
+// waves a SIMD holds one or two, whose iteration time is the dependent chain, and the rounding needs no launch of its own.
+// `fp32`: the caller asked for single-precision iterations, which only the large tiles have, so they win earlier.  Both
+// sides take their time in steps of whole waves per SIMD (1024 of them), so the lines lie where a step is full.  Whole
+// calls, T = 300 (us, small / large double / large fp32):
+//   M = 32 (a block per wave): 1792 blocks 147 / 159 / 153, 2070 blocks 208 / 221 / 161, 2944 blocks 204 / 228 / 169,
+//     3080 blocks 268 / 230 / 168;
+//   M = 16 (4): 7680 blocks 130 / 152 / 142, 8280 blocks 182 / 222 / 151, 57 344 blocks 797 / 827 / 509, 65 536 blocks
+//     863 / 856 / 529;
+//   M = 8 (4): 8280 blocks 83 / 83 / 85, 9216 blocks 87 / 83 / 85, 10 240 blocks 90 / 84 / 85;
+//   M = 4 (16; the large tiles hold 64): 46 000 blocks 78 / 93 / 85, 49 283 blocks 97 / 93 / 85, 65 536 blocks 100 / 92 / 83,
+//     66 000 blocks 113 / 159 / 94, 106 000 blocks 154 / 166 / 104, 114 920 blocks 179 / 165 / 102.
+constexpr bool small_tiles_win(int M, bool fp32, int64_t nblocks) {
+  if (M == 4) return nblocks <= 49152 || (!fp32 && nblocks > 65536 && nblocks <= 114688);
+  if (M == 8) return nblocks < 8700;
+  if (M == 16) return nblocks <= (fp32 ? 8192 : 62000);
+  return M == 32 && nblocks <= (fp32 ? 2048 : 3072);
 }
 
 // Below this many blocks a 16 x 16 block has a wave of its own: 51 instead of 98 vector instructions in the chain of an

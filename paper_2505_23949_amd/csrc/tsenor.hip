@@ -286,11 +286,13 @@ BatchEntry entry_of(const tsenor_problem& p, char* ws) {
 }
 
 // grid of the kernels that stride over a matrix 8 weights (or 1) at a time: x over a row, y over rows,
-// about `target` workgroups in all, sized for the largest matrix of the batch
+// about `target` workgroups in all, sized for the largest matrix of the batch (vec_only: of those with derived outputs)
 dim3 strided_grid(const Batch& b, bool vec_only, unsigned target, bool for_absmax) {
   unsigned gx = 1, gy = 1;
   for (int k = 0; k < b.count; ++k) {
     const BatchEntry& e = b.e[k];
+    // (derived outputs need cols % 8 == 0, which is only checked of the matrices that ask for them)
+    if (vec_only && !e.packed_out && !e.pruned_out && !e.prev_mask) continue;
     const int64_t per_row = (vec_only || e.absmax_vec) ? e.p.cols / 8 : e.p.cols;
     const unsigned x = (unsigned)std::min<int64_t>((per_row + 255) / 256, 16);
     gx = std::max(gx, x);

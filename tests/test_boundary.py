@@ -124,6 +124,33 @@ def test_limits_checked_before_any_launch(lib):
     assert lib.tsenor_last_hip_error() == 0
 
 
+def test_batch_with_a_matrix_of_one_4_wide_block_column(lib):
+    # A matrix of 4 columns fused with one that asks for derived outputs: the grid of the kernel behind those must be
+    # described without it (it has no whole vector of 8 weights in a row).  In a process that sees no GPU, so that the call
+    # gets past its checks and its first launch fails.
+    from paper_2505_23949_amd import binding as b
+
+    prog = """
+import ctypes
+from paper_2505_23949_amd import binding as b
+lib = b.load()
+def problem(cols, **kw):
+    p = b.tsenor_problem(W=0x100000, mask=0x200000, dtype=b.TSENOR_F32, rows=64, cols=cols, ld=cols, N=2, M=4, tau=1.0,
+                         tau_mode=b.TSENOR_TAU_ABSOLUTE, iters=10, local_search_steps=10)
+    for k, v in kw.items():
+        setattr(p, k, v)
+    return p
+for other in (dict(packed_out=0x300000), dict(pruned_out=0x300000), dict(prev_mask=0x300000)):
+    for mine in ({}, dict(objective_out=0x400000)):
+        arr = (b.tsenor_problem * 2)(problem(64, **other), problem(4, **mine))
+        print(lib.tsenor_mask_batched(arr, 2, ctypes.c_void_p(0x10000), 1 << 40, None))
+"""
+    r = subprocess.run([sys.executable, "-c", prog], capture_output=True, text=True, cwd=ROOT,
+                       env=dict(os.environ, HIP_VISIBLE_DEVICES="-1"))
+    assert r.returncode == 0, (r.returncode, r.stderr)
+    assert r.stdout.split() == [str(b.TSENOR_ERR_HIP)] * 6
+
+
 def test_workspace_bytes(lib):
     from paper_2505_23949_amd import binding as b
 

@@ -55,3 +55,28 @@ def test_derived_outputs_at_every_alignment(M, dtype, offset):
         bar = imp.size * 2.0 ** -53
         got = objective.cpu().numpy()
         assert abs(got[0] - max(mine, theirs)) <= bar * got[0] and abs(got[1] - theirs) <= bar * theirs
+
+
+def test_batch_with_a_matrix_of_one_4_wide_block_column():
+    # fused with matrices that ask for derived outputs, a matrix of 4 columns (plain, and with its objective) is what it is
+    # in a call of its own
+    import torch
+
+    from paper_2505_23949_amd import binding as b
+
+    dev = torch.device("cuda:0")
+    rng = np.random.Generator(np.random.Philox(77))
+    kw = dict(tau_mode=b.TSENOR_TAU_REL_MATRIX_MAX)
+    keep, probs, outs, singles = [], [], [], []
+    for cols, want in ((4, ()), (64, ("packed", "pruned")), (4, ("objective",)), (64, ("objective",))):
+        W = torch.from_numpy(rng.standard_normal((64, cols), dtype=np.float32)).to(dev)
+        print(f"[case] 4-wide batch cols={cols} {want}", flush=True)
+        keep.append(W)
+        singles.append(b.solve(W, 2, 4, 0.01, 50, **{"want_" + k: True for k in want}, **kw))
+        outs.append({k: torch.zeros_like(singles[-1][k]) for k in ("mask",) + want})
+        probs.append(b.make_problem(W, 2, 4, 0.01, 50, mask=outs[-1]["mask"], **{k + "_out": outs[-1][k] for k in want}, **kw))
+    b.tsenor_mask_batched(probs, torch.empty(b.tsenor_workspace_bytes(probs), dtype=torch.uint8, device=dev))
+    torch.cuda.synchronize()
+    for out, single in zip(outs, singles):
+        for k in out:
+            assert torch.equal(out[k], single[k]), k

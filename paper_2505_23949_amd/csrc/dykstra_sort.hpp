@@ -177,11 +177,12 @@ __device__ __forceinline__ void all_gather_x(real (&v)[TH]) {
     all_gather_x<T, real, TH, S - 1>(v);
   }
 }
-// The float above x >= 0 (infinity stays).  The normaliser of a row is to be a float not below its largest K: the largest of
-// the K rounded to nearest, one step up, once per row.  (Every K rounded upwards: there is no such conversion, its 14
-// instructions per entry were a third of the 64-wide prologue; 32:64 8192x8192 with early exit: 796 -> 777 us a call.)
-__device__ __forceinline__ float next_up(float x) {
-  return x < __builtin_huge_valf() ? __uint_as_float(__float_as_uint(x) + 1u) : x;
+// The smallest float not below x >= 0.  The normaliser of a row is to be such a float for its largest K, and no larger one: where
+// K itself is near 2^32 a step of floats is 512 of the 700 that a row may spread.  Taken once per lane and row, of the
+// largest K it holds (5 instructions; rounding every K upwards took 14 per entry, a third of the 64-wide prologue).
+__device__ __forceinline__ float round_up(double x) {
+  const float f = (float)x;
+  return (double)f < x ? __uint_as_float(__float_as_uint(f) + 1u) : f;
 }
 // Maximum over the lanes of a lane-row of a value per tile row (all TH registers, butterfly): afterwards
 // every lane holds the maximum of each of its tile rows.
@@ -550,7 +551,7 @@ __global__ __launch_bounds__((DykstraLaunch<M, FAST, ADAPT, TILES>::kThreads), (
   double kap[ZERO_T ? 1 : TH][ZERO_T ? 1 : TW];
   // Normaliser of every in-kernel row: kappa = exp(K - mrow) <= ~1.  Any per-row constant gives the same
   // iterates, because the first step of Algorithm 1 rescales every row (with TSENOR_FLAG_COLS_FIRST: every
-  // column, which is the in-kernel row); a single precision value a little above the row's largest K is
+  // column, which is the in-kernel row); the single precision value next above the row's largest K is
   // enough.  Per row rather than per block, so that one huge entry does not push the other rows of its
   // block below the range of a double.
   float mrow[TH];
@@ -593,16 +594,22 @@ __global__ __launch_bounds__((DykstraLaunch<M, FAST, ADAPT, TILES>::kThreads), (
             if constexpr (!kPotentials) c[(A0 + a) * TW + b] = scan_key_of_k(K, mat_row(ri, cj) * M + mat_col(ri, cj));
           } else {
             kap[A0 + a][b] = K;
-            mrow[A0 + a] = b == 0 ? (float)K : fmaxf(mrow[A0 + a], (float)K);
           }
         }
+      if constexpr (!ZERO_T) {
+#pragma unroll
+        for (int a = 0; a < NA; ++a) {
+          double largest = kap[A0 + a][0];
+#pragma unroll
+          for (int b = 1; b < TW; ++b) largest = vmax(largest, kap[A0 + a][b]);
+          mrow[A0 + a] = round_up(largest);
+        }
+      }
     };
     row_chunks<0, NA, TH>(rows);
   }
   if constexpr (!ZERO_T) {
     all_reduce_max_x<T, TH>(mrow);
-#pragma unroll
-    for (int a = 0; a < TH; ++a) mrow[a] = next_up(mrow[a]);
 #pragma unroll
     for (int a = 0; a < TH; ++a)
 #pragma unroll

@@ -63,21 +63,21 @@ __global__ __launch_bounds__(Team::W * kWave, 2) void team_kernel(Batch batch) {
   for (int a = 0; a < TH; ++a) ri[a] = row0 + (a ^ rx);
   const auto addr = tile_addr<TH, 1>(p, at.r0, at.c0, ri, cj);
   double kap[TH];
-  float mrow[TH];  // a little above the largest K of every row (see dykstra_sort_kernel)
+  float mrow[TH];  // not below the largest K of every row (see dykstra_sort_kernel)
   {
     float imp[TH][1];
     tile_importance<0, TH>(p, addr, imp);
 #pragma unroll
     for (int a = 0; a < TH; ++a) {
       kap[a] = tau_eff * (double)imp[a][0];
-      mrow[a] = (float)kap[a];
+      mrow[a] = round_up(kap[a]);
     }
   }
   all_reduce_max_x<T, TH>(mrow);
 #pragma unroll
   for (int a = 0; a < TH; ++a) {
     mrow[a] = fmaxf(mrow[a], lane_xor<16>(mrow[a]));
-    mrow[a] = next_up(fmaxf(mrow[a], lane_xor<32>(mrow[a])));
+    mrow[a] = fmaxf(mrow[a], lane_xor<32>(mrow[a]));
     kap[a] = exp(fmax(kap[a] - (double)mrow[a], kMinLogKernel));
   }
 

@@ -182,6 +182,32 @@ def test_absolute_tau_row_spread_around_700(dev, M, N):
         assert mask[0, 1] == 1 and mask[M + 1, M + 2] == 1 and mask[2 * M + 3, 3 * M + 2] == 1
 
 
+@pytest.mark.parametrize("M,N,top", [(4, 2, 1), (8, 4, 1), (16, 8, 2), (32, 16, 4), (64, 32, 8)])
+def test_absolute_tau_where_a_step_of_floats_is_most_of_the_row_spread(dev, M, N, top):
+    # K = 2^32 at `top` entries of every row and column and 2^32 - 512, two floats further down, at the others: a spread of
+    # 512 in every row, inside the supported ~700 only as long as the row normaliser is the largest K itself.  A constant
+    # taken off every entry changes nothing (the first row scaling removes it), so the plan is the oracle's for 512 and 0:
+    # with (N / top)^T > e^512 the lower entries fill up what the upper ones leave.
+    import torch
+
+    from paper_2505_23949_amd import binding
+
+    low = (np.arange(M)[None, :] - np.arange(M)[:, None]) % M >= top
+    shifted = np.where(low, 0.0, 512.0).astype(np.float32)
+    T = 1000
+    assert T * np.log(N / top) > 1.2 * 512
+    want = np.exp(oracle.mask(shifted, N, M, 1.0, T, tau_mode=oracle.TAU_ABSOLUTE, return_plan=True)["log_S"])
+    assert np.abs(want.sum(axis=1) - N).max() < 1e-9
+    Wf = (shifted.astype(np.float64) + (2.0 ** 32 - 512.0)).astype(np.float32)
+    assert np.array_equal(Wf.astype(np.float64) - (2.0 ** 32 - 512.0), shifted)
+    for flags in (0, binding.TSENOR_FLAG_TILES_LARGE, binding.TSENOR_FLAG_TILES_SMALL):
+        print(f"[case] K near 2^32, {N}:{M} flags={flags}", flush=True)
+        res = binding.solve(torch.from_numpy(Wf).to(dev), N, M, 1.0, T, tau_mode=binding.TSENOR_TAU_ABSOLUTE, flags=flags,
+                            want_plan=True)
+        torch.cuda.synchronize()
+        assert np.abs(res["plan"].cpu().numpy() - want).max() <= PLAN_ATOL
+
+
 @pytest.mark.parametrize("M,N", [(4, 2), (16, 8), (32, 16), (64, 32)])
 def test_parity_cols_first_and_strict(dev, M, N):
     base = synth.Workload(f"flags_{N}of{M}", 2 * M, 3 * M, N, M, 0.004, 40, "f32", "student_t", 500 + M)

@@ -480,11 +480,11 @@ struct DykstraLaunch {
   // to 256 registers.  FAST: the more waves, the nearer the issue of plain fp32 instructions comes to its limit (1.13 ns
   // per instruction and SIMD with two waves, 1.05 with four).  M = 32: four waves of 128 registers, the loop fits and ~30
   // registers of the double-precision code around it spill (4096x14336: iteration kernel 1425 us, 1470 with three waves).
-  // M = 16: three (four the same to 0.4 % slower), M <= 8: under 120 registers whatever is asked for (five spill: 1 %
-  // slower).  M = 64: three, ~90 registers spill outside the loop (8192x28672, T = 500: 10.5 ms, two waves 11.0, four 31);
+  // M = 16: three (four the same to 0.4 % slower).  M = 8: four (129 registers with three; two spill outside the loop).  M = 4:
+  // four fit whatever is asked for (five spill: 1 % slower).  M = 64: three, ~90 registers spill outside the loop (8192x28672, T = 500: 10.5 ms, two waves 11.0, four 31);
   // with the early exit, where a block may run a dozen iterations and the code around the loop is most of the work, two
   // (8192x8192: 0.85 ms, three 1.05).
-  static constexpr int kWavesPerSimd = FAST && !(M == 64 && ADAPT) ? (M == 32 ? 4 : 3) : 2;
+  static constexpr int kWavesPerSimd = FAST && !(M == 64 && ADAPT) ? (M == 32 || M == 8 ? 4 : 3) : 2;
 };
 
 // ZERO_T: the instantiation for T = 0 (no iterations, keys are K itself).  It is a template parameter
@@ -547,6 +547,8 @@ __global__ __launch_bounds__((DykstraLaunch<M, FAST, ADAPT, TILES>::kThreads), (
   constexpr bool kPotentials = M >= 8 || SMALL;
   [[maybe_unused]] double c[kPotentials ? 1 : E];  // sort keys
   __shared__ double pot[2][kPotentials && SMALL ? BPW : 1][M];  // small tiles: potentials of the matrix rows and columns
+  using RoundingSpace = std::conditional_t<SMALL, RoundingLds<M, BPW>, char>;
+  [[maybe_unused]] __shared__ RoundingSpace lds;
   int iters_done = 0;
   double kap[ZERO_T ? 1 : TH][ZERO_T ? 1 : TW];
   // Normaliser of every in-kernel row: kappa = exp(K - mrow) <= ~1.  Any per-row constant gives the same
@@ -813,16 +815,24 @@ __global__ __launch_bounds__((DykstraLaunch<M, FAST, ADAPT, TILES>::kThreads), (
       // every row and column of the block has an owner among its lanes (on fine tiles several, with the same values)
       if constexpr (SMALL) {
 #pragma unroll
-        for (int a = 0; a < OWN_R; ++a)
-          pot[p.transpose ? 1 : 0][lane / LPB][gy * TH + (a ^ rx2)] = lu_own[a] - (double)mrow[a];
+        for (int a = 0; a < OWN_R; ++a) {
+          const int ri = gy * TH + (a ^ rx2);
+          pot[p.transpose ? 1 : 0][lane / LPB][ri] = lu_own[a];
+          lds.minus_largest[lane / LPB][ri] = -(double)mrow[a];
+        }
 #pragma unroll
         for (int b = 0; b < OWN_C; ++b) pot[p.transpose ? 0 : 1][lane / LPB][gx * TW + (b ^ ry2)] = lv_own[b];
       } else {
         if (group == 0 && threadIdx.x == 0) batch.e[which].hdr->tau_eff = tau_eff;
         if (active) {
           BlockPotentials<M>* out = static_cast<BlockPotentials<M>*>(batch.e[which].potentials) + blk;
+          float* largest = normalisers_of<M>(batch.e[which], blk);
 #pragma unroll
-          for (int a = 0; a < OWN_R; ++a) out->u[gy * TH + (a ^ rx2)] = lu_own[a] - (double)mrow[a];
+          for (int a = 0; a < OWN_R; ++a) {
+            const int ri = gy * TH + (a ^ rx2);
+            out->u[ri] = lu_own[a];
+            largest[ri] = mrow[a];
+          }
 #pragma unroll
           for (int b = 0; b < OWN_C; ++b) out->v[gx * TW + (b ^ ry2)] = lv_own[b];
         }
@@ -882,9 +892,11 @@ __global__ __launch_bounds__((DykstraLaunch<M, FAST, ADAPT, TILES>::kThreads), (
   }
   if constexpr (kPotentials) {
     if constexpr (SMALL) {
-      __shared__ RoundingLds<M, BPW> lds;
       wave_sync();
-      round_blocks<M, LPB, false>(p, batch.e[which], blk, active, r0, c0, lane, tau_eff, pot[0], pot[1], lds);
+      if (p.transpose)
+        round_blocks<M, LPB, false, true>(p, batch.e[which], blk, active, r0, c0, lane, tau_eff, pot[0], pot[1], lds);
+      else
+        round_blocks<M, LPB, false, false>(p, batch.e[which], blk, active, r0, c0, lane, tau_eff, pot[0], pot[1], lds);
     }
   } else {
     // a lane has its whole block: the greedy selection follows in registers

@@ -31,7 +31,13 @@ __device__ __forceinline__ int mask_popc(mask_t v) {
 // (rowm[r] bit c == colm[c] bit r == S[r][c]), column counters of the greedy selection, the importance block.
 template <int M, int G>
 struct RoundingLds {
-  block_mask_t<M> rowm[G][M], colm[G][M];
+  union {
+    struct {
+      block_mask_t<M> rowm[G][M], colm[G][M];
+    };
+    // until the sort keys are formed: minus the normaliser of every in-kernel row (BlockPotentials)
+    double minus_largest[G][M];
+  };
   unsigned int colcnt[G][M];
   // (rows padded by one float: lane r reads row r, and with a row length of M every lane would hit the same bank)
   static constexpr int kImpLd = M + 1;
@@ -296,13 +302,20 @@ __global__ __launch_bounds__(kWave) void finalize_kernel(Batch batch) {
 // sort of M*M keys across the lanes of a block, and the M*M dependent steps of the scan are gone.
 // ------------------------------------------------------------------------------------------------------------------
 
-// What the iterations hand to the rounding, per block: log S = min(K + (u + v), 0) with u per in-kernel row and v per
-// in-kernel column (in-kernel rows are matrix columns under TSENOR_FLAG_COLS_FIRST).
+// What the iterations hand to the rounding, per block: log S = min((K - m) + (u + v), 0) with u per in-kernel row and v per
+// in-kernel column (in-kernel rows are matrix columns under TSENOR_FLAG_COLS_FIRST), and m the normaliser of the in-kernel
+// row, a float not below its largest K.  m and u stay apart: the largest K may be anything, and u - m in one number keeps
+// of u what the size of m leaves (with K = 2^28 masks came out other than those of the same block shifted to K <= 640).
 template <int M>
 struct BlockPotentials {
   double u[M], v[M];
 };
 static_assert(sizeof(BlockPotentials<8>) <= 2 * 8 * 8, "fits the two bytes per weight the workspace has for it (M >= 8)");
+// m is left where the block's counters go later, M floats of the slot that for M = 4 holds the greedy selection's mask
+template <int M>
+__device__ __forceinline__ float* normalisers_of(const BatchEntry& e, int64_t blk) {
+  return reinterpret_cast<float*>(static_cast<char*>(e.rowmask) + blk * (int64_t)(M * sizeof(block_mask_t<M>)));
+}
 
 // Scan key of an entry: positive doubles whose order is descending plan, ties by ascending index.  `index` (below 2^12) is the
 // entry's place in what is being sorted: a block, a row or a column.
@@ -390,8 +403,8 @@ __device__ __forceinline__ int nth_set_bit(mask_t h, int N) {
 // Algorithm 2 for the blocks of one wave.  A block owns LPB >= M consecutive lanes; lane r of the first M is its row r and
 // its column r, further ones repeat what lane r % M does.  blk: the lane's block (a valid one also for idle lanes, which
 // write nothing: `active`), at matrix position (r0, c0).  row_pot, col_pot (LDS, T > 0): the potentials of the matrix rows
-// and columns of the wave's blocks.  To be called by whole waves.
-template <int M, int LPB, bool ZERO_T>
+// and columns of the wave's blocks; lds.minus_largest goes with them.  To be called by whole waves.
+template <int M, int LPB, bool ZERO_T, bool COLS_FIRST>
 __device__ __forceinline__ void round_blocks(const DevProblem& p, const BatchEntry& e, int64_t blk, bool active, int64_t r0,
                                              int64_t c0, int lane, double tau_eff, const double (*row_pot)[M],
                                              const double (*col_pot)[M], RoundingLds<M, kWave / LPB>& lds) {
@@ -411,20 +424,26 @@ __device__ __forceinline__ void round_blocks(const DevProblem& p, const BatchEnt
   double c[M];
   auto keys = [&](auto rows_tag) {
     constexpr bool ROWS = decltype(rows_tag)::value;
-    double own = 0.0;
-    if constexpr (!ZERO_T) own = ROWS ? row_pot[g][ql] : col_pot[g][ql];
+    const auto importance = [&](int k) { return (double)lds.imp[g][ROWS ? ql * LD + k : k * LD + ql]; };
+    if constexpr (ZERO_T) {
 #pragma unroll
-    for (int k = 0; k < M; ++k) {
-      const double imp = (double)lds.imp[g][ROWS ? ql * LD + k : k * LD + ql];
-      if constexpr (ZERO_T) {
-        c[k] = scan_key_of_k(tau_eff * imp, k);
-      } else {
-        // (the same operations in both passes: an entry has one key)
-        const double other = ROWS ? col_pot[g][k] : row_pot[g][k];
-        c[k] = scan_key(fma(tau_eff, imp, own + other), k);
+      for (int k = 0; k < M; ++k) {
+        c[k] = scan_key_of_k(tau_eff * importance(k), k);
+        if (k % 8 == 7) __builtin_amdgcn_sched_barrier(0);
       }
-      // a few entries at a time: with all their LDS reads in flight the keys no longer fit the registers
-      if (k % 8 == 7) __builtin_amdgcn_sched_barrier(0);
+    } else {
+      const double own = ROWS ? row_pot[g][ql] : col_pot[g][ql];
+      // m belongs to the in-kernel row: this lane's line, or the line it crosses at k
+      constexpr bool kMine = ROWS != COLS_FIRST;
+      const double mine = lds.minus_largest[g][ql];
+#pragma unroll
+      for (int k = 0; k < M; ++k) {
+        // (K - m) + (u + v), the same operations in both passes: an entry has one key
+        const double other = ROWS ? col_pot[g][k] : row_pot[g][k];
+        c[k] = scan_key(fma(tau_eff, importance(k), kMine ? mine : lds.minus_largest[g][k]) + (own + other), k);
+        // a few entries at a time: with all their LDS reads in flight the keys no longer fit the registers
+        if (k % 8 == 7) __builtin_amdgcn_sched_barrier(0);
+      }
     }
   };
   using yes = std::integral_constant<bool, true>;
@@ -556,10 +575,14 @@ __global__ __launch_bounds__(kWave, M <= 32 ? 4 : 2) void round_kernel(Batch bat
     tau_eff = e.hdr->tau_eff;
     const BlockPotentials<M>* src = static_cast<const BlockPotentials<M>*>(e.potentials) + blk;
     const double of_row = src->u[ql], of_col = src->v[ql];
+    lds.minus_largest[g][ql] = -(double)normalisers_of<M>(e, blk)[ql];
     row_pot[g][ql] = p.transpose ? of_col : of_row;
     col_pot[g][ql] = p.transpose ? of_row : of_col;
   }
-  round_blocks<M, M, ZERO_T>(p, e, blk, active, at.r0, at.c0, lane, tau_eff, row_pot, col_pot, lds);
+  if (!ZERO_T && p.transpose)
+    round_blocks<M, M, ZERO_T, true>(p, e, blk, active, at.r0, at.c0, lane, tau_eff, row_pot, col_pot, lds);
+  else
+    round_blocks<M, M, ZERO_T, false>(p, e, blk, active, at.r0, at.c0, lane, tau_eff, row_pot, col_pot, lds);
 }
 
 }  // namespace tsenor_dev

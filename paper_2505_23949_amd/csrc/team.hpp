@@ -137,7 +137,8 @@ __global__ __launch_bounds__(Team::W * kWave, 2) void team_kernel(Batch batch) {
   double lu[TH];
   lu[0] = log(U);
   const double lv = log(V);
-  pot[p.transpose ? 1 : 0][0][ri[0]] = lu[0] - (double)mrow[0];
+  pot[p.transpose ? 1 : 0][0][ri[0]] = lu[0];
+  lds.minus_largest[0][ri[0]] = -(double)mrow[0];
   pot[p.transpose ? 0 : 1][0][col] = lv;
   if (threadIdx.x == 0 && e.iters_done_out) e.iters_done_out[blk] = iters_done;
   if (e.plan_out) {
@@ -151,8 +152,12 @@ __global__ __launch_bounds__(Team::W * kWave, 2) void team_kernel(Batch batch) {
     }
   }
   __syncthreads();
-  if (wave == 0)
-    round_blocks<M, kWave, false>(p, e, blk, true, at.r0, at.c0, lane, tau_eff, pot[0], pot[1], lds);
+  if (wave == 0) {
+    if (p.transpose)
+      round_blocks<M, kWave, false, true>(p, e, blk, true, at.r0, at.c0, lane, tau_eff, pot[0], pot[1], lds);
+    else
+      round_blocks<M, kWave, false, false>(p, e, blk, true, at.r0, at.c0, lane, tau_eff, pot[0], pot[1], lds);
+  }
 }
 
 }  // namespace tsenor_dev

@@ -208,6 +208,27 @@ def test_absolute_tau_where_a_step_of_floats_is_most_of_the_row_spread(dev, M, N
         assert np.abs(res["plan"].cpu().numpy() - want).max() <= PLAN_ATOL
 
 
+@pytest.mark.parametrize("M,N", [(8, 4), (16, 7), (32, 16), (64, 32)])
+def test_a_constant_on_every_importance_changes_nothing(dev, M, N):
+    # Algorithm 1 removes a constant from K with its first row (column) scaling.  K = 32 k and K = 32 k + 2^28 for whole
+    # numbers k (every number exact): plan and mask are the same bit for bit, so nothing on the way may lose what the size of
+    # K leaves no room for.  The few levels make many entries whose plans tie or nearly tie.
+    import torch
+
+    from paper_2505_23949_amd import binding
+
+    k = np.random.Generator(np.random.Philox(31 + M)).integers(0, 21, (20 * M, 30 * M)).astype(np.float32)
+    for flags in (0, binding.TSENOR_FLAG_COLS_FIRST, binding.TSENOR_FLAG_TILES_LARGE,
+                  binding.TSENOR_FLAG_TILES_LARGE | binding.TSENOR_FLAG_COLS_FIRST, binding.TSENOR_FLAG_TILES_SMALL):
+        print(f"[case] K + 2^28 {N}:{M} flags={flags}", flush=True)
+        small, large = (binding.solve(torch.from_numpy(W).to(dev), N, M, 32.0, 60, tau_mode=binding.TSENOR_TAU_ABSOLUTE,
+                                      flags=flags, want_plan=True)
+                        for W in (k, k + np.float32(2.0 ** 23)))
+        torch.cuda.synchronize()
+        for name in ("plan", "mask"):
+            assert torch.equal(small[name], large[name]), (name, int((small[name] != large[name]).sum()))
+
+
 @pytest.mark.parametrize("M,N", [(4, 2), (16, 8), (32, 16), (64, 32)])
 def test_parity_cols_first_and_strict(dev, M, N):
     base = synth.Workload(f"flags_{N}of{M}", 2 * M, 3 * M, N, M, 0.004, 40, "f32", "student_t", 500 + M)

@@ -66,7 +66,8 @@ __device__ __forceinline__ mask_t bit_transpose(mask_t x, int ql) {
 }
 
 // The best of the swaps (i', j') of Eq. (5) that a lane i' may take part in: `cand` are its columns j', row_i and row_q the
-// importance of row i and of its own.  Higher score wins, equal scores go to the lower column.
+// importance of row i and of its own.  Higher score wins, equal scores go to the lower column.  (A score that is not a
+// number, as of importances that overflowed, counts as the lowest there is: any candidate is better than none.)
 struct SwapBest {
   double score;
   int column;
@@ -83,7 +84,7 @@ __device__ __forceinline__ void scan_candidate(unsigned int& word, int first, co
 }
 template <class mask_t>
 __device__ __forceinline__ SwapBest best_candidate(mask_t cand, const float* row_i, const float* row_q, double base) {
-  SwapBest best = {-std::numeric_limits<double>::infinity(), 0};
+  SwapBest best = {-std::numeric_limits<double>::infinity(), (sizeof(mask_t) == 8 ? __ffsll((long long)cand) : __ffs((int)cand)) - 1};
   unsigned int word = (unsigned int)cand;
   while (word != 0) scan_candidate(word, 0, row_i, row_q, base, best);
   if constexpr (sizeof(mask_t) == 8) {
@@ -172,11 +173,11 @@ __device__ __forceinline__ void local_search_and_write(const DevProblem& p, cons
         best_candidate(cand, &lds.imp[g][i * LD], &lds.imp[g][qm * LD], (double)lds.imp[g][qm * LD + j]);
     // the best of the block: lanes are rows i', so among equal scores the first lane has the lowest flat index
     const double top = block_max<M>(best.score);
-    const unsigned long long winners = __ballot(part && best.score == top) & gmask;
+    const unsigned long long winners = __ballot(cand != 0 && best.score == top) & gmask;
     const int winner = winners ? __ffsll((long long)winners) - 1 : 0;
     const int ip = winner - g * LPB, jp = __shfl(best.column, winner, kWave);
     if (open) ++rounds;
-    const bool apply = open && top > (p.strict ? 0.0 : -std::numeric_limits<double>::infinity());
+    const bool apply = winners != 0 && (!p.strict || top > 0.0);
     if (open && !apply) open = false;  // nothing changes any more for this block
     wave_sync();
     if (apply && ql == 0) {

@@ -82,3 +82,25 @@ def test_workgroup_per_64_wide_block(blocks):
         assert np.abs(res["plan"].cpu().numpy() - np.exp(log_S)).max() <= 1e-9
         assert np.array_equal(res["mask"].cpu().numpy(), mask)
         assert np.array_equal(res["stats"].cpu().numpy(), stats)
+
+
+@pytest.mark.parametrize("M,N", [(4, 3), (8, 3), (16, 7), (32, 5), (64, 29)])
+def test_swaps_fill_every_row_whatever_their_scores(M, N):
+    # Squares of finite weights that overflow: a swap that gives up an infinite importance scores minus infinity or no number
+    # at all.  Without the printed rule a valid swap is applied whatever its score, so no row or column stays short.
+    import torch
+
+    from oracle import exact
+    from paper_2505_23949_amd import binding as b
+
+    rng = np.random.Generator(np.random.Philox(700 + M))
+    some = rng.standard_normal((6 * M, 7 * M), dtype=np.float32)
+    some[rng.random(some.shape) < 0.6] = 3e19
+    for name, W in (("all", np.full_like(some, 3e19)), ("some", some)):
+        for T, flags in ((0, 0), (20, 0), (20, b.TSENOR_FLAG_TILES_LARGE)):
+            print(f"[case] infinite importances: {name}, {N}:{M} T={T} flags={flags}", flush=True)
+            res = b.solve(torch.from_numpy(W).to("cuda:0"), N, M, 0.01, T, tau_mode=b.TSENOR_TAU_REL_MATRIX_MAX, flags=flags,
+                          importance=b.TSENOR_IMPORTANCE_SQUARE, want_stats=True)
+            torch.cuda.synchronize()
+            assert exact.is_transposable_nm(res["mask"].cpu().numpy(), N, M)
+            assert int(res["stats"][3]) == 0

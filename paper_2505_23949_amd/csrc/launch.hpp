@@ -37,10 +37,18 @@ struct Variant {
 //   M = 8 (4): 8280 blocks 83 / 83 / 85, 9216 blocks 87 / 83 / 85, 10 240 blocks 90 / 84 / 85;
 //   M = 4 (16; the large tiles hold 64): 46 000 blocks 78 / 93 / 85, 49 283 blocks 97 / 93 / 85, 65 536 blocks 100 / 92 / 83,
 //     66 000 blocks 113 / 159 / 94, 106 000 blocks 154 / 166 / 104, 114 920 blocks 179 / 165 / 102.
-constexpr bool small_tiles_win(int M, bool fp32, int64_t nblocks) {
+// With the early exit (`adaptive`) a wave runs until the slowest of its blocks stops, and the large tiles put up to four times
+// as many blocks into it, so M <= 8 keeps the small tiles for longer.  T = 300, normal weights, tol 1e-2 and 1e-3 (small /
+// large double / large fp32):
+//   M = 4: 52 000 blocks 67 / 87 / 72 and 116 / 115 / 95, 60 000 blocks 69 / 87 and 116 / 116, 120 000 blocks 117 / 133 and
+//     211 / 195; M = 8: 9500 blocks 74 / 100 / 91 and 109 / 111 / 104, 12 500 blocks 76 / 100 / 90 and 130 / 108 / 99;
+//   M = 4 and 8, heavy-tailed weights, tol 1e-3: 60 000 blocks 43 / 70, 12 500 blocks 37 / 43;
+//   M = 16, heavy-tailed: 8600 blocks 54 / - / 57.
+constexpr bool small_tiles_win(int M, bool fp32, bool adaptive, int64_t nblocks) {
+  if (M == 4 && adaptive) return nblocks <= (fp32 ? 55000 : 114688);
   if (M == 4) return nblocks <= 49152 || (!fp32 && nblocks > 65536 && nblocks <= 114688);
-  if (M == 8) return nblocks < 8700;
-  if (M == 16) return nblocks <= (fp32 ? 8192 : 62000);
+  if (M == 8) return nblocks < (adaptive ? (fp32 ? 12000 : 13000) : 8700);
+  if (M == 16) return nblocks <= (fp32 ? (adaptive ? 9000 : 8192) : 62000);
   return M == 32 && nblocks <= (fp32 ? 2048 : 3072);
 }
 

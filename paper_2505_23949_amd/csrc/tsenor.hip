@@ -215,6 +215,7 @@ inline Variant variant_of(const tsenor_problem& p) {
   v.M = p.M;
   v.zero_t = p.iters == 0;
   v.simple = (p.flags & TSENOR_FLAG_SIMPLE_ROUNDING) != 0;
+  v.adaptive = p.tol > 0.0 && p.iters > 0;
   // the tiling is decided from the matrix's own number of blocks, never from what it is fused with: the two
   // tilings differ in the order of the additions inside a row or column sum
   const int64_t nblocks = (p.rows / p.M) * (p.cols / p.M);
@@ -222,11 +223,10 @@ inline Variant variant_of(const tsenor_problem& p) {
   const bool tiled = !v.zero_t && !v.simple && !(p.flags & TSENOR_FLAG_TILES_LARGE);
   const bool team = tiled && nblocks < team_below_blocks(p.M);
   const bool small = team || (p.M <= 32 && tiled &&
-                              ((p.flags & TSENOR_FLAG_TILES_SMALL) != 0 || small_tiles_win(p.M, fp32, nblocks)));
+                              ((p.flags & TSENOR_FLAG_TILES_SMALL) != 0 || small_tiles_win(p.M, fp32, v.adaptive, nblocks)));
   v.tiles = !small ? kLargeTiles : team ? kTeam : nblocks < finest_tiles_below_blocks(p.M) ? kFinestTiles : kSmallTiles;
   // the small tiles (launches that cannot fill the chip: bound by latency, not by issue) iterate in double only
   v.fast = p.iters > 0 && fp32 && !small;
-  v.adaptive = p.tol > 0.0 && p.iters > 0;
   return v;
 }
 

@@ -678,6 +678,25 @@ def test_early_exit_with_fp32_iterations(dev, M, N, dtype, tol):
         assert same[agree].mean() >= 0.95
 
 
+@pytest.mark.parametrize("M,block_rows,block_cols,small_alone", [(4, 208, 250, False), (8, 100, 125, False), (4, 180, 200, True)])
+def test_early_exit_keeps_the_small_tiles_for_longer(dev, M, block_rows, block_cols, small_alone):
+    # With the early exit the library stays on the small tiles up to more blocks than with a fixed count of iterations.  The
+    # two tilings add in another order, so the plan says which one a call took: the same bits as with the tiling asked for.
+    import torch
+
+    from paper_2505_23949_amd import binding
+
+    W = torch.randn((block_rows * M, block_cols * M), device=dev, generator=torch.Generator(device=dev).manual_seed(12))
+    for tol, small in ((1e-3, True), (0.0, small_alone)):
+        print(f"[case] tiling of {block_rows * block_cols} blocks, M={M} tol={tol}", flush=True)
+        got, on_small, on_large = (binding.solve(W, M // 2, M, 0.01, 40, tau_mode=binding.TSENOR_TAU_REL_MATRIX_MAX, tol=tol,
+                                                 flags=flags, want_plan=True)["plan"]
+                                   for flags in (0, binding.TSENOR_FLAG_TILES_SMALL, binding.TSENOR_FLAG_TILES_LARGE))
+        torch.cuda.synchronize()
+        assert not torch.equal(on_small, on_large), "the case should tell the tilings apart"
+        assert torch.equal(got, on_small if small else on_large)
+
+
 def test_zero_iterations_rounds_the_importance(dev):
     from dataclasses import replace
 

@@ -52,18 +52,25 @@ def useful_ops_per_entry_iter(M: int, fp32: bool) -> float:
 # Vector instructions the compiled default-mode iteration loop issues per wave and iteration, and the matrix
 # entries a wave holds (counted in the ISA of the built library, `v_*` lines between the loop label and its
 # branch; cross-lane ds_swizzle and LDS accesses issue on another pipeline and are not counted).  Keyed by
-# (M, small tiles).
+# (M, layout): the small tiles, the finest ones (a 16 x 16 block per wave) and the team (a 64 x 64 block on eight waves, of
+# which a row counts one) serve small launches.
 LOOP_VALU_PER_WAVE_ITER = {
-    (4, False): (108, 1024), (4, True): (36, 256), (8, False): (104, 1024), (8, True): (40, 256),
-    (16, False): (176, 2048), (16, True): (98, 1024), (32, False): (164, 2048), (32, True): (110, 1024),
-    (64, False): (384, 4096),
+    (4, "large"): (108, 1024), (4, "small"): (36, 256), (8, "large"): (104, 1024), (8, "small"): (40, 256),
+    (16, "large"): (176, 2048), (16, "small"): (98, 1024), (16, "finest"): (52, 256),
+    (32, "large"): (164, 2048), (32, "small"): (110, 1024), (64, "large"): (384, 4096), (64, "team"): (95, 512),
 }
-def small_launch_of(M: int, fp32: bool, nblocks: int) -> bool:
-    """The library's own choice of the small tiles (for M = 64 of a workgroup per block), mirrored here to pick the row
-    of the table above and to say which precision a call iterates in."""
+
+
+def layout_of(M: int, fp32: bool, nblocks: int) -> str:
+    """The library's own choice for a single matrix and a fixed count of iterations, mirrored here to pick the row of the
+    table above and to say which precision a call iterates in (single precision, if asked for, on the large tiles)."""
     if M == 4:
-        return nblocks <= 49152 or (not fp32 and 65536 < nblocks <= 114688)
-    return nblocks < {8: 8700, 16: 8193 if fp32 else 62001, 32: 2049 if fp32 else 3073, 64: 257}[M]
+        small = nblocks <= 49152 or (not fp32 and 65536 < nblocks <= 114688)
+    else:
+        small = nblocks <= {8: 8699, 16: 8192 if fp32 else 62000, 32: 2048 if fp32 else 3072, 64: 64 if fp32 else 256}[M]
+    if not small:
+        return "large"
+    return "team" if M == 64 else "finest" if M == 16 and nblocks < 1800 else "small"
 
 
 def recorded_traffic(workload: str, fp32: bool):
@@ -241,7 +248,7 @@ def bench_matrix(args, name):
     steps = args.steps
     fp32_flag = binding.TSENOR_FLAG_FP32_ITERATIONS
     # a matrix this small runs on the small tiles, which iterate in double whatever the flag says
-    small_launch = small_launch_of(w.M, True, nblocks)
+    small_launch = layout_of(w.M, True, nblocks) != "large"
     headline_fp32 = args.precision == "fp32" and not small_launch
     no_cpu, no_modes = args.no_cpu_baseline, args.no_other_modes
     if args.tol > 0.0:
@@ -319,8 +326,7 @@ def bench_matrix(args, name):
             roofline["pass_traffic_over_algorithmic"] = round(
                 traffic["pass"] / roofline["algorithmic_bytes_per_pass"], 2)
         if not fp32 and w.iters > 0:
-            small = small_launch_of(w.M, False, nblocks)
-            counted = LOOP_VALU_PER_WAVE_ITER.get((w.M, small))
+            counted = LOOP_VALU_PER_WAVE_ITER.get((w.M, layout_of(w.M, False, nblocks)))
             if counted:
                 # second view of the same measurement: the vector instructions the loop issues against the issue
                 # slots of the chip (1024 SIMDs, one double-precision wave instruction per 4 cycles), at the

@@ -89,8 +89,9 @@ enum {
    * double-precision evaluation to ~1e-5 instead of ~1e-13, and the greedy order - hence the mask - can
    * differ from it in a block where two plan entries are closer than that (none in 8192 blocks of the
    * 16:32 test workload).  Sort keys, swap scores and all results stay in double.  Off by default.  A matrix that
-   * runs on the small tiles or on a workgroup per block (below) iterates in double whatever this flag says: such a launch is bound by latency,
-   * not by instruction issue, and single precision would buy nothing. */
+   * runs on the small tiles (below), and one of at most 64 blocks of 64 x 64 unless TSENOR_FLAG_TILES_LARGE is set, iterates
+   * in double whatever this flag says: such a launch is bound by latency, not by instruction issue, and single precision
+   * would buy nothing. */
   TSENOR_FLAG_FP32_ITERATIONS = 1u << 2,
   /* Accepted for callers that set them, and without effect: there is one way the greedy selection (Algorithm 2 lines 1-6) is
    * found for each block size.  Setting both is an error. */
@@ -101,9 +102,10 @@ enum {
    * fewest instructions per entry: best for full matrices.  SMALL tiles (M <= 32, iters > 0, not with
    * TSENOR_FLAG_SIMPLE_ROUNDING; ignored otherwise): 16 entries per lane (4 for M <= 8, and for M = 16 in small matrices),
    * more lanes per block, a shorter dependent chain per iteration: best while the launch cannot fill the
-   * chip anyway; on them the whole path, Algorithm 2 included, runs in one kernel.  A few 64 x 64 blocks (fewer
-   * than 257) get a workgroup each, in one kernel as well, unless LARGE is asked for.  Default: chosen by the number of blocks of the matrix (and earlier for the large tiles when
-   * TSENOR_FLAG_FP32_ITERATIONS is set, which only they honour).  Setting both is an error. */
+   * chip anyway; on them the whole path, Algorithm 2 included, runs in one kernel.  A few 64 x 64 blocks
+   * (fewer than 257 in a launch) get a workgroup each, in one kernel as well, unless LARGE is asked for.  Default: chosen by
+   * the number of blocks of the matrix (and earlier for the large tiles when TSENOR_FLAG_FP32_ITERATIONS is set, which only
+   * they honour; later with tol > 0).  Setting both is an error. */
   TSENOR_FLAG_TILES_LARGE = 1u << 5,
   TSENOR_FLAG_TILES_SMALL = 1u << 6,
   /* Ablation arm "Simple" of App. B.2.1 in place of Algorithm 2: per block, keep the N largest plan entries
@@ -183,7 +185,8 @@ int tsenor_mask_ex(const tsenor_problem* p, void* workspace, size_t workspace_by
  * matrices: problems may differ in every field, and those that share M and the kernel variant (default, fp32
  * iterations, iters == 0, tiling, ...) go through the kernels together, up to 16 matrices per launch: one
  * launch of every kernel serves the whole group.  The kernel variant of a problem is chosen from that problem
- * alone, so the results are those of `count` separate tsenor_mask_ex calls, bit for bit. */
+ * alone, and where a fused launch of many small matrices lays their blocks out otherwise than a call of their own would, it
+ * adds in the same order: the results are those of `count` separate tsenor_mask_ex calls, bit for bit. */
 int tsenor_mask_batched(const tsenor_problem* problems, int count, void* workspace, size_t workspace_bytes,
                         tsenor_stream_t stream);
 

@@ -62,6 +62,7 @@ constexpr int ilog2(int x) { return x <= 1 ? 0 : 1 + ilog2(x / 2); }
 // lane-row has lanes, the last exchange steps of a reduction have no registers left to split: they add the
 // partner's value into the same register instead (both lanes end up owning the same sum).
 // kFinestTiles: a 16 x 16 block on a whole wave, for launches that leave SIMDs without a wave even so.
+// kFinestOrderTiles: the small tiles of 16 x 16 blocks with their additions in the order of the finest ones.
 template <int M, int TILES = kLargeTiles>
 struct Tiling;
 template <>
@@ -119,11 +120,52 @@ struct Tiling<16, kFinestTiles> {
   static constexpr bool STORE_E = true;
 };
 template <>
+struct Tiling<16, kFinestOrderTiles> {
+  static constexpr int NX = 2, NY = 2;  // 16 lanes per block, 4 x 4 tiles
+  static constexpr int XM[2] = {3, 1}, YM[2] = {4, 8};
+  static constexpr bool STORE_E = true;
+};
+template <>
 struct Tiling<32, kSmallTiles> {
   static constexpr int NX = 3, NY = 3;  // 64 lanes per block, 4 x 4 tiles
   static constexpr int XM[3] = {7, 3, 1}, YM[3] = {8, 16, 32};
   static constexpr bool STORE_E = true;
 };
+
+// Two layouts of a block that add in the same order, so that a launch may take either.  A sum of two numbers does not depend on
+// which of two lanes forms it, so the exchange steps of a reduction are a tree over the rows or columns whatever the layout;
+// what has an order is the run of fused multiply-adds down a column inside a lane.  The finer layout (16 x 16: 2 x 2 tiles on
+// a wave; 64 x 64: eight rows of one column per lane, team.hpp) starts that run of column c at row r(c) and goes on with rows
+// r(c) ^ 1, r(c) ^ 2, ..., since its rows are offset by r.  The coarser layout has columns of different r in a lane.  With one
+// offset o for rows and columns both - register a holds row a ^ o, register b column b ^ o, o over all values along a lane-row
+// and along a lane-column - the k-th row of the run, k ^ r(c) = k ^ b ^ o, is in register k ^ b: the same in every lane.
+// order_run: length of those runs (0: a tiling without such a partner, one run over all rows of the tile).
+template <int M, int TILES>
+constexpr int order_run() {
+  return M == 64 && TILES == kLargeTiles ? 8 : M == 16 && TILES == kFinestOrderTiles ? 2 : 0;
+}
+// Sum of the capped entries of a tile row in the finer layout's order: over the lanes that differ by 7, 3, 1 (64 x 64), or the
+// two columns of a lane and then the next lane (16 x 16).
+template <int RUN, class real, int TW, int H = TW / 2>
+__device__ __forceinline__ real row_tree(real (&s)[TW]) {
+  if constexpr (H >= 1) {
+#pragma unroll
+    for (int b = 0; b < H; ++b) s[b] += s[b ^ (RUN == TW ? 2 * H - 1 : H)];
+    return row_tree<RUN, real, TW, H / 2>(s);
+  } else {
+    return s[0];
+  }
+}
+// in-kernel column of a block that tile column `b` (its register with the lane's offset taken off) of lane-column gx is
+template <int M, int TILES>
+__device__ __forceinline__ int column_in_block(int gx, int b) {
+  if constexpr (M == 16 && TILES == kFinestOrderTiles) {
+    // the column pairs of two finest lanes 7 apart (a step of their row reduction), the pair in bit 0
+    return 2 * (b & 1 ? gx ^ 7 : gx) + (b >> 1);
+  } else {
+    return gx * (M >> Tiling<M, TILES>::NX) + b;
+  }
+}
 
 // registers a lane owns after a reduce-scatter of `count` values over 2^steps lanes (at least one)
 constexpr int owned(int count, int steps) { return (count >> steps) > 0 ? (count >> steps) : 1; }
@@ -270,7 +312,8 @@ __device__ __forceinline__ void chain_phase(bool on) {
 // values alive and spills them).
 // ADAPT (early exit): `frozen` lanes apply factors of exactly 1 (their block has stopped; its state no longer
 // changes), and the largest |factor - 1| among the rows and columns this lane owns is returned.
-template <class T, bool STORE, bool LDS_GATHER = false, bool ADAPT = false, class real, int TH, int TW, int OR>
+// RUN: order_run() of the tiling.
+template <class T, bool STORE, bool LDS_GATHER = false, bool ADAPT = false, int RUN = 0, class real, int TH, int TW, int OR>
 __device__ __forceinline__ real dykstra_iteration(real (&kap)[TH][TW], real (&Uown)[OR], real (&V)[TW], real Nd,
                                                   real floor_, real* xr = nullptr, int rx = 0, bool frozen = false) {
   real worst = 0;
@@ -281,13 +324,17 @@ __device__ __forceinline__ real dykstra_iteration(real (&kap)[TH][TW], real (&Uo
   // projection onto C1 (line 3) of the plan capped by the previous iteration
 #pragma unroll
   for (int a = 0; a < TH; ++a) {
-    real s = 0;
+    real s = 0, leaf[RUN ? TW : 1];
 #pragma unroll
     for (int b = 0; b < TW; ++b) {
       const real ev = clamp01(kap[a][b] * V[b]);
       if constexpr (STORE) e[a][b] = ev;
-      s = b == 0 ? ev : s + ev;  // (0 + x is not a no-op for the compiler: it would keep the add)
+      if constexpr (RUN > 0)
+        leaf[b] = ev;
+      else
+        s = b == 0 ? ev : s + ev;  // (0 + x is not a no-op for the compiler: it would keep the add)
     }
+    if constexpr (RUN > 0) s = row_tree<RUN>(leaf);
     R[a] = s;
   }
   chain_phase(true);
@@ -324,15 +371,28 @@ __device__ __forceinline__ real dykstra_iteration(real (&kap)[TH][TW], real (&Uo
   }
 #pragma unroll
   for (int b = 0; b < TW; ++b) {
-    real s = 0;
-#pragma unroll
-    for (int a = 0; a < TH; ++a) {
-      real ev;
+    const auto entry = [&](int a) {
       if constexpr (STORE)
-        ev = e[a][b];
+        return e[a][b];
       else
-        ev = clamp01(kap[a][b] * Vc[b]);
-      s = vfma(ev, R[a], s);
+        return clamp01(kap[a][b] * Vc[b]);
+    };
+    real s = 0;
+    if constexpr (RUN == 0) {
+#pragma unroll
+      for (int a = 0; a < TH; ++a) s = vfma(entry(a), R[a], s);
+    } else {
+      static_assert(TH <= 2 * RUN, "at most two runs");
+#pragma unroll
+      for (int a0 = 0; a0 < TH; a0 += RUN) {
+        real run = 0;
+#pragma unroll
+        for (int k = 0; k < RUN; ++k) {
+          const int a = a0 + (k ^ (b % RUN));
+          run = vfma(entry(a), R[a], run);
+        }
+        s = a0 == 0 ? run : s + run;
+      }
     }
     C[b] = s;
   }
@@ -519,7 +579,9 @@ __global__ __launch_bounds__((DykstraLaunch<M, FAST, ADAPT, TILES>::kThreads), (
   // register (a, b) of this lane <-> in-kernel coordinates (ri, cj) of the block.  Each phase of the
   // kernel takes its own opaque copy of the lane offsets, so that element addresses are recomputed where
   // they are needed instead of being kept in registers across the iteration loop.
-  const int rx = shift_lane(gx, SHX), ry = reg_xor_y<T, TW>(q);
+  constexpr int RUN = FAST ? 0 : order_run<M, TILES>();
+  const int rx_own = shift_lane(gx, SHX), ry_own = reg_xor_y<T, TW>(q);
+  const int rx = RUN ? rx_own ^ ry_own : rx_own, ry = RUN ? rx : ry_own;
   auto fresh = [](int v) {
     asm volatile("" : "+v"(v));
     return v;
@@ -535,7 +597,7 @@ __global__ __launch_bounds__((DykstraLaunch<M, FAST, ADAPT, TILES>::kThreads), (
 #pragma unroll
     for (int a = 0; a < TH; ++a) ri[a] = gy * TH + (a ^ rxp);
 #pragma unroll
-    for (int b = 0; b < TW; ++b) cj[b] = gx * TW + (b ^ ryp);
+    for (int b = 0; b < TW; ++b) cj[b] = column_in_block<M, TILES>(gx, b ^ ryp);
     return tile_addr<TH, TW>(p, r0, c0, ri, cj);
   };
   // rows of a tile loaded at a time: the fp32 variant lives in half the registers (two halves); the 8 x 8
@@ -572,7 +634,7 @@ __global__ __launch_bounds__((DykstraLaunch<M, FAST, ADAPT, TILES>::kThreads), (
           for (int a = 0; a < NA; ++a)
 #pragma unroll
             for (int b = 0; b < TW; ++b) {
-              const int ri = gy * TH + ((A0 + a) ^ rx0), cj = gx * TW + (b ^ ry0);
+              const int ri = gy * TH + ((A0 + a) ^ rx0), cj = column_in_block<M, TILES>(gx, b ^ ry0);
               plan_out[(r0 + mat_row(ri, cj)) * p.cols + c0 + mat_col(ri, cj)] = exp(tau_eff * (double)imp[a][b]);
               __builtin_amdgcn_sched_barrier(0);
             }
@@ -592,7 +654,7 @@ __global__ __launch_bounds__((DykstraLaunch<M, FAST, ADAPT, TILES>::kThreads), (
           const double K = tau_eff * (double)imp[a][b];  // K of Algorithm 1 line 1
           if constexpr (ZERO_T) {
             // no iterations: the greedy order is descending K itself
-            const int ri = gy * TH + ((A0 + a) ^ rx0), cj = gx * TW + (b ^ ry0);
+            const int ri = gy * TH + ((A0 + a) ^ rx0), cj = column_in_block<M, TILES>(gx, b ^ ry0);
             if constexpr (!kPotentials) c[(A0 + a) * TW + b] = scan_key_of_k(K, mat_row(ri, cj) * M + mat_col(ri, cj));
           } else {
             kap[A0 + a][b] = K;
@@ -668,14 +730,14 @@ __global__ __launch_bounds__((DykstraLaunch<M, FAST, ADAPT, TILES>::kThreads), (
           // all its blocks are
           for (int t = 0; t < p.T; ++t) {
             double worst =
-                dykstra_iteration<T, T::STORE_E, kLdsGather, true>(kap, Uown, V, Nd, 1e-300, xr, rx, frozen);
+                dykstra_iteration<T, T::STORE_E, kLdsGather, true, RUN>(kap, Uown, V, Nd, 1e-300, xr, rx, frozen);
             if ((t + 1) % TSENOR_ADAPTIVE_CHECK_EVERY == 0) {
               freeze_if(block_max<LPB>(worst) <= p.tol, t + 1);
               if (__all(frozen)) break;
             }
           }
         } else {
-          for (int t = 0; t < p.T; ++t) dykstra_iteration<T, T::STORE_E, kLdsGather>(kap, Uown, V, Nd, 1e-300, xr, rx);
+          for (int t = 0; t < p.T; ++t) dykstra_iteration<T, T::STORE_E, kLdsGather, false, RUN>(kap, Uown, V, Nd, 1e-300, xr, rx);
         }
       }
       if constexpr (FAST) {
@@ -821,7 +883,7 @@ __global__ __launch_bounds__((DykstraLaunch<M, FAST, ADAPT, TILES>::kThreads), (
           lds.minus_largest[lane / LPB][ri] = -(double)mrow[a];
         }
 #pragma unroll
-        for (int b = 0; b < OWN_C; ++b) pot[p.transpose ? 0 : 1][lane / LPB][gx * TW + (b ^ ry2)] = lv_own[b];
+        for (int b = 0; b < OWN_C; ++b) pot[p.transpose ? 0 : 1][lane / LPB][column_in_block<M, TILES>(gx, b ^ ry2)] = lv_own[b];
       } else {
         if (group == 0 && threadIdx.x == 0) batch.e[which].hdr->tau_eff = tau_eff;
         if (active) {
@@ -834,7 +896,7 @@ __global__ __launch_bounds__((DykstraLaunch<M, FAST, ADAPT, TILES>::kThreads), (
             largest[ri] = mrow[a];
           }
 #pragma unroll
-          for (int b = 0; b < OWN_C; ++b) out->v[gx * TW + (b ^ ry2)] = lv_own[b];
+          for (int b = 0; b < OWN_C; ++b) out->v[column_in_block<M, TILES>(gx, b ^ ry2)] = lv_own[b];
         }
       }
       if (active && q == 0 && batch.e[which].iters_done_out) batch.e[which].iters_done_out[blk] = iters_done;
@@ -866,7 +928,7 @@ __global__ __launch_bounds__((DykstraLaunch<M, FAST, ADAPT, TILES>::kThreads), (
           for (int a = 0; a < NA; ++a)
 #pragma unroll
             for (int b = 0; b < TW; ++b) {
-              const int ri = gy * TH + ((A0 + a) ^ rx2), cj = gx * TW + (b ^ ry2);
+              const int ri = gy * TH + ((A0 + a) ^ rx2), cj = column_in_block<M, TILES>(gx, b ^ ry2);
               plan_out[(r0 + mat_row(ri, cj)) * p.cols + c0 + mat_col(ri, cj)] = exp(fmin(log_plan(imp[a][b], A0 + a, b), 0.0));
               __builtin_amdgcn_sched_barrier(0);
             }
@@ -882,7 +944,7 @@ __global__ __launch_bounds__((DykstraLaunch<M, FAST, ADAPT, TILES>::kThreads), (
           for (int a = 0; a < NA; ++a)
 #pragma unroll
             for (int b = 0; b < TW; ++b) {
-              const int ri = gy * TH + ((A0 + a) ^ rx2), cj = gx * TW + (b ^ ry2);
+              const int ri = gy * TH + ((A0 + a) ^ rx2), cj = column_in_block<M, TILES>(gx, b ^ ry2);
               c[(A0 + a) * TW + b] = scan_key(log_plan(imp[a][b], A0 + a, b), mat_row(ri, cj) * M + mat_col(ri, cj));
             }
         };

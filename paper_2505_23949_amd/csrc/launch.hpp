@@ -5,18 +5,22 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <algorithm>
+
 #include "problem.hpp"
 
 namespace tsenor_dev {
 
-// how the Dykstra kernel spreads a block over lanes (see Tiling in dykstra_sort.hpp)
-enum { kLargeTiles, kSmallTiles, kFinestTiles, kTeam };
+// how the Dykstra kernel spreads a block over lanes (see Tiling in dykstra_sort.hpp and team.hpp)
+enum { kLargeTiles, kSmallTiles, kFinestTiles, kFinestOrderTiles, kTeam };
 
 // kernel variant of a problem: problems with the same variant can share one fused launch
 struct Variant {
   int M;
   bool fast, zero_t;
-  int tiles;        // the Dykstra kernel's tiling (decided per problem, so that fusing never changes results)
+  // The Dykstra kernel's tiling, decided per problem, so that fusing never changes results.  kFinestTiles and kTeam, which only
+  // pay in a small launch, each have a second layout that adds in the same order: which of the two runs is decided per launch.
+  int tiles;
   bool simple;      // TSENOR_FLAG_SIMPLE_ROUNDING
   bool adaptive;    // tol > 0: the early-exit instantiation of the Dykstra kernel
   bool operator==(const Variant& o) const {
@@ -52,15 +56,24 @@ constexpr bool small_tiles_win(int M, bool fp32, bool adaptive, int64_t nblocks)
   return M == 32 && nblocks <= (fp32 ? 2048 : 3072);
 }
 
-// Below this many blocks a 16 x 16 block has a wave of its own: 51 instead of 98 vector instructions in the chain of an
-// iteration, four times the waves.  Whole calls, T = 300 (us, finest / small tiles): 256 blocks 67 / 88, 1024 blocks
-// 73 / 89, 1536 blocks 81 / 90, 2304 blocks 104 / 90 (from three waves on a SIMD on, issue decides).
+// Below this many blocks in a matrix a 16 x 16 block adds in the order of the finest tiles, and below this many in a launch
+// it has a wave of its own: 52 instead of 98 vector instructions in the chain of an iteration, four times the waves.  Whole
+// calls, T = 300 (us, finest / small tiles): 256 blocks 67 / 88, 1024 blocks 73 / 89, 1536 blocks 81 / 90, 2304 blocks
+// 104 / 90 (from three waves on a SIMD on, issue decides).  Fused matrices of 1024 blocks (us, finest tiles / small tiles in
+// their order): 4 131 / 96, 16 436 / 247.  (For single matrices that order costs the small tiles 4-9 %: the shorter run means
+// an addition more per column, and its exchange steps come in the slower order.)
 constexpr int64_t finest_tiles_below_blocks(int M) { return M == 16 ? 1800 : 0; }
 
-// Below this many blocks a 64 x 64 block has a workgroup of its own (team.hpp), which iterates in double: one workgroup per
-// CU.  Whole calls, T = 300 (us, team / large tiles in double / with fp32 iterations): 64 blocks 185 / 292 / 369, 256 blocks
-// 189 / 299 / 377, 300 blocks 354 / 300.
+// Below this many blocks in a launch a 64 x 64 block has a workgroup of its own (team.hpp), which iterates in double: one
+// workgroup per CU.  Whole calls, T = 300 (us, team / large tiles in double / with fp32 iterations): 64 blocks 173 / 286 /
+// 254, 256 blocks 180 / 296 / 270, 300 blocks 354 / 300.  Fused: 4 matrices of 256 blocks 677 / 307, 16 2684 / 1009.
 constexpr int64_t team_below_blocks(int M) { return M == 64 ? 257 : 0; }
+// Whether a matrix iterates in the team's order, in double: with the fp32 flag only up to the number of blocks at which even
+// kMaxBatch such matrices fused are one wave per SIMD, where the large tiles hardly take longer in double than in single
+// precision (16 matrices of 64 blocks 304 / 268 us a call; of 128 blocks 510 / 332).
+constexpr bool team_order_wins(int M, bool fp32, int64_t nblocks) {
+  return nblocks < (fp32 ? std::min<int64_t>(team_below_blocks(M), 1024 / kMaxBatch + 1) : team_below_blocks(M));
+}
 
 // Enqueues the kernels of one fused launch that depend on M: tile load + Algorithm 1 (for M = 4 with the greedy selection, on
 // small launches the whole path), then Algorithm 2 + mask write.  `b.count` non-degenerate problems of variant v.

@@ -22,7 +22,10 @@ inline bool assign_groups(Batch& b, int64_t per_group) {
 template <int M>
 bool launch_block_kernels(Batch& b, const Variant& v, hipStream_t stream, hipEvent_t ev_sorted, hipEvent_t ev_greedy) {
   constexpr int BPW = kWave >> (Tiling<M>::NX + Tiling<M>::NY);
-  if (v.tiles != kLargeTiles) {
+  int64_t nblocks = 0;  // of the whole launch
+  for (int k = 0; k < b.count; ++k) nblocks += b.e[k].p.nblocks;
+  const bool team_fits = nblocks < team_below_blocks(M);
+  if (v.tiles != kLargeTiles && !(v.tiles == kTeam && !team_fits)) {
     // the small tiles carry Algorithm 2 behind the iterations: this one kernel is the whole path
     const auto launch = [&](auto tiles) {
       constexpr int TILES = decltype(tiles)::value;
@@ -41,7 +44,9 @@ bool launch_block_kernels(Batch& b, const Variant& v, hipStream_t stream, hipEve
       if (v.tiles == kSmallTiles) ok = launch(std::integral_constant<int, kSmallTiles>{});
     }
     if constexpr (finest_tiles_below_blocks(M) > 0) {
-      if (v.tiles == kFinestTiles) ok = launch(std::integral_constant<int, kFinestTiles>{});
+      if (v.tiles == kFinestTiles)
+        ok = nblocks < finest_tiles_below_blocks(M) ? launch(std::integral_constant<int, kFinestTiles>{})
+                                                    : launch(std::integral_constant<int, kFinestOrderTiles>{});
     }
     if constexpr (M == Team::M) {
       if (v.tiles == kTeam) {

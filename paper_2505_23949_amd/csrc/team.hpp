@@ -10,9 +10,10 @@
 //     column - no gather, the lane that needs a column scaling is the one that forms it.  Two buffers, so that one barrier
 //     per iteration is enough: a buffer is written again two barriers after it was read.
 // The rows are rescaled between the LDS write and the barrier.  Rounding follows in the first wave (round_blocks).
-// 64 blocks of 32:64, T = 300: 292 us a call on the large tiles (369 with fp32 iterations), 185 here; of the 0.5 us per
-// iteration the issue of two waves' 89 instructions is 0.36, the LDS round trip with the barrier the rest.  (32 x 32 blocks on
-// four waves the same way: 285 ns per iteration, as on one wave with its 110 instructions - not kept.)
+// 64 blocks of 32:64, T = 300: 286 us a call on the large tiles (254 with fp32 iterations), 173 here; of the 0.5 us per
+// iteration the issue of two waves' 95 instructions is 0.36, the LDS round trip with the barrier the rest.  (32 x 32 blocks on
+// four waves the same way: 285 ns per iteration, as on one wave with its 110 instructions - not kept.)  A launch that fills the
+// chip takes the large tiles, which add in the same order with fewer instructions per block (384 against 760).
 #pragma once
 #include "dykstra_sort.hpp"
 
@@ -50,8 +51,11 @@ __global__ __launch_bounds__(Team::W * kWave, 2) void team_kernel(Batch batch) {
   const BatchEntry& e = batch.e[which];
   const DevProblem p = e.p;
   const int64_t blk = blockIdx.x - batch.first[which];
-  const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave, col = lane;
+  const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
   const int row0 = wave * TH, rx = shift_lane(lane & 15, SHX);
+  // The column of a lane, so that the row sums are added in the order of the large tiles (order_run in dykstra_sort.hpp): the
+  // steps over lanes 15, 7 and 3 apart change rx and keep the parity of bits 0 and 1, the later ones change one of the rest.
+  const int gx = (((lane ^ (lane >> 1)) & 1) * 7) ^ (((lane >> 4) & 1) * 3) ^ ((lane >> 5) & 1), col = gx * TH + rx;
   const BlockAt at = block_at(p, blk, M);
   const double tau_eff = tau_eff_of(e);
   if (e.tau_eff_out && blk == 0 && threadIdx.x == 0) *e.tau_eff_out = tau_eff;
@@ -100,17 +104,17 @@ __global__ __launch_bounds__(Team::W * kWave, 2) void team_kernel(Batch batch) {
     double C = ev[0] * R[0];
 #pragma unroll
     for (int a = 1; a < TH; ++a) C = fma(ev[a], R[a], C);
-    part[t & 1][wave][col] = C;
+    part[t & 1][wave][lane] = C;
 #pragma unroll
     for (int a = 0; a < TH; ++a) kap[a] *= R[a];
     __syncthreads();
     double s[T::W];
 #pragma unroll
-    for (int k = 0; k < T::W; ++k) s[k] = part[t & 1][k][col];
+    for (int k = 0; k < T::W; ++k) s[k] = part[t & 1][k][lane];
 #pragma unroll
-    for (int h = T::W / 2; h >= 1; h /= 2)
+    for (int h = 1; h < T::W; h *= 2)  // (neighbours first, as the large tiles' lane-columns do)
 #pragma unroll
-      for (int k = 0; k < h; ++k) s[k] += s[k + h];
+      for (int k = 0; k < T::W; k += 2 * h) s[k] += s[k + h];
     C = Nd * fast_rcp(vmax(s[0], floor_));
     V *= C;
     // lines 5-6 (cap and dual update) are the clamp at the top of the next pass

@@ -104,3 +104,52 @@ def test_swaps_fill_every_row_whatever_their_scores(M, N):
             torch.cuda.synchronize()
             assert exact.is_transposable_nm(res["mask"].cpu().numpy(), N, M)
             assert int(res["stats"][3]) == 0
+
+
+OPTIONS = {"plain": {}, "columns first": {"cols_first": True}, "bf16, column scale": {"bf16": True, "scale": True},
+           "early exit": {"tol": 1e-2}, "early exit, columns first, bf16": {"tol": 1e-2, "cols_first": True, "bf16": True},
+           "additive term, square, previous mask": {"add": True, "prev": True}, "printed swap rule": {"strict": True}}
+
+
+@pytest.mark.parametrize("options", list(OPTIONS))
+@pytest.mark.parametrize("M,block_rows,block_cols,count", [(16, 30, 59, 2), (16, 9, 11, 16), (16, 1, 1, 2), (64, 11, 23, 2), (64, 2, 5, 16),
+                                                           (64, 1, 1, 2)])
+def test_a_batch_is_its_calls_on_every_layout(M, block_rows, block_cols, count, options):
+    # 16 x 16 and 64 x 64 blocks of small matrices have a wave or a workgroup each as long as the launch is small; a fused
+    # launch of several such matrices (here on both sides of its lines, 1800 and 257 blocks) takes the coarser layout, which
+    # adds in the same order: every output is that of the calls of their own, bit for bit.  (1, 1): idle lanes.
+    import torch
+
+    from paper_2505_23949_amd import binding as b
+
+    dev, o = torch.device("cuda:0"), OPTIONS[options]
+    N, (rows, cols) = M // 2 - 1, (block_rows * M, block_cols * M)
+    flags = (b.TSENOR_FLAG_COLS_FIRST if o.get("cols_first") else 0) | (b.TSENOR_FLAG_STRICT_PAPER if o.get("strict") else 0)
+    gen = torch.Generator(device=dev).manual_seed(M + count)
+    dtype = torch.bfloat16 if o.get("bf16") else torch.float32
+    keep, probs, outs, singles = [], [], [], []
+    print(f"[case] layouts of {count} x {block_rows * block_cols} blocks of {N}:{M}, {options}", flush=True)
+    for _ in range(count):
+        W, V = ((0.3 * torch.randn((rows, cols), device=dev, generator=gen)).to(dtype) for _ in range(2))
+        kw = dict(tau_mode=b.TSENOR_TAU_REL_MATRIX_MAX, flags=flags, tol=o.get("tol", 0.0))
+        if o.get("scale"):
+            kw["col_scale"] = torch.empty(cols, device=dev).log_normal_(0.0, 1.0, generator=gen)
+        if o.get("add"):
+            kw.update(add=V, add_scale=0.5, importance=b.TSENOR_IMPORTANCE_SQUARE)
+        if o.get("prev"):
+            kw["prev_mask"] = ((torch.arange(rows, device=dev)[:, None] + torch.arange(cols, device=dev)) % M < N).to(torch.uint8)
+        singles.append(b.solve(W, N, M, 0.01, 40, want_plan=True, want_stats=True, want_objective=True, want_iters_done=True, **kw))
+        outs.append({k: torch.zeros_like(singles[-1][k]) for k in ("mask", "plan", "stats", "objective", "iters_done")})
+        probs.append(b.make_problem(W, N, M, 0.01, 40, mask=outs[-1]["mask"], **{k + "_out": v for k, v in outs[-1].items() if k != "mask"},
+                                    **kw))
+        keep += [W, kw]
+    work = torch.empty(b.tsenor_workspace_bytes(probs), dtype=torch.uint8, device=dev)
+    b.tsenor_mask_batched(probs, work)
+    if M == 64:
+        keep[1]["flags"] |= b.TSENOR_FLAG_TILES_LARGE  # the coarser layout of the first matrix alone
+        outs.append(b.solve(keep[0], N, M, 0.01, 40, want_plan=True, want_stats=True, want_objective=True, want_iters_done=True, **keep[1]))
+        singles.append(singles[0])
+    torch.cuda.synchronize()
+    for out, single in zip(outs, singles):
+        for k in ("mask", "plan", "stats", "objective", "iters_done"):
+            assert torch.equal(out[k], single[k]), k

@@ -241,52 +241,54 @@ def test_parity_cols_first_and_strict(dev, M, N):
     _check(base, g, got, ref, feasible=False)
 
 
-@pytest.mark.parametrize("M,N", [(4, 2), (8, 3), (16, 8), (32, 16), (32, 5), (64, 32)])
-def test_both_greedy_kernels_give_the_sequential_selection(dev, M, N):
-    # greedy selection only (strict mode, L = 0), so the mask IS the greedy kernel's output; inputs with many
-    # exact ties (values rounded to a few levels) make chunks in which one row or column occurs many times
+@pytest.mark.parametrize("M,N", [(4, 1), (4, 2), (4, 3), (8, 3), (16, 8), (32, 16), (32, 5), (64, 32)])
+def test_selection_on_both_tilings_is_the_sequential_one(dev, M, N):
+    # strict mode with L = 0: the mask IS the greedy selection's output (M = 4 on the large tiles: in the registers of a lane;
+    # otherwise by deferred acceptance); inputs with many exact ties (values rounded to a few levels) where T = 0 leaves the
+    # order to the index.  Numbers of blocks around the 64 of a wave of the large 4 x 4 tiles, and one block alone.  The flags
+    # that once chose the selection's kernel are accepted and change nothing.
     import torch
 
     from paper_2505_23949_amd import binding
 
     rng = np.random.Generator(np.random.Philox(5000 + M + N))
-    rows, cols = 5 * M, 7 * M
-    for levels, iters in ((0, 40), (3, 0), (1, 0)):
-        Wf = rng.standard_normal((rows, cols)).astype(np.float32)
-        if levels:
-            Wf = np.round(Wf * levels) / np.float32(levels)
-        W = torch.from_numpy(Wf).to(dev)
-        ref = oracle.mask(Wf, N, M, 0.01, iters, tau_mode=oracle.TAU_REL_MATRIX_MAX, L=0, strict_paper=True)
-        full = oracle.mask(Wf, N, M, 0.01, iters, tau_mode=oracle.TAU_REL_MATRIX_MAX)
-        for name, flag in (("one lane", binding.TSENOR_FLAG_GREEDY_ONE_LANE),
-                           ("M lanes", binding.TSENOR_FLAG_GREEDY_M_LANES)):
-            print(f"[case] greedy kernel '{name}' {N}:{M} levels={levels} T={iters}", flush=True)
-            res = binding.solve(W, N, M, 0.01, iters, tau_mode=binding.TSENOR_TAU_REL_MATRIX_MAX,
-                                local_search_steps=0, flags=flag | binding.TSENOR_FLAG_STRICT_PAPER, want_stats=True)
-            torch.cuda.synchronize()
-            assert np.array_equal(res["mask"].cpu().numpy(), ref["mask"]), (name, levels)
-            assert np.array_equal(res["stats"].cpu().numpy(), ref["stats"]), (name, levels)
-            res = binding.solve(W, N, M, 0.01, iters, tau_mode=binding.TSENOR_TAU_REL_MATRIX_MAX, flags=flag,
-                                want_stats=True)
-            torch.cuda.synchronize()
-            assert np.array_equal(res["mask"].cpu().numpy(), full["mask"]), (name, levels)
-            assert np.array_equal(res["stats"].cpu().numpy(), full["stats"]), (name, levels)
+    for (block_rows, block_cols), cases in (((5, 7), ((0, 40), (3, 0), (1, 0))), ((1, 1), ((0, 40), (3, 0))), ((3, 21), ((0, 40), (3, 0))),
+                                            ((5, 13), ((0, 40), (3, 0))), ((3, 43), ((0, 40), (3, 0)))):
+        if block_rows * block_cols > 35 and M > 4:
+            continue
+        for levels, iters in cases:
+            Wf = rng.standard_normal((block_rows * M, block_cols * M)).astype(np.float32)
+            if levels:
+                Wf = np.round(Wf * levels) / np.float32(levels)
+            W = torch.from_numpy(Wf).to(dev)
+            ref = oracle.mask(Wf, N, M, 0.01, iters, tau_mode=oracle.TAU_REL_MATRIX_MAX, L=0, strict_paper=True)
+            full = oracle.mask(Wf, N, M, 0.01, iters, tau_mode=oracle.TAU_REL_MATRIX_MAX)
+            for name, tiles in (("large", binding.TSENOR_FLAG_TILES_LARGE), ("small", binding.TSENOR_FLAG_TILES_SMALL)):
+                print(f"[case] selection on {name} tiles {N}:{M} {block_rows}x{block_cols} blocks levels={levels} T={iters}", flush=True)
+                for want, L, flags in ((ref, 0, binding.TSENOR_FLAG_STRICT_PAPER), (full, 10, 0)):
+                    got = [binding.solve(W, N, M, 0.01, iters, tau_mode=binding.TSENOR_TAU_REL_MATRIX_MAX, local_search_steps=L,
+                                         flags=tiles | flags | extra, want_stats=True)
+                           for extra in (0, binding.TSENOR_FLAG_GREEDY_ONE_LANE, binding.TSENOR_FLAG_GREEDY_M_LANES)]
+                    torch.cuda.synchronize()
+                    assert np.array_equal(got[0]["mask"].cpu().numpy(), want["mask"]), (name, levels)
+                    assert np.array_equal(got[0]["stats"].cpu().numpy(), want["stats"]), (name, levels)
+                    assert all(torch.equal(g[k], got[0][k]) for g in got[1:] for k in ("mask", "stats"))
 
 
 @pytest.mark.parametrize("M,N,block_rows,block_cols", [(16, 8, 10, 33), (32, 16, 3, 43), (8, 3, 9, 50), (64, 32, 2, 35)])
-def test_one_lane_greedy_with_a_ragged_last_workgroup(dev, M, N, block_rows, block_cols):
-    # the one-lane greedy kernel runs in workgroups of four waves (64 blocks per wave) for M <= 32: block counts
-    # that leave the last workgroup with idle waves and the last wave with idle lanes
+def test_rounding_with_a_ragged_last_wave(dev, M, N, block_rows, block_cols):
+    # the rounding kernel behind the large tiles holds 64 / M blocks per wave, the iterations up to 16 per wave and four waves
+    # per workgroup: block counts that leave the last workgroup with idle waves and the last wave with idle lanes
     import torch
 
     from paper_2505_23949_amd import binding
 
-    w = synth.Workload(f"ragged_greedy_{N}of{M}", block_rows * M, block_cols * M, N, M, 0.01, 25, "f32", "wanda", 4300 + M)
+    w = synth.Workload(f"ragged_{N}of{M}", block_rows * M, block_cols * M, N, M, 0.01, 25, "f32", "wanda", 4300 + M)
     g = synth.generate(w)
     W, cs = _to_device(g, w, dev)
-    print(f"[case] one-lane greedy, {block_rows * block_cols} blocks of {N}:{M}", flush=True)
+    print(f"[case] ragged last wave, {block_rows * block_cols} blocks of {N}:{M}", flush=True)
     res = binding.solve(W, N, M, w.tau, w.iters, col_scale=cs, tau_mode=w.tau_mode, want_stats=True,
-                        flags=binding.TSENOR_FLAG_GREEDY_ONE_LANE | binding.TSENOR_FLAG_TILES_LARGE)
+                        flags=binding.TSENOR_FLAG_TILES_LARGE)
     torch.cuda.synchronize()
     ref = oracle.mask(g["W_f32"], N, M, w.tau, w.iters, col_scale=g["col_scale"], tau_mode=w.tau_mode)
     assert np.array_equal(res["mask"].cpu().numpy(), ref["mask"])
@@ -349,6 +351,7 @@ def test_randomised_configurations(dev):
         iters = int(rng.choice([0, 1, 7, 30, 120]))
         strict, cols_first = bool(rng.integers(0, 4) == 0), bool(rng.integers(0, 2))
         L = int(rng.choice([0, 1, 10]))
+        # (accepted, without effect)
         greedy = int(rng.choice([0, binding.TSENOR_FLAG_GREEDY_ONE_LANE, binding.TSENOR_FLAG_GREEDY_M_LANES]))
         greedy |= int(rng.choice([0, binding.TSENOR_FLAG_TILES_LARGE, binding.TSENOR_FLAG_TILES_SMALL]))
         fp32 = bool(rng.integers(0, 4) == 0)
@@ -492,8 +495,8 @@ def test_randomised_configurations(dev):
 @pytest.mark.parametrize("M,N,dtype", [(16, 8, "f32"), (32, 16, "bf16"), (32, 7, "f32"), (16, 3, "bf16"),
                                        (4, 2, "f32"), (4, 1, "bf16"), (8, 4, "bf16"), (8, 3, "f32")])
 def test_both_tilings_of_the_dykstra_kernel(dev, M, N, dtype):
-    # ragged block counts for both tilings (blocks per wave, small / large: M = 32: 1 / 2; M = 16: 4 / 8;
-    # M = 8: 4 / 16; M = 4: 16 / 64)
+    # ragged block counts for both tilings (blocks per wave, small / large: M = 32: 1 / 2; M = 16: 1 / 8, since so few
+    # blocks have a wave each; M = 8: 4 / 16; M = 4: 16 / 64)
     import torch
 
     from paper_2505_23949_amd import binding

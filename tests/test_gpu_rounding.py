@@ -1,4 +1,5 @@
-"""round_kernel (Algorithm 2 for M >= 8 by deferred acceptance) against the oracle's sequential selection and swaps."""
+"""Algorithm 2 by deferred acceptance, and the layouts of small launches it runs behind, against the oracle's sequential
+selection and swaps and against each other."""
 import numpy as np
 import pytest
 
@@ -57,6 +58,43 @@ def test_fine_tilings_of_16_wide_blocks(blocks):
         assert np.abs(res["plan"].cpu().numpy() - np.exp(ref["log_S"])).max() <= 1e-9
         assert np.array_equal(res["mask"].cpu().numpy(), ref["mask"])
         assert np.array_equal(res["stats"].cpu().numpy(), ref["stats"])
+
+
+@pytest.mark.parametrize("name,options", [("early exit", {"tol": 1e-2, "T": 300}),
+                                          ("early exit, columns first", {"tol": 1e-3, "T": 300, "cols_first": True}),
+                                          ("bf16, column scale", {"bf16": True, "scale": True}),
+                                          ("bf16, columns first, column scale", {"bf16": True, "scale": True, "cols_first": True}),
+                                          ("printed swap rule", {"strict": True})])
+def test_four_16_wide_blocks_per_wave(name, options):
+    # the small tiles of 16 x 16 blocks, four to a wave, which serve 1800 to 62 000 blocks: 1802 blocks leave two of the last
+    # wave's idle; with the early exit the blocks of a wave stop at iterations of their own
+    import torch
+
+    from paper_2505_23949_amd import binding as b
+
+    dev, N, M, T = torch.device("cuda:0"), 7, 16, options.get("T", 60)
+    rng = np.random.Generator(np.random.Philox(55))
+    W = torch.from_numpy(rng.standard_normal((34 * M, 53 * M), dtype=np.float32))
+    if options.get("bf16"):
+        W = W.to(torch.bfloat16)
+    cs = rng.lognormal(0.0, 1.0, W.shape[1]).astype(np.float32) if options.get("scale") else None
+    tol, cols_first, strict = options.get("tol", 0.0), options.get("cols_first", False), options.get("strict", False)
+    print(f"[case] small tiles of 16 x 16 blocks, {name}", flush=True)
+    res = b.solve(W.to(dev), N, M, 0.01, T, col_scale=None if cs is None else torch.from_numpy(cs).to(dev),
+                  tau_mode=b.TSENOR_TAU_REL_MATRIX_MAX, tol=tol, local_search_steps=2, want_plan=True, want_stats=True,
+                  want_iters_done=True, flags=(b.TSENOR_FLAG_COLS_FIRST if cols_first else 0) | (b.TSENOR_FLAG_STRICT_PAPER if strict else 0))
+    torch.cuda.synchronize()
+    imp = oracle.importance(W.float().numpy(), cs)
+    te = oracle.tau_eff(imp, 0.01, synth.TAU_REL_MATRIX_MAX)
+    log_S, done = oracle.dykstra_adaptive(imp, N, M, te, T, tol, cols_first=cols_first)
+    mask, stats = oracle.round_plan(log_S, imp, N, M, L=2, strict_paper=strict)
+    if tol > 0.0:
+        assert done.min() < done.max(), "the blocks should stop at different iterations"
+    assert np.array_equal(res["iters_done"].cpu().numpy(), done)
+    # 1e-9: what the parity tests ask of a plan computed in double on both sides
+    assert np.abs(res["plan"].cpu().numpy() - np.exp(log_S)).max() <= 1e-9
+    assert np.array_equal(res["mask"].cpu().numpy(), mask)
+    assert np.array_equal(res["stats"].cpu().numpy(), stats)
 
 
 @pytest.mark.parametrize("blocks", [(1, 1), (16, 16), (1, 257)])

@@ -6,14 +6,25 @@
 namespace tsenor_dev {
 
 // Sums of the per-block objectives, workgroup by workgroup (blockIdx.y: matrix).  Every order is fixed: bitwise
-// reproducible.  One workgroup per matrix took 0.1 ms for 262 144 blocks (256 dependent loads per thread).
+// reproducible.  One workgroup per matrix took 0.1 ms for 262 144 blocks (256 dependent loads per thread); up to
+// kObjectiveAloneBlocks (four) the first workgroup does it alone and writes the result, so that a call that wants only the
+// sums of small matrices has one launch of one workgroup each for them (2:4, two matrices of 741 blocks: 18.0 us a call with
+// 64 and a second launch, 17.0 so).
+constexpr int64_t kObjectiveAloneBlocks = 4 * 256;
+__device__ __forceinline__ bool previous_mask_wins(const BatchEntry& e, double2 sums) { return e.prev_mask && sums.y > sums.x; }
+__device__ __forceinline__ void write_objectives(const BatchEntry& e, double2 sums) {
+  e.objective_out[0] = previous_mask_wins(e, sums) ? sums.y : sums.x;
+  e.objective_out[1] = e.prev_mask ? sums.y : 0.0;
+}
 __global__ __launch_bounds__(256) void objective_kernel(Batch batch) {
   const BatchEntry& e = batch.e[blockIdx.y];
-  if (!e.block_objective) return;
+  const bool alone = e.p.nblocks <= kObjectiveAloneBlocks;
+  if (!e.block_objective || (alone && blockIdx.x != 0)) return;
   const double2* objective = reinterpret_cast<const double2*>(e.block_objective);
   __shared__ double2 part[4];
   double a = 0.0, b = 0.0;
-  for (int64_t k = (int64_t)blockIdx.x * 256 + threadIdx.x; k < e.p.nblocks; k += kObjectiveGroups * 256) {
+  const int64_t step = (alone ? 1 : kObjectiveGroups) * 256;
+  for (int64_t k = (int64_t)blockIdx.x * 256 + threadIdx.x; k < e.p.nblocks; k += step) {
     const double2 v = objective[k];
     a += v.x;
     b += v.y;
@@ -30,14 +41,17 @@ __global__ __launch_bounds__(256) void objective_kernel(Batch batch) {
       b += part[w].y;
     }
     reinterpret_cast<double2*>(e.absmax_partial)[blockIdx.x] = make_double2(a, b);
+    if (alone && e.objective_out) write_objectives(e, make_double2(a, b));
   }
 }
 
 // The objectives of the mask found and of the previous mask, in every lane of the calling wave (a butterfly gives all
-// lanes the same sum).
+// lanes the same sum; what one workgroup has summed comes through it as it is).
 __device__ __forceinline__ double2 objectives_of(const BatchEntry& e) {
   static_assert(kObjectiveGroups == 64, "one partial sum per lane");
-  double2 v = reinterpret_cast<const double2*>(e.absmax_partial)[threadIdx.x % 64];
+  const int lane = threadIdx.x % 64;
+  double2 v = make_double2(0.0, 0.0);
+  if (lane == 0 || e.p.nblocks > kObjectiveAloneBlocks) v = reinterpret_cast<const double2*>(e.absmax_partial)[lane];
   for (int s = 1; s < 64; s <<= 1) {
     v.x += __shfl_xor(v.x, s, 64);
     v.y += __shfl_xor(v.y, s, 64);
@@ -106,11 +120,8 @@ __global__ __launch_bounds__(256) void emit_kernel(Batch batch) {
   bool use_prev = false;
   if (e.block_objective) {
     const double2 sums = objectives_of(e);
-    use_prev = prev_mask && sums.y > sums.x;
-    if (e.objective_out && blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x == 0) {
-      e.objective_out[0] = use_prev ? sums.y : sums.x;
-      e.objective_out[1] = prev_mask ? sums.y : 0.0;
-    }
+    use_prev = previous_mask_wins(e, sums);
+    if (e.objective_out && blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x == 0) write_objectives(e, sums);
   }
   if (!use_prev && !packed_out && !pruned_out) return;
   const int64_t rows = e.rows;

@@ -329,11 +329,12 @@ int run_group(Batch& b, const Variant& v, hipStream_t stream, hipEvent_t* ev = n
   auto mark = [&](int k) {
     if (ev) (void)hipEventRecord(ev[k], stream);
   };
-  bool any_rel = false, any_objective = false, any_emit = false, any_stats = false;
+  bool any_rel = false, any_objective = false, any_partial_sums = false, any_emit = false, any_stats = false;
   for (int k = 0; k < b.count; ++k) {
     const BatchEntry& e = b.e[k];
     any_rel |= e.p.tau_mode == TSENOR_TAU_REL_MATRIX_MAX;
     any_objective |= e.block_objective != nullptr;
+    any_partial_sums |= e.block_objective && e.p.nblocks > kObjectiveAloneBlocks;
     any_emit |= e.packed_out || e.pruned_out || e.prev_mask;
     any_stats |= e.stats_out != nullptr;
   }
@@ -355,10 +356,10 @@ int run_group(Batch& b, const Variant& v, hipStream_t stream, hipEvent_t* ev = n
     case 64: ok = launch_block_kernels<64>(b, v, stream, ev_sorted, ev_greedy); break;
   }
   if (!ok) return TSENOR_ERR_SHAPE;  // (ruled out by the checks before the first launch)
-  if (any_objective) objective_kernel<<<dim3(kObjectiveGroups, (unsigned)b.count), 256, 0, stream>>>(b);
+  if (any_objective) objective_kernel<<<dim3(any_partial_sums ? kObjectiveGroups : 1, (unsigned)b.count), 256, 0, stream>>>(b);
   if (any_emit)
     emit_kernel<<<strided_grid(b, true, 2048, false), 256, 0, stream>>>(b);
-  else if (any_objective)  // (only the sums are wanted)
+  else if (any_partial_sums)  // (only the sums are wanted)
     emit_kernel<<<dim3(1, 1, (unsigned)b.count), 256, 0, stream>>>(b);
   if (any_stats)
     stats_kernel<<<dim3(kStatsGroups, (unsigned)b.count), 256, 0, stream>>>(b, (int)rowmask_bytes_per_block(v.M));

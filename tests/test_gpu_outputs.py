@@ -80,3 +80,39 @@ def test_batch_with_a_matrix_of_one_4_wide_block_column():
     for out, single in zip(outs, singles):
         for k in out:
             assert torch.equal(out[k], single[k]), k
+
+
+@pytest.mark.parametrize("blocks", [(1, 1), (32, 32), (25, 41)])
+def test_objective_alone_and_with_derived_outputs(blocks):
+    # one block, and the two sides of the line (1024 blocks) up to which one workgroup sums the objectives and writes them:
+    # the same bits whether the call also has derived outputs or not, alone or fused with the other sizes
+    import torch
+
+    import oracle
+    from paper_2505_23949_amd import binding as b
+
+    dev, N, M = torch.device("cuda:0"), 3, 8
+    rng = np.random.Generator(np.random.Philox(90 + blocks[1]))
+    Wf = rng.standard_normal((blocks[0] * M, blocks[1] * M), dtype=np.float32)
+    W = torch.from_numpy(Wf).to(dev)
+    first = torch.from_numpy((np.add.outer(np.arange(Wf.shape[0]), np.arange(Wf.shape[1])) % M < N).astype(np.uint8)).to(dev)
+    print(f"[case] objective of {blocks[0] * blocks[1]} blocks", flush=True)
+    kw = dict(tau_mode=b.TSENOR_TAU_REL_MATRIX_MAX, want_objective=True)
+    alone, packed, safe = b.solve(W, N, M, 0.01, 30, **kw), b.solve(W, N, M, 0.01, 30, want_packed=True, **kw), \
+        b.solve(W, N, M, 0.01, 30, prev_mask=first, **kw)
+    small = torch.from_numpy(rng.standard_normal((M, 2 * M), dtype=np.float32)).to(dev)
+    masks, sums = [torch.empty(x.shape, dtype=torch.uint8, device=dev) for x in (W, small)], torch.zeros((2, 2), dtype=torch.float64, device=dev)
+    probs = [b.make_problem(x, N, M, 0.01, 30, mask=m, objective_out=o, tau_mode=b.TSENOR_TAU_REL_MATRIX_MAX, flags=b.TSENOR_FLAG_TILES_LARGE)
+             for x, m, o in zip((W, small), masks, sums)]
+    b.tsenor_mask_batched(probs, torch.empty(b.tsenor_workspace_bytes(probs), dtype=torch.uint8, device=dev))
+    torch.cuda.synchronize()
+    imp = np.abs(Wf)
+    # the importance terms are the same numbers on both sides; the two sums of `size` of them differ by their order
+    bar = imp.size * 2.0 ** -53
+    for res, theirs in ((alone, 0.0), (packed, 0.0), (safe, oracle.objective(first.cpu().numpy(), imp, M))):
+        want, got = oracle.objective(res["mask"].cpu().numpy(), imp, M), res["objective"].cpu().numpy()
+        assert abs(got[0] - want) <= bar * want and abs(got[1] - theirs) <= bar * max(theirs, 1e-300)
+    assert torch.equal(alone["objective"], packed["objective"])
+    for x, m, o in zip((Wf, small.cpu().numpy()), masks, sums.cpu().numpy()):
+        want = oracle.objective(m.cpu().numpy(), np.abs(x), M)
+        assert abs(o[0] - want) <= bar * want and o[1] == 0.0

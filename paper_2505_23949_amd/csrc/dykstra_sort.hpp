@@ -116,13 +116,13 @@ struct Tiling<16, kSmallTiles> {
 template <>
 struct Tiling<16, kFinestTiles> {
   static constexpr int NX = 3, NY = 3;  // 64 lanes per block, 2 x 2 tiles
-  static constexpr int XM[3] = {7, 3, 1}, YM[3] = {8, 16, 32};
+  static constexpr int XM[3] = {7, 3, 1}, YM[3] = {8, 32, 16};
   static constexpr bool STORE_E = true;
 };
 template <>
 struct Tiling<16, kFinestOrderTiles> {
   static constexpr int NX = 2, NY = 2;  // 16 lanes per block, 4 x 4 tiles
-  static constexpr int XM[2] = {3, 1}, YM[2] = {4, 8};
+  static constexpr int XM[2] = {3, 1}, YM[2] = {8, 4};  // (steps of the finest tiles' lane-columns after their first: 32 and 16)
   static constexpr bool STORE_E = true;
 };
 template <>

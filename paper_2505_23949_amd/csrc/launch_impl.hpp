@@ -45,7 +45,7 @@ bool launch_block_kernels(Batch& b, const Variant& v, hipStream_t stream, hipEve
     }
     if constexpr (finest_tiles_below_blocks(M) > 0) {
       if (v.tiles == kFinestTiles)
-        ok = nblocks < finest_tiles_below_blocks(M) ? launch(std::integral_constant<int, kFinestTiles>{})
+        ok = nblocks <= kFinestTilesLaunch ? launch(std::integral_constant<int, kFinestTiles>{})
                                                     : launch(std::integral_constant<int, kFinestOrderTiles>{});
     }
     if constexpr (M == Team::M) {

@@ -154,7 +154,7 @@ OPTIONS = {"plain": {}, "columns first": {"cols_first": True}, "bf16, column sca
                                                            (64, 1, 1, 2)])
 def test_a_batch_is_its_calls_on_every_layout(M, block_rows, block_cols, count, options):
     # 16 x 16 and 64 x 64 blocks of small matrices have a wave or a workgroup each as long as the launch is small; a fused
-    # launch of several such matrices (here on both sides of its lines, 1800 and 257 blocks) takes the coarser layout, which
+    # launch of several such matrices (here on both sides of its lines, 2048 and 257 blocks) takes the coarser layout, which
     # adds in the same order: every output is that of the calls of their own, bit for bit.  (1, 1): idle lanes.
     import torch
 

@@ -170,8 +170,8 @@ enum { TSENOR_IMPORTANCE_ABS = 0, TSENOR_IMPORTANCE_SQUARE = 1 };
 
 /* Bytes of device scratch that tsenor_mask_ex / tsenor_mask_batched need for these problems
  * (the sum over the batch).  0 on invalid arguments.  The scratch holds what passes between the kernels of
- * the path: the potentials of every block (two bytes per weight are set aside), the mask greedy selection leaves (Algorithm 2
- * line 6), per-block counters and per-block objective values of Eq. 1. */
+ * the path: the potentials of every block (two bytes per weight are set aside) with its row normalisers, or the mask greedy
+ * selection leaves (Algorithm 2 line 6), per-block counters and per-block objective values of Eq. 1. */
 size_t tsenor_workspace_bytes(const tsenor_problem* problems, int count);
 
 /* The whole path (tile load -> Algorithm 1 -> Algorithm 2 -> mask write) for one matrix: Eq. 1 solved block

@@ -215,9 +215,10 @@ def tsenor_mask_ex_static(problem, stream=None) -> None:
 
 
 NUM_STAGES = 4
-# what a stage holds depends on the block size (tsenor_profile.h): for M >= 8 the third is the whole of Algorithm 2 and the
-# fourth the optional outputs
-STAGE_NAMES = ("reset+absmax", "dykstra+sort", "greedy", "local_search+write")
+# What a stage holds depends on the block size (tsenor_profile.h).  "iterations": Algorithm 1, for M = 4 with the greedy
+# selection, in a small launch the whole path; "rounding": Algorithm 2 with the mask write (M >= 8); "finish+outputs": for
+# M = 4 the swaps with the mask write, and the optional outputs.
+STAGE_NAMES = ("reset+maximum", "iterations", "rounding", "finish+outputs")
 
 
 def tsenor_mask_ex_profile(problem, workspace, repeats, stream=None, want_clock=False):

@@ -18,8 +18,8 @@
 //
 // Precision.  Default: everything in double (MI355X issues fp64 vector operations at 16 lanes/clk/SIMD),
 // which reproduces a double-precision reference to ~1e-13.  FAST: the first kWarmIters iterations in
-// double, then the loop in fp32 (a shorter instruction, and half the registers: three waves per SIMD
-// instead of two; four for M = 32) on kappa32 = fl32(kappa U V) with fp32 scalings relative to the double ones.  fp32 has 8
+// double, then the loop in fp32 (a shorter instruction, and half the registers: three or four waves per SIMD
+// instead of two) on kappa32 = fl32(kappa U V) with fp32 scalings relative to the double ones.  fp32 has 8
 // exponent bits, so every kChunk iterations the relative scalings are checked and, when one has drifted past
 // 2^+-kDriftBits, they are multiplied into the double ones and kappa32 is rebuilt as
 // fl32(exp(K - row max + log U + log V)) from a fresh read of the importance (kappa itself is not kept: the kernel is
@@ -538,10 +538,10 @@ struct DykstraLaunch {
   static constexpr int kThreads = kWavesPerGroup * kWave;
   // Waves per SIMD the register budget is set for.  Double: the loop holds twice the state of the fp32 one, two waves of up
   // to 256 registers.  FAST: the more waves, the nearer the issue of plain fp32 instructions comes to its limit (1.13 ns
-  // per instruction and SIMD with two waves, 1.05 with four).  M = 32: four waves of 128 registers, the loop fits and ~30
+  // per instruction and SIMD with two waves, 1.05 with four).  M = 32: four waves of 128 registers, the loop fits and 42
   // registers of the double-precision code around it spill (4096x14336: iteration kernel 1425 us, 1470 with three waves).
-  // M = 16: three (four the same to 0.4 % slower).  M = 8: four (129 registers with three; two spill outside the loop).  M = 4:
-  // four fit whatever is asked for (five spill: 1 % slower).  M = 64: three, ~90 registers spill outside the loop (8192x28672, T = 500: 10.5 ms, two waves 11.0, four 31);
+  // M = 16: three (four the same to 0.4 % slower).  M = 8: four (129 registers with three; three spill outside the loop).  M = 4:
+  // four fit whatever is asked for (five spill: 1 % slower).  M = 64: three, 93 registers spill outside the loop (8192x28672, T = 500: 10.5 ms, two waves 11.0, four 31);
   // with the early exit, where a block may run a dozen iterations and the code around the loop is most of the work, two
   // (8192x8192: 0.85 ms, three 1.05).
   static constexpr int kWavesPerSimd = FAST && !(M == 64 && ADAPT) ? (M == 32 || M == 8 ? 4 : 3) : 2;

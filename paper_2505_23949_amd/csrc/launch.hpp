@@ -61,7 +61,7 @@ constexpr bool small_tiles_win(int M, bool fp32, bool adaptive, int64_t nblocks)
 // Whole calls, T = 300 (us, finest / small tiles): 256 blocks 67 / 88, 1024 blocks 73 / 89, 1536 blocks 81 / 90, 2304 blocks
 // 104 / 90 (from three waves on a SIMD on, issue decides).  Fused matrices of 1024 blocks (us, finest tiles / small tiles in
 // their order): 2 85 / 94, 3 107 / 89, 4 131 / 90, 16 436 / 243.  (Single matrices above the line keep the small tiles' own
-// order, whose loop is 1-4 % faster.)
+// order, whose loop is 1-5 % faster.)
 constexpr int64_t finest_tiles_below_blocks(int M) { return M == 16 ? 1800 : 0; }
 constexpr int64_t kFinestTilesLaunch = 2048;
 

@@ -52,7 +52,7 @@ struct BatchEntry {
   float* absmax_partial;        // partial maxima of the importance, absmax_count of them (relative tau only)
   int absmax_count;
   void* potentials;             // BlockPotentials of every block (M >= 8)
-  void* rowmask;                // greedy's mask (M = 4), then the blocks' counters
+  void* rowmask;                // greedy's mask (M = 4) or the row normalisers (M >= 8), then the blocks' counters
   double* block_objective;      // NULL: no objective asked for
   uint8_t* mask;                // outputs of the caller (NULL where optional and not asked for)
   double* plan_out;

@@ -550,9 +550,10 @@ __device__ __forceinline__ void round_blocks(const DevProblem& p, const BatchEnt
 }
 
 // The stand-alone kernel: 64/M blocks per wave, one wave per workgroup; the potentials come from the workspace.
-// Bound by instruction issue: of ~2 500 vector instructions per wave before the swaps (M = 32) the two sorts are 764 and
-// the keys 512.  57 344 blocks of 16:32: 0.206 ms with the swaps, where the sort across lanes (0.20 ms of the iteration
-// kernel), the scan kernel (0.077 ms) and the swap kernel (0.104 ms) took 0.38 ms; 16 384 blocks of 32:64: 0.34 ms for 0.78.
+// Bound by instruction issue: 3 650 vector instructions per wave (M = 32, the swaps of 16:32 4096x14336 included), of which the
+// two sorts are 764 and the keys 384; 2 060 up to the first proposals.  57 344 blocks of 16:32: 0.198 ms, where the sort across
+// lanes (0.20 ms of the iteration kernel), the scan kernel (0.077 ms) and the swap kernel (0.104 ms) took 0.38 ms; 57 344 of
+// 32:64: 0.99-1.17 ms (two waves per SIMD: 224 registers, 19 KB of LDS).  Seven registers spill for M = 32, none elsewhere.
 template <int M, bool ZERO_T>
 __global__ __launch_bounds__(kWave, M <= 32 ? 4 : 2) void round_kernel(Batch batch) {
   constexpr int G = kWave / M;

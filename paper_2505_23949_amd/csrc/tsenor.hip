@@ -175,7 +175,8 @@ struct WsLayout {
   size_t header, partials, potentials, accept, objective, total;
 };
 
-// greedy's output (M row bit masks per block, 32-bit words up to M = 32, 64-bit for M = 64), then the block's counters
+// M words per block, 32-bit up to M = 32, 64-bit for M = 64: greedy's row bit masks (M = 4) or the row normalisers, then the
+// block's counters
 inline size_t rowmask_bytes_per_block(int M) { return (size_t)M * (M > 32 ? 8 : 4); }
 
 WsLayout layout_of(const tsenor_problem& p) {

@@ -67,7 +67,7 @@ def layout_of(M: int, fp32: bool, nblocks: int) -> str:
     if M == 4:
         small = nblocks <= 49152 or (not fp32 and 65536 < nblocks <= 114688)
     else:
-        small = nblocks <= {8: 8699, 16: 8192 if fp32 else 62000, 32: 2048 if fp32 else 3072, 64: 64 if fp32 else 256}[M]
+        small = nblocks <= {8: 8699, 16: 8192 if fp32 else 62000, 32: 2048 if fp32 else 3072, 64: 256}[M]
     if not small:
         return "large"
     return "team" if M == 64 else "finest" if M == 16 and nblocks < 1800 else "small"

@@ -89,9 +89,9 @@ enum {
    * double-precision evaluation to ~1e-5 instead of ~1e-13, and the greedy order - hence the mask - can
    * differ from it in a block where two plan entries are closer than that (none in 8192 blocks of the
    * 16:32 test workload).  Sort keys, swap scores and all results stay in double.  Off by default.  A matrix that
-   * runs on the small tiles (below), and one of at most 64 blocks of 64 x 64 unless TSENOR_FLAG_TILES_LARGE is set, iterates
-   * in double whatever this flag says: such a launch is bound by latency, not by instruction issue, and single precision
-   * would buy nothing. */
+   * runs on the small tiles (below), and one of fewer than 257 blocks of 64 x 64, iterates in double whatever this flag says:
+   * such a launch is bound by latency, not by instruction issue, and single precision would buy nothing.  A batch of many such
+   * matrices is another matter: with TSENOR_FLAG_TILES_LARGE they iterate in single precision. */
   TSENOR_FLAG_FP32_ITERATIONS = 1u << 2,
   /* Accepted for callers that set them, and without effect: there is one way the greedy selection (Algorithm 2 lines 1-6) is
    * found for each block size.  Setting both is an error. */

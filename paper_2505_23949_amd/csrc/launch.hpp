@@ -5,8 +5,6 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
-#include <algorithm>
-
 #include "problem.hpp"
 
 namespace tsenor_dev {
@@ -69,12 +67,10 @@ constexpr int64_t kFinestTilesLaunch = 2048;
 // workgroup per CU.  Whole calls, T = 300 (us, team / large tiles in double / with fp32 iterations): 64 blocks 173 / 286 /
 // 254, 256 blocks 180 / 296 / 270, 300 blocks 354 / 300.  Fused: 4 matrices of 256 blocks 677 / 307, 16 2684 / 1009.
 constexpr int64_t team_below_blocks(int M) { return M == 64 ? 257 : 0; }
-// Whether a matrix iterates in the team's order, in double: with the fp32 flag only up to the number of blocks at which even
-// kMaxBatch such matrices fused are one wave per SIMD, where the large tiles hardly take longer in double than in single
-// precision (16 matrices of 64 blocks 304 / 268 us a call; of 128 blocks 510 / 332).
-constexpr bool team_order_wins(int M, bool fp32, int64_t nblocks) {
-  return nblocks < (fp32 ? std::min<int64_t>(team_below_blocks(M), 1024 / kMaxBatch + 1) : team_below_blocks(M));
-}
+// Below as many blocks in a matrix it iterates in the team's order, in double whatever the fp32 flag says.  A call of its own
+// gains from that (256 blocks 180 us, 270 with fp32 iterations on the large tiles); a fused launch of many takes the large
+// tiles in double where they could iterate in single precision (16 matrices of 64 blocks 304 / 268, of 128 blocks 510 / 332,
+// of 256 blocks 1009 / 673), which a caller that wants them asks for with TSENOR_FLAG_TILES_LARGE.
 
 // Enqueues the kernels of one fused launch that depend on M: tile load + Algorithm 1 (for M = 4 with the greedy selection, on
 // small launches the whole path), then Algorithm 2 + mask write.  `b.count` non-degenerate problems of variant v.

@@ -230,7 +230,7 @@ inline Variant variant_of(const tsenor_problem& p) {
   const int64_t nblocks = (p.rows / p.M) * (p.cols / p.M);
   const bool fp32 = (p.flags & TSENOR_FLAG_FP32_ITERATIONS) != 0;
   const bool tiled = !v.zero_t && !v.simple && !(p.flags & TSENOR_FLAG_TILES_LARGE);
-  const bool team = tiled && team_order_wins(p.M, fp32, nblocks);
+  const bool team = tiled && nblocks < team_below_blocks(p.M);
   const bool small = team || (p.M <= 32 && tiled &&
                               ((p.flags & TSENOR_FLAG_TILES_SMALL) != 0 || small_tiles_win(p.M, fp32, v.adaptive, nblocks)));
   v.tiles = !small ? kLargeTiles : team ? kTeam : nblocks < finest_tiles_below_blocks(p.M) ? kFinestTiles : kSmallTiles;

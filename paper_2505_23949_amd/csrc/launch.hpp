@@ -39,6 +39,8 @@ struct Variant {
 //   M = 8 (4): 8280 blocks 83 / 83 / 85, 9216 blocks 87 / 83 / 85, 10 240 blocks 90 / 84 / 85;
 //   M = 4 (16; the large tiles hold 64): 46 000 blocks 78 / 93 / 85, 49 283 blocks 97 / 93 / 85, 65 536 blocks 100 / 92 / 83,
 //     66 000 blocks 113 / 159 / 94, 106 000 blocks 154 / 166 / 104, 114 920 blocks 179 / 165 / 102.
+// T = 100 puts the lines at the same places; at T = 20 the small tiles stay ahead a little beyond them, by less than 2 us (M = 4,
+// 52 000 blocks 21.0 / 22.1, M = 8, 9000 blocks 21.4 / 23.1), but for M = 16 (65 536 blocks 146 / 152).
 // With the early exit (`adaptive`) a wave runs until the slowest of its blocks stops, and the large tiles put up to four times
 // as many blocks into it, so M <= 8 keeps the small tiles for longer.  T = 300, normal weights, tol 1e-2 and 1e-3 (small /
 // large double / large fp32):

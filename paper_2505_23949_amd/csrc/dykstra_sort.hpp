@@ -46,7 +46,8 @@ namespace tsenor_dev {
 constexpr double kMinLogKernel = -700.0;  // exp(-700) is still a normal double
 constexpr int kWarmIters = 4;             // FAST: iterations done in double before switching to fp32
 constexpr int kRowChunks64 = 2;           // M = 64: the 8 x 8 tile is loaded in this many pieces (loads in flight cost registers)
-constexpr int kChunk = 8;                 // FAST: iterations between range checks of the fp32 scalings
+constexpr int kChunk = 8;                 // iterations between looks for a repetition, FAST: and range checks of the scalings
+constexpr int kRepeatWindow = 24;         // iterations over which a repetition is looked for (RepeatCheck)
 constexpr int kDriftBits = 40;            // FAST: fold the fp32 scalings back beyond 2^+-kDriftBits
 constexpr double kLogFloor32 = -83.0;     // FAST: rebuilt entries are kept within [e^-83, e^55] ~ [2^-120, 2^80]
 constexpr double kLogCeil32 = 55.0;
@@ -520,6 +521,54 @@ __device__ __forceinline__ float dykstra_iteration_f32(const float (&kap)[TH][TW
   return worst;
 }
 
+// Whether the iterations of a wave have begun to repeat themselves.  An iteration is a function of the scalings alone (the
+// tile it reads stays as it is), so once the scalings of all blocks of a wave are, bit for bit, what they were d iterations
+// ago, all later states are known, and whole periods of d iterations are as good as done.
+// Once a block has converged to the precision of its numbers its last bits run through a short cycle: of 512 blocks of 16:32
+// with fp32 iterations 57 % end in one of period 2, 14 % of 1, 4, 6 or 8, hardly any in a period that does not divide 24.  So
+// the state is compared every kChunk iterations with one 8, 16 or 24 iterations old.
+// Measured, us a call before and with it (fp32 iterations): 32:64 8192x28672 T = 500 10 405 / 2919 (a block runs about 60
+// iterations), 16:32 4096x14336 T = 300 1627 / 1399 (two blocks per wave, which go on until both repeat), 15:16 4672x5264 T = 500
+// 1186 / 526; where no block repeats itself before T the looks cost less than 1 %.
+// That state is kept in LDS: the kernels whose register budget is that of their loop have none to spare for it.
+template <class real, int OWN_R, int OWN_C>
+struct RepeatCheck {
+  using Seen = real[OWN_R + OWN_C][kWave];
+  Seen& seen;  // the scalings every lane owns, after `noted` iterations
+  int lane, noted;
+  static __device__ __forceinline__ bool differ(float x, float y) { return __float_as_uint(x) != __float_as_uint(y); }
+  static __device__ __forceinline__ bool differ(double x, double y) { return __double_as_longlong(x) != __double_as_longlong(y); }
+  template <int NU, int NV>
+  __device__ __forceinline__ void note(const real (&U)[NU], const real (&V)[NV], int t) {
+#pragma unroll
+    for (int a = 0; a < OWN_R; ++a) seen[a][lane] = U[a];
+#pragma unroll
+    for (int b = 0; b < OWN_C; ++b) seen[OWN_R + b][lane] = V[b];
+    noted = t;
+  }
+  // t iterations are done: the number that are as good as done
+  template <int NU, int NV>
+  __device__ __forceinline__ int look(const real (&U)[NU], const real (&V)[NV], int t, int T) {
+    // (the whole state only if a first scaling of every lane is as it was)
+    bool changed = __any(differ(U[0], seen[0][lane]));
+    if (!changed) {
+#pragma unroll
+      for (int a = 1; a < OWN_R; ++a) changed |= differ(U[a], seen[a][lane]);
+#pragma unroll
+      for (int b = 0; b < OWN_C; ++b) changed |= differ(V[b], seen[OWN_R + b][lane]);
+      changed = __any(changed);
+    }
+    const int d = t - noted;
+    if (!changed) {
+      while (T - t >= d) t += d;
+      noted = t;
+    } else if (d >= kRepeatWindow) {
+      note(U, V, t);
+    }
+    return t;
+  }
+};
+
 // calls f(integral_constant<A0>) for A0 = 0, NA, 2 NA, ... < TH: a tile is loaded NA rows at a time
 template <int A0, int NA, int TH, class F>
 __device__ __forceinline__ void row_chunks(F& f) {
@@ -533,8 +582,10 @@ template <int M, bool FAST, bool ADAPT = false, int TILES = kLargeTiles>
 struct DykstraLaunch {
   // with the early exit the waves of a launch run for very different times; one-wave workgroups let the
   // dispatcher refill every wave slot as it frees (a four-wave workgroup holds its slots until its slowest wave).
+  // So do the 64-wide fp32 waves, one block each, which leave when their block repeats itself (8192x28672, T = 500: 3.15 ms, in
+  // four-wave workgroups 3.67; for two and more blocks per wave there is no clear difference).
   // The small tiles carry the rounding behind the iterations, whose steps synchronise one wave at a time.
-  static constexpr int kWavesPerGroup = (ADAPT || TILES != kLargeTiles) ? 1 : 4;
+  static constexpr int kWavesPerGroup = (ADAPT || (FAST && M == 64) || TILES != kLargeTiles) ? 1 : 4;
   static constexpr int kThreads = kWavesPerGroup * kWave;
   // Waves per SIMD the register budget is set for.  Double: the loop holds twice the state of the fp32 one, two waves of up
   // to 256 registers.  FAST: the more waves, the nearer the issue of plain fp32 instructions comes to its limit (1.13 ns
@@ -828,6 +879,10 @@ __global__ __launch_bounds__((DykstraLaunch<M, FAST, ADAPT, TILES>::kThreads), (
 #pragma unroll
         for (int b = 0; b < TW; ++b) V32[b] = 1.0f;
         bool all_frozen = false;
+        using Repeat = RepeatCheck<float, OWN_R, OWN_C>;
+        __shared__ typename Repeat::Seen seen[ADAPT ? 1 : WPG];
+        Repeat repeat{seen[ADAPT ? 0 : wave_in_group], lane};
+        if constexpr (!ADAPT) repeat.note(U32, V32, kWarmIters);
         for (int t = kWarmIters; t < p.T && !all_frozen;) {
           const int stop = (p.T - t > kChunk) ? t + kChunk : p.T;
           // (in fp32 the exchange also carries the updated scalings, which pays wherever a block spans lanes:
@@ -847,6 +902,7 @@ __global__ __launch_bounds__((DykstraLaunch<M, FAST, ADAPT, TILES>::kThreads), (
           } else {
             for (; t < stop; ++t) dykstra_iteration_f32<T, kLdsGather32>(kap32, U32, V32, Nf, xr, rx);
           }
+          if constexpr (!ADAPT) t = repeat.look(U32, V32, t, p.T);
           // (the scalings of the rows and columns this lane owns: every row and column has its owner, and the
           // other copies of a scaling are the same number)
           float mxs = U32[0], mns = U32[0];
@@ -859,6 +915,7 @@ __global__ __launch_bounds__((DykstraLaunch<M, FAST, ADAPT, TILES>::kThreads), (
             fold();
             take_logs();
             rebuild();
+            if constexpr (!ADAPT) repeat.note(U32, V32, t);
           }
         }
         fold();

@@ -12,9 +12,9 @@
 //     U_i *= R_i;   V_j *= C_j
 // which is lines 3-6 of Algorithm 1 in exact arithmetic: the row scaling acts on the plan capped by
 // the previous iteration, the column scaling on the row-scaled plan, and the cap with its dual is the
-// min(., 1) at the top of the next pass (App. A.2 listing, same order of operations).  The kernel keeps
-// kappa_ij U_i as one number per entry (updated by R_i every iteration), so an iteration costs four
-// operations per entry - multiply-and-clamp, add, fused multiply-add, multiply - and no transcendental.
+// min(., 1) at the top of the next pass (App. A.2 listing, same order of operations).  The kernel forms
+// kappa_ij U_i once per entry and iteration, so an iteration costs four operations per entry - multiply-and-clamp,
+// add, fused multiply-add, multiply - and no transcendental.
 //
 // Precision.  Default: everything in double (MI355X issues fp64 vector operations at 16 lanes/clk/SIMD),
 // which reproduces a double-precision reference to ~1e-13.  FAST: the first kWarmIters iterations in
@@ -57,13 +57,16 @@ constexpr int ilog2(int x) { return x <= 1 ? 0 : 1 + ilog2(x / 2); }
 
 // Per-M tiling.  XM[s] / YM[s]: lane masks of the exchange steps along a lane-row / lane-column.
 // The top bit of XM[s] is lane bit NX-1-s (mirror masks keep the exchanges on DPP); YM[s] is a single
-// lane bit, listed cheapest mechanism first because the first step moves the most registers.
+// lane bit, listed cheapest mechanism first because the first step moves the most registers, or 7: a DPP move that also turns
+// round the lanes along the lane-row, in place of one through the LDS crossbar (column_lane; 8:16 4096x4096 844 us a call with
+// the crossbar, 828 with it, and with fp32 iterations 531 and 517).
 // Small tiles: a finer tiling (more lanes per block, fewer entries per lane) for launches that cannot fill the
 // chip anyway: the dependent chain of an iteration is shorter.  Where a tile has fewer rows than the
 // lane-row has lanes, the last exchange steps of a reduction have no registers left to split: they add the
 // partner's value into the same register instead (both lanes end up owning the same sum).
 // kFinestTiles: a 16 x 16 block on a whole wave, for launches that leave SIMDs without a wave even so.
 // kFinestOrderTiles: the small tiles of 16 x 16 blocks with their additions in the order of the finest ones.
+// SWAPS: exchanges 16 lanes apart by v_permlane swaps (swap_step).  KEEP: form of an iteration in double (dykstra_iteration).
 template <int M, int TILES = kLargeTiles>
 struct Tiling;
 template <>
@@ -71,66 +74,95 @@ struct Tiling<4, kLargeTiles> {
   static constexpr int NX = 0, NY = 0;
   static constexpr int XM[1] = {1}, YM[1] = {1};
   static constexpr bool STORE_E = true;
+  static constexpr bool SWAPS = false;
+  static constexpr bool KEEP = true;
 };
 template <>
 struct Tiling<8, kLargeTiles> {
   static constexpr int NX = 1, NY = 1;
   static constexpr int XM[1] = {1}, YM[1] = {2};
   static constexpr bool STORE_E = true;
+  static constexpr bool SWAPS = false;
+  static constexpr bool KEEP = true;
 };
 template <>
 struct Tiling<16, kLargeTiles> {
   static constexpr int NX = 2, NY = 1;  // 8 lanes per block, 8 x 4 tiles
-  static constexpr int XM[2] = {3, 1}, YM[1] = {4};
+  static constexpr int XM[2] = {3, 1}, YM[1] = {7};
   static constexpr bool STORE_E = true;
+  static constexpr bool SWAPS = false;
+  static constexpr bool KEEP = true;
 };
 template <>
 struct Tiling<32, kLargeTiles> {
   static constexpr int NX = 3, NY = 2;  // 32 lanes per block, 8 x 4 tiles
   static constexpr int XM[3] = {7, 3, 1}, YM[2] = {8, 16};
   static constexpr bool STORE_E = true;
+  static constexpr bool SWAPS = false;
+  static constexpr bool KEEP = false;
 };
 template <>
 struct Tiling<64, kLargeTiles> {
   static constexpr int NX = 3, NY = 3;  // 64 lanes per block, 8 x 8 tiles; too large to hold e as doubles
   static constexpr int XM[3] = {7, 3, 1}, YM[3] = {8, 16, 32};
   static constexpr bool STORE_E = false;
+  static constexpr bool SWAPS = false;
+  static constexpr bool KEEP = false;
 };
 template <>
 struct Tiling<4, kSmallTiles> {
   static constexpr int NX = 1, NY = 1;  // 4 lanes per block, 2 x 2 tiles
   static constexpr int XM[1] = {1}, YM[1] = {2};
   static constexpr bool STORE_E = true;
+  static constexpr bool SWAPS = false;
+  static constexpr bool KEEP = true;
 };
 template <>
 struct Tiling<8, kSmallTiles> {
   static constexpr int NX = 2, NY = 2;  // 16 lanes per block, 2 x 2 tiles
-  static constexpr int XM[2] = {3, 1}, YM[2] = {8, 4};
+  static constexpr int XM[2] = {3, 1}, YM[2] = {8, 7};
   static constexpr bool STORE_E = true;
+  static constexpr bool SWAPS = false;
+  static constexpr bool KEEP = true;
 };
 template <>
 struct Tiling<16, kSmallTiles> {
   static constexpr int NX = 2, NY = 2;  // 16 lanes per block, 4 x 4 tiles
-  static constexpr int XM[2] = {3, 1}, YM[2] = {8, 4};
+  static constexpr int XM[2] = {3, 1}, YM[2] = {8, 7};
   static constexpr bool STORE_E = true;
+  static constexpr bool SWAPS = false;
+  static constexpr bool KEEP = true;
 };
 template <>
 struct Tiling<16, kFinestTiles> {
   static constexpr int NX = 3, NY = 3;  // 64 lanes per block, 2 x 2 tiles
   static constexpr int XM[3] = {7, 3, 1}, YM[3] = {8, 32, 16};
   static constexpr bool STORE_E = true;
+  static constexpr bool SWAPS = true;
+  static constexpr bool KEEP = true;
 };
 template <>
 struct Tiling<16, kFinestOrderTiles> {
   static constexpr int NX = 2, NY = 2;  // 16 lanes per block, 4 x 4 tiles
   static constexpr int XM[2] = {3, 1}, YM[2] = {8, 4};  // (steps of the finest tiles' lane-columns after their first: 32 and 16)
   static constexpr bool STORE_E = true;
+  static constexpr bool SWAPS = false;
+  static constexpr bool KEEP = true;
 };
 template <>
 struct Tiling<32, kSmallTiles> {
   static constexpr int NX = 3, NY = 3;  // 64 lanes per block, 4 x 4 tiles
   static constexpr int XM[3] = {7, 3, 1}, YM[3] = {8, 16, 32};
   static constexpr bool STORE_E = true;
+  static constexpr bool SWAPS = false;
+  static constexpr bool KEEP = true;
+};
+
+// The exchanges of a wave that has its SIMD to itself (swap_step).  The sums are the same bit for bit: what differs is which
+// register a lane holds a column in, and a row sum adds the columns of a lane in pairs.
+template <class T>
+struct LoneTiling : T {
+  static constexpr bool SWAPS = true;
 };
 
 // Two layouts of a block that add in the same order, so that a launch may take either.  A sum of two numbers does not depend on
@@ -159,13 +191,23 @@ __device__ __forceinline__ real row_tree(real (&s)[TW]) {
 }
 // in-kernel column of a block that tile column `b` (its register with the lane's offset taken off) of lane-column gx is
 template <int M, int TILES>
-__device__ __forceinline__ int column_in_block(int gx, int b) {
+__device__ __forceinline__ int column_in_block(int gx, int b) {  // (gx: of column_lane)
   if constexpr (M == 16 && TILES == kFinestOrderTiles) {
     // the column pairs of two finest lanes 7 apart (a step of their row reduction), the pair in bit 0
     return 2 * (b & 1 ? gx ^ 7 : gx) + (b >> 1);
   } else {
     return gx * (M >> Tiling<M, TILES>::NX) + b;
   }
+}
+
+// Lane-column of a lane for its columns.  A step that pairs lanes 7 apart along a lane-column also turns round the order of
+// four lanes along the lane-row: so does the assignment of columns in every other lane-row, and the two lanes hold the same ones.
+template <class T>
+__device__ __forceinline__ int column_lane(int gx, int q) {
+  bool turned = false;
+#pragma unroll
+  for (int s = 0; s < T::NY; ++s) turned |= T::YM[s] == 7;
+  return turned && (q & 4) ? gx ^ 3 : gx;
 }
 
 // registers a lane owns after a reduce-scatter of `count` values over 2^steps lanes (at least one)
@@ -181,6 +223,11 @@ constexpr int shift_lane(int x, int sh) { return sh >= 0 ? x << sh : x >> -sh; }
 __device__ __forceinline__ double fast_rcp(double d) {
   const double x = __builtin_amdgcn_rcp(d);
   return fma(fma(-d, x, 1.0), x, x);
+}
+// n/d the same way; the multiplication stands beside the refinement instead of behind it
+__device__ __forceinline__ double fast_div(double n, double d) {
+  const double x = __builtin_amdgcn_rcp(d), nx = n * x;
+  return fma(fma(-d, x, 1.0), nx, nx);
 }
 __device__ __forceinline__ float fast_rcp(float d) { return __builtin_amdgcn_rcpf(d); }
 __device__ __forceinline__ double clamp01(double x) { return fmin(fmax(x, 0.0), 1.0); }
@@ -243,12 +290,30 @@ __device__ __forceinline__ void all_reduce_max_x(float (&v)[TH]) {
   }
 }
 
-// The same over the lanes of a lane-column; step s pairs lanes that differ in lane bit YM[s].
+// Whether a step along a lane-column is a v_permlane swap of two registers instead of a move: both lanes of a pair then hold
+// the same columns in the same registers, the halving step keeps one of them (or the sum of one, in both) in each lane, and no
+// lane selects.
+// 32 lanes apart always (64 x 64: 376 instead of 384 instructions per iteration in double, 279 instead of 283 in fp32); 16 lanes
+// apart only where a wave has its SIMD to itself and waits out the latency of the LDS crossbar (4096x32 16:32: 99.6 us a call
+// through the crossbar, 94.4 with swaps; with two waves on a SIMD 148.3 and 151.2), and for the finest tiles, whose steps
+// have no register to split (512x640 8:16, two waves on some SIMDs: 80.0 and 76.3).
+template <class T, int S>
+constexpr bool swap_step() {
+  return T::YM[S] == 32 || (T::SWAPS && T::YM[S] == 16);
+}
+// The same over the lanes of a lane-column; step s pairs lanes that differ by YM[s].
 template <class T, class real, int TW, int S = 0>
 __device__ __forceinline__ void reduce_scatter_y(real (&v)[TW]) {
   if constexpr (S < T::NY) {
     constexpr int h = TW >> (S + 1);
-    if constexpr (h >= 1) {
+    if constexpr (swap_step<T, S>()) {
+      if constexpr (h >= 1) {
+#pragma unroll
+        for (int b = 0; b < h; ++b) v[b] = swap_sum<T::YM[S]>(v[b], v[b + h]);
+      } else {
+        v[0] = swap_sum<T::YM[S]>(v[0], v[0]);
+      }
+    } else if constexpr (h >= 1) {
 #pragma unroll
       for (int b = 0; b < h; ++b) v[b] += lane_xor<T::YM[S]>(v[b + h]);
     } else {
@@ -264,7 +329,12 @@ __device__ __forceinline__ void all_gather_y(real (&v)[TW]) {
     constexpr int h = TW >> (S + 1);
     if constexpr (h >= 1) {
 #pragma unroll
-      for (int b = 0; b < h; ++b) v[b + h] = lane_xor<T::YM[S]>(v[b]);
+      for (int b = 0; b < h; ++b) {
+        if constexpr (swap_step<T, S>())
+          swap_spread<T::YM[S]>(v[b], v[b + h]);
+        else
+          v[b + h] = lane_xor<T::YM[S]>(v[b]);
+      }
     }
     all_gather_y<T, real, TW, S - 1, LAST>(v);
   }
@@ -283,76 +353,141 @@ constexpr int gather_split_y() {
     return 0;
   }
 }
-// register offset of a lane along y: lane bit YM[s] set <-> register bit log2(TW >> (s+1))
-template <class T, int TW, int S = 0>
+// register offset of a lane along y: lane bit s of the lane-column set <-> register bit log2(TW >> (s+1)).  OWN: of the columns it
+// owns after a reduction; else of the columns in its tile, for which the pairs of a swap step agree.
+template <class T, int TW, bool OWN, int S = 0>
 __device__ __forceinline__ int reg_xor_y(int q) {
-  if constexpr (S < T::NY)
-    return ((q & T::YM[S]) ? (TW >> (S + 1)) : 0) | reg_xor_y<T, TW, S + 1>(q);
-  else
+  if constexpr (S < T::NY) {
+    constexpr int bit = T::YM[S] == 7 ? 4 : T::YM[S];  // (xor 7: the lane-column's part of the mask)
+    const int mine = !OWN && swap_step<T, S>() ? 0 : (q & bit) ? (TW >> (S + 1)) : 0;
+    return mine | reg_xor_y<T, TW, OWN, S + 1>(q);
+  } else {
     return 0;
+  }
 }
+
+// How factors and scalings of the rows go round: moves between lanes; both through LDS; factors by moves, scalings through LDS
+enum Gather { kLanesOnly, kRowsInLds, kScalingsInLds };
 
 // An iteration alternates between two kinds of code: long runs of independent per-entry arithmetic, and the
 // short dependent chains between them (exchange steps of a reduction, reciprocal, gather of the result) on
 // which the next run waits.  A wave raises its priority for the chains, so that the SIMD issues their few
 // instructions ahead of another wave's long run instead of behind it: with equal priorities the waves of a
 // SIMD fell into step and stalled together (measured: 11-16 % of the fp32 loop, 1-2 % of the double one).
+// A wave alone on its SIMD has nobody to be ahead of, and every instruction of its own counts (LONE: 512x512 2:4 31.0 us a call
+// with the six instructions of an iteration, 28.1 without; with two waves on a SIMD 52.0 and 55.5).
+template <bool LONE = false>
 __device__ __forceinline__ void chain_phase(bool on) {
+  if constexpr (LONE) return;
   if (on)
     __builtin_amdgcn_s_setprio(1);
   else
     __builtin_amdgcn_s_setprio(0);
 }
 
-// One iteration of Algorithm 1 (lines 3-6) on the register tile of this lane.  The row scalings are folded
-// into the tile as they are found (kap holds kappa_ij U_i), so an entry costs one multiply with its column
-// scaling, and only the scalings of the rows this lane owns are kept as numbers (Uown, for the potentials at
-// the end).  `floor_` bounds the sums from below (keeps the scalings finite on degenerate input).  STORE
-// keeps the capped entries of the row pass for the column pass; otherwise they are recomputed from an
-// opaque copy of V (for tiles too large to hold twice: without the copy the compiler keeps the row pass's
-// values alive and spills them).
+// One iteration of Algorithm 1 (lines 3-6) in double on the register tile of this lane.  Every entry costs a multiply with its
+// column scaling; where the row scalings are is the FORM:
+//   kKeep: kap stays as it is.  x holds kappa_ij U_i when an iteration begins, the capped entries after the row pass, and is
+//     formed anew from kap at the end.  So the state is the scalings alone, which RepeatCheck relies on, and no rounding
+//     accumulates in the tile.  U: the scalings of all rows of the tile.  The row sums need no floor of their own: the
+//     multiplies with the column scalings are multiply-adds, so that every entry is at least the floor; the column sums
+//     begin with it.  (Two instructions and two links of the dependent chain less than a maximum behind each sum.)
+//   kFold: the row scalings are folded into kap as they are found, U holds the owned rows only; x takes the capped entries.
+//     32-wide large tiles: gathering U besides the factors through LDS made their loop 3 % slower.
+//   kRecompute: the same for tiles too large to be held twice (no x): the capped entries are recomputed in the column pass
+//     from an opaque copy of V (without the copy the compiler keeps the row pass's values alive and spills them).
+// `floor_` bounds the sums from below (keeps the scalings finite on degenerate input).
 // ADAPT (early exit): `frozen` lanes apply factors of exactly 1 (their block has stopped; its state no longer
 // changes), and the largest |factor - 1| among the rows and columns this lane owns is returned.
-// RUN: order_run() of the tiling.
-template <class T, bool STORE, bool LDS_GATHER = false, bool ADAPT = false, int RUN = 0, class real, int TH, int TW, int OR>
-__device__ __forceinline__ real dykstra_iteration(real (&kap)[TH][TW], real (&Uown)[OR], real (&V)[TW], real Nd,
-                                                  real floor_, real* xr = nullptr, int rx = 0, bool frozen = false) {
-  real worst = 0;
+// RUN: order_run() of the tiling.  LONE: no other wave shares the SIMD (chain_phase).
+struct NoTile {};
+enum Form { kRecompute, kFold, kKeep };
+template <class T, Form FORM, Gather GATHER = kLanesOnly, bool ADAPT = false, int RUN = 0, bool LONE = false, class Tile, int TH, int TW, int NU>
+__device__ __forceinline__ double dykstra_iteration(double (&kap)[TH][TW], Tile& x, double (&U)[NU], double (&V)[TW],
+                                                    double (&Vown)[owned(TW, T::NY)], double Nd,
+                                                    double floor_, double* xr = nullptr, int rx = 0,
+                                                    bool frozen = false) {
+  constexpr bool KEEP = FORM == kKeep, STORE = FORM != kRecompute;
+  double worst = 0;
   constexpr int OWN_R = owned(TH, T::NX), OWN_C = owned(TW, T::NY);
-  static_assert(OR == OWN_R, "one scaling per owned row");
-  real e[STORE ? TH : 1][STORE ? TW : 1];
-  real R[TH], C[TW];
+  static_assert(NU == (KEEP ? TH : OWN_R), "scalings of every row, or of the owned ones");
+  // Where no lane multiplies a scaling of another's row, the factors that go round are 1 / row sum, without their N: the column
+  // sums then come out divided by N, and their reciprocals are the column factors.  (Not on the small tiles: M = 4 on the
+  // large ones is the only block without lanes to exchange with.)
+  constexpr bool BARE = KEEP && (GATHER != kLanesOnly || OWN_R == TH);
+  double R[TH], C[TW];
   // projection onto C1 (line 3) of the plan capped by the previous iteration
+  if constexpr (KEEP && RUN == 0) {
+    constexpr bool PAIRS = T::NY == 3;
+    // (column by column: the scalings of the owned columns are there before the gathered ones)
 #pragma unroll
-  for (int a = 0; a < TH; ++a) {
-    real s = 0, leaf[RUN ? TW : 1];
+    for (int b = 0; b < TW; ++b)
 #pragma unroll
-    for (int b = 0; b < TW; ++b) {
-      const real ev = clamp01(kap[a][b] * V[b]);
-      if constexpr (STORE) e[a][b] = ev;
-      if constexpr (RUN > 0)
-        leaf[b] = ev;
-      else
-        s = b == 0 ? ev : s + ev;  // (0 + x is not a no-op for the compiler: it would keep the add)
+      for (int a = 0; a < TH; ++a) {
+        x[a][b] = clamp01(fma(x[a][b], V[b], floor_));
+        if constexpr (!PAIRS) R[a] = b == 0 ? x[a][b] : R[a] + x[a][b];  // (0 + x is not a no-op for the compiler)
+      }
+    if constexpr (PAIRS) {
+      // in pairs: a shorter chain, and the same sum whatever the lane's offset of the columns is (see LoneTiling)
+#pragma unroll
+      for (int a = 0; a < TH; ++a) {
+        double s[TW];
+#pragma unroll
+        for (int b = 0; b < TW; ++b) s[b] = x[a][b];
+#pragma unroll
+        for (int h = 1; h < TW; h *= 2)
+#pragma unroll
+          for (int b = 0; b < TW; b += 2 * h) s[b] += s[b + h];
+        R[a] = s[0];
+      }
     }
-    if constexpr (RUN > 0) s = row_tree<RUN>(leaf);
-    R[a] = s;
+  } else {
+#pragma unroll
+    for (int a = 0; a < TH; ++a) {
+      double s = 0, leaf[RUN ? TW : 1];
+#pragma unroll
+      for (int b = 0; b < TW; ++b) {
+        double ev;
+        if constexpr (KEEP)
+          ev = clamp01(fma(x[a][b], V[b], floor_));
+        else
+          ev = clamp01(kap[a][b] * V[b]);
+        if constexpr (STORE) x[a][b] = ev;
+        if constexpr (RUN > 0)
+          leaf[b] = ev;
+        else
+          s = b == 0 ? ev : s + ev;
+      }
+      if constexpr (RUN > 0) s = row_tree<RUN>(leaf);
+      R[a] = s;
+    }
   }
-  chain_phase(true);
-  reduce_scatter_x<T, real, TH>(R);
+  chain_phase<LONE>(true);
+  reduce_scatter_x<T, double, TH>(R);
 #pragma unroll
   for (int a = 0; a < OWN_R; ++a) {
-    R[a] = Nd * fast_rcp(vmax(R[a], floor_));
-    if constexpr (ADAPT) {
-      worst = vmax(worst, fabs(R[a] - real(1)));
-      R[a] = frozen ? real(1) : R[a];
+    const double s = KEEP ? R[a] : vmax(R[a], floor_);  // (KEEP: every entry is at least the floor)
+    double factor;
+    if constexpr (BARE) {
+      R[a] = fast_rcp(s);
+      factor = Nd * R[a];
+    } else if constexpr (KEEP) {
+      factor = fast_div(Nd, s);
+    } else {
+      factor = Nd * fast_rcp(s);
     }
-    Uown[a] *= R[a];
+    if constexpr (ADAPT) {
+      worst = vmax(worst, fabs(factor - 1.0));
+      factor = frozen ? 1.0 : factor;
+    }
+    U[a] *= factor;
+    if constexpr (!BARE) R[a] = factor;
   }
-  if constexpr (LDS_GATHER) {
-    // the owner of a row leaves its scaling in LDS and every lane of the lane-row picks up all TH of them:
+  if constexpr (GATHER == kRowsInLds) {
+    // the owner of a row leaves its factor in LDS and every lane of the lane-row picks up all TH of them:
     // LDS instructions instead of vector-ALU moves.  The lanes of a wave run in lock step, so the exchange
     // needs no barrier, only that the compiler keeps the accesses where they are.
+    static_assert(!KEEP, "");
 #pragma unroll
     for (int a = 0; a < OWN_R; ++a) xr[a ^ rx] = R[a];
     asm volatile("" ::: "memory");
@@ -360,11 +495,21 @@ __device__ __forceinline__ real dykstra_iteration(real (&kap)[TH][TW], real (&Uo
     for (int a = OWN_R; a < TH; ++a) R[a] = xr[a ^ rx];  // (the owned rows' factors are at hand)
     asm volatile("" ::: "memory");
   } else {
-    all_gather_x<T, real, TH>(R);
+    all_gather_x<T, double, TH>(R);
+    if constexpr (GATHER == kScalingsInLds) {
+      // the factors on DPP moves, for the column pass waits for them; the scalings, which it does not need, through LDS
+      static_assert(KEEP && OWN_R % 2 == 0, "pairs of rows");
+#pragma unroll
+      for (int a = 0; a < OWN_R; a += 2) *reinterpret_cast<double2*>(xr + (a ^ rx)) = make_double2(U[a], U[a + 1]);
+      asm volatile("" ::: "memory");
+    } else if constexpr (KEEP) {
+#pragma unroll
+      for (int a = OWN_R; a < TH; ++a) U[a] *= R[a];
+    }
   }
-  chain_phase(false);
+  chain_phase<LONE>(false);
   // projection onto C2 (line 4)
-  real Vc[TW];
+  double Vc[TW];
 #pragma unroll
   for (int b = 0; b < TW; ++b) {
     Vc[b] = V[b];
@@ -374,56 +519,76 @@ __device__ __forceinline__ real dykstra_iteration(real (&kap)[TH][TW], real (&Uo
   for (int b = 0; b < TW; ++b) {
     const auto entry = [&](int a) {
       if constexpr (STORE)
-        return e[a][b];
+        return x[a][b];
       else
         return clamp01(kap[a][b] * Vc[b]);
     };
-    real s = 0;
+    double s = KEEP ? floor_ : 0;
     if constexpr (RUN == 0) {
 #pragma unroll
-      for (int a = 0; a < TH; ++a) s = vfma(entry(a), R[a], s);
+      for (int a = 0; a < TH; ++a) s = fma(entry(a), R[a], s);
     } else {
       static_assert(TH <= 2 * RUN, "at most two runs");
 #pragma unroll
       for (int a0 = 0; a0 < TH; a0 += RUN) {
-        real run = 0;
+        double run = KEEP ? floor_ : 0;
 #pragma unroll
         for (int k = 0; k < RUN; ++k) {
           const int a = a0 + (k ^ (b % RUN));
-          run = vfma(entry(a), R[a], run);
+          run = fma(entry(a), R[a], run);
         }
         s = a0 == 0 ? run : s + run;
       }
     }
     C[b] = s;
   }
-  chain_phase(true);
-  reduce_scatter_y<T, real, TW>(C);
+  if constexpr (GATHER == kScalingsInLds) {
+#pragma unroll
+    for (int a = OWN_R; a < TH; a += 2) {
+      const double2 u = *reinterpret_cast<const double2*>(xr + (a ^ rx));
+      U[a] = u.x;
+      U[a + 1] = u.y;
+    }
+    asm volatile("" ::: "memory");
+  }
+  chain_phase<LONE>(true);
+  reduce_scatter_y<T, double, TW>(C);
 #pragma unroll
   for (int b = 0; b < OWN_C; ++b) {
-    C[b] = Nd * fast_rcp(vmax(C[b], floor_));
+    // (KEEP: the floor is the addend the column sum begins with)
+    if constexpr (BARE)
+      C[b] = fast_rcp(C[b]);
+    else if constexpr (KEEP)
+      C[b] = fast_div(Nd, C[b]);
+    else
+      C[b] = Nd * fast_rcp(vmax(C[b], floor_));
     if constexpr (ADAPT) {
-      worst = vmax(worst, fabs(C[b] - real(1)));
-      C[b] = frozen ? real(1) : C[b];
+      worst = vmax(worst, fabs(C[b] - 1.0));
+      C[b] = frozen ? 1.0 : C[b];
     }
   }
   // the owner of a column applies its factor and the new scalings (not the factors) are gathered: every lane
   // would have formed the same products
 #pragma unroll
-  for (int b = 0; b < OWN_C; ++b) V[b] *= C[b];
+  for (int b = 0; b < OWN_C; ++b) V[b] = Vown[b] *= C[b];
   // the steps of the gather down to the last one that goes through the LDS crossbar are issued before the
   // rescaling of the tile, the rest after it: the tile's multiplies cover the latency of those moves
   constexpr int SPLIT = gather_split_y<T, TW>();
-  all_gather_y<T, real, TW, T::NY - 1, SPLIT>(V);
-  chain_phase(false);
+  all_gather_y<T, double, TW, T::NY - 1, SPLIT>(V);
+  chain_phase<LONE>(false);
   if constexpr (SPLIT > 0) __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
   for (int a = 0; a < TH; ++a)
 #pragma unroll
-    for (int b = 0; b < TW; ++b) kap[a][b] *= R[a];
+    for (int b = 0; b < TW; ++b) {
+      if constexpr (KEEP)
+        x[a][b] = kap[a][b] * U[a];
+      else
+        kap[a][b] *= R[a];
+    }
   if constexpr (SPLIT > 0) {
     __builtin_amdgcn_sched_barrier(0);
-    all_gather_y<T, real, TW, SPLIT - 1>(V);
+    all_gather_y<T, double, TW, SPLIT - 1>(V);
   }
   // lines 5-6 (cap and dual update) are the clamp at the top of the next pass
   return worst;
@@ -454,7 +619,7 @@ __device__ __forceinline__ float max_as_is(float a, float b) {
 // ADAPT as in dykstra_iteration.
 template <class T, bool LDS_GATHER = false, bool ADAPT = false, int TH, int TW>
 __device__ __forceinline__ float dykstra_iteration_f32(const float (&kap)[TH][TW], float (&U)[TH], float (&V)[TW],
-                                                       float Nf, float2* xr = nullptr, int rx = 0,
+                                                       float (&Vown)[owned(TW, T::NY)], float Nf, float2* xr = nullptr, int rx = 0,
                                                        bool frozen = false) {
   constexpr int OWN_R = owned(TH, T::NX), OWN_C = owned(TW, T::NY);
   float worst = 0;
@@ -515,7 +680,7 @@ __device__ __forceinline__ float dykstra_iteration_f32(const float (&kap)[TH][TW
     }
   }
 #pragma unroll
-  for (int b = 0; b < OWN_C; ++b) V[b] *= C[b];
+  for (int b = 0; b < OWN_C; ++b) V[b] = Vown[b] *= C[b];
   all_gather_y<T, float, TW>(V);
   chain_phase(false);
   return worst;
@@ -527,35 +692,46 @@ __device__ __forceinline__ float dykstra_iteration_f32(const float (&kap)[TH][TW
 // Once a block has converged to the precision of its numbers its last bits run through a short cycle: of 512 blocks of 16:32
 // with fp32 iterations 57 % end in one of period 2, 14 % of 1, 4, 6 or 8, hardly any in a period that does not divide 24.  So
 // the state is compared every kChunk iterations with one 8, 16 or 24 iterations old.
-// Measured, us a call before and with it (fp32 iterations): 32:64 8192x28672 T = 500 10 405 / 2919 (a block runs about 60
-// iterations), 16:32 4096x14336 T = 300 1627 / 1399 (two blocks per wave, which go on until both repeat), 15:16 4672x5264 T = 500
-// 1186 / 526; where no block repeats itself before T the looks cost less than 1 %.
-// That state is kept in LDS: the kernels whose register budget is that of their loop have none to spare for it.
-template <class real, int OWN_R, int OWN_C>
+// IN_LDS: that state is kept in LDS (`space`), for the kernels whose register budget is that of their loop; small launches, where a
+// wave has its SIMD to itself and waits for every LDS access, keep it in registers.
+template <class real, int OWN_R, int OWN_C, bool IN_LDS>
 struct RepeatCheck {
-  using Seen = real[OWN_R + OWN_C][kWave];
-  Seen& seen;  // the scalings every lane owns, after `noted` iterations
+  using Space = std::conditional_t<IN_LDS, real[OWN_R + OWN_C][kWave], char>;
+  using Seen = std::conditional_t<IN_LDS, Space&, real[OWN_R + OWN_C]>;  // the scalings this lane owns, `noted` iterations done
+  Seen seen;
   int lane, noted;
+  static __device__ __forceinline__ RepeatCheck make(Space& space, int lane) {
+    if constexpr (IN_LDS)
+      return {space, lane, 0};
+    else
+      return {{}, lane, 0};
+  }
+  __device__ __forceinline__ real& at(int k) {
+    if constexpr (IN_LDS)
+      return seen[k][lane];
+    else
+      return seen[k];
+  }
   static __device__ __forceinline__ bool differ(float x, float y) { return __float_as_uint(x) != __float_as_uint(y); }
   static __device__ __forceinline__ bool differ(double x, double y) { return __double_as_longlong(x) != __double_as_longlong(y); }
   template <int NU, int NV>
   __device__ __forceinline__ void note(const real (&U)[NU], const real (&V)[NV], int t) {
 #pragma unroll
-    for (int a = 0; a < OWN_R; ++a) seen[a][lane] = U[a];
+    for (int a = 0; a < OWN_R; ++a) at(a) = U[a];
 #pragma unroll
-    for (int b = 0; b < OWN_C; ++b) seen[OWN_R + b][lane] = V[b];
+    for (int b = 0; b < OWN_C; ++b) at(OWN_R + b) = V[b];
     noted = t;
   }
   // t iterations are done: the number that are as good as done
   template <int NU, int NV>
   __device__ __forceinline__ int look(const real (&U)[NU], const real (&V)[NV], int t, int T) {
     // (the whole state only if a first scaling of every lane is as it was)
-    bool changed = __any(differ(U[0], seen[0][lane]));
+    bool changed = __any(differ(U[0], at(0)));
     if (!changed) {
 #pragma unroll
-      for (int a = 1; a < OWN_R; ++a) changed |= differ(U[a], seen[a][lane]);
+      for (int a = 1; a < OWN_R; ++a) changed |= differ(U[a], at(a));
 #pragma unroll
-      for (int b = 0; b < OWN_C; ++b) changed |= differ(V[b], seen[OWN_R + b][lane]);
+      for (int b = 0; b < OWN_C; ++b) changed |= differ(V[b], at(OWN_R + b));
       changed = __any(changed);
     }
     const int d = t - noted;
@@ -582,10 +758,10 @@ template <int M, bool FAST, bool ADAPT = false, int TILES = kLargeTiles>
 struct DykstraLaunch {
   // with the early exit the waves of a launch run for very different times; one-wave workgroups let the
   // dispatcher refill every wave slot as it frees (a four-wave workgroup holds its slots until its slowest wave).
-  // So do the 64-wide fp32 waves, one block each, which leave when their block repeats itself (8192x28672, T = 500: 3.15 ms, in
-  // four-wave workgroups 3.67; for two and more blocks per wave there is no clear difference).
+  // The 64-wide fp32 waves, one block each, leave when their block repeats itself: two to a workgroup (8192x28672 student, T =
+  // 500: 2.91 ms, one 2.94, four 3.25; 4096x4096 normal, which does not repeat, T = 300: 563 us, 610, 581).
   // The small tiles carry the rounding behind the iterations, whose steps synchronise one wave at a time.
-  static constexpr int kWavesPerGroup = (ADAPT || (FAST && M == 64) || TILES != kLargeTiles) ? 1 : 4;
+  static constexpr int kWavesPerGroup = (ADAPT || TILES != kLargeTiles) ? 1 : FAST && M == 64 ? 2 : 4;
   static constexpr int kThreads = kWavesPerGroup * kWave;
   // Waves per SIMD the register budget is set for.  Double: the loop holds twice the state of the fp32 one, two waves of up
   // to 256 registers.  FAST: the more waves, the nearer the issue of plain fp32 instructions comes to its limit (1.13 ns
@@ -604,10 +780,11 @@ struct DykstraLaunch {
 // lives in one wave from its tile load to its mask, the potentials that Algorithm 2 starts from go to LDS instead of the
 // workspace, and Algorithm 2 runs behind; no further kernel follows.  (4096 x 32, 16:32, T = 300: 120 us a call with a sort
 // across the lanes and the scan of its result, 106 with round_blocks.)
-template <int M, bool FAST, bool ZERO_T = false, int TILES = kLargeTiles, bool ADAPT = false>
+// LONE: for small tiles in a launch that gives a SIMD no second wave.
+template <int M, bool FAST, bool ZERO_T = false, int TILES = kLargeTiles, bool ADAPT = false, bool LONE = false>
 __global__ __launch_bounds__((DykstraLaunch<M, FAST, ADAPT, TILES>::kThreads), (DykstraLaunch<M, FAST, ADAPT, TILES>::kWavesPerSimd)) void dykstra_sort_kernel(
     Batch batch) {
-  using T = Tiling<M, TILES>;
+  using T = std::conditional_t<LONE, LoneTiling<Tiling<M, TILES>>, Tiling<M, TILES>>;
   constexpr bool SMALL = TILES != kLargeTiles;
   const int which = find_problem(batch, blockIdx.x);
   const DevProblem p = batch.e[which].p;
@@ -618,7 +795,7 @@ __global__ __launch_bounds__((DykstraLaunch<M, FAST, ADAPT, TILES>::kThreads), (
                 E = TH * TW, SHX = ilog2(TH) - T::NX, WPG = DykstraLaunch<M, FAST, ADAPT, TILES>::kWavesPerGroup;
   const int lane = threadIdx.x & (kWave - 1), wave_in_group = threadIdx.x / kWave;
   const int64_t wave = (int64_t)group * WPG + wave_in_group;
-  const int q = lane % LPB, gx = q % GX, gy = q / GX;
+  const int q = lane % LPB, gx = q % GX, gy = q / GX, gc = column_lane<T>(gx, q);
   int64_t blk = wave * BPW + lane / LPB;
   const bool active = blk < p.nblocks;
   if (!active) blk = p.nblocks - 1;  // idle lanes shadow the last block and write nothing
@@ -631,8 +808,9 @@ __global__ __launch_bounds__((DykstraLaunch<M, FAST, ADAPT, TILES>::kThreads), (
   // kernel takes its own opaque copy of the lane offsets, so that element addresses are recomputed where
   // they are needed instead of being kept in registers across the iteration loop.
   constexpr int RUN = FAST ? 0 : order_run<M, TILES>();
-  const int rx_own = shift_lane(gx, SHX), ry_own = reg_xor_y<T, TW>(q);
-  const int rx = RUN ? rx_own ^ ry_own : rx_own, ry = RUN ? rx : ry_own;
+  const int rx_own = shift_lane(gx, SHX), ry_tile = reg_xor_y<T, TW, false>(q);
+  const int rx = RUN ? rx_own ^ ry_tile : rx_own, ry = RUN ? rx : ry_tile;
+  const int ry_own = ry ^ ry_tile ^ reg_xor_y<T, TW, true>(q);  // offset of the columns this lane owns
   auto fresh = [](int v) {
     asm volatile("" : "+v"(v));
     return v;
@@ -648,7 +826,7 @@ __global__ __launch_bounds__((DykstraLaunch<M, FAST, ADAPT, TILES>::kThreads), (
 #pragma unroll
     for (int a = 0; a < TH; ++a) ri[a] = gy * TH + (a ^ rxp);
 #pragma unroll
-    for (int b = 0; b < TW; ++b) cj[b] = column_in_block<M, TILES>(gx, b ^ ryp);
+    for (int b = 0; b < TW; ++b) cj[b] = column_in_block<M, TILES>(gc, b ^ ryp);
     return tile_addr<TH, TW>(p, r0, c0, ri, cj);
   };
   // rows of a tile loaded at a time: the fp32 variant lives in half the registers (two halves); the 8 x 8
@@ -685,7 +863,7 @@ __global__ __launch_bounds__((DykstraLaunch<M, FAST, ADAPT, TILES>::kThreads), (
           for (int a = 0; a < NA; ++a)
 #pragma unroll
             for (int b = 0; b < TW; ++b) {
-              const int ri = gy * TH + ((A0 + a) ^ rx0), cj = column_in_block<M, TILES>(gx, b ^ ry0);
+              const int ri = gy * TH + ((A0 + a) ^ rx0), cj = column_in_block<M, TILES>(gc, b ^ ry0);
               plan_out[(r0 + mat_row(ri, cj)) * p.cols + c0 + mat_col(ri, cj)] = exp(tau_eff * (double)imp[a][b]);
               __builtin_amdgcn_sched_barrier(0);
             }
@@ -705,7 +883,7 @@ __global__ __launch_bounds__((DykstraLaunch<M, FAST, ADAPT, TILES>::kThreads), (
           const double K = tau_eff * (double)imp[a][b];  // K of Algorithm 1 line 1
           if constexpr (ZERO_T) {
             // no iterations: the greedy order is descending K itself
-            const int ri = gy * TH + ((A0 + a) ^ rx0), cj = column_in_block<M, TILES>(gx, b ^ ry0);
+            const int ri = gy * TH + ((A0 + a) ^ rx0), cj = column_in_block<M, TILES>(gc, b ^ ry0);
             if constexpr (!kPotentials) c[(A0 + a) * TW + b] = scan_key_of_k(K, mat_row(ri, cj) * M + mat_col(ri, cj));
           } else {
             kap[A0 + a][b] = K;
@@ -754,41 +932,69 @@ __global__ __launch_bounds__((DykstraLaunch<M, FAST, ADAPT, TILES>::kThreads), (
     // FAST: the tile of the fp32 phase, fl32(kap U V)
     float kap32[FAST ? TH : 1][FAST ? TW : 1];
     {
-      double Uown[OWN_R], V[TW];
+      // whether the tile is held twice (see dykstra_iteration)
+      constexpr Form kForm = FAST || !T::STORE_E ? kRecompute : T::KEEP ? kKeep : kFold;
+      constexpr bool kKept = kForm == kKeep;
+      double Uown[kKept ? TH : OWN_R], V[TW], Vown[OWN_C];
 #pragma unroll
-      for (int a = 0; a < OWN_R; ++a) Uown[a] = 1.0;
+      for (double& u : Uown) u = 1.0;
 #pragma unroll
       for (int b = 0; b < TW; ++b) V[b] = 1.0;
+#pragma unroll
+      for (double& v : Vown) v = 1.0;
       if constexpr (FAST) {
         // the entries are recomputed in the column pass: this phase must fit the registers of the fp32 loop
         const int t_double = p.T < kWarmIters ? p.T : kWarmIters;
+        NoTile once;
         for (int t = 0; t < t_double; ++t) {
-          double worst = dykstra_iteration<T, false, false, ADAPT>(kap, Uown, V, Nd, 1e-300, (double*)nullptr, 0, frozen);
+          double worst = dykstra_iteration<T, kRecompute, kLanesOnly, ADAPT>(kap, once, Uown, V, Vown, Nd, 1e-300, nullptr, 0, frozen);
           if constexpr (ADAPT) {
             if ((t + 1) % TSENOR_ADAPTIVE_CHECK_EVERY == 0) freeze_if(block_max<LPB>(worst) <= p.tol, t + 1);
           }
         }
       } else {
-        // In the 32- and 64-wide kernels the row scalings of an iteration are gathered through LDS (measured
+        // In the 32- and 64-wide kernels the row factors of an iteration are gathered through LDS (measured
         // ~1 % faster than DPP moves; doing the same for the column scalings as well exposed a second LDS round
-        // trip and gained nothing): lane-row r of the wave keeps its 8 row scalings at xrows[wave][r][0..8)
-        constexpr bool kLdsGather = M >= 32 && !SMALL;
-        __shared__ double xrows[kLdsGather ? WPG : 1][kLdsGather ? kWave >> T::NX : 1][TH];
-        double* xr = kLdsGather ? &xrows[wave_in_group][lane >> T::NX][0] : nullptr;
+        // trip and gained nothing), in the 8- and 16-wide ones the row scalings (two respectively eight multiplies fewer):
+        // lane-row r of the wave keeps those of its rows at xrows[wave][r][0..TH)
+        constexpr Gather kGather = SMALL || LPB == 1 ? kLanesOnly : kForm == kKeep ? kScalingsInLds : kRowsInLds;
+        using Tile = std::conditional_t<kForm != kRecompute, double[TH][TW], NoTile>;
+        constexpr bool kLds = kGather != kLanesOnly;
+        __shared__ __align__(16) double xrows[kLds ? WPG : 1][kLds ? kWave >> T::NX : 1][TH];
+        double* xr = kLds ? &xrows[wave_in_group][lane >> T::NX][0] : nullptr;
+        Tile x;
+        if constexpr (kKept) {
+#pragma unroll
+          for (int a = 0; a < TH; ++a)
+#pragma unroll
+            for (int b = 0; b < TW; ++b) x[a][b] = kap[a][b];
+        }
+        const auto iterate = [&]() {
+          return dykstra_iteration<T, kForm, kGather, ADAPT, RUN, LONE>(kap, x, Uown, V, Vown, Nd, 1e-300, xr, rx, frozen);
+        };
         if constexpr (ADAPT) {
           // iteration count as a bound: every TSENOR_ADAPTIVE_CHECK_EVERY-th iteration the largest |factor - 1|
           // of the block is compared with the tolerance; a block that passes is frozen, the wave leaves when
           // all its blocks are
           for (int t = 0; t < p.T; ++t) {
-            double worst =
-                dykstra_iteration<T, T::STORE_E, kLdsGather, true, RUN>(kap, Uown, V, Nd, 1e-300, xr, rx, frozen);
+            const double worst = iterate();
             if ((t + 1) % TSENOR_ADAPTIVE_CHECK_EVERY == 0) {
               freeze_if(block_max<LPB>(worst) <= p.tol, t + 1);
               if (__all(frozen)) break;
             }
           }
+        } else if constexpr (kKept) {
+          using Repeat = RepeatCheck<double, OWN_R, OWN_C, !SMALL>;
+          __shared__ typename Repeat::Space seen[WPG];
+          Repeat repeat = Repeat::make(seen[wave_in_group], lane);
+          repeat.note(Uown, Vown, 0);
+          for (int t = 0; t < p.T;) {
+            const int stop = (p.T - t > kRepeatWindow) ? t + kRepeatWindow : p.T;
+            for (; t < stop; ++t) iterate();
+            t = repeat.look(Uown, Vown, t, p.T);
+          }
         } else {
-          for (int t = 0; t < p.T; ++t) dykstra_iteration<T, T::STORE_E, kLdsGather, false, RUN>(kap, Uown, V, Nd, 1e-300, xr, rx);
+          for (int t = 0; t < p.T; ++t) iterate();
         }
       }
       if constexpr (FAST) {
@@ -804,7 +1010,7 @@ __global__ __launch_bounds__((DykstraLaunch<M, FAST, ADAPT, TILES>::kThreads), (
 #pragma unroll
       for (int a = 0; a < OWN_R; ++a) u_own[a] = Uown[a];
 #pragma unroll
-      for (int b = 0; b < OWN_C; ++b) v_own[b] = V[b];
+      for (int b = 0; b < OWN_C; ++b) v_own[b] = Vown[b];
     }
     double lu_own[OWN_R], lv_own[OWN_C];  // (set by take_logs)
     auto take_logs = [&]() {
@@ -827,7 +1033,7 @@ __global__ __launch_bounds__((DykstraLaunch<M, FAST, ADAPT, TILES>::kThreads), (
       if (p.T > kWarmIters && !(ADAPT && __all(frozen))) {
         // fp32 phase: kap32 = fl32(kap U V) for the double scalings U V reached so far, and fp32 scalings
         // U32, V32 relative to them.  kap is not kept: a rebuild reloads the importance.
-        float U32[TH], V32[TW];
+        float U32[TH], V32[TW], V32own[OWN_C];
         const float Nf = (float)p.N;
         const float hi = __builtin_ldexpf(1.0f, kDriftBits), lo = __builtin_ldexpf(1.0f, -kDriftBits);
         auto rebuild = [&]() {
@@ -859,6 +1065,8 @@ __global__ __launch_bounds__((DykstraLaunch<M, FAST, ADAPT, TILES>::kThreads), (
           for (int a = 0; a < TH; ++a) U32[a] = 1.0f;
 #pragma unroll
           for (int b = 0; b < TW; ++b) V32[b] = 1.0f;
+#pragma unroll
+          for (float& v : V32own) v = 1.0f;
         };
         auto fold = [&]() {
 #pragma unroll
@@ -869,7 +1077,7 @@ __global__ __launch_bounds__((DykstraLaunch<M, FAST, ADAPT, TILES>::kThreads), (
           }
 #pragma unroll
           for (int b = 0; b < OWN_C; ++b) {
-            const double v = v_own[b] * (double)V32[b];
+            const double v = v_own[b] * (double)V32own[b];
             v_exp[b] += __builtin_amdgcn_frexp_exp(v);
             v_own[b] = __builtin_amdgcn_frexp_mant(v);
           }
@@ -878,11 +1086,13 @@ __global__ __launch_bounds__((DykstraLaunch<M, FAST, ADAPT, TILES>::kThreads), (
         for (int a = 0; a < TH; ++a) U32[a] = 1.0f;
 #pragma unroll
         for (int b = 0; b < TW; ++b) V32[b] = 1.0f;
+#pragma unroll
+        for (float& v : V32own) v = 1.0f;
         bool all_frozen = false;
-        using Repeat = RepeatCheck<float, OWN_R, OWN_C>;
-        __shared__ typename Repeat::Seen seen[ADAPT ? 1 : WPG];
-        Repeat repeat{seen[ADAPT ? 0 : wave_in_group], lane};
-        if constexpr (!ADAPT) repeat.note(U32, V32, kWarmIters);
+        using Repeat = RepeatCheck<float, OWN_R, OWN_C, true>;
+        __shared__ typename Repeat::Space seen[ADAPT ? 1 : WPG];
+        Repeat repeat = Repeat::make(seen[ADAPT ? 0 : wave_in_group], lane);
+        if constexpr (!ADAPT) repeat.note(U32, V32own, kWarmIters);
         for (int t = kWarmIters; t < p.T && !all_frozen;) {
           const int stop = (p.T - t > kChunk) ? t + kChunk : p.T;
           // (in fp32 the exchange also carries the updated scalings, which pays wherever a block spans lanes:
@@ -893,29 +1103,29 @@ __global__ __launch_bounds__((DykstraLaunch<M, FAST, ADAPT, TILES>::kThreads), (
           if constexpr (ADAPT) {
             for (; t < stop && !all_frozen; ++t) {
               const float worst =
-                  dykstra_iteration_f32<T, kLdsGather32, true>(kap32, U32, V32, Nf, xr, rx, frozen);
+                  dykstra_iteration_f32<T, kLdsGather32, true>(kap32, U32, V32, V32own, Nf, xr, rx, frozen);
               if ((t + 1) % TSENOR_ADAPTIVE_CHECK_EVERY == 0) {
                 freeze_if(block_max<LPB>((double)worst) <= p.tol, t + 1);
                 all_frozen = __all(frozen);
               }
             }
           } else {
-            for (; t < stop; ++t) dykstra_iteration_f32<T, kLdsGather32>(kap32, U32, V32, Nf, xr, rx);
+            for (; t < stop; ++t) dykstra_iteration_f32<T, kLdsGather32>(kap32, U32, V32, V32own, Nf, xr, rx);
           }
-          if constexpr (!ADAPT) t = repeat.look(U32, V32, t, p.T);
+          if constexpr (!ADAPT) t = repeat.look(U32, V32own, t, p.T);
           // (the scalings of the rows and columns this lane owns: every row and column has its owner, and the
           // other copies of a scaling are the same number)
           float mxs = U32[0], mns = U32[0];
 #pragma unroll
           for (int a = 1; a < OWN_R; ++a) mxs = fmaxf(mxs, U32[a]), mns = fminf(mns, U32[a]);
 #pragma unroll
-          for (int b = 0; b < OWN_C; ++b) mxs = fmaxf(mxs, V32[b]), mns = fminf(mns, V32[b]);
+          for (int b = 0; b < OWN_C; ++b) mxs = fmaxf(mxs, V32own[b]), mns = fminf(mns, V32own[b]);
           // wave-uniform: fold the fp32 scalings into the double ones when any lane's have drifted
           if (t < p.T && __any(!(mxs < hi && mns > lo))) {
             fold();
             take_logs();
             rebuild();
-            if constexpr (!ADAPT) repeat.note(U32, V32, t);
+            if constexpr (!ADAPT) repeat.note(U32, V32own, t);
           }
         }
         fold();
@@ -929,7 +1139,7 @@ __global__ __launch_bounds__((DykstraLaunch<M, FAST, ADAPT, TILES>::kThreads), (
     }
 
     take_logs();
-    const int rx2 = fresh(rx), ry2 = fresh(ry);
+    const int rx2 = fresh(rx), ry2 = fresh(ry), ryo = fresh(ry_own);
     if constexpr (kPotentials) {
       // every row and column of the block has an owner among its lanes (on fine tiles several, with the same values)
       if constexpr (SMALL) {
@@ -940,7 +1150,7 @@ __global__ __launch_bounds__((DykstraLaunch<M, FAST, ADAPT, TILES>::kThreads), (
           lds.minus_largest[lane / LPB][ri] = -(double)mrow[a];
         }
 #pragma unroll
-        for (int b = 0; b < OWN_C; ++b) pot[p.transpose ? 0 : 1][lane / LPB][column_in_block<M, TILES>(gx, b ^ ry2)] = lv_own[b];
+        for (int b = 0; b < OWN_C; ++b) pot[p.transpose ? 0 : 1][lane / LPB][column_in_block<M, TILES>(gc, b ^ ryo)] = lv_own[b];
       } else {
         if (group == 0 && threadIdx.x == 0) batch.e[which].hdr->tau_eff = tau_eff;
         if (active) {
@@ -953,7 +1163,7 @@ __global__ __launch_bounds__((DykstraLaunch<M, FAST, ADAPT, TILES>::kThreads), (
             largest[ri] = mrow[a];
           }
 #pragma unroll
-          for (int b = 0; b < OWN_C; ++b) out->v[column_in_block<M, TILES>(gx, b ^ ry2)] = lv_own[b];
+          for (int b = 0; b < OWN_C; ++b) out->v[column_in_block<M, TILES>(gc, b ^ ryo)] = lv_own[b];
         }
       }
       if (active && q == 0 && batch.e[which].iters_done_out) batch.e[which].iters_done_out[blk] = iters_done;
@@ -985,7 +1195,7 @@ __global__ __launch_bounds__((DykstraLaunch<M, FAST, ADAPT, TILES>::kThreads), (
           for (int a = 0; a < NA; ++a)
 #pragma unroll
             for (int b = 0; b < TW; ++b) {
-              const int ri = gy * TH + ((A0 + a) ^ rx2), cj = column_in_block<M, TILES>(gx, b ^ ry2);
+              const int ri = gy * TH + ((A0 + a) ^ rx2), cj = column_in_block<M, TILES>(gc, b ^ ry2);
               plan_out[(r0 + mat_row(ri, cj)) * p.cols + c0 + mat_col(ri, cj)] = exp(fmin(log_plan(imp[a][b], A0 + a, b), 0.0));
               __builtin_amdgcn_sched_barrier(0);
             }
@@ -1001,7 +1211,7 @@ __global__ __launch_bounds__((DykstraLaunch<M, FAST, ADAPT, TILES>::kThreads), (
           for (int a = 0; a < NA; ++a)
 #pragma unroll
             for (int b = 0; b < TW; ++b) {
-              const int ri = gy * TH + ((A0 + a) ^ rx2), cj = column_in_block<M, TILES>(gx, b ^ ry2);
+              const int ri = gy * TH + ((A0 + a) ^ rx2), cj = column_in_block<M, TILES>(gc, b ^ ry2);
               c[(A0 + a) * TW + b] = scan_key(log_plan(imp[a][b], A0 + a, b), mat_row(ri, cj) * M + mat_col(ri, cj));
             }
         };

@@ -55,6 +55,46 @@ __device__ __forceinline__ float lane_xor(float v) {
   return __int_as_float(lane_xor_i32<MASK>(__float_as_int(v)));
 }
 
+// v_permlane16_swap / v_permlane32_swap: every lane whose bit BIT is clear gives its `b` for the `a` of the lane that differs from
+// it in that bit.  Afterwards the two lanes of a pair hold, in `a` and `b`, the two values of one of the registers each.
+template <int BIT>
+__device__ __forceinline__ void lane_swap(double& a, double& b) {
+  static_assert(BIT == 16 || BIT == 32, "");
+  const unsigned al = (unsigned)__double2loint(a), ah = (unsigned)__double2hiint(a);
+  const unsigned bl = (unsigned)__double2loint(b), bh = (unsigned)__double2hiint(b);
+  if constexpr (BIT == 16) {
+    const auto l = __builtin_amdgcn_permlane16_swap(al, bl, false, false), h = __builtin_amdgcn_permlane16_swap(ah, bh, false, false);
+    a = __hiloint2double((int)h[0], (int)l[0]), b = __hiloint2double((int)h[1], (int)l[1]);
+  } else {
+    const auto l = __builtin_amdgcn_permlane32_swap(al, bl, false, false), h = __builtin_amdgcn_permlane32_swap(ah, bh, false, false);
+    a = __hiloint2double((int)h[0], (int)l[0]), b = __hiloint2double((int)h[1], (int)l[1]);
+  }
+}
+template <int BIT>
+__device__ __forceinline__ void lane_swap(float& a, float& b) {
+  static_assert(BIT == 16 || BIT == 32, "");
+  const unsigned x = __float_as_uint(a), y = __float_as_uint(b);
+  if constexpr (BIT == 16) {
+    const auto r = __builtin_amdgcn_permlane16_swap(x, y, false, false);
+    a = __uint_as_float(r[0]), b = __uint_as_float(r[1]);
+  } else {
+    const auto r = __builtin_amdgcn_permlane32_swap(x, y, false, false);
+    a = __uint_as_float(r[0]), b = __uint_as_float(r[1]);
+  }
+}
+// sum over the two lanes of a pair: of `a` in the lane with the bit clear, of `b` in the other (a == b: in both)
+template <int BIT, class real>
+__device__ __forceinline__ real swap_sum(real a, real b) {
+  lane_swap<BIT>(a, b);
+  return a + b;
+}
+// the values of the two lanes of a pair in both of them: that of the lane with the bit clear in `a`, the other's in `b`
+template <int BIT, class real>
+__device__ __forceinline__ void swap_spread(real& a, real& b) {
+  b = a;
+  lane_swap<BIT>(a, b);
+}
+
 // max over the LPB consecutive lanes that hold a block (LPB a power of two)
 template <int LPB, int STEP = 1>
 __device__ __forceinline__ double block_max(double v) {

@@ -57,13 +57,15 @@ constexpr bool small_tiles_win(int M, bool fp32, bool adaptive, int64_t nblocks)
 }
 
 // Below this many blocks in a matrix a 16 x 16 block adds in the order of the finest tiles, and in a launch of up to two waves
-// per SIMD it has a wave of its own: 52 instead of 98 vector instructions in the chain of an iteration, four times the waves.
-// Whole calls, T = 300 (us, finest / small tiles): 256 blocks 67 / 88, 1024 blocks 73 / 89, 1536 blocks 81 / 90, 2304 blocks
-// 104 / 90 (from three waves on a SIMD on, issue decides).  Fused matrices of 1024 blocks (us, finest tiles / small tiles in
-// their order): 2 85 / 94, 3 107 / 89, 4 131 / 90, 16 436 / 243.  (Single matrices above the line keep the small tiles' own
-// order, whose loop is 1-5 % faster.)
-constexpr int64_t finest_tiles_below_blocks(int M) { return M == 16 ? 1800 : 0; }
+// per SIMD it has a wave of its own: 51 instead of 103 vector instructions in the chain of an iteration, four times the waves.
+// Whole calls, T = 300 (us, finest / small tiles): 1024 blocks 53.6 / 75, 1280 blocks 76.3 / 74.8, 1792 blocks 77.0 / 75.0 (from
+// the second wave on a SIMD on).  Fused matrices of 1024 blocks (us, finest tiles / small tiles in their order): 2 85 / 94, 3
+// 107 / 89, 4 131 / 90, 16 436 / 243.
+constexpr int64_t finest_tiles_below_blocks(int M) { return M == 16 ? 1025 : 0; }
 constexpr int64_t kFinestTilesLaunch = 2048;
+
+// SIMDs of the chip: a launch of no more waves gives each of them at most one
+constexpr unsigned kSimds = 1024;
 
 // Below this many blocks in a launch a 64 x 64 block has a workgroup of its own (team.hpp), which iterates in double: one
 // workgroup per CU.  Whole calls, T = 300 (us, team / large tiles in double / with fp32 iterations): 64 blocks 173 / 286 /

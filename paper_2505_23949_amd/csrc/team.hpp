@@ -25,19 +25,6 @@ struct Team {
   static constexpr int XM[4] = {15, 7, 3, 1};
 };
 
-// sum of v over the two lanes of a pair, in both of them (BIT = 16, 32: the lane bit in which they differ)
-template <int BIT>
-__device__ __forceinline__ double pair_sum(double v) {
-  const unsigned lo = (unsigned)__double2loint(v), hi = (unsigned)__double2hiint(v);
-  if constexpr (BIT == 16) {
-    const auto l = __builtin_amdgcn_permlane16_swap(lo, lo, false, false), h = __builtin_amdgcn_permlane16_swap(hi, hi, false, false);
-    return __hiloint2double((int)h[0], (int)l[0]) + __hiloint2double((int)h[1], (int)l[1]);
-  } else {
-    const auto l = __builtin_amdgcn_permlane32_swap(lo, lo, false, false), h = __builtin_amdgcn_permlane32_swap(hi, hi, false, false);
-    return __hiloint2double((int)h[0], (int)l[0]) + __hiloint2double((int)h[1], (int)l[1]);
-  }
-}
-
 template <bool ADAPT>
 __global__ __launch_bounds__(Team::W * kWave, 2) void team_kernel(Batch batch) {
   using T = Team;
@@ -95,7 +82,8 @@ __global__ __launch_bounds__(Team::W * kWave, 2) void team_kernel(Batch batch) {
 #pragma unroll
     for (int a = 0; a < TH; ++a) R[a] = ev[a] = clamp01(kap[a] * V);
     reduce_scatter_x<T, double, TH>(R);
-    R[0] = pair_sum<32>(pair_sum<16>(R[0]));
+    R[0] = swap_sum<16>(R[0], R[0]);
+    R[0] = swap_sum<32>(R[0], R[0]);
     R[0] = Nd * fast_rcp(vmax(R[0], floor_));
     double worst = ADAPT ? fabs(R[0] - 1.0) : 0.0;
     U *= R[0];

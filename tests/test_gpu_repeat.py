@@ -48,3 +48,30 @@ def test_repeated_states(M, tiles, dist):
             assert ran.any()
             for name in ("plan", "mask"):
                 assert torch.equal(got[0][name][ran], got[1][name][ran])
+
+
+@pytest.mark.parametrize("M,shape,count", [(4, (512, 512), 2), (4, (60, 68), 3), (8, (512, 512), 2), (16, (512, 512), 2), (16, (512, 1024), 3),
+                                           (32, (512, 1024), 3)])
+@pytest.mark.parametrize("tol", [0.0, 1e-3])
+def test_waves_alone_on_their_simd(M, shape, count, tol):
+    # one matrix gives every SIMD at most one wave, a batch of them more (the second case: neither does): other exchanges
+    # between the lanes, the same additions
+    import torch
+
+    from paper_2505_23949_amd import binding as b
+
+    dev = torch.device("cuda:0")
+    rng = np.random.Generator(np.random.Philox(70 + M))
+    Ws = [torch.from_numpy(rng.standard_normal(shape, dtype=np.float32)).to(dev) for _ in range(count)]
+    for flags in (0, b.TSENOR_FLAG_COLS_FIRST):
+        print(f"[case] lone waves M={M} {shape} x {count} tol={tol} flags={flags}", flush=True)
+        single = [b.solve(W, M // 2, M, 0.01, 90, tau_mode=b.TSENOR_TAU_REL_MATRIX_MAX, want_plan=True, tol=tol, flags=flags) for W in Ws]
+        masks = [torch.zeros(shape, dtype=torch.uint8, device=dev) for _ in Ws]
+        plans = [torch.zeros(shape, dtype=torch.float64, device=dev) for _ in Ws]
+        problems = [b.make_problem(W, M // 2, M, 0.01, 90, mask=m, plan_out=p, tau_mode=b.TSENOR_TAU_REL_MATRIX_MAX, tol=tol, flags=flags)
+                    for W, m, p in zip(Ws, masks, plans)]
+        b.tsenor_mask_batched(problems, torch.empty(b.tsenor_workspace_bytes(problems), dtype=torch.uint8, device=dev))
+        torch.cuda.synchronize()
+        for s, m, p in zip(single, masks, plans):
+            assert torch.equal(s["mask"], m)
+            assert torch.equal(s["plan"], p)

@@ -95,11 +95,18 @@ __device__ __forceinline__ void swap_spread(real& a, real& b) {
   lane_swap<BIT>(a, b);
 }
 
-// max over the LPB consecutive lanes that hold a block (LPB a power of two)
+// Max over the LPB consecutive lanes that hold a block (LPB a power of two).  Every step pairs groups whose lanes hold the same
+// number already, so any lane of the other group will do: moves by DPP up to 16 lanes, swaps beyond, none through the LDS crossbar.
 template <int LPB, int STEP = 1>
 __device__ __forceinline__ double block_max(double v) {
   if constexpr (STEP < LPB) {
-    v = fmax(v, lane_xor<STEP>(v));
+    if constexpr (STEP >= 16) {
+      double a = v, b = v;
+      lane_swap<STEP>(a, b);
+      v = fmax(a, b);
+    } else {
+      v = fmax(v, lane_xor<STEP == 4 ? 7 : STEP == 8 ? 15 : STEP>(v));
+    }
     return block_max<LPB, STEP * 2>(v);
   } else {
     return v;

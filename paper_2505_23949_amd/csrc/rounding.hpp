@@ -94,6 +94,13 @@ __device__ __forceinline__ SwapBest best_candidate(mask_t cand, const float* row
   return best;
 }
 
+// the mask of lane `lane`, the same for the whole wave
+__device__ __forceinline__ unsigned int mask_of_lane(unsigned int v, int lane) { return (unsigned)__builtin_amdgcn_readlane((int)v, lane); }
+__device__ __forceinline__ unsigned long long mask_of_lane(unsigned long long v, int lane) {
+  return (unsigned long long)(unsigned)__builtin_amdgcn_readlane((int)v, lane) |
+         (unsigned long long)(unsigned)__builtin_amdgcn_readlane((int)(v >> 32), lane) << 32;
+}
+
 template <int M, int STEP = 1>
 __device__ __forceinline__ double group_sum(double v) {
   if constexpr (STEP < M) {
@@ -156,9 +163,15 @@ __device__ __forceinline__ void local_search_and_write(const DevProblem& p, cons
 
   int rounds = 0, nonpos = 0;
   bool open = any_short;  // this block may still take swaps
+  // A wave of one block keeps the masks in the registers of the rows' and columns' lanes and reads those of row i and column j
+  // from there; several blocks to a wave have theirs in LDS.
+  constexpr bool kInLanes = LPB == kWave;
+  mask_t Srow = part ? lds.rowm[g][qm] : (mask_t)0, Scol = part ? lds.colm[g][qm] : (mask_t)0;
   while (any_short) {
-    const mask_t Srow = part ? lds.rowm[g][qm] : (mask_t)0;
-    const mask_t Scol = part ? lds.colm[g][qm] : (mask_t)0;
+    if constexpr (!kInLanes) {
+      Srow = part ? lds.rowm[g][qm] : (mask_t)0;
+      Scol = part ? lds.colm[g][qm] : (mask_t)0;
+    }
     const unsigned long long rb = __ballot(part && popc(Srow) < p.N) & gmask;
     const unsigned long long cb = __ballot(part && popc(Scol) < p.N) & gmask;
     if (rb == 0 || cb == 0 || (p.strict && rounds >= p.L)) open = false;
@@ -167,27 +180,47 @@ __device__ __forceinline__ void local_search_and_write(const DevProblem& p, cons
     const int i = open ? (__ffsll((long long)rb) - 1 - g * LPB) : 0;
     const int j = open ? (__ffsll((long long)cb) - 1 - g * LPB) : 0;
     // line 11 for i' = this lane: columns j' with S[i'][j'] = 1 and S[i][j'] = 0, provided S[i'][j] = 0
-    mask_t cand = Srow & ~lds.rowm[g][i];
-    if (!open || !part || ((lds.colm[g][j] >> qm) & 1)) cand = 0;
+    mask_t row_i, col_j;
+    if constexpr (kInLanes)
+      row_i = mask_of_lane(Srow, i), col_j = mask_of_lane(Scol, j);
+    else
+      row_i = lds.rowm[g][i], col_j = lds.colm[g][j];
+    mask_t cand = Srow & ~row_i;
+    if (!open || !part || ((col_j >> qm) & 1)) cand = 0;
     const SwapBest best =
         best_candidate(cand, &lds.imp[g][i * LD], &lds.imp[g][qm * LD], (double)lds.imp[g][qm * LD + j]);
     // the best of the block: lanes are rows i', so among equal scores the first lane has the lowest flat index
     const double top = block_max<M>(best.score);
     const unsigned long long winners = __ballot(cand != 0 && best.score == top) & gmask;
     const int winner = winners ? __ffsll((long long)winners) - 1 : 0;
-    const int ip = winner - g * LPB, jp = __shfl(best.column, winner, kWave);
+    const int ip = winner - g * LPB;
+    const int jp = kInLanes ? __builtin_amdgcn_readlane(best.column, winner) : __shfl(best.column, winner, kWave);
     if (open) ++rounds;
     const bool apply = winners != 0 && (!p.strict || top > 0.0);
     if (open && !apply) open = false;  // nothing changes any more for this block
+    // line 13: remove (i', j'), insert (i', j) and (i, j')
+    if constexpr (kInLanes) {
+      if (apply) {
+        if (ql == ip) Srow = (Srow & ~(one << jp)) | (one << j);
+        if (ql == i) Srow |= one << jp;
+        if (ql == jp) Scol = (Scol & ~(one << ip)) | (one << i);
+        if (ql == j) Scol |= one << ip;
+        if (!(top > 0.0)) ++nonpos;
+      }
+      continue;
+    }
     wave_sync();
     if (apply && ql == 0) {
-      // line 13: remove (i', j'), insert (i', j) and (i, j')
       lds.rowm[g][ip] = (lds.rowm[g][ip] & ~(one << jp)) | (one << j);
       lds.rowm[g][i] |= one << jp;
       lds.colm[g][jp] = (lds.colm[g][jp] & ~(one << ip)) | (one << i);
       lds.colm[g][j] |= one << ip;
       if (!(top > 0.0)) ++nonpos;
     }
+    wave_sync();
+  }
+  if (kInLanes && any_short) {
+    if (part) lds.rowm[g][qm] = Srow;
     wave_sync();
   }
 

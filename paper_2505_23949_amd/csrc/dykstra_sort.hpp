@@ -389,14 +389,14 @@ __device__ __forceinline__ void chain_phase(bool on) {
 // column scaling; where the row scalings are is the FORM:
 //   kKeep: kap stays as it is.  x holds kappa_ij U_i when an iteration begins, the capped entries after the row pass, and is
 //     formed anew from kap at the end.  So the state is the scalings alone, which RepeatCheck relies on, and no rounding
-//     accumulates in the tile.  U: the scalings of all rows of the tile.  The row sums need no floor of their own: the
-//     multiplies with the column scalings are multiply-adds, so that every entry is at least the floor; the column sums
-//     begin with it.  (Two instructions and two links of the dependent chain less than a maximum behind each sum.)
+//     accumulates in the tile.  U: the scalings of all rows of the tile.
 //   kFold: the row scalings are folded into kap as they are found, U holds the owned rows only; x takes the capped entries.
 //     32-wide large tiles: gathering U besides the factors through LDS made their loop 3 % slower.
 //   kRecompute: the same for tiles too large to be held twice (no x): the capped entries are recomputed in the column pass
 //     from an opaque copy of V (without the copy the compiler keeps the row pass's values alive and spills them).
-// `floor_` bounds the sums from below (keeps the scalings finite on degenerate input).
+// `floor_` bounds the sums from below (keeps the scalings finite on degenerate input): the multiplies with the column scalings
+// are multiply-adds, so that every entry is at least the floor, and the column sums begin with it.  (An instruction and a link
+// of the dependent chain less than a maximum behind each sum.)
 // ADAPT (early exit): `frozen` lanes apply factors of exactly 1 (their block has stopped; its state no longer
 // changes), and the largest |factor - 1| among the rows and columns this lane owns is returned.
 // RUN: order_run() of the tiling.  LONE: no other wave shares the SIMD (chain_phase).
@@ -451,7 +451,7 @@ __device__ __forceinline__ double dykstra_iteration(double (&kap)[TH][TW], Tile&
         if constexpr (KEEP)
           ev = clamp01(fma(x[a][b], V[b], floor_));
         else
-          ev = clamp01(kap[a][b] * V[b]);
+          ev = clamp01(fma(kap[a][b], V[b], floor_));
         if constexpr (STORE) x[a][b] = ev;
         if constexpr (RUN > 0)
           leaf[b] = ev;
@@ -466,15 +466,12 @@ __device__ __forceinline__ double dykstra_iteration(double (&kap)[TH][TW], Tile&
   reduce_scatter_x<T, double, TH>(R);
 #pragma unroll
   for (int a = 0; a < OWN_R; ++a) {
-    const double s = KEEP ? R[a] : vmax(R[a], floor_);  // (KEEP: every entry is at least the floor)
-    double factor;
+    double factor;  // (every entry is at least the floor, so that the sums are)
     if constexpr (BARE) {
-      R[a] = fast_rcp(s);
+      R[a] = fast_rcp(R[a]);
       factor = Nd * R[a];
-    } else if constexpr (KEEP) {
-      factor = fast_div(Nd, s);
     } else {
-      factor = Nd * fast_rcp(s);
+      factor = fast_div(Nd, R[a]);
     }
     if constexpr (ADAPT) {
       worst = vmax(worst, fabs(factor - 1.0));
@@ -521,9 +518,9 @@ __device__ __forceinline__ double dykstra_iteration(double (&kap)[TH][TW], Tile&
       if constexpr (STORE)
         return x[a][b];
       else
-        return clamp01(kap[a][b] * Vc[b]);
+        return clamp01(fma(kap[a][b], Vc[b], floor_));
     };
-    double s = KEEP ? floor_ : 0;
+    double s = floor_;
     if constexpr (RUN == 0) {
 #pragma unroll
       for (int a = 0; a < TH; ++a) s = fma(entry(a), R[a], s);
@@ -531,7 +528,7 @@ __device__ __forceinline__ double dykstra_iteration(double (&kap)[TH][TW], Tile&
       static_assert(TH <= 2 * RUN, "at most two runs");
 #pragma unroll
       for (int a0 = 0; a0 < TH; a0 += RUN) {
-        double run = KEEP ? floor_ : 0;
+        double run = floor_;
 #pragma unroll
         for (int k = 0; k < RUN; ++k) {
           const int a = a0 + (k ^ (b % RUN));
@@ -555,13 +552,7 @@ __device__ __forceinline__ double dykstra_iteration(double (&kap)[TH][TW], Tile&
   reduce_scatter_y<T, double, TW>(C);
 #pragma unroll
   for (int b = 0; b < OWN_C; ++b) {
-    // (KEEP: the floor is the addend the column sum begins with)
-    if constexpr (BARE)
-      C[b] = fast_rcp(C[b]);
-    else if constexpr (KEEP)
-      C[b] = fast_div(Nd, C[b]);
-    else
-      C[b] = Nd * fast_rcp(vmax(C[b], floor_));
+    C[b] = BARE ? fast_rcp(C[b]) : fast_div(Nd, C[b]);  // (the floor is the addend the column sum begins with)
     if constexpr (ADAPT) {
       worst = vmax(worst, fabs(C[b] - 1.0));
       C[b] = frozen ? 1.0 : C[b];

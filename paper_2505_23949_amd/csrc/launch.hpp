@@ -58,10 +58,11 @@ constexpr bool small_tiles_win(int M, bool fp32, bool adaptive, int64_t nblocks)
 
 // Below this many blocks in a matrix a 16 x 16 block adds in the order of the finest tiles, and in a launch of up to two waves
 // per SIMD it has a wave of its own: 51 instead of 103 vector instructions in the chain of an iteration, four times the waves.
-// Whole calls, T = 300 (us, finest / small tiles): 1024 blocks 53.6 / 75, 1280 blocks 76.3 / 74.8, 1792 blocks 77.0 / 75.0 (from
-// the second wave on a SIMD on).  Fused matrices of 1024 blocks (us, finest tiles / small tiles in their order): 2 85 / 94, 3
-// 107 / 89, 4 131 / 90, 16 436 / 243.
-constexpr int64_t finest_tiles_below_blocks(int M) { return M == 16 ? 1025 : 0; }
+// Whole calls, T = 300 (us, finest / small tiles): 256 blocks 45 / 70, 1024 blocks 53.6 / 75, 1280 blocks 76.3 / 74.7, 1792 blocks
+// 77.9 / 75.3; where blocks repeat a state (RepeatCheck) a wave of its own stops with its block: 1376 blocks of 12:16, Wanda-style,
+// T = 200 60.5 / 64.3.  From three waves on a SIMD on, issue decides (2304 blocks 104 / 90).  Fused matrices of 1024 blocks (us,
+// finest tiles / small tiles in their order): 2 85 / 94, 3 107 / 89, 4 131 / 90, 16 436 / 243.
+constexpr int64_t finest_tiles_below_blocks(int M) { return M == 16 ? 1800 : 0; }
 constexpr int64_t kFinestTilesLaunch = 2048;
 
 // SIMDs of the chip: a launch of no more waves gives each of them at most one

@@ -80,18 +80,18 @@ __global__ __launch_bounds__(Team::W * kWave, 2) void team_kernel(Batch batch) {
     // projection onto C1 (line 3) of the plan capped by the previous iteration
     double ev[TH], R[TH];
 #pragma unroll
-    for (int a = 0; a < TH; ++a) R[a] = ev[a] = clamp01(kap[a] * V);
+    for (int a = 0; a < TH; ++a) R[a] = ev[a] = clamp01(fma(kap[a], V, floor_));
     reduce_scatter_x<T, double, TH>(R);
     R[0] = swap_sum<16>(R[0], R[0]);
     R[0] = swap_sum<32>(R[0], R[0]);
-    R[0] = Nd * fast_rcp(vmax(R[0], floor_));
+    R[0] = fast_div(Nd, R[0]);
     double worst = ADAPT ? fabs(R[0] - 1.0) : 0.0;
     U *= R[0];
     all_gather_x<T, double, TH>(R);
     // projection onto C2 (line 4)
-    double C = ev[0] * R[0];
+    double C = floor_;
 #pragma unroll
-    for (int a = 1; a < TH; ++a) C = fma(ev[a], R[a], C);
+    for (int a = 0; a < TH; ++a) C = fma(ev[a], R[a], C);
     part[t & 1][wave][lane] = C;
 #pragma unroll
     for (int a = 0; a < TH; ++a) kap[a] *= R[a];
@@ -103,7 +103,7 @@ __global__ __launch_bounds__(Team::W * kWave, 2) void team_kernel(Batch batch) {
     for (int h = 1; h < T::W; h *= 2)  // (neighbours first, as the large tiles' lane-columns do)
 #pragma unroll
       for (int k = 0; k < T::W; k += 2 * h) s[k] += s[k + h];
-    C = Nd * fast_rcp(vmax(s[0], floor_));
+    C = fast_div(Nd, s[0]);
     V *= C;
     // lines 5-6 (cap and dual update) are the clamp at the top of the next pass
     if constexpr (ADAPT) {

@@ -376,7 +376,7 @@ enum Gather { kLanesOnly, kRowsInLds, kScalingsInLds };
 // SIMD fell into step and stalled together (measured: 11-16 % of the fp32 loop, 1-2 % of the double one).
 // A wave alone on its SIMD has nobody to be ahead of, and every instruction of its own counts (LONE: 512x512 2:4 31.0 us a call
 // with the six instructions of an iteration, 28.1 without; with two waves on a SIMD 52.0 and 55.5).
-template <bool LONE = false>
+template <bool LONE>
 __device__ __forceinline__ void chain_phase(bool on) {
   if constexpr (LONE) return;
   if (on)
@@ -608,11 +608,14 @@ __device__ __forceinline__ float max_as_is(float a, float b) {
 // sum and the multiply-add of the column sum per entry, all at the full fp32 rate.  A scaling grows by at most
 // 2^10 per iteration (keeps everything finite on degenerate input).
 // ADAPT as in dykstra_iteration.
-template <class T, bool LDS_GATHER = false, bool ADAPT = false, int TH, int TW>
+template <class T, bool LDS_GATHER = false, bool ADAPT = false, bool LONE = false, int TH, int TW>
 __device__ __forceinline__ float dykstra_iteration_f32(const float (&kap)[TH][TW], float (&U)[TH], float (&V)[TW],
                                                        float (&Vown)[owned(TW, T::NY)], float Nf, float2* xr = nullptr, int rx = 0,
                                                        bool frozen = false) {
   constexpr int OWN_R = owned(TH, T::NX), OWN_C = owned(TW, T::NY);
+  // (the factors of a lane's own rows without their N, as in dykstra_iteration: four of 92 instructions of 4 x 4 blocks)
+  constexpr bool BARE = OWN_R == TH;
+  [[maybe_unused]] const float cap = 1024.0f / Nf;
   float worst = 0;
   float e[TH][TW], R[TH], C[TW];
 #pragma unroll
@@ -623,14 +626,15 @@ __device__ __forceinline__ float dykstra_iteration_f32(const float (&kap)[TH][TW
       R[a] = b == 0 ? e[a][b] : R[a] + e[a][b];
     }
   }
-  chain_phase(true);
+  chain_phase<LONE>(true);
   reduce_scatter_x<T, float, TH>(R);
 #pragma unroll
   for (int a = 0; a < OWN_R; ++a) {
-    R[a] = fminf(Nf * fast_rcp(R[a]), 1024.0f);  // factor of an owned row (a NaN from an empty row gives the cap)
+    // factor of an owned row (a NaN from an empty row gives the cap)
+    R[a] = BARE ? fminf(fast_rcp(R[a]), cap) : fminf(Nf * fast_rcp(R[a]), 1024.0f);
     if constexpr (ADAPT) {
-      worst = fmaxf(worst, fabsf(R[a] - 1.0f));
-      R[a] = frozen ? 1.0f : R[a];
+      worst = fmaxf(worst, fabsf((BARE ? Nf * R[a] : R[a]) - 1.0f));
+      if constexpr (!BARE) R[a] = frozen ? 1.0f : R[a];
     }
   }
   if constexpr (LDS_GATHER) {
@@ -652,19 +656,19 @@ __device__ __forceinline__ float dykstra_iteration_f32(const float (&kap)[TH][TW
   } else {
     all_gather_x<T, float, TH>(R);
 #pragma unroll
-    for (int a = 0; a < TH; ++a) U[a] *= R[a];
+    for (int a = 0; a < TH; ++a) U[a] *= !BARE ? R[a] : ADAPT && frozen ? 1.0f : Nf * R[a];
   }
-  chain_phase(false);
+  chain_phase<LONE>(false);
 #pragma unroll
   for (int b = 0; b < TW; ++b) {
 #pragma unroll
     for (int a = 0; a < TH; ++a) C[b] = a == 0 ? e[a][b] * R[a] : fmaf(e[a][b], R[a], C[b]);
   }
-  chain_phase(true);
+  chain_phase<LONE>(true);
   reduce_scatter_y<T, float, TW>(C);
 #pragma unroll
   for (int b = 0; b < OWN_C; ++b) {
-    C[b] = Nf * fast_rcp(max_as_is(C[b], Nf * 0x1p-10f));
+    C[b] = BARE ? fast_rcp(max_as_is(C[b], 0x1p-10f)) : Nf * fast_rcp(max_as_is(C[b], Nf * 0x1p-10f));
     if constexpr (ADAPT) {
       worst = fmaxf(worst, fabsf(C[b] - 1.0f));
       C[b] = frozen ? 1.0f : C[b];
@@ -673,7 +677,7 @@ __device__ __forceinline__ float dykstra_iteration_f32(const float (&kap)[TH][TW
 #pragma unroll
   for (int b = 0; b < OWN_C; ++b) V[b] = Vown[b] *= C[b];
   all_gather_y<T, float, TW>(V);
-  chain_phase(false);
+  chain_phase<LONE>(false);
   return worst;
 }
 
@@ -745,14 +749,15 @@ __device__ __forceinline__ void row_chunks(F& f) {
   }
 }
 
-template <int M, bool FAST, bool ADAPT = false, int TILES = kLargeTiles>
+template <int M, bool FAST, bool ADAPT = false, int TILES = kLargeTiles, bool LONE = false>
 struct DykstraLaunch {
   // with the early exit the waves of a launch run for very different times; one-wave workgroups let the
   // dispatcher refill every wave slot as it frees (a four-wave workgroup holds its slots until its slowest wave).
   // The 64-wide fp32 waves, one block each, leave when their block repeats itself: two to a workgroup (8192x28672 student, T =
-  // 500: 2.91 ms, one 2.94, four 3.25; 4096x4096 normal, which does not repeat, T = 300: 563 us, 610, 581).
+  // 500: 2.91 ms, one 2.94, four 3.25; 4096x4096 normal, which does not repeat, T = 300: 563 us, 610, 581).  In a launch of one wave per SIMD four, which go to the four of a CU
+  // (2048x2048 normal, T = 300: 285 us, two 302).
   // The small tiles carry the rounding behind the iterations, whose steps synchronise one wave at a time.
-  static constexpr int kWavesPerGroup = (ADAPT || TILES != kLargeTiles) ? 1 : FAST && M == 64 ? 2 : 4;
+  static constexpr int kWavesPerGroup = (ADAPT || TILES != kLargeTiles) ? 1 : FAST && M == 64 && !LONE ? 2 : 4;
   static constexpr int kThreads = kWavesPerGroup * kWave;
   // Waves per SIMD the register budget is set for.  Double: the loop holds twice the state of the fp32 one, two waves of up
   // to 256 registers.  FAST: the more waves, the nearer the issue of plain fp32 instructions comes to its limit (1.13 ns
@@ -771,11 +776,11 @@ struct DykstraLaunch {
 // lives in one wave from its tile load to its mask, the potentials that Algorithm 2 starts from go to LDS instead of the
 // workspace, and Algorithm 2 runs behind; no further kernel follows.  (4096 x 32, 16:32, T = 300: 120 us a call with a sort
 // across the lanes and the scan of its result, 106 with round_blocks.)
-// LONE: for small tiles in a launch that gives a SIMD no second wave.
+// LONE: for a launch that gives a SIMD no second wave.
 template <int M, bool FAST, bool ZERO_T = false, int TILES = kLargeTiles, bool ADAPT = false, bool LONE = false>
-__global__ __launch_bounds__((DykstraLaunch<M, FAST, ADAPT, TILES>::kThreads), (DykstraLaunch<M, FAST, ADAPT, TILES>::kWavesPerSimd)) void dykstra_sort_kernel(
+__global__ __launch_bounds__((DykstraLaunch<M, FAST, ADAPT, TILES, LONE>::kThreads), (DykstraLaunch<M, FAST, ADAPT, TILES, LONE>::kWavesPerSimd)) void dykstra_sort_kernel(
     Batch batch) {
-  using T = std::conditional_t<LONE, LoneTiling<Tiling<M, TILES>>, Tiling<M, TILES>>;
+  using T = std::conditional_t<LONE && TILES != kLargeTiles, LoneTiling<Tiling<M, TILES>>, Tiling<M, TILES>>;
   constexpr bool SMALL = TILES != kLargeTiles;
   const int which = find_problem(batch, blockIdx.x);
   const DevProblem p = batch.e[which].p;
@@ -783,7 +788,7 @@ __global__ __launch_bounds__((DykstraLaunch<M, FAST, ADAPT, TILES>::kThreads), (
   double* tau_eff_out = batch.e[which].tau_eff_out;
   const unsigned int group = blockIdx.x - batch.first[which];  // workgroup index within the matrix
   constexpr int GX = 1 << T::NX, GY = 1 << T::NY, TH = M / GY, TW = M / GX, LPB = GX * GY, BPW = kWave / LPB,
-                E = TH * TW, SHX = ilog2(TH) - T::NX, WPG = DykstraLaunch<M, FAST, ADAPT, TILES>::kWavesPerGroup;
+                E = TH * TW, SHX = ilog2(TH) - T::NX, WPG = DykstraLaunch<M, FAST, ADAPT, TILES, LONE>::kWavesPerGroup;
   const int lane = threadIdx.x & (kWave - 1), wave_in_group = threadIdx.x / kWave;
   const int64_t wave = (int64_t)group * WPG + wave_in_group;
   const int q = lane % LPB, gx = q % GX, gy = q / GX, gc = column_lane<T>(gx, q);
@@ -1101,7 +1106,7 @@ __global__ __launch_bounds__((DykstraLaunch<M, FAST, ADAPT, TILES>::kThreads), (
               }
             }
           } else {
-            for (; t < stop; ++t) dykstra_iteration_f32<T, kLdsGather32>(kap32, U32, V32, V32own, Nf, xr, rx);
+            for (; t < stop; ++t) dykstra_iteration_f32<T, kLdsGather32, false, LONE>(kap32, U32, V32, V32own, Nf, xr, rx);
           }
           if constexpr (!ADAPT) t = repeat.look(U32, V32own, t, p.T);
           // (the scalings of the rows and columns this lane owns: every row and column has its owner, and the

@@ -19,6 +19,15 @@ inline bool assign_groups(Batch& b, int64_t per_group) {
   return true;
 }
 
+// Whether a launch of that many waves on the large tiles gives a SIMD no second one.  Only 64 x 64 blocks (257 to 1024 of them)
+// and 4 x 4 ones come there without a flag: the other sizes have the small tiles for launches like that.
+template <int M>
+constexpr bool kLoneOnLargeTiles = M == 64 || M == 4;
+template <int M>
+bool lone_on_large_tiles(int64_t waves) {
+  return kLoneOnLargeTiles<M> && waves <= (int64_t)kSimds;
+}
+
 template <int M>
 bool launch_block_kernels(Batch& b, const Variant& v, hipStream_t stream, hipEvent_t ev_sorted, hipEvent_t ev_greedy) {
   constexpr int BPW = kWave >> (Tiling<M>::NX + Tiling<M>::NY);
@@ -74,9 +83,15 @@ bool launch_block_kernels(Batch& b, const Variant& v, hipStream_t stream, hipEve
     if (!assign_groups(b, (int64_t)BPW * L::kWavesPerGroup)) return false;
     dykstra_sort_kernel<M, true, false, false, true><<<b.first[b.count], L::kThreads, 0, stream>>>(b);
   } else if (v.fast) {
-    using L = DykstraLaunch<M, true>;
-    if (!assign_groups(b, (int64_t)BPW * L::kWavesPerGroup)) return false;
-    dykstra_sort_kernel<M, true><<<b.first[b.count], L::kThreads, 0, stream>>>(b);
+    if (lone_on_large_tiles<M>(nblocks / BPW)) {
+      using L = DykstraLaunch<M, true, false, kLargeTiles, true>;
+      if (!assign_groups(b, (int64_t)BPW * L::kWavesPerGroup)) return false;
+      dykstra_sort_kernel<M, true, false, kLargeTiles, false, kLoneOnLargeTiles<M>><<<b.first[b.count], L::kThreads, 0, stream>>>(b);
+    } else {
+      using L = DykstraLaunch<M, true>;
+      if (!assign_groups(b, (int64_t)BPW * L::kWavesPerGroup)) return false;
+      dykstra_sort_kernel<M, true><<<b.first[b.count], L::kThreads, 0, stream>>>(b);
+    }
   } else {
     using L = DykstraLaunch<M, false>;
     using LA = DykstraLaunch<M, false, true>;
@@ -88,6 +103,8 @@ bool launch_block_kernels(Batch& b, const Variant& v, hipStream_t stream, hipEve
       if (any_plan) dykstra_sort_kernel<M, false, true><<<b.first[b.count], L::kThreads, 0, stream>>>(b);
     } else if (v.adaptive)
       dykstra_sort_kernel<M, false, false, false, true><<<b.first[b.count], LA::kThreads, 0, stream>>>(b);
+    else if (lone_on_large_tiles<M>(nblocks / BPW))
+      dykstra_sort_kernel<M, false, false, kLargeTiles, false, kLoneOnLargeTiles<M>><<<b.first[b.count], L::kThreads, 0, stream>>>(b);
     else
       dykstra_sort_kernel<M, false><<<b.first[b.count], L::kThreads, 0, stream>>>(b);
   }

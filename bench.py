@@ -55,9 +55,9 @@ def useful_ops_per_entry_iter(M: int, fp32: bool) -> float:
 # (M, layout): the small tiles, the finest ones (a 16 x 16 block per wave) and the team (a 64 x 64 block on eight waves, of
 # which a row counts one) serve small launches.
 LOOP_VALU_PER_WAVE_ITER = {
-    (4, "large"): (108, 1024), (4, "small"): (36, 256), (8, "large"): (104, 1024), (8, "small"): (40, 256),
-    (16, "large"): (176, 2048), (16, "small"): (98, 1024), (16, "finest"): (52, 256),
-    (32, "large"): (164, 2048), (32, "small"): (110, 1024), (64, "large"): (384, 4096), (64, "team"): (95, 512),
+    (4, "large"): (96, 1024), (4, "small"): (35, 256), (8, "large"): (98, 1024), (8, "small"): (41, 256),
+    (16, "large"): (178, 2048), (16, "small"): (103, 1024), (16, "finest"): (51, 256),
+    (32, "large"): (162, 2048), (32, "small"): (107, 1024), (64, "large"): (374, 4096), (64, "team"): (93, 512),
 }
 
 
@@ -65,9 +65,9 @@ def layout_of(M: int, fp32: bool, nblocks: int) -> str:
     """The library's own choice for a single matrix and a fixed count of iterations, mirrored here to pick the row of the
     table above and to say which precision a call iterates in (single precision, if asked for, on the large tiles)."""
     if M == 4:
-        small = nblocks <= 49152 or (not fp32 and 65536 < nblocks <= 114688)
+        small = nblocks <= 49152 or (not fp32 and 65536 < nblocks <= 102400)
     else:
-        small = nblocks <= {8: 8699, 16: 8192 if fp32 else 62000, 32: 2048 if fp32 else 3072, 64: 256}[M]
+        small = nblocks <= {8: 12288, 16: 8192 if fp32 else 62000, 32: 2048 if fp32 else 3072, 64: 256}[M]
     if not small:
         return "large"
     return "team" if M == 64 else "finest" if M == 16 and nblocks < 1800 else "small"
@@ -295,8 +295,15 @@ def bench_matrix(args, name):
             out.update({"tol": tol, "mean_iterations": round(float(done.float().mean()), 1),
                         "kernel_ms": round(dyk_ms, 4)})
             return out, mask
+        # Waves stop once the states of their blocks repeat bit for bit (in double not those of the 32- and 64-wide large tiles), so
+        # the kernel may run fewer than T iterations.  The rate at which it iterates is taken where all of them run: an early
+        # exit whose tolerance no block meets.
+        may_stop = layout_of(w.M, fp32, nblocks) != "team" and (fp32 or w.M < 32 or layout_of(w.M, False, nblocks) != "large")
+        every = binding.make_problem(W, w.N, w.M, w.tau, w.iters, mask=torch.empty_like(mask), col_scale=cs, tau_mode=w.tau_mode,
+                                     flags=fp32_flag if fp32 else 0, tol=1e-300)
+        every_ms = binding.tsenor_mask_ex_profile(every, work, max(3, steps // 2))[1] if w.iters > 0 and may_stop else dyk_ms
         ops = useful_ops_per_entry_iter(w.M, fp32)
-        achieved = ops * entry_iters / (dyk_ms * 1e-3) / 1e12
+        achieved = ops * entry_iters / (every_ms * 1e-3) / 1e12
         peak = PEAK_F32_PLAIN_TLANEOPS if fp32 else PEAK_F64_TLANEOPS
         plain = not (args.rows or args.absolute_tau or args.iters >= 0)
         traffic = recorded_traffic(w.name, fp32) if plain else {"kernel": None, "pass": None}
@@ -304,10 +311,13 @@ def bench_matrix(args, name):
             "bound": "alu", "kernel": f"dykstra_sort_kernel<{w.M}{', fp32 iterations' if fp32 else ''}>",
             "achieved": round(achieved, 3), "peak": round(peak, 3), "unit": "T lane-ops/s",
             "frac": round(achieved / peak, 4), "traffic": traffic["kernel"], "kernel_ms": round(dyk_ms, 4),
+            "kernel_ms_every_iteration": round(every_ms, 4),
             "useful_ops_per_entry_iteration": ops,
             "note": ("bound by vector-ALU issue, not memory. achieved = useful vector operations (a multiply-add is "
-                     "one) x rows x cols x T / kernel time, kernel time from HIP events at the stage boundaries of "
-                     f"{steps} back-to-back passes; peak = "
+                     "one) x rows x cols x T / kernel_ms_every_iteration, the time of the kernel where all T iterations "
+                     "are run (with the early exit at a tolerance that no block meets); kernel_ms, from HIP events at "
+                     f"the stage boundaries of {steps} back-to-back passes, is the time of the calls measured, whose "
+                     "waves stop once their state repeats itself bit for bit; peak = "
                      + ("the rate measured on this chip for plain (unpacked) fp32 multiplies and adds; the published "
                         "157.3 TFLOP/s (78.6 T multiply-adds/s) needs the packed instructions, which are not used"
                         if fp32 else "256 CUs x 4 SIMDs x 16 lanes/clk x 2.4 GHz, the fp64 vector issue rate")
@@ -316,7 +326,7 @@ def bench_matrix(args, name):
             "stage_ms": {n: round(v, 4) for n, v in zip(binding.STAGE_NAMES, stage_ms)},
             "staged_ms_per_step": round(sum(stage_ms), 4),
             "shader_clock_mhz_in_loop": round(clock_mhz, 1),
-            "vs_9op_model": round(NINE_OP_MODEL_LANE_OPS * entry_iters / (dyk_ms * 1e-3) / 1e12 / peak, 4),
+            "vs_9op_model": round(NINE_OP_MODEL_LANE_OPS * entry_iters / (every_ms * 1e-3) / 1e12 / peak, 4),
             "algorithmic_bytes_per_pass": weights * (esize + 1) + (0 if cs is None else 4 * w.cols),
             "pass_traffic_recorded_in_profiles": traffic["pass"],
         }
@@ -334,10 +344,10 @@ def bench_matrix(args, name):
                 per_wave, entries = counted
                 issued = per_wave * (weights / entries) * w.iters
                 roofline["loop_valu_per_wave_iteration"] = per_wave
-                roofline["loop_issue_frac_of_peak_clock"] = round(issued / (1024 * (dyk_ms * 1e-3) * 2.4e9 / 4.0), 4)
+                roofline["loop_issue_frac_of_peak_clock"] = round(issued / (1024 * (every_ms * 1e-3) * 2.4e9 / 4.0), 4)
                 if clock_mhz > 0:
                     roofline["loop_issue_frac_of_held_clock"] = round(
-                        issued / (1024 * (dyk_ms * 1e-3) * clock_mhz * 1e6 / 4.0), 4)
+                        issued / (1024 * (every_ms * 1e-3) * clock_mhz * 1e6 / 4.0), 4)
         out["roofline"] = roofline
         return out, mask
 

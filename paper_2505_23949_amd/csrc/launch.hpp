@@ -32,15 +32,14 @@ struct Variant {
 // `fp32`: the caller asked for single-precision iterations, which only the large tiles have, so they win earlier.  Both
 // sides take their time in steps of whole waves per SIMD (1024 of them), so the lines lie where a step is full.  Whole
 // calls, T = 300 (us, small / large double / large fp32):
-//   M = 32 (a block per wave): 1792 blocks 147 / 159 / 153, 2070 blocks 208 / 221 / 161, 2944 blocks 204 / 228 / 169,
-//     3080 blocks 268 / 230 / 168;
-//   M = 16 (4): 7680 blocks 130 / 152 / 142, 8280 blocks 182 / 222 / 151, 57 344 blocks 797 / 827 / 509, 65 536 blocks
-//     863 / 856 / 529;
-//   M = 8 (4): 8280 blocks 83 / 83 / 85, 9216 blocks 87 / 83 / 85, 10 240 blocks 90 / 84 / 85;
-//   M = 4 (16; the large tiles hold 64): 46 000 blocks 78 / 93 / 85, 49 283 blocks 97 / 93 / 85, 65 536 blocks 100 / 92 / 83,
-//     66 000 blocks 113 / 159 / 94, 106 000 blocks 154 / 166 / 104, 114 920 blocks 179 / 165 / 102.
-// T = 100 puts the lines at the same places; at T = 20 the small tiles stay ahead a little beyond them, by less than 2 us (M = 4,
-// 52 000 blocks 21.0 / 22.1, M = 8, 9000 blocks 21.4 / 23.1), but for M = 16 (65 536 blocks 146 / 152).
+//   M = 32 (a block per wave): 3040 blocks 212 / 230 / 172, 3104 blocks 264 / 229 / 169; for fp32 1792 blocks 147 / - / 153, 2070
+//     blocks 208 / - / 161;
+//   M = 16 (4): 61 440 blocks 848 / 860 / 534, 62 976 blocks 892 / 863 / 539; for fp32 7680 blocks 130 / - / 142, 8280 blocks
+//     182 / - / 151;
+//   M = 8 (4): 8320 blocks 79 / 85 / 85, 11 264 blocks 83 / 87 / 86, 12 288 blocks 85 / 88 / 86, 12 416 blocks 102 / 88 / 86;
+//   M = 4 (16; the large tiles hold 64): 48 128 blocks 82 / 89 / 81, 50 176 blocks 94 / 86 / 80, 65 536 blocks 99 / 87 / 80,
+//     67 584 blocks 113 / 149 / 96, 98 304 blocks 146 / 153 / 100, 102 400 blocks 149 / 149, 114 688 blocks 156 / 150 / 101.
+// T = 20 and T = 100 put the lines at the same places within 2 us, but for M = 16 at T = 20 (65 536 blocks 146 / 152).
 // With the early exit (`adaptive`) a wave runs until the slowest of its blocks stops, and the large tiles put up to four times
 // as many blocks into it, so M <= 8 keeps the small tiles for longer.  T = 300, normal weights, tol 1e-2 and 1e-3 (small /
 // large double / large fp32):
@@ -50,8 +49,8 @@ struct Variant {
 //   M = 16, heavy-tailed: 8600 blocks 54 / - / 57.
 constexpr bool small_tiles_win(int M, bool fp32, bool adaptive, int64_t nblocks) {
   if (M == 4 && adaptive) return nblocks <= (fp32 ? 55000 : 114688);
-  if (M == 4) return nblocks <= 49152 || (!fp32 && nblocks > 65536 && nblocks <= 114688);
-  if (M == 8) return nblocks < (adaptive ? (fp32 ? 12000 : 13000) : 8700);
+  if (M == 4) return nblocks <= 49152 || (!fp32 && nblocks > 65536 && nblocks <= 102400);
+  if (M == 8) return nblocks <= (adaptive ? (fp32 ? 12000 : 13000) : 12288);
   if (M == 16) return nblocks <= (fp32 ? (adaptive ? 9000 : 8192) : 62000);
   return M == 32 && nblocks <= (fp32 ? 2048 : 3072);
 }

@@ -394,9 +394,10 @@ __device__ __forceinline__ void chain_phase(bool on) {
 //     32-wide large tiles: gathering U besides the factors through LDS made their loop 3 % slower.
 //   kRecompute: the same for tiles too large to be held twice (no x): the capped entries are recomputed in the column pass
 //     from an opaque copy of V (without the copy the compiler keeps the row pass's values alive and spills them).
-// `floor_` bounds the sums from below (keeps the scalings finite on degenerate input): the multiplies with the column scalings
-// are multiply-adds, so that every entry is at least the floor, and the column sums begin with it.  (An instruction and a link
-// of the dependent chain less than a maximum behind each sum.)
+// No sum needs a floor.  The first row sum holds the row's largest entry, and with every entry at least e^kMinLogKernel and every
+// row factor at least N/M the first column sum is at least N e^kMinLogKernel, whose reciprocal is finite; later ones see lines
+// that were scaled to N and then changed by factors of at least 1/M on either side.  (A floor as an addend, 1e-300 in every entry,
+// took the place of the smallest entries: with rows that spread over 690 the plan was off by 1e-3, by 1e-7 over 680.)
 // ADAPT (early exit): `frozen` lanes apply factors of exactly 1 (their block has stopped; its state no longer
 // changes), and the largest |factor - 1| among the rows and columns this lane owns is returned.
 // RUN: order_run() of the tiling.  LONE: no other wave shares the SIMD (chain_phase).
@@ -404,8 +405,7 @@ struct NoTile {};
 enum Form { kRecompute, kFold, kKeep };
 template <class T, Form FORM, Gather GATHER = kLanesOnly, bool ADAPT = false, int RUN = 0, bool LONE = false, class Tile, int TH, int TW, int NU>
 __device__ __forceinline__ double dykstra_iteration(double (&kap)[TH][TW], Tile& x, double (&U)[NU], double (&V)[TW],
-                                                    double (&Vown)[owned(TW, T::NY)], double Nd,
-                                                    double floor_, double* xr = nullptr, int rx = 0,
+                                                    double (&Vown)[owned(TW, T::NY)], double Nd, double* xr = nullptr, int rx = 0,
                                                     bool frozen = false) {
   constexpr bool KEEP = FORM == kKeep, STORE = FORM != kRecompute;
   double worst = 0;
@@ -424,7 +424,7 @@ __device__ __forceinline__ double dykstra_iteration(double (&kap)[TH][TW], Tile&
     for (int b = 0; b < TW; ++b)
 #pragma unroll
       for (int a = 0; a < TH; ++a) {
-        x[a][b] = clamp01(fma(x[a][b], V[b], floor_));
+        x[a][b] = clamp01(x[a][b] * V[b]);
         if constexpr (!PAIRS) R[a] = b == 0 ? x[a][b] : R[a] + x[a][b];  // (0 + x is not a no-op for the compiler)
       }
     if constexpr (PAIRS) {
@@ -449,9 +449,9 @@ __device__ __forceinline__ double dykstra_iteration(double (&kap)[TH][TW], Tile&
       for (int b = 0; b < TW; ++b) {
         double ev;
         if constexpr (KEEP)
-          ev = clamp01(fma(x[a][b], V[b], floor_));
+          ev = clamp01(x[a][b] * V[b]);
         else
-          ev = clamp01(fma(kap[a][b], V[b], floor_));
+          ev = clamp01(kap[a][b] * V[b]);
         if constexpr (STORE) x[a][b] = ev;
         if constexpr (RUN > 0)
           leaf[b] = ev;
@@ -466,7 +466,7 @@ __device__ __forceinline__ double dykstra_iteration(double (&kap)[TH][TW], Tile&
   reduce_scatter_x<T, double, TH>(R);
 #pragma unroll
   for (int a = 0; a < OWN_R; ++a) {
-    double factor;  // (every entry is at least the floor, so that the sums are)
+    double factor;
     if constexpr (BARE) {
       R[a] = fast_rcp(R[a]);
       factor = Nd * R[a];
@@ -518,21 +518,21 @@ __device__ __forceinline__ double dykstra_iteration(double (&kap)[TH][TW], Tile&
       if constexpr (STORE)
         return x[a][b];
       else
-        return clamp01(fma(kap[a][b], Vc[b], floor_));
+        return clamp01(kap[a][b] * Vc[b]);
     };
-    double s = floor_;
+    double s = 0;
     if constexpr (RUN == 0) {
 #pragma unroll
-      for (int a = 0; a < TH; ++a) s = fma(entry(a), R[a], s);
+      for (int a = 0; a < TH; ++a) s = a == 0 ? entry(a) * R[a] : fma(entry(a), R[a], s);
     } else {
       static_assert(TH <= 2 * RUN, "at most two runs");
 #pragma unroll
       for (int a0 = 0; a0 < TH; a0 += RUN) {
-        double run = floor_;
+        double run = 0;
 #pragma unroll
         for (int k = 0; k < RUN; ++k) {
           const int a = a0 + (k ^ (b % RUN));
-          run = fma(entry(a), R[a], run);
+          run = k == 0 ? entry(a) * R[a] : fma(entry(a), R[a], run);
         }
         s = a0 == 0 ? run : s + run;
       }
@@ -552,7 +552,7 @@ __device__ __forceinline__ double dykstra_iteration(double (&kap)[TH][TW], Tile&
   reduce_scatter_y<T, double, TW>(C);
 #pragma unroll
   for (int b = 0; b < OWN_C; ++b) {
-    C[b] = BARE ? fast_rcp(C[b]) : fast_div(Nd, C[b]);  // (the floor is the addend the column sum begins with)
+    C[b] = BARE ? fast_rcp(C[b]) : fast_div(Nd, C[b]);
     if constexpr (ADAPT) {
       worst = vmax(worst, fabs(C[b] - 1.0));
       C[b] = frozen ? 1.0 : C[b];
@@ -943,7 +943,7 @@ __global__ __launch_bounds__((DykstraLaunch<M, FAST, ADAPT, TILES, LONE>::kThrea
         const int t_double = p.T < kWarmIters ? p.T : kWarmIters;
         NoTile once;
         for (int t = 0; t < t_double; ++t) {
-          double worst = dykstra_iteration<T, kRecompute, kLanesOnly, ADAPT>(kap, once, Uown, V, Vown, Nd, 1e-300, nullptr, 0, frozen);
+          double worst = dykstra_iteration<T, kRecompute, kLanesOnly, ADAPT>(kap, once, Uown, V, Vown, Nd, nullptr, 0, frozen);
           if constexpr (ADAPT) {
             if ((t + 1) % TSENOR_ADAPTIVE_CHECK_EVERY == 0) freeze_if(block_max<LPB>(worst) <= p.tol, t + 1);
           }
@@ -966,7 +966,7 @@ __global__ __launch_bounds__((DykstraLaunch<M, FAST, ADAPT, TILES, LONE>::kThrea
             for (int b = 0; b < TW; ++b) x[a][b] = kap[a][b];
         }
         const auto iterate = [&]() {
-          return dykstra_iteration<T, kForm, kGather, ADAPT, RUN, LONE>(kap, x, Uown, V, Vown, Nd, 1e-300, xr, rx, frozen);
+          return dykstra_iteration<T, kForm, kGather, ADAPT, RUN, LONE>(kap, x, Uown, V, Vown, Nd, xr, rx, frozen);
         };
         if constexpr (ADAPT) {
           // iteration count as a bound: every TSENOR_ADAPTIVE_CHECK_EVERY-th iteration the largest |factor - 1|

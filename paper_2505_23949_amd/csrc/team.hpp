@@ -72,7 +72,7 @@ __global__ __launch_bounds__(Team::W * kWave, 2) void team_kernel(Batch batch) {
     kap[a] = exp(fmax(kap[a] - (double)mrow[a], kMinLogKernel));
   }
 
-  const double Nd = (double)p.N, floor_ = 1e-300;
+  const double Nd = (double)p.N;
   double U = 1.0, V = 1.0;  // scalings of the owned row (register 0) and of this lane's column
   int iters_done = p.T;
   const long long cycles0 = clock64(), ticks0 = wall_clock64();
@@ -80,7 +80,7 @@ __global__ __launch_bounds__(Team::W * kWave, 2) void team_kernel(Batch batch) {
     // projection onto C1 (line 3) of the plan capped by the previous iteration
     double ev[TH], R[TH];
 #pragma unroll
-    for (int a = 0; a < TH; ++a) R[a] = ev[a] = clamp01(fma(kap[a], V, floor_));
+    for (int a = 0; a < TH; ++a) R[a] = ev[a] = clamp01(kap[a] * V);
     reduce_scatter_x<T, double, TH>(R);
     R[0] = swap_sum<16>(R[0], R[0]);
     R[0] = swap_sum<32>(R[0], R[0]);
@@ -89,9 +89,9 @@ __global__ __launch_bounds__(Team::W * kWave, 2) void team_kernel(Batch batch) {
     U *= R[0];
     all_gather_x<T, double, TH>(R);
     // projection onto C2 (line 4)
-    double C = floor_;
+    double C = ev[0] * R[0];
 #pragma unroll
-    for (int a = 0; a < TH; ++a) C = fma(ev[a], R[a], C);
+    for (int a = 1; a < TH; ++a) C = fma(ev[a], R[a], C);
     part[t & 1][wave][lane] = C;
 #pragma unroll
     for (int a = 0; a < TH; ++a) kap[a] *= R[a];

@@ -48,6 +48,8 @@ constexpr int kWarmIters = 4;             // FAST: iterations done in double bef
 constexpr int kRowChunks64 = 2;           // M = 64: the 8 x 8 tile is loaded in this many pieces (loads in flight cost registers)
 constexpr int kChunk = 8;                 // iterations between looks for a repetition, FAST: and range checks of the scalings
 constexpr int kRepeatWindow = 24;         // iterations over which a repetition is looked for (RepeatCheck)
+constexpr int kRaiseBits = 512;           // kKeep: what goes from a large row scaling into its row of the tile (raise_rows)
+constexpr double kRaiseAbove = 0x1p+400;
 constexpr int kDriftBits = 40;            // FAST: fold the fp32 scalings back beyond 2^+-kDriftBits
 constexpr double kLogFloor32 = -83.0;     // FAST: rebuilt entries are kept within [e^-83, e^55] ~ [2^-120, 2^80]
 constexpr double kLogCeil32 = 55.0;
@@ -916,6 +918,9 @@ __global__ __launch_bounds__((DykstraLaunch<M, FAST, ADAPT, TILES, LONE>::kThrea
     // 4096x4096: 462 -> 450 us a call).
     constexpr int OWN_R = owned(TH, T::NX), OWN_C = owned(TW, T::NY);
     double u_own[OWN_R], v_own[OWN_C];
+    // whether the tile is held twice (see dykstra_iteration)
+    constexpr Form kForm = FAST || !T::STORE_E ? kRecompute : T::KEEP ? kKeep : kFold;
+    constexpr bool kKept = kForm == kKeep;
     [[maybe_unused]] int u_exp[OWN_R] = {}, v_exp[OWN_C] = {};
     // early exit: a block whose factors have passed the tolerance is frozen at that iteration
     bool frozen = false;
@@ -928,9 +933,6 @@ __global__ __launch_bounds__((DykstraLaunch<M, FAST, ADAPT, TILES, LONE>::kThrea
     // FAST: the tile of the fp32 phase, fl32(kap U V)
     float kap32[FAST ? TH : 1][FAST ? TW : 1];
     {
-      // whether the tile is held twice (see dykstra_iteration)
-      constexpr Form kForm = FAST || !T::STORE_E ? kRecompute : T::KEEP ? kKeep : kFold;
-      constexpr bool kKept = kForm == kKeep;
       double Uown[kKept ? TH : OWN_R], V[TW], Vown[OWN_C];
 #pragma unroll
       for (double& u : Uown) u = 1.0;
@@ -968,6 +970,26 @@ __global__ __launch_bounds__((DykstraLaunch<M, FAST, ADAPT, TILES, LONE>::kThrea
         const auto iterate = [&]() {
           return dykstra_iteration<T, kForm, kGather, ADAPT, RUN, LONE>(kap, x, Uown, V, Vown, Nd, xr, rx, frozen);
         };
+        // A row whose entries but one lie near e^-700 has its scaling grow to their reciprocal and, on the way to the others'
+        // balance, beyond the range of a double (15:16, every entry 0 or 1, spread 680: e^717; as an infinity it would stay one).
+        // So what is large of it goes into the row of the tile, by a power of two: the products are the same bit for bit.  Looked
+        // for every kRepeatWindow iterations: a row sums to N / M^2 at least, so in these it grows by 2^288 at most.
+        [[maybe_unused]] int raised = 0;  // bit a: tile row a
+        [[maybe_unused]] const auto raise_rows = [&]() {
+          bool large = false;
+#pragma unroll
+          for (int a = 0; a < OWN_R; ++a) large |= Uown[a] > kRaiseAbove;
+          if (__builtin_expect(__any(large), 0)) {
+#pragma unroll
+            for (int a = 0; a < (kKept ? TH : 0); ++a) {
+              const bool raise = Uown[a] > kRaiseAbove && !((raised >> a) & 1);
+              Uown[a] = raise ? ldexp(Uown[a], -kRaiseBits) : Uown[a];
+#pragma unroll
+              for (int b = 0; b < TW; ++b) kap[a][b] = raise ? ldexp(kap[a][b], kRaiseBits) : kap[a][b];
+              raised |= raise ? 1 << a : 0;
+            }
+          }
+        };
         if constexpr (ADAPT) {
           // iteration count as a bound: every TSENOR_ADAPTIVE_CHECK_EVERY-th iteration the largest |factor - 1|
           // of the block is compared with the tolerance; a block that passes is frozen, the wave leaves when
@@ -977,6 +999,9 @@ __global__ __launch_bounds__((DykstraLaunch<M, FAST, ADAPT, TILES, LONE>::kThrea
             if ((t + 1) % TSENOR_ADAPTIVE_CHECK_EVERY == 0) {
               freeze_if(block_max<LPB>(worst) <= p.tol, t + 1);
               if (__all(frozen)) break;
+              if constexpr (kKept) {
+                if ((t + 1) % kRepeatWindow == 0) raise_rows();
+              }
             }
           }
         } else if constexpr (kKept) {
@@ -987,10 +1012,15 @@ __global__ __launch_bounds__((DykstraLaunch<M, FAST, ADAPT, TILES, LONE>::kThrea
           for (int t = 0; t < p.T;) {
             const int stop = (p.T - t > kRepeatWindow) ? t + kRepeatWindow : p.T;
             for (; t < stop; ++t) iterate();
+            raise_rows();
             t = repeat.look(Uown, Vown, t, p.T);
           }
         } else {
           for (int t = 0; t < p.T; ++t) iterate();
+        }
+        if constexpr (kKept) {
+#pragma unroll
+          for (int a = 0; a < OWN_R; ++a) u_exp[a] = (raised >> a) & 1 ? kRaiseBits : 0;
         }
       }
       if constexpr (FAST) {
@@ -1014,7 +1044,7 @@ __global__ __launch_bounds__((DykstraLaunch<M, FAST, ADAPT, TILES, LONE>::kThrea
 #pragma unroll
       for (int a = 0; a < OWN_R; ++a) {
         lu_own[a] = log(u_own[a]);
-        if constexpr (FAST) lu_own[a] = fma((double)u_exp[a], kLn2, lu_own[a]);
+        if constexpr (FAST || kKept) lu_own[a] = fma((double)u_exp[a], kLn2, lu_own[a]);
         __builtin_amdgcn_sched_barrier(0);
       }
 #pragma unroll

@@ -49,3 +49,17 @@ def test_rows_that_spread_over_the_range(M, kind):
                 for flags in (0, b.TSENOR_FLAG_TILES_LARGE, b.TSENOR_FLAG_TILES_SMALL):
                     print(f"[case] spread {N}:{M} {kind} T={T} spread={spread} flags={flags}", flush=True)
                     assert np.abs(_plan(W, N, M, spread, T, flags) - ref).max() < PLAN_ATOL
+
+
+@pytest.mark.parametrize("M,blocks", [(4, 24), (8, 12), (16, 8), (32, 5)])
+def test_row_scalings_beyond_a_double(M, blocks):
+    # with N = M - 1 the scaling of a row with a single one passes e^710 on its way, and comes back: the kernels that keep their
+    # tile (all but the large tiles of 32 x 32 and 64 x 64 blocks) follow it
+    from paper_2505_23949_amd import binding as b
+
+    W, N, T, spread = _sparse(M, blocks, 20 + M, "share of ones"), M - 1, 900, 690.0
+    ref = np.exp(oracle.dykstra(W, N, M, oracle.tau_eff(W, 1.0 / spread, oracle.TAU_REL_MATRIX_MAX), T))
+    for flags in (0, b.TSENOR_FLAG_TILES_SMALL) if M == 32 else (0, b.TSENOR_FLAG_TILES_LARGE, b.TSENOR_FLAG_TILES_SMALL):
+        for tol in (0.0, 1e-300):
+            print(f"[case] large scalings {N}:{M} flags={flags} tol={tol}", flush=True)
+            assert np.abs(_plan(W, N, M, spread, T, flags, tol) - ref).max() < PLAN_ATOL

@@ -94,7 +94,7 @@ __device__ __forceinline__ SwapBest best_candidate(mask_t cand, const float* row
   return best;
 }
 
-// the mask of lane `lane`, the same for the whole wave
+// the mask of lane `lane`, which is to be the same number in every lane
 __device__ __forceinline__ unsigned int mask_of_lane(unsigned int v, int lane) { return (unsigned)__builtin_amdgcn_readlane((int)v, lane); }
 __device__ __forceinline__ unsigned long long mask_of_lane(unsigned long long v, int lane) {
   return (unsigned long long)(unsigned)__builtin_amdgcn_readlane((int)v, lane) |
@@ -135,7 +135,8 @@ __device__ __forceinline__ void local_search_and_write(const DevProblem& p, cons
   double* block_objective = e.block_objective;
   const uint8_t* prev_mask = e.prev_mask;
   const bool want_stats = e.stats_out != nullptr;
-  const int g = lane / LPB, ql = lane % LPB;
+  constexpr bool kInLanes = LPB == kWave;  // a wave has one block (see the swaps below)
+  const int g = kInLanes ? 0 : lane / LPB, ql = lane % LPB;
   const bool part = ql < M;
   const int qm = ql % M;  // (an index that stays inside the block's LDS rows also for the lanes that only tag along)
   const mask_t one = 1;
@@ -164,8 +165,8 @@ __device__ __forceinline__ void local_search_and_write(const DevProblem& p, cons
   int rounds = 0, nonpos = 0;
   bool open = any_short;  // this block may still take swaps
   // A wave of one block keeps the masks in the registers of the rows' and columns' lanes and reads those of row i and column j
-  // from there; several blocks to a wave have theirs in LDS.
-  constexpr bool kInLanes = LPB == kWave;
+  // from there; several blocks to a wave have theirs in LDS.  Such a wave takes every decision from ballots, so that all its
+  // lanes agree on i, j, the winner and whether to go on, those that only tag along too: readlane takes one lane number.
   mask_t Srow = part ? lds.rowm[g][qm] : (mask_t)0, Scol = part ? lds.colm[g][qm] : (mask_t)0;
   while (any_short) {
     if constexpr (!kInLanes) {
@@ -177,8 +178,8 @@ __device__ __forceinline__ void local_search_and_write(const DevProblem& p, cons
     if (rb == 0 || cb == 0 || (p.strict && rounds >= p.L)) open = false;
     if (!__any(open)) break;
     // line 10: the lowest-index row i and column j that are short
-    const int i = open ? (__ffsll((long long)rb) - 1 - g * LPB) : 0;
-    const int j = open ? (__ffsll((long long)cb) - 1 - g * LPB) : 0;
+    const int i = kInLanes || open ? (__ffsll((long long)rb) - 1 - g * LPB) : 0;
+    const int j = kInLanes || open ? (__ffsll((long long)cb) - 1 - g * LPB) : 0;
     // line 11 for i' = this lane: columns j' with S[i'][j'] = 1 and S[i][j'] = 0, provided S[i'][j] = 0
     mask_t row_i, col_j;
     if constexpr (kInLanes)
@@ -196,7 +197,9 @@ __device__ __forceinline__ void local_search_and_write(const DevProblem& p, cons
     const int ip = winner - g * LPB;
     const int jp = kInLanes ? __builtin_amdgcn_readlane(best.column, winner) : __shfl(best.column, winner, kWave);
     if (open) ++rounds;
-    const bool apply = winners != 0 && (!p.strict || top > 0.0);
+    // (block_max() covers the block's M lanes: the maximum is the winner's)
+    const bool gain = kInLanes ? (__ballot(top > 0.0) >> winner) & 1 : top > 0.0;
+    const bool apply = winners != 0 && (!p.strict || gain);
     if (open && !apply) open = false;  // nothing changes any more for this block
     // line 13: remove (i', j'), insert (i', j) and (i, j')
     if constexpr (kInLanes) {
@@ -205,7 +208,7 @@ __device__ __forceinline__ void local_search_and_write(const DevProblem& p, cons
         if (ql == i) Srow |= one << jp;
         if (ql == jp) Scol = (Scol & ~(one << ip)) | (one << i);
         if (ql == j) Scol |= one << ip;
-        if (!(top > 0.0)) ++nonpos;
+        if (!gain) ++nonpos;
       }
       continue;
     }
@@ -215,7 +218,7 @@ __device__ __forceinline__ void local_search_and_write(const DevProblem& p, cons
       lds.rowm[g][i] |= one << jp;
       lds.colm[g][jp] = (lds.colm[g][jp] & ~(one << ip)) | (one << i);
       lds.colm[g][j] |= one << ip;
-      if (!(top > 0.0)) ++nonpos;
+      if (!gain) ++nonpos;
     }
     wave_sync();
   }

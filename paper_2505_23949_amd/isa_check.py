@@ -13,8 +13,14 @@ numbers silently:
 writing side (H2).  Hand-written instructions are recognised by how they are printed: without the encoding suffix
 the compiler gives its own 32-bit ones (`v_min_f32` against `v_min_f32_e32`), or as the one form written with it
 (`v_mul_f32_e64 ... clamp`).  The 64-bit minimum and maximum print without a suffix whoever wrote them; all of
-them are treated as hand-written, which only makes the check stricter.  `listing()` compiles one translation
-unit to such a listing.
+them are treated as hand-written, which only makes the check stricter.
+
+v_readlane takes one lane number for the whole wave.  Given a number that may differ between lanes the compiler puts a
+v_readfirstlane before it, and which lane's number is used is then its choice:
+
+  L1  the lane number of a v_readlane that was fetched from a vector register by v_readfirstlane.
+
+`varying_lane_numbers()` scans for it.  `listing()` compiles one translation unit to such a listing.
 """
 from __future__ import annotations
 
@@ -79,6 +85,26 @@ def hazards(text: str, name: str = "") -> list[str]:
     return found
 
 
+def varying_lane_numbers(text: str, name: str = "") -> list[str]:
+    """The uses of kind L1 found in an ISA listing, one line of description each."""
+    found = []
+    fetched: set[str] = set()   # scalar registers that hold what v_readfirstlane (or a copy of it) left there
+    for number, line in enumerate(text.split("\n"), 1):
+        if not line.startswith("\t") or line.strip().startswith((".", ";")):
+            if re.match(r"^[A-Za-z_]\S*:", line):
+                fetched = set()   # another function (labels inside one begin with a dot)
+            continue
+        op, _, rest = line.split(";")[0].strip().partition(" ")
+        operands = re.split(r",\s*", rest.strip())
+        if op == "v_readlane_b32" and operands[2] in fetched:
+            found.append(f"L1 {name}:{number}: `{op} {rest.strip()}` reads a lane number that may differ between lanes")
+        copied = op == "s_mov_b32" and len(operands) > 1 and operands[1] in fetched
+        wide = re.match(r"^s\[(\d+):(\d+)\]$", operands[0])
+        written = {f"s{k}" for k in range(int(wide.group(1)), int(wide.group(2)) + 1)} if wide else {operands[0]}
+        fetched = fetched | written if op == "v_readfirstlane_b32" or copied else fetched - written
+    return found
+
+
 def listing(source: Path) -> str:
     """ISA listing of the device code of one translation unit, compiled with the flags of the library."""
     with tempfile.TemporaryDirectory() as tmp:
@@ -89,15 +115,15 @@ def listing(source: Path) -> str:
 
 
 def check_all(jobs: int = 6) -> list[str]:
-    """Hazards in every translation unit of the library."""
+    """Hazards and varying lane numbers in every translation unit of the library."""
     from concurrent.futures import ThreadPoolExecutor
 
     with ThreadPoolExecutor(max_workers=jobs) as pool:
         texts = list(pool.map(listing, _build.SOURCES))
-    return [h for src, text in zip(_build.SOURCES, texts) for h in hazards(text, Path(src).name)]
+    return [h for src, text in zip(_build.SOURCES, texts) for check in (hazards, varying_lane_numbers) for h in check(text, Path(src).name)]
 
 
 if __name__ == "__main__":
     problems = check_all()
-    print("\n".join(problems) if problems else "no hazards around hand-written instructions")
+    print("\n".join(problems) if problems else "no hazards around hand-written instructions, no varying lane numbers")
     raise SystemExit(1 if problems else 0)

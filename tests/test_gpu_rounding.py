@@ -122,6 +122,30 @@ def test_workgroup_per_64_wide_block(blocks):
         assert np.array_equal(res["stats"].cpu().numpy(), stats)
 
 
+@pytest.mark.parametrize("M,N", [(16, 9), (32, 21), (64, 45)])
+def test_printed_swap_rule_in_a_wave_of_one_block(M, N):
+    # Small launches of these sizes give a block a wave of its own, whose lanes beyond the block's rows have to agree with the
+    # others on every swap.  One iteration leaves greedy selection so short that blocks take several.
+    import torch
+
+    from paper_2505_23949_amd import binding as b
+
+    dev = torch.device("cuda:0")
+    W = np.random.Generator(np.random.Philox(60 + M)).standard_normal((5 * M, 7 * M), dtype=np.float32)
+    imp = oracle.importance(W)
+    log_S = oracle.dykstra(imp, N, M, oracle.tau_eff(imp, 0.01, synth.TAU_REL_MATRIX_MAX), 1)
+    masks = {L: oracle.round_plan(log_S, imp, N, M, L=L, strict_paper=True) for L in (2, 60)}
+    longer = (masks[2][0] != masks[60][0]).reshape(5, M, 7, M).any(axis=(1, 3))
+    assert longer.sum() >= 5, "several blocks should take three and more swaps"
+    for L in (2, 60):
+        print(f"[case] printed swap rule {N}:{M} L={L}", flush=True)
+        res = b.solve(torch.from_numpy(W).to(dev), N, M, 0.01, 1, tau_mode=b.TSENOR_TAU_REL_MATRIX_MAX, local_search_steps=L,
+                      want_stats=True, flags=b.TSENOR_FLAG_STRICT_PAPER)
+        torch.cuda.synchronize()
+        assert np.array_equal(res["mask"].cpu().numpy(), masks[L][0])
+        assert np.array_equal(res["stats"].cpu().numpy(), masks[L][1])
+
+
 @pytest.mark.parametrize("M,N", [(4, 3), (8, 3), (16, 7), (32, 5), (64, 29)])
 def test_swaps_fill_every_row_whatever_their_scores(M, N):
     # Squares of finite weights that overflow: a swap that gives up an infinite importance scores minus infinity or no number

@@ -29,6 +29,21 @@ def test_scanner_finds_planted_hazards_and_only_those():
     assert isa_check.hazards(PLANTED_H1.replace("v_min_f32 ", "v_min_f32_e32 ")) == []
 
 
+PLANTED_L1 = """
+kernel:
+\tv_readfirstlane_b32 s4, v9
+\ts_mov_b32 s6, s4
+.LBB0_1:
+\tv_readlane_b32 s5, v1, s6
+"""
+
+
+def test_scanner_finds_lane_numbers_that_vary():
+    assert len(isa_check.varying_lane_numbers(PLANTED_L1)) == 1 and isa_check.varying_lane_numbers(PLANTED_L1)[0].startswith("L1")
+    assert isa_check.varying_lane_numbers(PLANTED_L1.replace("v_readfirstlane_b32 s4, v9", "s_ff1_i32_b64 s4, s[8:9]")) == []
+    assert isa_check.varying_lane_numbers(PLANTED_L1.replace(".LBB0_1:", "\ts_ff1_i32_b64 s6, s[8:9]")) == []
+
+
 def test_no_hazard_in_the_library():
     problems = isa_check.check_all()
     assert problems == [], "\n".join(problems)

@@ -377,8 +377,13 @@ enum Gather { kLanesOnly, kRowsInLds, kScalingsInLds };
 // instructions ahead of another wave's long run instead of behind it: with equal priorities the waves of a
 // SIMD fell into step and stalled together (measured: 11-16 % of the fp32 loop, 1-2 % of the double one).
 // A wave alone on its SIMD has nobody to be ahead of, and every instruction of its own counts (LONE: 512x512 2:4 31.0 us a call
-// with the six instructions of an iteration, 28.1 without; with two waves on a SIMD 52.0 and 55.5).
-template <bool LONE>
+// with the six instructions of an iteration, 28.1 without; with two waves on a SIMD 52.0 and 55.5).  That is so while its stream is
+// the only one: where launches of several streams share the SIMDs, the priorities would gain (16:32, 812 blocks, T = 300: one
+// stream 96 us without, 101 with; four streams 290 and 285; 506 blocks on four streams 200 and 191).  The iterations in fp32 keep
+// them: alone they cost a lone wave 2-3 %, with two to four streams 4-14 % are lost without (64 x 64, 306 blocks, T = 300: one stream
+// 250 us without, 254 with; four streams 368 and 317; 4 x 4, 65 024 blocks 82 and 85, four streams 220 and 210).  (A fixed
+// priority for every wave, by its slot on the SIMD, is worse than none: the last ones wait for the others to end.)
+template <bool LONE = false>
 __device__ __forceinline__ void chain_phase(bool on) {
   if constexpr (LONE) return;
   if (on)
@@ -610,7 +615,7 @@ __device__ __forceinline__ float max_as_is(float a, float b) {
 // sum and the multiply-add of the column sum per entry, all at the full fp32 rate.  A scaling grows by at most
 // 2^10 per iteration (keeps everything finite on degenerate input).
 // ADAPT as in dykstra_iteration.
-template <class T, bool LDS_GATHER = false, bool ADAPT = false, bool LONE = false, int TH, int TW>
+template <class T, bool LDS_GATHER = false, bool ADAPT = false, int TH, int TW>
 __device__ __forceinline__ float dykstra_iteration_f32(const float (&kap)[TH][TW], float (&U)[TH], float (&V)[TW],
                                                        float (&Vown)[owned(TW, T::NY)], float Nf, float2* xr = nullptr, int rx = 0,
                                                        bool frozen = false) {
@@ -628,7 +633,7 @@ __device__ __forceinline__ float dykstra_iteration_f32(const float (&kap)[TH][TW
       R[a] = b == 0 ? e[a][b] : R[a] + e[a][b];
     }
   }
-  chain_phase<LONE>(true);
+  chain_phase(true);
   reduce_scatter_x<T, float, TH>(R);
 #pragma unroll
   for (int a = 0; a < OWN_R; ++a) {
@@ -660,13 +665,13 @@ __device__ __forceinline__ float dykstra_iteration_f32(const float (&kap)[TH][TW
 #pragma unroll
     for (int a = 0; a < TH; ++a) U[a] *= !BARE ? R[a] : ADAPT && frozen ? 1.0f : Nf * R[a];
   }
-  chain_phase<LONE>(false);
+  chain_phase(false);
 #pragma unroll
   for (int b = 0; b < TW; ++b) {
 #pragma unroll
     for (int a = 0; a < TH; ++a) C[b] = a == 0 ? e[a][b] * R[a] : fmaf(e[a][b], R[a], C[b]);
   }
-  chain_phase<LONE>(true);
+  chain_phase(true);
   reduce_scatter_y<T, float, TW>(C);
 #pragma unroll
   for (int b = 0; b < OWN_C; ++b) {
@@ -679,7 +684,7 @@ __device__ __forceinline__ float dykstra_iteration_f32(const float (&kap)[TH][TW
 #pragma unroll
   for (int b = 0; b < OWN_C; ++b) V[b] = Vown[b] *= C[b];
   all_gather_y<T, float, TW>(V);
-  chain_phase<LONE>(false);
+  chain_phase(false);
   return worst;
 }
 
@@ -1136,7 +1141,7 @@ __global__ __launch_bounds__((DykstraLaunch<M, FAST, ADAPT, TILES, LONE>::kThrea
               }
             }
           } else {
-            for (; t < stop; ++t) dykstra_iteration_f32<T, kLdsGather32, false, LONE>(kap32, U32, V32, V32own, Nf, xr, rx);
+            for (; t < stop; ++t) dykstra_iteration_f32<T, kLdsGather32>(kap32, U32, V32, V32own, Nf, xr, rx);
           }
           if constexpr (!ADAPT) t = repeat.look(U32, V32own, t, p.T);
           // (the scalings of the rows and columns this lane owns: every row and column has its owner, and the

@@ -19,14 +19,12 @@ inline bool assign_groups(Batch& b, int64_t per_group) {
   return true;
 }
 
-// Whether a launch of that many waves on the large tiles gives a SIMD no second one.  Only 64 x 64 blocks (257 to 1024 of them)
-// and 4 x 4 ones come there without a flag: the other sizes have the small tiles for launches like that.
+// Whether the workgroups assigned give a SIMD no second wave.
+inline bool lone_waves(const Batch& b, int waves_per_group) { return (uint64_t)b.first[b.count] * waves_per_group <= kSimds; }
+// Block sizes that come to the large tiles with so few without a flag: 64 x 64 (257 to 1024 blocks) and 4 x 4.  The others have
+// the small tiles for launches like that.
 template <int M>
 constexpr bool kLoneOnLargeTiles = M == 64 || M == 4;
-template <int M>
-bool lone_on_large_tiles(int64_t waves) {
-  return kLoneOnLargeTiles<M> && waves <= (int64_t)kSimds;
-}
 
 template <int M>
 bool launch_block_kernels(Batch& b, const Variant& v, hipStream_t stream, hipEvent_t ev_sorted, hipEvent_t ev_greedy) {
@@ -44,7 +42,7 @@ bool launch_block_kernels(Batch& b, const Variant& v, hipStream_t stream, hipEve
       if (!assign_groups(b, (int64_t)BPWS)) return false;
       // (launches in the finest tiles' order are larger than that)
       constexpr bool kLone = TILES != kFinestOrderTiles;
-      const bool lone = kLone && b.first[b.count] <= kSimds;
+      const bool lone = kLone && lone_waves(b, L::kWavesPerGroup);
       if (v.adaptive && lone)
         dykstra_sort_kernel<M, false, false, TILES, true, kLone><<<b.first[b.count], L::kThreads, 0, stream>>>(b);
       else if (v.adaptive)
@@ -83,13 +81,15 @@ bool launch_block_kernels(Batch& b, const Variant& v, hipStream_t stream, hipEve
     if (!assign_groups(b, (int64_t)BPW * L::kWavesPerGroup)) return false;
     dykstra_sort_kernel<M, true, false, false, true><<<b.first[b.count], L::kThreads, 0, stream>>>(b);
   } else if (v.fast) {
-    if (lone_on_large_tiles<M>(nblocks / BPW)) {
-      using L = DykstraLaunch<M, true, false, kLargeTiles, true>;
-      if (!assign_groups(b, (int64_t)BPW * L::kWavesPerGroup)) return false;
-      dykstra_sort_kernel<M, true, false, kLargeTiles, false, kLoneOnLargeTiles<M>><<<b.first[b.count], L::kThreads, 0, stream>>>(b);
+    // (fp32 iterations keep their priorities: a launch of lone waves differs in its workgroups, DykstraLaunch)
+    using L = DykstraLaunch<M, true>;
+    using LL = DykstraLaunch<M, true, false, kLargeTiles, true>;
+    constexpr bool kLone = LL::kWavesPerGroup != L::kWavesPerGroup;
+    if (!assign_groups(b, (int64_t)BPW * LL::kWavesPerGroup)) return false;
+    if (kLone && lone_waves(b, LL::kWavesPerGroup)) {
+      dykstra_sort_kernel<M, true, false, kLargeTiles, false, kLone><<<b.first[b.count], LL::kThreads, 0, stream>>>(b);
     } else {
-      using L = DykstraLaunch<M, true>;
-      if (!assign_groups(b, (int64_t)BPW * L::kWavesPerGroup)) return false;
+      if (kLone && !assign_groups(b, (int64_t)BPW * L::kWavesPerGroup)) return false;
       dykstra_sort_kernel<M, true><<<b.first[b.count], L::kThreads, 0, stream>>>(b);
     }
   } else {
@@ -103,7 +103,7 @@ bool launch_block_kernels(Batch& b, const Variant& v, hipStream_t stream, hipEve
       if (any_plan) dykstra_sort_kernel<M, false, true><<<b.first[b.count], L::kThreads, 0, stream>>>(b);
     } else if (v.adaptive)
       dykstra_sort_kernel<M, false, false, false, true><<<b.first[b.count], LA::kThreads, 0, stream>>>(b);
-    else if (lone_on_large_tiles<M>(nblocks / BPW))
+    else if (kLoneOnLargeTiles<M> && lone_waves(b, L::kWavesPerGroup))
       dykstra_sort_kernel<M, false, false, kLargeTiles, false, kLoneOnLargeTiles<M>><<<b.first[b.count], L::kThreads, 0, stream>>>(b);
     else
       dykstra_sort_kernel<M, false><<<b.first[b.count], L::kThreads, 0, stream>>>(b);

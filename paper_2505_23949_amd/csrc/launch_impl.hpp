@@ -40,15 +40,13 @@ bool launch_block_kernels(Batch& b, const Variant& v, hipStream_t stream, hipEve
       using L = DykstraLaunch<M, false, false, TILES>;
       static_assert(L::kWavesPerGroup == 1 && DykstraLaunch<M, false, true, TILES>::kWavesPerGroup == 1, "");
       if (!assign_groups(b, (int64_t)BPWS)) return false;
-      // (launches in the finest tiles' order are larger than that)
-      constexpr bool kLone = TILES != kFinestOrderTiles;
-      const bool lone = kLone && lone_waves(b, L::kWavesPerGroup);
+      const bool lone = lone_waves(b, L::kWavesPerGroup);
       if (v.adaptive && lone)
-        dykstra_sort_kernel<M, false, false, TILES, true, kLone><<<b.first[b.count], L::kThreads, 0, stream>>>(b);
+        dykstra_sort_kernel<M, false, false, TILES, true, true><<<b.first[b.count], L::kThreads, 0, stream>>>(b);
       else if (v.adaptive)
         dykstra_sort_kernel<M, false, false, TILES, true><<<b.first[b.count], L::kThreads, 0, stream>>>(b);
       else if (lone)
-        dykstra_sort_kernel<M, false, false, TILES, false, kLone><<<b.first[b.count], L::kThreads, 0, stream>>>(b);
+        dykstra_sort_kernel<M, false, false, TILES, false, true><<<b.first[b.count], L::kThreads, 0, stream>>>(b);
       else
         dykstra_sort_kernel<M, false, false, TILES><<<b.first[b.count], L::kThreads, 0, stream>>>(b);
       return true;

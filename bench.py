@@ -61,11 +61,11 @@ LOOP_VALU_PER_WAVE_ITER = {
 }
 
 
-def layout_of(M: int, fp32: bool, nblocks: int) -> str:
+def layout_of(M: int, fp32: bool, nblocks: int, iters: int) -> str:
     """The library's own choice for a single matrix and a fixed count of iterations, mirrored here to pick the row of the
     table above and to say which precision a call iterates in (single precision, if asked for, on the large tiles)."""
     if M == 4:
-        small = nblocks <= 49152 or (not fp32 and 65536 < nblocks <= 102400)
+        small = nblocks <= 49152 or (not fp32 and 65536 < nblocks <= (114688 if iters <= 150 else 102400))
     else:
         small = nblocks <= {8: 12288, 16: 8192 if fp32 else 62000, 32: 2048 if fp32 else 3072, 64: 256}[M]
     if not small:
@@ -248,7 +248,7 @@ def bench_matrix(args, name):
     steps = args.steps
     fp32_flag = binding.TSENOR_FLAG_FP32_ITERATIONS
     # a matrix this small runs on the small tiles, which iterate in double whatever the flag says
-    small_launch = layout_of(w.M, True, nblocks) != "large"
+    small_launch = layout_of(w.M, True, nblocks, w.iters) != "large"
     headline_fp32 = args.precision == "fp32" and not small_launch
     no_cpu, no_modes = args.no_cpu_baseline, args.no_other_modes
     if args.tol > 0.0:
@@ -298,7 +298,7 @@ def bench_matrix(args, name):
         # Waves stop once the states of their blocks repeat bit for bit (in double not those of the 32- and 64-wide large tiles), so
         # the kernel may run fewer than T iterations.  The rate at which it iterates is taken where all of them run: an early
         # exit whose tolerance no block meets.
-        may_stop = layout_of(w.M, fp32, nblocks) != "team" and (fp32 or w.M < 32 or layout_of(w.M, False, nblocks) != "large")
+        may_stop = layout_of(w.M, fp32, nblocks, w.iters) != "team" and (fp32 or w.M < 32 or layout_of(w.M, False, nblocks, w.iters) != "large")
         every = binding.make_problem(W, w.N, w.M, w.tau, w.iters, mask=torch.empty_like(mask), col_scale=cs, tau_mode=w.tau_mode,
                                      flags=fp32_flag if fp32 else 0, tol=1e-300)
         every_ms = binding.tsenor_mask_ex_profile(every, work, max(3, steps // 2))[1] if w.iters > 0 and may_stop else dyk_ms
@@ -336,7 +336,7 @@ def bench_matrix(args, name):
             roofline["pass_traffic_over_algorithmic"] = round(
                 traffic["pass"] / roofline["algorithmic_bytes_per_pass"], 2)
         if not fp32 and w.iters > 0:
-            counted = LOOP_VALU_PER_WAVE_ITER.get((w.M, layout_of(w.M, False, nblocks)))
+            counted = LOOP_VALU_PER_WAVE_ITER.get((w.M, layout_of(w.M, False, nblocks, w.iters)))
             if counted:
                 # second view of the same measurement: the vector instructions the loop issues against the issue
                 # slots of the chip (1024 SIMDs, one double-precision wave instruction per 4 cycles), at the

@@ -39,7 +39,9 @@ struct Variant {
 //   M = 8 (4): 8320 blocks 79 / 85 / 85, 11 264 blocks 83 / 87 / 86, 12 288 blocks 85 / 88 / 86, 12 416 blocks 102 / 88 / 86;
 //   M = 4 (16; the large tiles hold 64): 48 128 blocks 82 / 89 / 81, 50 176 blocks 94 / 86 / 80, 65 536 blocks 99 / 87 / 80,
 //     67 584 blocks 113 / 149 / 96, 98 304 blocks 146 / 153 / 100, 102 400 blocks 149 / 149, 114 688 blocks 156 / 150 / 101.
-// T = 20 and T = 100 put the lines at the same places within 2 us, but for M = 16 at T = 20 (65 536 blocks 146 / 152).
+// T = 20 and T = 100 put the lines at the same places within 2 us, but for M = 16 at T = 20 (65 536 blocks 146 / 152), and for M = 4
+// from 102 401 to 114 688 blocks, where the large tiles make up for their second kernel only over many iterations (108 240
+// blocks, T = 20, 100, 150, 200, 300: 29.7 / 32.0, 63.0 / 64.8, 85.3 / 86.0, 107.5 / 107.6, 151.6 / 150.0; student weights the same).
 // With the early exit (`adaptive`) a wave runs until the slowest of its blocks stops, and the large tiles put up to four times
 // as many blocks into it, so M <= 8 keeps the small tiles for longer.  T = 300, normal weights, tol 1e-2 and 1e-3 (small /
 // large double / large fp32):
@@ -47,9 +49,9 @@ struct Variant {
 //     211 / 195; M = 8: 9500 blocks 74 / 100 / 91 and 109 / 111 / 104, 12 500 blocks 76 / 100 / 90 and 130 / 108 / 99;
 //   M = 4 and 8, heavy-tailed weights, tol 1e-3: 60 000 blocks 43 / 70, 12 500 blocks 37 / 43;
 //   M = 16, heavy-tailed: 8600 blocks 54 / - / 57.
-constexpr bool small_tiles_win(int M, bool fp32, bool adaptive, int64_t nblocks) {
+constexpr bool small_tiles_win(int M, bool fp32, bool adaptive, int iters, int64_t nblocks) {
   if (M == 4 && adaptive) return nblocks <= (fp32 ? 55000 : 114688);
-  if (M == 4) return nblocks <= 49152 || (!fp32 && nblocks > 65536 && nblocks <= 102400);
+  if (M == 4) return nblocks <= 49152 || (!fp32 && nblocks > 65536 && nblocks <= (iters <= 150 ? 114688 : 102400));
   if (M == 8) return nblocks <= (adaptive ? (fp32 ? 12000 : 13000) : 12288);
   if (M == 16) return nblocks <= (fp32 ? (adaptive ? 9000 : 8192) : 62000);
   return M == 32 && nblocks <= (fp32 ? 2048 : 3072);

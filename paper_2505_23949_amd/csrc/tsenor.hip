@@ -232,7 +232,7 @@ inline Variant variant_of(const tsenor_problem& p) {
   const bool tiled = !v.zero_t && !v.simple && !(p.flags & TSENOR_FLAG_TILES_LARGE);
   const bool team = tiled && nblocks < team_below_blocks(p.M);
   const bool small = team || (p.M <= 32 && tiled &&
-                              ((p.flags & TSENOR_FLAG_TILES_SMALL) != 0 || small_tiles_win(p.M, fp32, v.adaptive, nblocks)));
+                              ((p.flags & TSENOR_FLAG_TILES_SMALL) != 0 || small_tiles_win(p.M, fp32, v.adaptive, p.iters, nblocks)));
   v.tiles = !small ? kLargeTiles : team ? kTeam : nblocks < finest_tiles_below_blocks(p.M) ? kFinestTiles : kSmallTiles;
   // the small tiles (launches that cannot fill the chip: bound by latency, not by issue) iterate in double only
   v.fast = p.iters > 0 && fp32 && !small;

@@ -215,3 +215,21 @@ def test_a_batch_is_its_calls_on_every_layout(M, block_rows, block_cols, count, 
     for out, single in zip(outs, singles):
         for k in ("mask", "plan", "stats", "objective", "iters_done"):
             assert torch.equal(out[k], single[k]), k
+
+
+@pytest.mark.parametrize("T,small", [(20, True), (150, True), (151, False)])
+def test_line_of_4_wide_blocks_goes_by_the_iterations(T, small):
+    # 102 401 to 114 688 blocks of 4 x 4 in double run on the small tiles up to 150 iterations and on the large ones beyond: the
+    # plan, whose sums the two add in different orders, is that of the one asked for by its flag, bit for bit
+    import torch
+
+    from paper_2505_23949_amd import binding as b
+
+    dev = torch.device("cuda:0")
+    W = torch.from_numpy(np.random.Generator(np.random.Philox(8)).standard_normal((4 * 317, 4 * 341), dtype=np.float32)).to(dev)
+    print(f"[case] line of 4 x 4 blocks T={T}", flush=True)
+    plans = [b.solve(W, 2, 4, 0.01, T, tau_mode=b.TSENOR_TAU_REL_MATRIX_MAX, want_plan=True, flags=flags)["plan"]
+             for flags in (0, b.TSENOR_FLAG_TILES_SMALL, b.TSENOR_FLAG_TILES_LARGE)]
+    torch.cuda.synchronize()
+    assert not torch.equal(plans[1], plans[2])
+    assert torch.equal(plans[0], plans[1 if small else 2])

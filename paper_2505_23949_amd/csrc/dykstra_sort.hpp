@@ -999,15 +999,17 @@ __global__ __launch_bounds__((DykstraLaunch<M, FAST, ADAPT, TILES, LONE>::kThrea
           // iteration count as a bound: every TSENOR_ADAPTIVE_CHECK_EVERY-th iteration the largest |factor - 1|
           // of the block is compared with the tolerance; a block that passes is frozen, the wave leaves when
           // all its blocks are
-          for (int t = 0; t < p.T; ++t) {
-            const double worst = iterate();
-            if ((t + 1) % TSENOR_ADAPTIVE_CHECK_EVERY == 0) {
-              freeze_if(block_max<LPB>(worst) <= p.tol, t + 1);
-              if (__all(frozen)) break;
-              if constexpr (kKept) {
-                if ((t + 1) % kRepeatWindow == 0) raise_rows();
+          bool all_frozen = false;
+          for (int t = 0; t < p.T && !all_frozen;) {
+            const int stop = kKept && p.T - t > kRepeatWindow ? t + kRepeatWindow : p.T;
+            for (; t < stop && !all_frozen; ++t) {
+              const double worst = iterate();
+              if ((t + 1) % TSENOR_ADAPTIVE_CHECK_EVERY == 0) {
+                freeze_if(block_max<LPB>(worst) <= p.tol, t + 1);
+                all_frozen = __all(frozen);
               }
             }
+            if constexpr (kKept) raise_rows();
           }
         } else if constexpr (kKept) {
           using Repeat = RepeatCheck<double, OWN_R, OWN_C, !SMALL>;

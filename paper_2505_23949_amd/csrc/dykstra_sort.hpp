@@ -726,9 +726,9 @@ struct RepeatCheck {
   }
   // t iterations are done: the number that are as good as done
   template <int NU, int NV>
-  __device__ __forceinline__ int look(const real (&U)[NU], const real (&V)[NV], int t, int T) {
+  __device__ __forceinline__ int look(const real (&U)[NU], const real (&V)[NV], int t, int T, real first) {
     // (the whole state only if a first scaling of every lane is as it was)
-    bool changed = __any(differ(U[0], at(0)));
+    bool changed = __any(differ(U[0], first));
     if (!changed) {
 #pragma unroll
       for (int a = 1; a < OWN_R; ++a) changed |= differ(U[a], at(a));
@@ -1018,9 +1018,10 @@ __global__ __launch_bounds__((DykstraLaunch<M, FAST, ADAPT, TILES, LONE>::kThrea
           repeat.note(Uown, Vown, 0);
           for (int t = 0; t < p.T;) {
             const int stop = (p.T - t > kRepeatWindow) ? t + kRepeatWindow : p.T;
+            const double first = repeat.at(0);
             for (; t < stop; ++t) iterate();
             raise_rows();
-            t = repeat.look(Uown, Vown, t, p.T);
+            t = repeat.look(Uown, Vown, t, p.T, first);
           }
         } else {
           for (int t = 0; t < p.T; ++t) iterate();
@@ -1127,6 +1128,7 @@ __global__ __launch_bounds__((DykstraLaunch<M, FAST, ADAPT, TILES, LONE>::kThrea
         Repeat repeat = Repeat::make(seen[ADAPT ? 0 : wave_in_group], lane);
         if constexpr (!ADAPT) repeat.note(U32, V32own, kWarmIters);
         for (int t = kWarmIters; t < p.T && !all_frozen;) {
+          [[maybe_unused]] const float first = ADAPT ? 0.0f : repeat.at(0);  // (on its way from LDS while the iterations run)
           const int stop = (p.T - t > kChunk) ? t + kChunk : p.T;
           // (in fp32 the exchange also carries the updated scalings, which pays wherever a block spans lanes:
           // -6 % for M = 8, -10 % for M = 16; in double the 16-wide kernel is 1.5 % faster with DPP moves)
@@ -1145,7 +1147,7 @@ __global__ __launch_bounds__((DykstraLaunch<M, FAST, ADAPT, TILES, LONE>::kThrea
           } else {
             for (; t < stop; ++t) dykstra_iteration_f32<T, kLdsGather32>(kap32, U32, V32, V32own, Nf, xr, rx);
           }
-          if constexpr (!ADAPT) t = repeat.look(U32, V32own, t, p.T);
+          if constexpr (!ADAPT) t = repeat.look(U32, V32own, t, p.T, first);
           // (the scalings of the rows and columns this lane owns: every row and column has its owner, and the
           // other copies of a scaling are the same number)
           float mxs = U32[0], mns = U32[0];

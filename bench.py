@@ -52,13 +52,8 @@ def useful_ops_per_entry_iter(M: int, fp32: bool) -> float:
 # Vector instructions the compiled default-mode iteration loop issues per wave and iteration, and the matrix
 # entries a wave holds (counted in the ISA of the built library, `v_*` lines between the loop label and its
 # branch; cross-lane ds_swizzle and LDS accesses issue on another pipeline and are not counted).  Keyed by
-# (M, layout): the small tiles, the finest ones (a 16 x 16 block per wave) and the team (a 64 x 64 block on eight waves, of
-# which a row counts one) serve small launches.
-LOOP_VALU_PER_WAVE_ITER = {
-    (4, "large"): (96, 1024), (4, "small"): (35, 256), (8, "large"): (98, 1024), (8, "small"): (41, 256),
-    (16, "large"): (178, 2048), (16, "small"): (103, 1024), (16, "finest"): (51, 256),
-    (32, "large"): (162, 2048), (32, "small"): (107, 1024), (64, "large"): (374, 4096), (64, "team"): (93, 512),
-}
+# (M, layout), for the kernels that run all T iterations; the team is a 64 x 64 block on eight waves, of which a row counts one.
+LOOP_VALU_PER_WAVE_ITER = {(32, "large"): (162, 2048), (64, "large"): (374, 4096), (64, "team"): (93, 512)}
 
 
 def layout_of(M: int, fp32: bool, nblocks: int, iters: int) -> str:
@@ -261,7 +256,6 @@ def bench_matrix(args, name):
         torch.cuda.synchronize()
         del ref_in, ref_out
 
-    entry_iters = float(weights) * w.iters
     esize = 2 if w.dtype == "bf16" else 4
     work = None
 
@@ -296,14 +290,22 @@ def bench_matrix(args, name):
                         "kernel_ms": round(dyk_ms, 4)})
             return out, mask
         # Waves stop once the states of their blocks repeat bit for bit (in double not those of the 32- and 64-wide large tiles), so
-        # the kernel may run fewer than T iterations.  The rate at which it iterates is taken where all of them run: an early
-        # exit whose tolerance no block meets.
-        may_stop = layout_of(w.M, fp32, nblocks, w.iters) != "team" and (fp32 or w.M < 32 or layout_of(w.M, False, nblocks, w.iters) != "large")
-        every = binding.make_problem(W, w.N, w.M, w.tau, w.iters, mask=torch.empty_like(mask), col_scale=cs, tau_mode=w.tau_mode,
-                                     flags=fp32_flag if fp32 else 0, tol=1e-300)
-        every_ms = binding.tsenor_mask_ex_profile(every, work, max(3, steps // 2))[1] if w.iters > 0 and may_stop else dyk_ms
+        # the kernel may run fewer than T iterations.  The rate at which it iterates is taken from the early-exit kernel of the same
+        # tiling, which does not look for repetitions: with the smallest tolerance a block runs until T, or until a check meets an
+        # iteration whose factors are all exactly 1.  The iterations it ran are counted.
+        layout = layout_of(w.M, fp32, nblocks, w.iters)
+        may_stop = w.iters > 0 and layout != "team" and (fp32 or w.M < 32 or layout != "large")
+        every_ms, mean_iters = dyk_ms, float(w.iters)
+        if may_stop:
+            ran = torch.zeros(nblocks, dtype=torch.int32, device=dev)
+            tiles = binding.TSENOR_FLAG_TILES_LARGE if layout == "large" else binding.TSENOR_FLAG_TILES_SMALL
+            every = binding.make_problem(W, w.N, w.M, w.tau, w.iters, mask=torch.empty_like(mask), col_scale=cs, tau_mode=w.tau_mode,
+                                         flags=(fp32_flag if fp32 else 0) | tiles, tol=1e-300, iters_done_out=ran)
+            every_ms = binding.tsenor_mask_ex_profile(every, work, max(3, steps // 2))[1]
+            mean_iters = float(ran.double().mean())
+        every_entry_iters = float(weights) * mean_iters
         ops = useful_ops_per_entry_iter(w.M, fp32)
-        achieved = ops * entry_iters / (every_ms * 1e-3) / 1e12
+        achieved = ops * every_entry_iters / (every_ms * 1e-3) / 1e12
         peak = PEAK_F32_PLAIN_TLANEOPS if fp32 else PEAK_F64_TLANEOPS
         plain = not (args.rows or args.absolute_tau or args.iters >= 0)
         traffic = recorded_traffic(w.name, fp32) if plain else {"kernel": None, "pass": None}
@@ -311,13 +313,14 @@ def bench_matrix(args, name):
             "bound": "alu", "kernel": f"dykstra_sort_kernel<{w.M}{', fp32 iterations' if fp32 else ''}>",
             "achieved": round(achieved, 3), "peak": round(peak, 3), "unit": "T lane-ops/s",
             "frac": round(achieved / peak, 4), "traffic": traffic["kernel"], "kernel_ms": round(dyk_ms, 4),
-            "kernel_ms_every_iteration": round(every_ms, 4),
+            "kernel_ms_every_iteration": round(every_ms, 4), "mean_iterations_of_that": round(mean_iters, 1),
+            "rate_of": f"dykstra_sort_kernel<{w.M}{', fp32 iterations' if fp32 else ''}{', early exit' if may_stop else ''}>",
             "useful_ops_per_entry_iteration": ops,
             "note": ("bound by vector-ALU issue, not memory. achieved = useful vector operations (a multiply-add is "
-                     "one) x rows x cols x T / kernel_ms_every_iteration, the time of the kernel where all T iterations "
-                     "are run (with the early exit at a tolerance that no block meets); kernel_ms, from HIP events at "
-                     f"the stage boundaries of {steps} back-to-back passes, is the time of the calls measured, whose "
-                     "waves stop once their state repeats itself bit for bit; peak = "
+                     "one) x rows x cols x mean_iterations_of_that / kernel_ms_every_iteration, both of the kernel named in "
+                     "rate_of: where the kernel stops waves whose state repeats itself bit for bit, that is the early-exit "
+                     "kernel of the same tiling at the smallest tolerance, which does not; kernel_ms, from HIP events at "
+                     f"the stage boundaries of {steps} back-to-back passes, is the time of the calls measured; peak = "
                      + ("the rate measured on this chip for plain (unpacked) fp32 multiplies and adds; the published "
                         "157.3 TFLOP/s (78.6 T multiply-adds/s) needs the packed instructions, which are not used"
                         if fp32 else "256 CUs x 4 SIMDs x 16 lanes/clk x 2.4 GHz, the fp64 vector issue rate")
@@ -326,7 +329,7 @@ def bench_matrix(args, name):
             "stage_ms": {n: round(v, 4) for n, v in zip(binding.STAGE_NAMES, stage_ms)},
             "staged_ms_per_step": round(sum(stage_ms), 4),
             "shader_clock_mhz_in_loop": round(clock_mhz, 1),
-            "vs_9op_model": round(NINE_OP_MODEL_LANE_OPS * entry_iters / (every_ms * 1e-3) / 1e12 / peak, 4),
+            "vs_9op_model": round(NINE_OP_MODEL_LANE_OPS * every_entry_iters / (every_ms * 1e-3) / 1e12 / peak, 4),
             "algorithmic_bytes_per_pass": weights * (esize + 1) + (0 if cs is None else 4 * w.cols),
             "pass_traffic_recorded_in_profiles": traffic["pass"],
         }
@@ -335,14 +338,14 @@ def bench_matrix(args, name):
         if traffic["pass"]:
             roofline["pass_traffic_over_algorithmic"] = round(
                 traffic["pass"] / roofline["algorithmic_bytes_per_pass"], 2)
-        if not fp32 and w.iters > 0:
-            counted = LOOP_VALU_PER_WAVE_ITER.get((w.M, layout_of(w.M, False, nblocks, w.iters)))
+        if not fp32 and w.iters > 0 and not may_stop:  # (the table counts the loops without the early exit)
+            counted = LOOP_VALU_PER_WAVE_ITER.get((w.M, layout))
             if counted:
                 # second view of the same measurement: the vector instructions the loop issues against the issue
                 # slots of the chip (1024 SIMDs, one double-precision wave instruction per 4 cycles), at the
                 # peak clock and at the clock the kernel's first wave saw
                 per_wave, entries = counted
-                issued = per_wave * (weights / entries) * w.iters
+                issued = per_wave * (weights / entries) * mean_iters
                 roofline["loop_valu_per_wave_iteration"] = per_wave
                 roofline["loop_issue_frac_of_peak_clock"] = round(issued / (1024 * (every_ms * 1e-3) * 2.4e9 / 4.0), 4)
                 if clock_mhz > 0:

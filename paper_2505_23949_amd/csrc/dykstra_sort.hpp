@@ -1128,7 +1128,9 @@ __global__ __launch_bounds__((DykstraLaunch<M, FAST, ADAPT, TILES, LONE>::kThrea
         Repeat repeat = Repeat::make(seen[ADAPT ? 0 : wave_in_group], lane);
         if constexpr (!ADAPT) repeat.note(U32, V32own, kWarmIters);
         for (int t = kWarmIters; t < p.T && !all_frozen;) {
-          [[maybe_unused]] const float first = ADAPT ? 0.0f : repeat.at(0);  // (on its way from LDS while the iterations run)
+          // (on its way from LDS while the iterations run; the 64-wide kernel has no register to spare for it: full launches lost 1 %)
+          constexpr bool kEarly = M != 64;
+          [[maybe_unused]] const float first = ADAPT || !kEarly ? 0.0f : repeat.at(0);
           const int stop = (p.T - t > kChunk) ? t + kChunk : p.T;
           // (in fp32 the exchange also carries the updated scalings, which pays wherever a block spans lanes:
           // -6 % for M = 8, -10 % for M = 16; in double the 16-wide kernel is 1.5 % faster with DPP moves)
@@ -1147,7 +1149,7 @@ __global__ __launch_bounds__((DykstraLaunch<M, FAST, ADAPT, TILES, LONE>::kThrea
           } else {
             for (; t < stop; ++t) dykstra_iteration_f32<T, kLdsGather32>(kap32, U32, V32, V32own, Nf, xr, rx);
           }
-          if constexpr (!ADAPT) t = repeat.look(U32, V32own, t, p.T, first);
+          if constexpr (!ADAPT) t = repeat.look(U32, V32own, t, p.T, kEarly ? first : repeat.at(0));
           // (the scalings of the rows and columns this lane owns: every row and column has its owner, and the
           // other copies of a scaling are the same number)
           float mxs = U32[0], mns = U32[0];

@@ -85,13 +85,14 @@ enum {
    * default is rows first as in Algorithm 1 */
   TSENOR_FLAG_COLS_FIRST = 1u << 1,
   /* Run the Dykstra iterations after the fourth in single precision (single-precision multiplies and
-   * adds issue 1.5-1.8 times as fast as double-precision ones on MI355X).  The potentials then carry ~1e-6 of rounding noise: the plan agrees with a
-   * double-precision evaluation to ~1e-5 instead of ~1e-13, and the greedy order - hence the mask - can
+   * adds issue 1.5-1.8 times as fast as double-precision ones on MI355X).  The potentials then carry ~1e-6 of rounding
+   * noise: the plan agrees with a double-precision evaluation to ~1e-5 instead of ~1e-13, and the greedy order - hence the mask - can
    * differ from it in a block where two plan entries are closer than that (none in 8192 blocks of the
    * 16:32 test workload).  Sort keys, swap scores and all results stay in double.  Off by default.  A matrix that
    * runs on the small tiles (below), and one of fewer than 257 blocks of 64 x 64, iterates in double whatever this flag says:
    * such a launch is bound by latency, not by instruction issue, and single precision would buy nothing.  A batch of many such
-   * matrices is another matter: with TSENOR_FLAG_TILES_LARGE they iterate in single precision. */
+   * matrices is another matter, and so are 64 x 64 blocks that converge early in a long run: with TSENOR_FLAG_TILES_LARGE they
+   * iterate in single precision. */
   TSENOR_FLAG_FP32_ITERATIONS = 1u << 2,
   /* Accepted for callers that set them, and without effect: there is one way the greedy selection (Algorithm 2 lines 1-6) is
    * found for each block size.  Setting both is an error. */
@@ -105,7 +106,7 @@ enum {
    * chip anyway; on them the whole path, Algorithm 2 included, runs in one kernel.  A few 64 x 64 blocks
    * (fewer than 257 in a launch) get a workgroup each, in one kernel as well, unless LARGE is asked for.  Default: chosen by
    * the number of blocks of the matrix (and earlier for the large tiles when TSENOR_FLAG_FP32_ITERATIONS is set, which only
-   * they honour; later with tol > 0).  Setting both is an error. */
+   * they honour; for M = 4 and, in double, 8 later with tol > 0).  Setting both is an error. */
   TSENOR_FLAG_TILES_LARGE = 1u << 5,
   TSENOR_FLAG_TILES_SMALL = 1u << 6,
   /* Ablation arm "Simple" of App. B.2.1 in place of Algorithm 2: per block, keep the N largest plan entries
@@ -160,7 +161,8 @@ typedef struct tsenor_problem {
                              TSENOR_ADAPTIVE_CHECK_EVERY-th iteration in which every row and column scaling factor
                              (N / row sum, N / column sum) was within tol of 1.  Changes the result by O(tol).
                              With TSENOR_FLAG_FP32_ITERATIONS the factors after the fourth iteration are
-                             single-precision numbers: a tol below ~1e-6 is then never met */
+                             single-precision numbers: a tol below ~1e-6 is then only met by
+                             factors that are exactly 1 */
   int32_t* iters_done_out; /* device, optional, one int per block (block-row major): iterations that block ran */
 } tsenor_problem;
 

@@ -46,8 +46,8 @@ namespace tsenor_dev {
 constexpr double kMinLogKernel = -700.0;  // exp(-700) is still a normal double
 constexpr int kWarmIters = 4;             // FAST: iterations done in double before switching to fp32
 constexpr int kRowChunks64 = 2;           // M = 64: the 8 x 8 tile is loaded in this many pieces (loads in flight cost registers)
-constexpr int kChunk = 8;                 // iterations between looks for a repetition, FAST: and range checks of the scalings
-constexpr int kRepeatWindow = 24;         // iterations over which a repetition is looked for (RepeatCheck)
+constexpr int kChunk = 8;                 // FAST: iterations between looks for a repetition and range checks of the scalings
+constexpr int kRepeatWindow = 24;         // iterations over which a repetition is looked for (RepeatCheck); in double also between looks
 constexpr int kRaiseBits = 512;           // kKeep: what goes from a large row scaling into its row of the tile (raise_rows)
 constexpr double kRaiseAbove = 0x1p+400;
 constexpr int kDriftBits = 40;            // FAST: fold the fp32 scalings back beyond 2^+-kDriftBits
@@ -295,7 +295,7 @@ __device__ __forceinline__ void all_reduce_max_x(float (&v)[TH]) {
 // Whether a step along a lane-column is a v_permlane swap of two registers instead of a move: both lanes of a pair then hold
 // the same columns in the same registers, the halving step keeps one of them (or the sum of one, in both) in each lane, and no
 // lane selects.
-// 32 lanes apart always (64 x 64: 376 instead of 384 instructions per iteration in double, 279 instead of 283 in fp32); 16 lanes
+// 32 lanes apart always (64 x 64: 8 of 382 instructions per iteration fewer in double, 4 of 283 in fp32); 16 lanes
 // apart only where a wave has its SIMD to itself and waits out the latency of the LDS crossbar (4096x32 16:32: 99.6 us a call
 // through the crossbar, 94.4 with swaps; with two waves on a SIMD 148.3 and 151.2), and for the finest tiles, whose steps
 // have no register to split (512x640 8:16, two waves on some SIMDs: 80.0 and 76.3).
@@ -693,7 +693,9 @@ __device__ __forceinline__ float dykstra_iteration_f32(const float (&kap)[TH][TW
 // ago, all later states are known, and whole periods of d iterations are as good as done.
 // Once a block has converged to the precision of its numbers its last bits run through a short cycle: of 512 blocks of 16:32
 // with fp32 iterations 57 % end in one of period 2, 14 % of 1, 4, 6 or 8, hardly any in a period that does not divide 24.  So
-// the state is compared every kChunk iterations with one 8, 16 or 24 iterations old.
+// the fp32 loops compare the state every kChunk iterations with one 8, 16 or 24 iterations old, the double ones every kRepeatWindow
+// iterations with the one before those.  The large tiles that fold (32 x 32 and 64 x 64 in double), the team and the kernels of the
+// early exit do not look.
 // IN_LDS: that state is kept in LDS (`space`), for the kernels whose register budget is that of their loop; small launches, where a
 // wave has its SIMD to itself and waits for every LDS access, keep it in registers.
 template <class real, int OWN_R, int OWN_C, bool IN_LDS>
@@ -761,19 +763,22 @@ struct DykstraLaunch {
   // with the early exit the waves of a launch run for very different times; one-wave workgroups let the
   // dispatcher refill every wave slot as it frees (a four-wave workgroup holds its slots until its slowest wave).
   // The 64-wide fp32 waves, one block each, leave when their block repeats itself: two to a workgroup (8192x28672 student, T =
-  // 500: 2.91 ms, one 2.94, four 3.25; 4096x4096 normal, which does not repeat, T = 300: 563 us, 610, 581).  In a launch of one wave per SIMD four, which go to the four of a CU
-  // (2048x2048 normal, T = 300: 285 us, two 302).
+  // 500: 2.91 ms, one 2.94, four 3.25; 4096x4096 normal, which does not repeat, T = 300: 563 us, 610, 581).  In a launch of one
+  // wave per SIMD four, which go to the four of a CU (2048x2048 normal, T = 300: 285 us, two 302).
   // The small tiles carry the rounding behind the iterations, whose steps synchronise one wave at a time.
   static constexpr int kWavesPerGroup = (ADAPT || TILES != kLargeTiles) ? 1 : FAST && M == 64 && !LONE ? 2 : 4;
   static constexpr int kThreads = kWavesPerGroup * kWave;
   // Waves per SIMD the register budget is set for.  Double: the loop holds twice the state of the fp32 one, two waves of up
   // to 256 registers.  FAST: the more waves, the nearer the issue of plain fp32 instructions comes to its limit (1.13 ns
-  // per instruction and SIMD with two waves, 1.05 with four).  M = 32: four waves of 128 registers, the loop fits and 42
-  // registers of the double-precision code around it spill (4096x14336: iteration kernel 1425 us, 1470 with three waves).
-  // M = 16: three (four the same to 0.4 % slower).  M = 8: four (129 registers with three; three spill outside the loop).  M = 4:
-  // four fit whatever is asked for (five spill: 1 % slower).  M = 64: three, 93 registers spill outside the loop (8192x28672, T = 500: 10.5 ms, two waves 11.0, four 31);
-  // with the early exit, where a block may run a dozen iterations and the code around the loop is most of the work, two
-  // (8192x8192: 0.85 ms, three 1.05).
+  // per instruction and SIMD with two waves, 1.05 with four).  M = 32: four waves of 128 registers, the loop fits and 37
+  // registers of the double-precision code around it spill (whole calls with four / three waves, us: 4096x14336 Wanda-style 1364 /
+  // 1464, normal 1745 / 1764; 4096 blocks, two waves to a SIMD anyway, 172 / 168).  M = 16: three (four the same to 0.4 % slower).
+  // M = 8: four (129 registers with three; three spill outside the loop).  M = 4: four fit whatever is asked for (five spill: 1 %
+  // slower).  M = 64: three, 131 registers spill outside the loop.  With three / two waves, T = 300 normal and T = 500 student-t,
+  // of which blocks run from 50 iterations to all: 57 344 blocks 7046 / 7128 and 3080 / 3200, 16 384 Wanda-style 1924 / 2066; 4096
+  // blocks 572 / 532 and 549 / 531, 1024 blocks, a wave to a SIMD, 269 / 254 and 394 / 379: full launches decide.  With the early
+  // exit, where a block may run a dozen iterations and the code around the loop is most of the work, two (8192x8192: 0.85 ms,
+  // three 1.05).
   static constexpr int kWavesPerSimd = FAST && !(M == 64 && ADAPT) ? (M == 32 || M == 8 ? 4 : 3) : 2;
 };
 
@@ -1133,7 +1138,7 @@ __global__ __launch_bounds__((DykstraLaunch<M, FAST, ADAPT, TILES, LONE>::kThrea
           [[maybe_unused]] const float first = ADAPT || !kEarly ? 0.0f : repeat.at(0);
           const int stop = (p.T - t > kChunk) ? t + kChunk : p.T;
           // (in fp32 the exchange also carries the updated scalings, which pays wherever a block spans lanes:
-          // -6 % for M = 8, -10 % for M = 16; in double the 16-wide kernel is 1.5 % faster with DPP moves)
+          // -6 % for M = 8, -10 % for M = 16)
           constexpr bool kLdsGather32 = M >= 8;
           __shared__ float2 xrows32[kLdsGather32 ? WPG : 1][kLdsGather32 ? kWave >> T::NX : 1][TH];
           float2* xr = kLdsGather32 ? &xrows32[wave_in_group][lane >> T::NX][0] : nullptr;

@@ -42,13 +42,16 @@ struct Variant {
 // T = 20 and T = 100 put the lines at the same places within 2 us, but for M = 16 at T = 20 (65 536 blocks 146 / 152), and for M = 4
 // from 102 401 to 114 688 blocks, where the large tiles make up for their second kernel only over many iterations (108 240
 // blocks, T = 20, 100, 150, 200, 300: 29.7 / 32.0, 63.0 / 64.8, 85.3 / 86.0, 107.5 / 107.6, 151.6 / 150.0; student weights the same).
-// With the early exit (`adaptive`) a wave runs until the slowest of its blocks stops, and the large tiles put up to four times
-// as many blocks into it, so M <= 8 keeps the small tiles for longer.  T = 300, normal weights, tol 1e-2 and 1e-3 (small /
-// large double / large fp32):
-//   M = 4: 52 000 blocks 67 / 87 / 72 and 116 / 115 / 95, 60 000 blocks 69 / 87 and 116 / 116, 120 000 blocks 117 / 133 and
-//     211 / 195; M = 8: 9500 blocks 74 / 100 / 91 and 109 / 111 / 104, 12 500 blocks 76 / 100 / 90 and 130 / 108 / 99;
-//   M = 4 and 8, heavy-tailed weights, tol 1e-3: 60 000 blocks 43 / 70, 12 500 blocks 37 / 43;
-//   M = 16, heavy-tailed: 8600 blocks 54 / - / 57.
+// Where states repeat the small tiles gain more than the large ones, which put up to four times as many blocks into a wave, in
+// single precision too (T = 500, student weights, tau = 0.01, small / large fp32): M = 32, 2000 blocks 177 / 222; M = 16, 8000
+// blocks 160 / 200; M = 8, 12 000 blocks 101 / 130; with tau = 0.002, where fewer repeat, 221 / 198, 197 / 209 and 130 / 151.
+// With the early exit (`adaptive`) a wave runs until the slowest of its blocks stops, and so M = 4 keeps the small tiles for longer,
+// M = 8 in double a little.  T = 300 (small / large double / large fp32), tol 1e-2 and 1e-3 on normal weights, 1e-5 on student ones:
+//   M = 4: 54 000 blocks 88 / 98 / 71, 143 / 134 / 96 and 57 / 86 / 69; 58 000 blocks 85 / 101 / 72, 141 / 132 / 93 and 54 / 91 /
+//     66; 114 000 blocks 130 / 157 / 90, 226 / 226 / 117 and 63 / 102 / 79; 120 000 blocks 138 / 158, 254 / 228 and 65 / 103;
+//   M = 8: 12 000 blocks 83 / 99 / 75, 124 / 131 / 102 and 39 / 53 / 46; 13 000 blocks 96 / 111 / 82, 150 / 128 / 99 and 41 / 55 / 47;
+//   M = 16: 9000 blocks 151 / 190 / 117, 255 / 312 / 158 and 46 / 68 / 62; 60 000 blocks 572 / 620, 1044 / 1114 and 145 / 163.
+// (The sides change with the tolerance and the weights; the lines weigh them.)
 constexpr bool small_tiles_win(int M, bool fp32, bool adaptive, int iters, int64_t nblocks) {
   if (M == 4 && adaptive) return nblocks <= (fp32 ? 55000 : 114688);
   if (M == 4) return nblocks <= 49152 || (!fp32 && nblocks > 65536 && nblocks <= (iters <= 150 ? 114688 : 102400));
@@ -74,7 +77,9 @@ constexpr unsigned kSimds = 1024;
 // 254, 256 blocks 180 / 296 / 270, 300 blocks 354 / 300.  Fused: 4 matrices of 256 blocks 677 / 307, 16 2684 / 1009.
 constexpr int64_t team_below_blocks(int M) { return M == 64 ? 257 : 0; }
 // Below as many blocks in a matrix it iterates in the team's order, in double whatever the fp32 flag says.  A call of its own
-// gains from that (256 blocks 180 us, 270 with fp32 iterations on the large tiles); a fused launch of many takes the large
+// gains from that (256 blocks, T = 300: normal 179 us, 246 with fp32 iterations on the large tiles, Wanda-style 192 / 303), but
+// where all blocks repeat early, which the team does not look for (student, T = 500: tau = 0.01 276 / 125, tau = 0.002 269 /
+// 326).  A fused launch of many takes the large
 // tiles in double where they could iterate in single precision (16 matrices of 64 blocks 304 / 268, of 128 blocks 510 / 332,
 // of 256 blocks 1009 / 673), which a caller that wants them asks for with TSENOR_FLAG_TILES_LARGE.
 

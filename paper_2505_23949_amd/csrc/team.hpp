@@ -12,7 +12,7 @@
 // The rows are rescaled between the LDS write and the barrier.  Rounding follows in the first wave (round_blocks).
 // 64 blocks of 32:64, T = 300: 286 us a call on the large tiles (254 with fp32 iterations), 171 here; of the 0.5 us per
 // iteration the issue of two waves' 93 instructions is 0.36, the LDS round trip with the barrier the rest.  (32 x 32 blocks on
-// four waves the same way: 285 ns per iteration, as on one wave with its 110 instructions - not kept.)  A launch that fills the
+// four waves the same way: 285 ns per iteration; one wave takes 267, for 115 instructions.)  A launch that fills the
 // chip takes the large tiles, which add in the same order with fewer instructions per block (374 against 744).
 #pragma once
 #include "dykstra_sort.hpp"

@@ -50,6 +50,9 @@ constexpr int kChunk = 8;                 // FAST: iterations between looks for 
 constexpr int kRepeatWindow = 24;         // iterations over which a repetition is looked for (RepeatCheck); in double also between looks
 constexpr int kRaiseBits = 512;           // kKeep: what goes from a large row scaling into its row of the tile (raise_rows)
 constexpr double kRaiseAbove = 0x1p+400;
+constexpr double kSmallStep = 0x1p-32;    // near_the_end(): factors of an iteration within this of 1 ...
+constexpr double kNearCap = 0x1p-20;      // ... no entry of the plan as near to the cap as this ...
+constexpr float kIncrementSum = 0x1p-26f; // ... and the sum of the increments before the plan is formed anew
 constexpr int kDriftBits = 40;            // FAST: fold the fp32 scalings back beyond 2^+-kDriftBits
 constexpr double kLogFloor32 = -83.0;     // FAST: rebuilt entries are kept within [e^-83, e^55] ~ [2^-120, 2^80]
 constexpr double kLogCeil32 = 55.0;
@@ -210,6 +213,14 @@ __device__ __forceinline__ int column_lane(int gx, int q) {
 #pragma unroll
   for (int s = 0; s < T::NY; ++s) turned |= T::YM[s] == 7;
   return turned && (q & 4) ? gx ^ 3 : gx;
+}
+
+// Whether the last iterations of a wave are done in increments (near_the_end): where a launch may take two layouts of a block whose
+// waves hold other numbers of blocks (order_run), or rows are summed in pairs (32-wide small tiles), the results would differ.  4 x 4
+// blocks have 64 or 16 to a wave, too many to converge together; on the 8-wide small tiles it gained nothing (the look 1 %).
+template <int M, int TILES>
+constexpr bool increments_at_the_end() {
+  return (TILES == kLargeTiles && (M == 8 || M == 16 || M == 32)) || (TILES == kSmallTiles && M == 16);
 }
 
 // registers a lane owns after a reduce-scatter of `count` values over 2^steps lanes (at least one)
@@ -592,6 +603,196 @@ __device__ __forceinline__ double dykstra_iteration(double (&kap)[TH][TW], Tile&
   return worst;
 }
 
+// The end of the iterations in double, in increments.  Once every factor of an iteration is within kSmallStep of 1 and no entry of
+// the plan is within kNearCap of the cap, an entry stays on its side of it for as long as the scalings move by less than that, and
+// an iteration is a linear map of the relative changes rho_i, gamma_j that the last one made to U_i and V_j (p: the plan where it
+// is below the cap, n_i and m_j the entries at the cap in row i and column j):
+//     rho'_i  = (n_i rho_i - sum_p p_ij gamma_j) / N
+//     gamma'_j = (m_j gamma_j - sum_p p_ij rho'_i - sum_cap (rho'_i - rho_i)) / N
+// up to their squares, 2^-64.  The increments are iterated in fp32 and their sums go into the double scalings: a relative error
+// of 2^-24 of an increment below 2^-32 is less than the rounding of a double iteration, whose factors carry 2^-48.  When the
+// iterations that are left, were each to change an entry by as much as the last one did, add up to less than 2^-60, all are done.
+// 96 plain fp32 instructions per lane of a 32 x 32 block for the 120 of an iteration in double, and exchanges of one instruction
+// instead of three: 115 at 2.5-4 cycles where an iteration in double has 162 at 4.  Calls before / with it (us): 16:32 4096x14336
+// bf16 Wanda-style, T = 300, 2792 / 2515; 8:16 3280x12832 Wanda-style tau = 0.02 2199 / 1276; 4:8 4096x4096 student-t 537 / 326; 8:16
+// 1072x2928 with its plan, small tiles, 198 / 184; normal weights, which never come so near, 842 / 841 (8:16) and 2535 / 2548 (4:8).
+// Error of the plan against a 64-bit evaluation (8, 16 and 32 wide, T = 100 to 500, three distributions): 0.98 of what it was, from
+// 0.86 to 1.03.
+// Called behind an iteration (t are done) with U_before and V_before the scalings before it; nothing happens unless the conditions
+// hold for the whole wave.  Returns the number of iterations done; if that is less than T the state is that after them.
+template <class T, Form FORM, bool LDS, bool ADAPT, int LPB, bool LONE, class Tile, class Freeze, int TH, int TW, int NU>
+__device__ __forceinline__ int near_the_end(double (&kap)[TH][TW], Tile& x, double (&U)[NU], double (&V)[TW],
+                                            double (&Vown)[owned(TW, T::NY)], const double (&U_before)[owned(TH, T::NX)],
+                                            const double (&V_before)[owned(TW, T::NY)], int N, int t, int iters, double tol, float2* xr,
+                                            int rx, const bool& frozen, Freeze& freeze_if) {
+  constexpr int OWN_R = owned(TH, T::NX), OWN_C = owned(TW, T::NY);
+  static_assert(FORM != kRecompute, "the increments take the registers of the capped entries");
+  bool moves = false;
+#pragma unroll
+  for (int a = 0; a < OWN_R; ++a) moves |= !(fabs(U[a] - U_before[a]) <= kSmallStep * U_before[a]);
+#pragma unroll
+  for (int b = 0; b < OWN_C; ++b) moves |= !(fabs(Vown[b] - V_before[b]) <= kSmallStep * V_before[b]);
+  if (__any(moves)) return t;
+  bool near = false;
+#pragma unroll
+  for (int a = 0; a < TH; ++a) {
+#pragma unroll
+    for (int b = 0; b < TW; ++b) near |= !(fabs((FORM == kKeep ? x[a][b] : kap[a][b]) * V[b] - 1.0) > kNearCap);
+    __builtin_amdgcn_sched_barrier(0);
+  }
+  if (__any(near)) return t;
+  // the plan and the entries at the cap, over N (from an opaque copy of V: the products of the look are not kept for it)
+  const float inv = 1.0f / (float)N;
+  float p[TH][TW], c[TH][TW];
+  double Vc[TW];
+#pragma unroll
+  for (int b = 0; b < TW; ++b) {
+    Vc[b] = V[b];
+    asm volatile("" : "+v"(Vc[b]));
+  }
+#pragma unroll
+  for (int a = 0; a < TH; ++a) {
+#pragma unroll
+    for (int b = 0; b < TW; ++b) {
+      const double entry = (FORM == kKeep ? x[a][b] : kap[a][b]) * Vc[b];
+      const bool at_cap = entry > 1.0;
+      p[a][b] = at_cap ? 0.0f : (float)entry * inv;
+      c[a][b] = at_cap ? inv : 0.0f;
+    }
+    __builtin_amdgcn_sched_barrier(0);
+  }
+  float rho[TH], gamma[TW], rows_at_cap[TH], cols_at_cap[TW];
+#pragma unroll
+  for (int a = 0; a < TH; ++a) {
+    rows_at_cap[a] = c[a][0];
+#pragma unroll
+    for (int b = 1; b < TW; ++b) rows_at_cap[a] += c[a][b];
+  }
+#pragma unroll
+  for (int b = 0; b < TW; ++b) {
+    cols_at_cap[b] = c[0][b];
+#pragma unroll
+    for (int a = 1; a < TH; ++a) cols_at_cap[b] += c[a][b];
+  }
+  reduce_scatter_x<T, float, TH>(rows_at_cap);
+  reduce_scatter_y<T, float, TW>(cols_at_cap);
+  float gamma_own[OWN_C], sum_r[OWN_R] = {}, sum_c[OWN_C] = {};
+#pragma unroll
+  for (int a = 0; a < OWN_R; ++a) rho[a] = (float)((U[a] - U_before[a]) * __builtin_amdgcn_rcp(U_before[a]));
+#pragma unroll
+  for (int b = 0; b < OWN_C; ++b)
+    gamma[b] = gamma_own[b] = (float)((Vown[b] - V_before[b]) * __builtin_amdgcn_rcp(V_before[b]));
+  if constexpr (!LDS) all_gather_x<T, float, TH>(rho);
+  all_gather_y<T, float, TW>(gamma);
+  for (bool go_on = true; go_on;) {
+    const int stop = iters - t > kChunk ? t + kChunk : iters;
+    float largest = 0.0f, s[TH];
+    for (; t < stop; ++t) {
+      float d[TH], q[TW];
+#pragma unroll
+      for (int b = 0; b < TW; ++b)
+#pragma unroll
+        for (int a = 0; a < TH; ++a) s[a] = b == 0 ? p[a][b] * gamma[b] : fmaf(p[a][b], gamma[b], s[a]);
+      chain_phase<LONE>(true);
+      reduce_scatter_x<T, float, TH>(s);
+      largest = 0.0f;
+#pragma unroll
+      for (int a = 0; a < OWN_R; ++a) {
+        s[a] = fmaf(rows_at_cap[a], rho[a], -s[a]);
+        if constexpr (ADAPT) s[a] = frozen ? 0.0f : s[a];
+        d[a] = s[a] - rho[a];
+        rho[a] = s[a];
+        sum_r[a] += s[a];
+        largest = fmaxf(largest, fabsf(s[a]));
+      }
+      if constexpr (LDS) {
+#pragma unroll
+        for (int a = 0; a < OWN_R; ++a) xr[a ^ rx] = make_float2(s[a], d[a]);
+        asm volatile("" ::: "memory");
+#pragma unroll
+        for (int a = OWN_R; a < TH; ++a) {
+          const float2 rd = xr[a ^ rx];
+          s[a] = rd.x;
+          d[a] = rd.y;
+        }
+        asm volatile("" ::: "memory");
+      } else {
+        all_gather_x<T, float, TH>(s);
+#pragma unroll
+        for (int a = OWN_R; a < TH; ++a) {
+          d[a] = s[a] - rho[a];
+          rho[a] = s[a];
+        }
+      }
+      chain_phase<LONE>(false);
+#pragma unroll
+      for (int b = 0; b < TW; ++b) {
+#pragma unroll
+        for (int a = 0; a < TH; ++a) {
+          q[b] = a == 0 ? p[a][b] * s[a] : fmaf(p[a][b], s[a], q[b]);
+          q[b] = fmaf(c[a][b], d[a], q[b]);
+        }
+      }
+      chain_phase<LONE>(true);
+      reduce_scatter_y<T, float, TW>(q);
+#pragma unroll
+      for (int b = 0; b < OWN_C; ++b) {
+        gamma_own[b] = fmaf(cols_at_cap[b], gamma_own[b], -q[b]);
+        if constexpr (ADAPT) gamma_own[b] = frozen ? 0.0f : gamma_own[b];
+        sum_c[b] += gamma_own[b];
+        gamma[b] = gamma_own[b];
+        largest = fmaxf(largest, fabsf(gamma_own[b]));
+      }
+      all_gather_y<T, float, TW>(gamma);
+      chain_phase<LONE>(false);
+      if constexpr (ADAPT) {
+        // (a tolerance below the precision of a double is never met, as by the factors of the iterations in double)
+        if ((t + 1) % TSENOR_ADAPTIVE_CHECK_EVERY == 0 && tol >= 0x1p-53) freeze_if(block_max<LPB>((double)largest) <= tol, t + 1);
+      }
+    }
+    // What the last one changed in the logarithm of an entry, rho_i + gamma_j (opposite constants in the two change nothing, and the
+    // map keeps what rounding leaves of them), is what may be left for each of the others.
+    float rho_hi = s[0], rho_lo = s[0], gamma_hi = gamma[0], gamma_lo = gamma[0], sum = 0.0f;
+#pragma unroll
+    for (int a = 1; a < TH; ++a) rho_hi = fmaxf(rho_hi, s[a]), rho_lo = fminf(rho_lo, s[a]);
+#pragma unroll
+    for (int b = 1; b < TW; ++b) gamma_hi = fmaxf(gamma_hi, gamma[b]), gamma_lo = fminf(gamma_lo, gamma[b]);
+    const float step = fmaxf(fabsf(rho_hi + gamma_hi), fabsf(rho_lo + gamma_lo));
+#pragma unroll
+    for (int a = 0; a < OWN_R; ++a) sum = fmaxf(sum, fabsf(sum_r[a]));
+#pragma unroll
+    for (int b = 0; b < OWN_C; ++b) sum = fmaxf(sum, fabsf(sum_c[b]));
+    if (!__any(!(step * (float)(iters - t) < 0x1p-60f))) t = iters;
+    go_on = t < iters && !__any(!(sum < kIncrementSum && largest <= 2.0f * (float)kSmallStep));
+  }
+#pragma unroll
+  for (int a = 0; a < OWN_R; ++a) U[a] = fma(U[a], (double)sum_r[a], U[a]);
+#pragma unroll
+  for (int b = 0; b < OWN_C; ++b) V[b] = Vown[b] = fma(Vown[b], (double)sum_c[b], Vown[b]);
+  all_gather_y<T, double, TW>(V);
+  // (the tile also when all iterations are done: it need not be kept beside p and c then)
+  float all[TH];
+#pragma unroll
+  for (int a = 0; a < OWN_R; ++a) all[a] = sum_r[a];
+  all_gather_x<T, float, TH>(all);
+#pragma unroll
+  for (int a = 0; a < TH; ++a) {
+    const double by = (double)all[a];
+    if constexpr (FORM == kKeep) {
+      if (a >= OWN_R) U[a] = fma(U[a], by, U[a]);
+    }
+#pragma unroll
+    for (int b = 0; b < TW; ++b) {
+      if constexpr (FORM == kKeep)
+        x[a][b] = kap[a][b] * U[a];
+      else
+        kap[a][b] = fma(kap[a][b], by, kap[a][b]);
+    }
+    __builtin_amdgcn_sched_barrier(0);
+  }
+  return t;
+}
+
 // x * y with the result clamped to [0, 1] by the output modifier: one instruction at the full fp32 rate
 // (measured on MI355X: 1.2 ns per wave-instruction per SIMD, as a plain v_mul_f32; v_min_f32 / v_max_f32 /
 // v_med3_f32 take 1.9 ns).  Written as the bare instruction so that it stays this one.
@@ -695,7 +896,7 @@ __device__ __forceinline__ float dykstra_iteration_f32(const float (&kap)[TH][TW
 // with fp32 iterations 57 % end in one of period 2, 14 % of 1, 4, 6 or 8, hardly any in a period that does not divide 24.  So
 // the fp32 loops compare the state every kChunk iterations with one 8, 16 or 24 iterations old, the double ones every kRepeatWindow
 // iterations with the one before those.  The large tiles that fold (32 x 32 and 64 x 64 in double), the team and the kernels of the
-// early exit do not look.
+// early exit do not look.  (In double the increments of near_the_end() usually come first where there are any.)
 // IN_LDS: that state is kept in LDS (`space`), for the kernels whose register budget is that of their loop; small launches, where a
 // wave has its SIMD to itself and waits for every LDS access, keep it in registers.
 template <class real, int OWN_R, int OWN_C, bool IN_LDS>
@@ -765,11 +966,14 @@ struct DykstraLaunch {
   // The 64-wide fp32 waves, one block each, leave when their block repeats itself: two to a workgroup (8192x28672 student, T =
   // 500: 2.91 ms, one 2.94, four 3.25; 4096x4096 normal, which does not repeat, T = 300: 563 us, 610, 581).  In a launch of one
   // wave per SIMD four, which go to the four of a CU (2048x2048 normal, T = 300: 285 us, two 302).
+  // The iterations in double of 8-, 16- and 32-wide blocks end at different times too (near_the_end): one (16:32 4096x14336
+  // Wanda-style 2515 us, two 2534, four 2578; normal weights the same within 0.3 %).
   // The small tiles carry the rounding behind the iterations, whose steps synchronise one wave at a time.
-  static constexpr int kWavesPerGroup = (ADAPT || TILES != kLargeTiles) ? 1 : FAST && M == 64 && !LONE ? 2 : 4;
+  static constexpr int kWavesPerGroup = (ADAPT || TILES != kLargeTiles) ? 1 : M == 64 && FAST && !LONE ? 2 : FAST || M == 4 || M == 64 ? 4 : 1;
   static constexpr int kThreads = kWavesPerGroup * kWave;
   // Waves per SIMD the register budget is set for.  Double: the loop holds twice the state of the fp32 one, two waves of up
-  // to 256 registers.  FAST: the more waves, the nearer the issue of plain fp32 instructions comes to its limit (1.13 ns
+  // to 256 registers; the 8-wide large tiles and the 16-wide small ones fit more with near_the_end() in them as well (168 registers;
+  // 128, of which six spill outside the loops).  FAST: the more waves, the nearer the issue of plain fp32 instructions comes to its limit (1.13 ns
   // per instruction and SIMD with two waves, 1.05 with four).  M = 32: four waves of 128 registers, the loop fits and 37
   // registers of the double-precision code around it spill (whole calls with four / three waves, us: 4096x14336 Wanda-style 1364 /
   // 1464, normal 1745 / 1764; 4096 blocks, two waves to a SIMD anyway, 172 / 168).  M = 16: three (four the same to 0.4 % slower).
@@ -779,7 +983,8 @@ struct DykstraLaunch {
   // blocks 572 / 532 and 549 / 531, 1024 blocks, a wave to a SIMD, 269 / 254 and 394 / 379: full launches decide.  With the early
   // exit, where a block may run a dozen iterations and the code around the loop is most of the work, two (8192x8192: 0.85 ms,
   // three 1.05).
-  static constexpr int kWavesPerSimd = FAST && !(M == 64 && ADAPT) ? (M == 32 || M == 8 ? 4 : 3) : 2;
+  static constexpr int kWavesPerSimd =
+      FAST && !(M == 64 && ADAPT) ? (M == 32 || M == 8 ? 4 : 3) : !LONE && M == 16 && TILES == kSmallTiles ? 4 : M == 8 && TILES == kLargeTiles ? 3 : 2;
 };
 
 // ZERO_T: the instantiation for T = 0 (no iterations, keys are K itself).  It is a template parameter
@@ -1000,20 +1205,45 @@ __global__ __launch_bounds__((DykstraLaunch<M, FAST, ADAPT, TILES, LONE>::kThrea
             }
           }
         };
+        constexpr bool kEnd = increments_at_the_end<M, TILES>();
+        // Behind a window of iterations over which a scaling of every lane has hardly changed (`first`: what it was before them): one
+        // more iteration, whose factors near_the_end() looks at, and the rest in increments if it may.
+        [[maybe_unused]] const auto try_the_end = [&]([[maybe_unused]] int& t, [[maybe_unused]] double first, [[maybe_unused]] auto&& one_more) {
+          if constexpr (kEnd) {
+            if (t + 1 >= p.T || __any(!(fabs(Uown[0] - first) <= kRepeatWindow * kSmallStep * first))) return false;
+            double U_before[OWN_R], V_before[OWN_C];
+#pragma unroll
+            for (int a = 0; a < OWN_R; ++a) U_before[a] = Uown[a];
+#pragma unroll
+            for (int b = 0; b < OWN_C; ++b) V_before[b] = Vown[b];
+            one_more();
+            const int before = t;
+            t = near_the_end<T, kForm, kLds, ADAPT, LPB, LONE>(kap, x, Uown, V, Vown, U_before, V_before, p.N, t, p.T, p.tol,
+                                                               reinterpret_cast<float2*>(xr), rx, frozen, freeze_if);
+            return t > before;
+          } else {
+            return false;
+          }
+        };
         if constexpr (ADAPT) {
           // iteration count as a bound: every TSENOR_ADAPTIVE_CHECK_EVERY-th iteration the largest |factor - 1|
           // of the block is compared with the tolerance; a block that passes is frozen, the wave leaves when
           // all its blocks are
           bool all_frozen = false;
-          for (int t = 0; t < p.T && !all_frozen;) {
-            const int stop = kKept && p.T - t > kRepeatWindow ? t + kRepeatWindow : p.T;
-            for (; t < stop && !all_frozen; ++t) {
-              const double worst = iterate();
-              if ((t + 1) % TSENOR_ADAPTIVE_CHECK_EVERY == 0) {
-                freeze_if(block_max<LPB>(worst) <= p.tol, t + 1);
-                all_frozen = __all(frozen);
-              }
+          int t = 0;
+          const auto one = [&]() {
+            const double worst = iterate();
+            ++t;
+            if (t % TSENOR_ADAPTIVE_CHECK_EVERY == 0) {
+              freeze_if(block_max<LPB>(worst) <= p.tol, t);
+              all_frozen = __all(frozen);
             }
+          };
+          while (t < p.T && !all_frozen) {
+            const int stop = (kKept || kEnd) && p.T - t > kRepeatWindow ? t + kRepeatWindow : p.T;
+            [[maybe_unused]] const double first = Uown[0];
+            while (t < stop && !all_frozen) one();
+            if (!all_frozen) try_the_end(t, first, one);
             if constexpr (kKept) raise_rows();
           }
         } else if constexpr (kKept) {
@@ -1025,8 +1255,19 @@ __global__ __launch_bounds__((DykstraLaunch<M, FAST, ADAPT, TILES, LONE>::kThrea
             const int stop = (p.T - t > kRepeatWindow) ? t + kRepeatWindow : p.T;
             const double first = repeat.at(0);
             for (; t < stop; ++t) iterate();
+            const bool summed = try_the_end(t, first, [&]() { iterate(), ++t; });
             raise_rows();
-            t = repeat.look(Uown, Vown, t, p.T, first);
+            if (summed)
+              repeat.note(Uown, Vown, t);
+            else
+              t = repeat.look(Uown, Vown, t, p.T, first);
+          }
+        } else if constexpr (kEnd) {
+          for (int t = 0; t < p.T;) {
+            const int stop = (p.T - t > kRepeatWindow) ? t + kRepeatWindow : p.T;
+            const double first = Uown[0];
+            for (; t < stop; ++t) iterate();
+            try_the_end(t, first, [&]() { iterate(), ++t; });
           }
         } else {
           for (int t = 0; t < p.T; ++t) iterate();

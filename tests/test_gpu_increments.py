@@ -1,0 +1,108 @@
+"""The last iterations in double, done in increments: the plan is that of the log-domain oracle after T iterations."""
+import numpy as np
+import pytest
+
+import oracle
+
+pytestmark = pytest.mark.gpu
+
+# The factors of an iteration carry 2^-48 and an entry of the plan what its block's convergence makes of them: up to 1e-12 with and
+# without increments (those add 2^-24 of changes below 2^-32).
+PLAN_ATOL = 1e-11
+
+
+def _weights(M, dist, blocks):
+    rng = np.random.Generator(np.random.Philox(60 + M))
+    if dist == "normal":
+        return rng.standard_normal((blocks[0] * M, blocks[1] * M), dtype=np.float32)
+    W = rng.standard_t(3, (blocks[0] * M, blocks[1] * M)).astype(np.float32)
+    if dist == "mixed":  # waves in which one block keeps the others from their increments
+        W[:, :] *= 0.02
+        for j in range(0, blocks[1], 7):
+            W[:, j * M:(j + 1) * M] = rng.standard_normal((blocks[0] * M, M), dtype=np.float32)
+    return W
+
+
+def _plan(W, N, M, tau, T, flags, tol=0.0):
+    import torch
+
+    from paper_2505_23949_amd import binding as b
+
+    got = b.solve(torch.from_numpy(W).to("cuda:0"), N, M, tau, T, tau_mode=b.TSENOR_TAU_REL_MATRIX_MAX, flags=flags, tol=tol, want_plan=True,
+                  want_iters_done=tol > 0.0)
+    torch.cuda.synchronize()
+    return got["plan"].cpu().numpy(), got["iters_done"].cpu().numpy() if tol > 0.0 else None
+
+
+@pytest.mark.parametrize("M,tiles", [(8, "large"), (16, "large"), (32, "large"), (16, "small")])
+@pytest.mark.parametrize("dist,tau", [("student", 0.01), ("student", 0.05), ("mixed", 0.02), ("normal", 0.2)])
+def test_plan_after_increments(M, tiles, dist, tau):
+    # before, at and behind the first windows, and every remainder of the eight increments between two looks
+    from paper_2505_23949_amd import binding as b
+
+    flags = b.TSENOR_FLAG_TILES_LARGE if tiles == "large" else b.TSENOR_FLAG_TILES_SMALL
+    W = _weights(M, dist, (4, 64 // M * 2 + 1))
+    te = oracle.tau_eff(np.abs(W), tau, oracle.TAU_REL_MATRIX_MAX)
+    for N in (M // 2, M // 4 + 1):
+        for T in (24, 25, 26, 48, 50, 73, 97, 100, *range(121, 129), 400):
+            for more in (0, b.TSENOR_FLAG_COLS_FIRST) if T == 100 else (0,):
+                print(f"[case] increments {N}:{M} {tiles} {dist} tau={tau} T={T} flags={flags | more}", flush=True)
+                ref = np.exp(oracle.dykstra(np.abs(W), N, M, te, T, cols_first=more != 0))
+                plan, _ = _plan(W, N, M, tau, T, flags | more)
+                assert np.abs(plan - ref).max() < PLAN_ATOL
+                same, done = _plan(W, N, M, tau, T, flags | more, 1e-300)
+                assert np.array_equal(plan, same)
+
+
+@pytest.mark.parametrize("M", [8, 16])
+def test_increments_of_many_iterations(M):
+    # slow blocks: the increments' sum passes its bound, and the plan they act on is formed anew
+    from paper_2505_23949_amd import binding as b
+
+    W, N, tau, T = _weights(M, "normal", (2, 64 // M)), M // 2, 0.02, 30000
+    te = oracle.tau_eff(np.abs(W), tau, oracle.TAU_REL_MATRIX_MAX)
+    print(f"[case] increments of many iterations {N}:{M}", flush=True)
+    ref = np.exp(oracle.dykstra(np.abs(W), N, M, te, T))
+    plan, _ = _plan(W, N, M, tau, T, b.TSENOR_FLAG_TILES_LARGE)
+    assert np.abs(plan - ref).max() < 1e-9
+
+
+@pytest.mark.parametrize("M", [8, 16, 32])
+def test_tolerance_met_in_increments(M):
+    # a tolerance far below where they begin, and far above the rounding of the factors: the count is the oracle's
+    from paper_2505_23949_amd import binding as b
+
+    W, N, tau, T, tol = _weights(M, "student", (3, 64 // M * 2)), M // 2, 0.05, 600, 1e-12
+    te = oracle.tau_eff(np.abs(W), tau, oracle.TAU_REL_MATRIX_MAX)
+    print(f"[case] tolerance met in increments {N}:{M}", flush=True)
+    log_S, done_ref = oracle.dykstra_adaptive(np.abs(W), N, M, te, T, tol)
+    plan, done = _plan(W, N, M, tau, T, b.TSENOR_FLAG_TILES_LARGE, tol)
+    # (factors at the tolerance carry 4e-15 and the increments 1e-7 of themselves: one look earlier or later)
+    assert np.abs(done.reshape(-1) - done_ref.reshape(-1)).max() <= b.TSENOR_ADAPTIVE_CHECK_EVERY
+    assert (done < T).any()
+    assert np.abs(plan - np.exp(log_S)).max() < PLAN_ATOL
+
+
+def test_increments_end_early():
+    # 32 x 32 blocks on the large tiles do not look for repeated states: 60 000 iterations are over after some thousands of steps
+    import torch
+
+    from paper_2505_23949_amd import binding as b
+
+    W = torch.from_numpy(np.tile(np.random.Generator(np.random.Philox(7)).random((32, 32)), (33, 33)).astype(np.float32)).to("cuda:0")
+    times = []
+    for T in (1200, 60000):
+        print(f"[case] increments end early T={T}", flush=True)
+        p = b.make_problem(W, 16, 32, 1.0, T, mask=torch.zeros(W.shape, dtype=torch.uint8, device=W.device),
+                           tau_mode=b.TSENOR_TAU_REL_MATRIX_MAX, flags=b.TSENOR_FLAG_TILES_LARGE)
+        work = torch.empty(b.tsenor_workspace_bytes([p]), dtype=torch.uint8, device=W.device)
+        best = float("inf")
+        for _ in range(3):
+            start, end = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            start.record()
+            b.tsenor_mask_ex(p, work)
+            end.record()
+            torch.cuda.synchronize()
+            best = min(best, start.elapsed_time(end))
+        times.append(best)
+    assert times[1] < 10 * times[0], times

@@ -1012,7 +1012,7 @@ __global__ __launch_bounds__((DykstraLaunch<M, FAST, ADAPT, TILES, LONE>::kThrea
   int64_t blk = wave * BPW + lane / LPB;
   const bool active = blk < p.nblocks;
   if (!active) blk = p.nblocks - 1;  // idle lanes shadow the last block and write nothing
-  const BlockAt at = block_at(p, blk, M);
+  const BlockAt at = place_of(batch.e[which], blk, M, blk);
   const int64_t r0 = at.r0, c0 = at.c0;
   const double tau_eff = tau_eff_of(batch.e[which]);
   if (tau_eff_out && group == 0 && threadIdx.x == 0) *tau_eff_out = tau_eff;

@@ -71,6 +71,28 @@ constexpr int64_t kFinestTilesLaunch = 2048;
 
 // SIMDs of the chip: a launch of no more waves gives each of them at most one
 constexpr unsigned kSimds = 1024;
+// blocks that a wave of the iterations holds
+constexpr int blocks_per_wave(int M, int tiles) {
+  return tiles == kLargeTiles ? (M == 4 ? 64 : M == 8 ? 16 : M == 16 ? 8 : M == 32 ? 2 : 1) : M == 4 ? 16 : M <= 16 ? 4 : 1;
+}
+
+// Whether the iterations of a matrix with a column scale take its blocks column by column, the largest scale first (place_of).
+// It pays where the waves of a launch follow each other on a SIMD or hold several blocks: on the small tiles from two waves on a SIMD
+// on, on the large ones when a launch has more waves than the chip holds at once; and over enough iterations to make up for
+// a list to look up and the lines of W that are read in parts (bf16 8 x 8 blocks: 16 bytes of each).  Whole calls, Wanda-style weights, row
+// by row / so (us):
+//   16:32 4096x14336 bf16 2507 / 2301, with fp32 iterations 1329 / 1236, a layer of seven such 5318 / 4818; 4:8 1800x2456 bf16, T = 500,
+//     290 / 218; 4:8 4096x11008 1657 / 1391; 8:16 4096x4096 tau = 0.005 845 / 790; 32:64 6144x2048 with fp32 iterations 709 / 614;
+//     small tiles, 8:16 1600x2048 230 / 219;
+//   T = 100: 8:16 4096x4096 351 / 340, with fp32 iterations 236 / 236 and 238 / 242; 1600x2048 with them (two waves on some SIMDs)
+//     T = 300 147 / 149, T = 100 80 / 81; 32:64 1152x1536 with them (a wave to a SIMD) 163 / 169.
+// 4 x 4 blocks have 64 or 16 to a wave, of which some row or other is slow whatever their scale (2:4 4096x4096 434 / 443, in double,
+// 3504x12496, T = 100, 1115 / 1188), and 64 x 64 blocks in double all run all iterations.
+constexpr bool orders_columns(const Variant& v, int iters, int64_t nblocks) {
+  if (v.M == 4 || (v.tiles != kLargeTiles && v.tiles != kSmallTiles) || (v.M == 64 && !v.fast && !v.adaptive)) return false;
+  const int64_t waves_per_simd = v.tiles == kSmallTiles ? 1 : v.fast && v.M != 64 ? 4 : 2;
+  return iters >= (v.fast && !v.adaptive ? 150 : 100) && nblocks > waves_per_simd * kSimds * blocks_per_wave(v.M, v.tiles);
+}
 
 // Below this many blocks in a launch a 64 x 64 block has a workgroup of its own (team.hpp), which iterates in double: one
 // workgroup per CU.  Whole calls, T = 300 (us, team / large tiles in double / with fp32 iterations): 64 blocks 173 / 286 /

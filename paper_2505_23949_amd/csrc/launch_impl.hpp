@@ -29,6 +29,7 @@ constexpr bool kLoneOnLargeTiles = M == 64 || M == 4;
 template <int M>
 bool launch_block_kernels(Batch& b, const Variant& v, hipStream_t stream, hipEvent_t ev_sorted, hipEvent_t ev_greedy) {
   constexpr int BPW = kWave >> (Tiling<M>::NX + Tiling<M>::NY);
+  static_assert(BPW == blocks_per_wave(M, kLargeTiles), "");
   int64_t nblocks = 0;  // of the whole launch
   for (int k = 0; k < b.count; ++k) nblocks += b.e[k].p.nblocks;
   const bool team_fits = nblocks < team_below_blocks(M);
@@ -37,6 +38,7 @@ bool launch_block_kernels(Batch& b, const Variant& v, hipStream_t stream, hipEve
     const auto launch = [&](auto tiles) {
       constexpr int TILES = decltype(tiles)::value;
       constexpr int BPWS = kWave >> (Tiling<M, TILES>::NX + Tiling<M, TILES>::NY);
+      static_assert(TILES != kSmallTiles || BPWS == blocks_per_wave(M, kSmallTiles), "");
       using L = DykstraLaunch<M, false, false, TILES>;
       static_assert(L::kWavesPerGroup == 1 && DykstraLaunch<M, false, true, TILES>::kWavesPerGroup == 1, "");
       if (!assign_groups(b, (int64_t)BPWS)) return false;

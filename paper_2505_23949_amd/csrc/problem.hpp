@@ -67,6 +67,7 @@ struct BatchEntry {
   uint8_t wide_store;           // mask rows can be written with 16-byte stores
   uint8_t wide_prev;            // the previous mask can be read with loads as wide as a block row (at most 16 bytes)
   uint8_t absmax_vec;           // rows of W (and of the additive term) can be read with 16-byte loads by the pre-pass
+  uint8_t by_columns;           // the iterations take the blocks column by column, in the order of column_order_of()
   uint8_t emit_vec;             // everything the derived outputs read and write can be moved 8 weights at a time
 };
 
@@ -90,6 +91,38 @@ struct BlockAt {
 __device__ __forceinline__ BlockAt block_at(const DevProblem& p, int64_t blk, int M) {
   const unsigned int b = (unsigned int)blk, bc = (unsigned int)p.bc, row = b / bc;
   return {(int64_t)row * M, (int64_t)(b - row * bc) * M};
+}
+
+constexpr size_t kAlign = 256;  // of the parts of a workspace slice
+__host__ __device__ inline size_t align_up(size_t x) { return (x + kAlign - 1) / kAlign * kAlign; }
+// M words per block, 32-bit up to M = 32, 64-bit for M = 64: greedy's row bit masks (M = 4) or the row normalisers, then the
+// block's counters
+__host__ __device__ inline size_t rowmask_bytes_per_block(int M) { return (size_t)M * (M > 32 ? 8 : 4); }
+
+// Block columns in the order the iterations take them (by_columns).  The list stands where something else is written after the
+// iterations: the potentials, which the one kernel of the small tiles keeps to itself, or the blocks' objectives, behind the row masks.
+enum { kOrderInPotentials = 1, kOrderInObjectives = 2 };
+__device__ __forceinline__ uint16_t* column_order_of(const BatchEntry& e, int M) {
+  char* at = static_cast<char*>(e.potentials);
+  if (e.by_columns == kOrderInObjectives)
+    at = static_cast<char*>(e.rowmask) + align_up((size_t)e.p.nblocks * rowmask_bytes_per_block(M));
+  return reinterpret_cast<uint16_t*>(at);
+}
+// The block that the iterations take at place `k` of a matrix.  With a column scale the blocks of a column, which share it, converge
+// in about the same number of iterations, and those under large scales in many times that of the others: so they go column by
+// column, the largest scale first.  The blocks of a wave then stop together, and the long waves begin early instead of ending the
+// launch alone (16:32 4096x14336 Wanda-style: the iterations a wave runs 113 -> 103 on average in fp32, and what the launch takes
+// beyond an even load of its SIMDs 11-16 % -> 3-4 %).  orders_columns() in launch.hpp has the calls it pays for.
+// (a branch of its own: with one division for both orders, launches without the list were 0.5-1 % slower.)
+__device__ __forceinline__ BlockAt place_of(const BatchEntry& e, int64_t k, int M, int64_t& blk) {
+  if (!e.by_columns) {
+    blk = k;
+    return block_at(e.p, k, M);
+  }
+  const unsigned at = (unsigned)k, block_rows = (unsigned)(e.rows / M), rank = at / block_rows, row = at - rank * block_rows,
+                 column = column_order_of(e, M)[rank];
+  blk = (int64_t)row * e.p.bc + column;
+  return {(int64_t)row * M, (int64_t)column * M};
 }
 
 __device__ __forceinline__ float load_element(const void* base, int dtype, int64_t index) {

@@ -76,16 +76,50 @@ __device__ __forceinline__ float absmax_rows(const DevProblem& p, int64_t r, int
   return m;
 }
 
+// Block columns by their largest column scale, descending (equal ones by index): each of the first ceil(bc / kOrderedPerGroup)
+// workgroups finds the places of kOrderedPerGroup columns by counting the keys before theirs, 16 threads to a column.  The bits of
+// the scales are compared, so that any content gives a permutation.
+constexpr int kOrderedPerGroup = 16, kMaxOrderedColumns = 4096;
+__device__ __forceinline__ void order_columns(const BatchEntry& e, int M, unsigned int group) {
+  if (!e.by_columns) return;
+  const int bc = (int)e.p.bc, first = (int)group * kOrderedPerGroup;
+  if (first >= bc) return;
+  __shared__ unsigned int key[kMaxOrderedColumns];
+  for (int k = (int)threadIdx.x; k < bc; k += 256) {
+    const unsigned int* scale = reinterpret_cast<const unsigned int*>(e.p.col_scale) + (int64_t)k * M;
+    unsigned int largest = 0;
+#pragma unroll 4
+    for (int j = 0; j < M; j += 4) {
+      const unsigned int a = scale[j], b = scale[j + 1], c = scale[j + 2], d = scale[j + 3];
+      largest = max(max(max(a, b), max(c, d)), largest);
+    }
+    key[k] = largest;
+  }
+  __syncthreads();
+  const int column = first + (int)threadIdx.x / 16;
+  const unsigned int mine = key[min(column, bc - 1)];
+  int before = 0;
+  for (int k = (int)threadIdx.x % 16; k < bc; k += 16) before += key[k] > mine || (key[k] == mine && k < column);
+  for (int s = 1; s < 16; s <<= 1) before += __shfl_xor(before, s, kWave);
+  if (column < bc && threadIdx.x % 16 == 0) column_order_of(e, M)[before] = (uint16_t)column;
+}
+
 // Largest importance of every matrix of the batch that uses the relative tau (App. B.1 parameter choice).
 // blockIdx.z: matrix; x and y stride over its columns and rows.  With absmax_vec every thread reads 8
 // consecutive weights of a row (and of the additive term) with 16-byte loads (needs cols % 8 == 0 and 16-byte aligned
 // rows and column scale); otherwise one weight at a time.  Squaring rounds monotonically, so a squared importance has its
 // maximum where the plain one has: it is squared once, at the end.  A matrix with fewer than 256 such vectors per row shares the
 // workgroup between rows.
-__global__ __launch_bounds__(256) void absmax_kernel(Batch batch) {
+// The last `gridDim.y - bands` rows of workgroups put block columns in order (order_columns).
+__global__ __launch_bounds__(256) void absmax_kernel(Batch batch, int M) {
   const BatchEntry& e = batch.e[blockIdx.z];
   const DevProblem p = e.p;
   if (p.tau_mode != TSENOR_TAU_REL_MATRIX_MAX) return;
+  const unsigned bands = (unsigned)e.absmax_count / gridDim.x;
+  if (blockIdx.y >= bands) {
+    order_columns(e, M, (blockIdx.y - bands) * gridDim.x + blockIdx.x);
+    return;
+  }
   const int64_t rows = e.rows;
   float m = 0.0f;
   if (e.absmax_vec) {
@@ -101,7 +135,7 @@ __global__ __launch_bounds__(256) void absmax_kernel(Batch batch) {
         c[0] = a.x, c[1] = a.y, c[2] = a.z, c[3] = a.w, c[4] = b.x, c[5] = b.y, c[6] = b.z, c[7] = b.w;
       }
       // a workgroup streams a contiguous band of rows (rows far apart cost a page-table walk per load)
-      const int64_t band = (rows + gridDim.y - 1) / gridDim.y;
+      const int64_t band = (rows + bands - 1) / bands;
       const int64_t r_end = (blockIdx.y + 1) * band < rows ? (blockIdx.y + 1) * band : rows;
       for (int64_t r = blockIdx.y * band + (int64_t)tr * kAbsmaxInFlight; r < r_end; r += (int64_t)rpp * kAbsmaxInFlight) {
         if (p.dtype == TSENOR_BF16) {
@@ -119,7 +153,7 @@ __global__ __launch_bounds__(256) void absmax_kernel(Batch batch) {
     }
     if (p.square) m = __fmul_rn(m, m);
   } else {
-    for (int64_t r = blockIdx.y; r < rows; r += gridDim.y)
+    for (int64_t r = blockIdx.y; r < rows; r += bands)
       for (int64_t c = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; c < p.cols; c += (int64_t)gridDim.x * blockDim.x)
         m = fmaxf(m, load_importance(p, r, c));
   }
@@ -168,16 +202,9 @@ inline int hip_status_of_launches() {
   return TSENOR_ERR_HIP;
 }
 
-constexpr size_t kAlign = 256;
-inline size_t align_up(size_t x) { return (x + kAlign - 1) / kAlign * kAlign; }
-
 struct WsLayout {
   size_t header, partials, potentials, accept, objective, total;
 };
-
-// M words per block, 32-bit up to M = 32, 64-bit for M = 64: greedy's row bit masks (M = 4) or the row normalisers, then the
-// block's counters
-inline size_t rowmask_bytes_per_block(int M) { return (size_t)M * (M > 32 ? 8 : 4); }
 
 WsLayout layout_of(const tsenor_problem& p) {
   WsLayout l;
@@ -282,6 +309,9 @@ BatchEntry entry_of(const tsenor_problem& p, char* ws) {
   e.objective_out = p.objective_out;
   e.prev_mask = p.prev_mask;
   e.iters_done_out = p.iters_done_out;
+  const Variant v = variant_of(p);
+  if (p.col_scale && p.tau_mode == TSENOR_TAU_REL_MATRIX_MAX && dp.bc <= kMaxOrderedColumns && orders_columns(v, p.iters, dp.nblocks))
+    e.by_columns = v.tiles == kLargeTiles ? kOrderInObjectives : kOrderInPotentials;
   const auto aligned = [](const void* ptr, size_t to) { return reinterpret_cast<uintptr_t>(ptr) % to == 0; };
   const size_t esize = p.dtype == TSENOR_BF16 ? 2 : 4;
   const bool rows_aligned =
@@ -342,9 +372,14 @@ int run_group(Batch& b, const Variant& v, hipStream_t stream, hipEvent_t* ev = n
   mark(0);
   if (any_stats) init_kernel<<<1, 4 * kMaxBatch, 0, stream>>>(b);
   if (any_rel) {
-    const dim3 grid = strided_grid(b, false, 512, true);
-    for (int k = 0; k < b.count; ++k) b.e[k].absmax_count = (int)(grid.x * grid.y);
-    absmax_kernel<<<grid, 256, 0, stream>>>(b);
+    dim3 grid = strided_grid(b, false, 512, true);
+    int64_t ordered = 0;
+    for (int k = 0; k < b.count; ++k) {
+      b.e[k].absmax_count = (int)(grid.x * grid.y);
+      if (b.e[k].by_columns) ordered = std::max(ordered, b.e[k].p.bc);
+    }
+    grid.y += (unsigned)((ordered + kOrderedPerGroup * grid.x - 1) / (kOrderedPerGroup * grid.x));
+    absmax_kernel<<<grid, 256, 0, stream>>>(b, v.M);
   }
   mark(1);
   hipEvent_t ev_sorted = ev ? ev[2] : nullptr, ev_greedy = ev ? ev[3] : nullptr;

@@ -243,6 +243,27 @@ __device__ __forceinline__ double fast_div(double n, double d) {
   return fma(fma(-d, x, 1.0), nx, nx);
 }
 __device__ __forceinline__ float fast_rcp(float d) { return __builtin_amdgcn_rcpf(d); }
+// exp(x) for |x| <= 708, below 1 ulp of error: e^x = 2^n e^r with |r| <= ln2 / 2 (n by the addition that leaves it in the low word),
+// e^r = 1 + r + r^2 q(r), q the polynomial of degree 9 that minimises the largest relative error (3.6e-18, Remez exchange).  16
+// instructions; the library's exp() spends four more on results that leave the range of a double, which no entry of a tile does.
+__device__ __forceinline__ double exp_in_range(double x) {
+  constexpr double kLog2e = 0x1.71547652b82fep+0, kLn2Hi = 0x1.62e42fefa39efp-1, kLn2Lo = 0x1.abc9e3b39803fp-56, kRound = 0x1.8p+52;
+  const double shifted = fma(x, kLog2e, kRound), n = shifted - kRound;
+  const double r = fma(n, -kLn2Lo, fma(n, -kLn2Hi, x));
+  double q = 0x1.ad7f6b5dc2ef6p-26;
+  q = fma(q, r, 0x1.28ad72bf7e407p-22);
+  q = fma(q, r, 0x1.71df255430ed3p-19);
+  q = fma(q, r, 0x1.a0199a0c78972p-16);
+  q = fma(q, r, 0x1.a01a012a57064p-13);
+  q = fma(q, r, 0x1.6c16c1842a09fp-10);
+  q = fma(q, r, 0x1.1111111127be6p-7);
+  q = fma(q, r, 0x1.555555555087dp-5);
+  q = fma(q, r, 0x1.55555555554fap-3);
+  q = fma(q, r, 0x1.000000000000ap-1);
+  q = fma(q, r, 1.0);
+  q = fma(q, r, 1.0);
+  return __builtin_amdgcn_ldexp(q, __double2loint(shifted));
+}
 __device__ __forceinline__ double clamp01(double x) { return fmin(fmax(x, 0.0), 1.0); }
 __device__ __forceinline__ float clamp01(float x) { return fminf(fmaxf(x, 0.0f), 1.0f); }
 __device__ __forceinline__ double vmax(double a, double b) { return fmax(a, b); }
@@ -984,7 +1005,7 @@ struct DykstraLaunch {
   // exit, where a block may run a dozen iterations and the code around the loop is most of the work, two (8192x8192: 0.85 ms,
   // three 1.05).
   static constexpr int kWavesPerSimd =
-      FAST && !(M == 64 && ADAPT) ? (M == 32 || M == 8 ? 4 : 3) : !LONE && M == 16 && TILES == kSmallTiles ? 4 : M == 8 && TILES == kLargeTiles ? 3 : 2;
+      FAST && !(M == 64 && ADAPT) ? (M == 16 || M == 64 ? 3 : 4) : !LONE && ((M == 16 && TILES == kSmallTiles) || (M == 8 && TILES == kLargeTiles)) ? 4 : 2;
 };
 
 // ZERO_T: the instantiation for T = 0 (no iterations, keys are K itself).  It is a template parameter
@@ -1071,7 +1092,7 @@ __global__ __launch_bounds__((DykstraLaunch<M, FAST, ADAPT, TILES, LONE>::kThrea
         auto plan_rows = [&](auto first) {
           constexpr int A0 = decltype(first)::value;
           float imp[NA][TW];
-          tile_importance<A0, NA>(p, addr, imp);
+          tile_importance<A0, NA, !SMALL>(p, addr, imp);
 #pragma unroll
           for (int a = 0; a < NA; ++a)
 #pragma unroll
@@ -1088,7 +1109,7 @@ __global__ __launch_bounds__((DykstraLaunch<M, FAST, ADAPT, TILES, LONE>::kThrea
     auto rows = [&](auto first) {
       constexpr int A0 = decltype(first)::value;
       float imp[NA][TW];
-      tile_importance<A0, NA>(p, addr, imp);
+      tile_importance<A0, NA, !SMALL>(p, addr, imp);
 #pragma unroll
       for (int a = 0; a < NA; ++a)
 #pragma unroll
@@ -1120,7 +1141,7 @@ __global__ __launch_bounds__((DykstraLaunch<M, FAST, ADAPT, TILES, LONE>::kThrea
     for (int a = 0; a < TH; ++a)
 #pragma unroll
       for (int b = 0; b < TW; ++b) {
-        kap[a][b] = exp(fmax(kap[a][b] - (double)mrow[a], kMinLogKernel));
+        kap[a][b] = exp_in_range(fmax(kap[a][b] - (double)mrow[a], kMinLogKernel));
         __builtin_amdgcn_sched_barrier(0);  // one exp at a time: interleaving them only costs registers
       }
 
@@ -1329,14 +1350,14 @@ __global__ __launch_bounds__((DykstraLaunch<M, FAST, ADAPT, TILES, LONE>::kThrea
           auto rows = [&](auto first) {
             constexpr int A0 = decltype(first)::value;
             float imp[NA][TW];
-            tile_importance<A0, NA>(p, addr, imp);
+            tile_importance<A0, NA, !SMALL>(p, addr, imp);
 #pragma unroll
             for (int a = 0; a < NA; ++a)
 #pragma unroll
               for (int b = 0; b < TW; ++b) {
                 const double K = tau_eff * (double)imp[a][b];
                 const double full = (K - (double)mrow[A0 + a]) + (lu[A0 + a] + lv[b]);
-                kap32[A0 + a][b] = (float)exp(fmin(fmax(full, kLogFloor32), kLogCeil32));
+                kap32[A0 + a][b] = (float)exp_in_range(fmin(fmax(full, kLogFloor32), kLogCeil32));
                 __builtin_amdgcn_sched_barrier(0);
               }
           };
@@ -1473,7 +1494,7 @@ __global__ __launch_bounds__((DykstraLaunch<M, FAST, ADAPT, TILES, LONE>::kThrea
         auto plan_rows = [&](auto first) {
           constexpr int A0 = decltype(first)::value;
           float imp[NA][TW];
-          tile_importance<A0, NA>(p, addr, imp);
+          tile_importance<A0, NA, !SMALL>(p, addr, imp);
 #pragma unroll
           for (int a = 0; a < NA; ++a)
 #pragma unroll
@@ -1489,7 +1510,7 @@ __global__ __launch_bounds__((DykstraLaunch<M, FAST, ADAPT, TILES, LONE>::kThrea
         auto rows = [&](auto first) {
           constexpr int A0 = decltype(first)::value;
           float imp[NA][TW];
-          tile_importance<A0, NA>(p, addr, imp);
+          tile_importance<A0, NA, !SMALL>(p, addr, imp);
 #pragma unroll
           for (int a = 0; a < NA; ++a)
 #pragma unroll

@@ -216,8 +216,12 @@ __device__ __forceinline__ void tile_values(const DevProblem& p, const TileAddr<
   }
 }
 
-// importance of tile rows [A0, A0 + NA): the same operations, in the same order, as load_importance
-template <int A0, int NA, int TH, int TW>
+// importance of tile rows [A0, A0 + NA): the same operations, in the same order, as load_importance.  SHORT: branches around the
+// multiplications by 1 and the square that is not asked for (three of four operations of an entry; small launches, which wait for
+// every basic block, do without the branches: 0.6 us of a 512 x 512 call).  With exp_in_range() and the scalar row addresses of
+// block_column_values(): 32:64 8192x8192 with the early exit 692 / 682 us, 32:64 6144x2048 Wanda-style, whose fp32 tiles are formed
+// anew, 612 / 566, 4096x4096 583 / 575; 16- and 32-wide calls 0-2 % faster.
+template <int A0, int NA, bool SHORT, int TH, int TW>
 __device__ __forceinline__ void tile_importance(const DevProblem& p, const TileAddr<TH, TW>& t, float (&imp)[NA][TW]) {
   if (p.dtype == TSENOR_BF16) {
     if (p.add)
@@ -230,30 +234,90 @@ __device__ __forceinline__ void tile_importance(const DevProblem& p, const TileA
     else
       tile_values<false, false, A0, NA>(p, t, imp);
   }
+  if constexpr (SHORT) {
 #pragma unroll
-  for (int a = 0; a < NA; ++a)
+    for (int a = 0; a < NA; ++a)
 #pragma unroll
-    for (int b = 0; b < TW; ++b) {
-      float m = __fmul_rn(__fmul_rn(fabsf(imp[a][b]), t.csa[A0 + a]), t.csb[b]);
-      if (p.square) m = __fmul_rn(m, m);
-      imp[a][b] = m;
+      for (int b = 0; b < TW; ++b) imp[a][b] = fabsf(imp[a][b]);
+    if (p.col_scale) {
+      if (p.transpose) {
+#pragma unroll
+        for (int a = 0; a < NA; ++a)
+#pragma unroll
+          for (int b = 0; b < TW; ++b) imp[a][b] = __fmul_rn(imp[a][b], t.csa[A0 + a]);
+      } else {
+#pragma unroll
+        for (int a = 0; a < NA; ++a)
+#pragma unroll
+          for (int b = 0; b < TW; ++b) imp[a][b] = __fmul_rn(imp[a][b], t.csb[b]);
+      }
     }
+    if (p.square) {
+#pragma unroll
+      for (int a = 0; a < NA; ++a)
+#pragma unroll
+        for (int b = 0; b < TW; ++b) imp[a][b] = __fmul_rn(imp[a][b], imp[a][b]);
+    }
+  } else {
+#pragma unroll
+    for (int a = 0; a < NA; ++a)
+#pragma unroll
+      for (int b = 0; b < TW; ++b) {
+        float m = __fmul_rn(__fmul_rn(fabsf(imp[a][b]), t.csa[A0 + a]), t.csb[b]);
+        if (p.square) m = __fmul_rn(m, m);
+        imp[a][b] = m;
+      }
+  }
+}
+
+// a number of the wave's first active lane, in scalar registers
+__device__ __forceinline__ int64_t of_first_lane(int64_t v) {
+  const unsigned lo = (unsigned)__builtin_amdgcn_readfirstlane((int)v), hi = (unsigned)__builtin_amdgcn_readfirstlane((int)(v >> 32));
+  return (int64_t)((uint64_t)hi << 32 | lo);
+}
+template <bool BF16>
+__device__ __forceinline__ float element_at(const char* at) {
+  if constexpr (BF16)
+    return __uint_as_float((unsigned int)*reinterpret_cast<const unsigned short*>(at) << 16);
+  else
+    return *reinterpret_cast<const float*>(at);
 }
 
 // importance of the M entries (r0 .. r0+M-1, c) of one matrix column, loads issued together; the same
-// operations, in the same order, as load_importance
-template <int M, bool BF16, bool ADD>
+// operations, in the same order, as load_importance.
+// ASCENDING: no lane's r0 is above that of a lane after it (blocks taken row by row: the kernels of their own that round).  The address of
+// a row is then one scalar, of the first lane's blocks, and the lane's part a 32-bit offset from it that is not negative: the blocks of
+// a wave lie in at most 64 rows and c is below ld, so the offset stays below 2^32 for ld < kFarLd.  (64-bit addresses of their own took
+// the lanes two to four instructions per entry, twice, 7 % of the rounding of 64-wide blocks.)
+constexpr int64_t kFarLd = (int64_t)1 << 21;
+template <int M, bool BF16, bool ADD, bool ASCENDING>
 __device__ __forceinline__ void block_column_values(const DevProblem& p, int64_t r0, int64_t c, float (&x)[M]) {
+  constexpr int SIZE = BF16 ? 2 : 4;
   float v[ADD ? M : 1];
+  const char *W = static_cast<const char*>(p.W), *V = static_cast<const char*>(p.add);
+  const int64_t step = p.ld * SIZE;
+  if (ASCENDING && p.ld < kFarLd) {
+    const int64_t first = of_first_lane(r0);
+    const unsigned off = ((unsigned)(r0 - first) * (unsigned)p.ld + (unsigned)c) * SIZE;
+    W += first * step;
+    if constexpr (ADD) V += first * step;
 #pragma unroll
-  for (int k = 0; k < M; ++k) {
-    const int64_t off = (r0 + k) * p.ld + c;
-    if constexpr (BF16) {
-      x[k] = __uint_as_float((unsigned int)reinterpret_cast<const unsigned short*>(p.W)[off] << 16);
-      if constexpr (ADD) v[k] = __uint_as_float((unsigned int)reinterpret_cast<const unsigned short*>(p.add)[off] << 16);
-    } else {
-      x[k] = reinterpret_cast<const float*>(p.W)[off];
-      if constexpr (ADD) v[k] = reinterpret_cast<const float*>(p.add)[off];
+    for (int k = 0; k < M; ++k) {
+      asm("" : "+s"(W), "+s"(V));  // (the row's address stays a scalar one, and `off` the lane's part of it)
+      x[k] = element_at<BF16>(W + off);
+      W += step;
+      if constexpr (ADD) {
+        v[k] = element_at<BF16>(V + off);
+        V += step;
+      }
+    }
+  } else {
+    const int64_t off = (r0 * p.ld + c) * SIZE;
+#pragma unroll
+    for (int k = 0; k < M; ++k) {
+      x[k] = element_at<BF16>(W + (off + k * step));
+      if constexpr (ADD) v[k] = element_at<BF16>(V + (off + k * step));
+      if (ASCENDING && k % 4 == 3) __builtin_amdgcn_sched_barrier(0);  // (their addresses would not fit the registers beside the rest)
     }
   }
   if constexpr (ADD) {
@@ -261,18 +325,18 @@ __device__ __forceinline__ void block_column_values(const DevProblem& p, int64_t
     for (int k = 0; k < M; ++k) x[k] = __fadd_rn(x[k], __fmul_rn(p.add_scale, v[k]));
   }
 }
-template <int M>
+template <int M, bool ASCENDING>
 __device__ __forceinline__ void block_column_importance(const DevProblem& p, int64_t r0, int64_t c, float (&imp)[M]) {
   if (p.dtype == TSENOR_BF16) {
     if (p.add)
-      block_column_values<M, true, true>(p, r0, c, imp);
+      block_column_values<M, true, true, ASCENDING>(p, r0, c, imp);
     else
-      block_column_values<M, true, false>(p, r0, c, imp);
+      block_column_values<M, true, false, ASCENDING>(p, r0, c, imp);
   } else {
     if (p.add)
-      block_column_values<M, false, true>(p, r0, c, imp);
+      block_column_values<M, false, true, ASCENDING>(p, r0, c, imp);
     else
-      block_column_values<M, false, false>(p, r0, c, imp);
+      block_column_values<M, false, false, ASCENDING>(p, r0, c, imp);
   }
   const float cs = p.col_scale ? p.col_scale[c] : 1.0f;
 #pragma unroll

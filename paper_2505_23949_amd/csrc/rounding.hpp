@@ -124,8 +124,8 @@ __device__ __forceinline__ int group_sum(int v) {
 // Algorithm 2 lines 7-13 and the mask write for the blocks of one wave.  A block owns LPB >= M consecutive lanes,
 // of which the first M take part: lane r owns row r and column r of the block as bit masks.  On entry lds.rowm
 // holds the mask greedy selection left.  blk: the lane's block (a valid one also for idle lanes, which write
-// nothing: `active`), at matrix position (r0, c0).  To be called by whole waves.
-template <int M, int LPB>
+// nothing: `active`), at matrix position (r0, c0).  ASCENDING: of block_column_values.  To be called by whole waves.
+template <int M, int LPB, bool ASCENDING>
 __device__ __forceinline__ void local_search_and_write(const DevProblem& p, const BatchEntry& e, int64_t blk, bool active,
                                                        int64_t r0, int64_t c0, int lane, RoundingLds<M, kWave / LPB>& lds) {
   using mask_t = block_mask_t<M>;
@@ -156,7 +156,7 @@ __device__ __forceinline__ void local_search_and_write(const DevProblem& p, cons
     // local search scores on the importance (Eq. 5), staged in LDS: this lane fetches column ql of its
     // block, all M loads in flight at once
     float col[M];
-    block_column_importance<M>(p, r0, c0 + qm, col);
+    block_column_importance<M, ASCENDING>(p, r0, c0 + qm, col);
 #pragma unroll
     for (int k = 0; k < M; ++k) lds.imp[g][k * LD + qm] = col[k];
   }
@@ -322,7 +322,7 @@ __global__ __launch_bounds__(kWave) void finalize_kernel(Batch batch) {
   if (!active) blk = p.nblocks - 1;  // idle groups shadow the last block and write nothing
   lds.rowm[g][ql] = rowmask[blk * M + ql];
   const BlockAt at = block_at(p, blk, M);
-  local_search_and_write<M, M>(p, batch.e[which], blk, active, at.r0, at.c0, lane, lds);
+  local_search_and_write<M, M, true>(p, batch.e[which], blk, active, at.r0, at.c0, lane, lds);
 }
 
 // ------------------------------------------------------------------------------------------------------------------
@@ -440,8 +440,9 @@ __device__ __forceinline__ int nth_set_bit(mask_t h, int N) {
 // Algorithm 2 for the blocks of one wave.  A block owns LPB >= M consecutive lanes; lane r of the first M is its row r and
 // its column r, further ones repeat what lane r % M does.  blk: the lane's block (a valid one also for idle lanes, which
 // write nothing: `active`), at matrix position (r0, c0).  row_pot, col_pot (LDS, T > 0): the potentials of the matrix rows
-// and columns of the wave's blocks; lds.minus_largest goes with them.  To be called by whole waves.
-template <int M, int LPB, bool ZERO_T, bool COLS_FIRST>
+// and columns of the wave's blocks; lds.minus_largest goes with them.  ASCENDING: of block_column_values.  To be called by whole
+// waves.
+template <int M, int LPB, bool ZERO_T, bool COLS_FIRST, bool ASCENDING = false>
 __device__ __forceinline__ void round_blocks(const DevProblem& p, const BatchEntry& e, int64_t blk, bool active, int64_t r0,
                                              int64_t c0, int lane, double tau_eff, const double (*row_pot)[M],
                                              const double (*col_pot)[M], RoundingLds<M, kWave / LPB>& lds) {
@@ -451,7 +452,7 @@ __device__ __forceinline__ void round_blocks(const DevProblem& p, const BatchEnt
   // the importance of the block, a column per lane (coalesced), into LDS
   {
     float col[M];
-    block_column_importance<M>(p, r0, c0 + ql, col);
+    block_column_importance<M, ASCENDING>(p, r0, c0 + ql, col);
 #pragma unroll
     for (int k = 0; k < M; ++k) lds.imp[g][k * LD + ql] = col[k];
   }
@@ -582,7 +583,7 @@ __device__ __forceinline__ void round_blocks(const DevProblem& p, const BatchEnt
     if (!__any(proposed)) break;
   }
   wave_sync();
-  local_search_and_write<M, LPB>(p, e, blk, active, r0, c0, lane, lds);
+  local_search_and_write<M, LPB, ASCENDING>(p, e, blk, active, r0, c0, lane, lds);
 }
 
 // The stand-alone kernel: 64/M blocks per wave, one wave per workgroup; the potentials come from the workspace.
@@ -618,9 +619,9 @@ __global__ __launch_bounds__(kWave, M <= 32 ? 4 : 2) void round_kernel(Batch bat
     col_pot[g][ql] = p.transpose ? of_row : of_col;
   }
   if (!ZERO_T && p.transpose)
-    round_blocks<M, M, ZERO_T, true>(p, e, blk, active, at.r0, at.c0, lane, tau_eff, row_pot, col_pot, lds);
+    round_blocks<M, M, ZERO_T, true, true>(p, e, blk, active, at.r0, at.c0, lane, tau_eff, row_pot, col_pot, lds);
   else
-    round_blocks<M, M, ZERO_T, false>(p, e, blk, active, at.r0, at.c0, lane, tau_eff, row_pot, col_pot, lds);
+    round_blocks<M, M, ZERO_T, false, true>(p, e, blk, active, at.r0, at.c0, lane, tau_eff, row_pot, col_pot, lds);
 }
 
 }  // namespace tsenor_dev

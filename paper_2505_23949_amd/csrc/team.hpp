@@ -57,7 +57,7 @@ __global__ __launch_bounds__(Team::W * kWave, 2) void team_kernel(Batch batch) {
   float mrow[TH];  // not below the largest K of every row (see dykstra_sort_kernel)
   {
     float imp[TH][1];
-    tile_importance<0, TH>(p, addr, imp);
+    tile_importance<0, TH, false>(p, addr, imp);
 #pragma unroll
     for (int a = 0; a < TH; ++a) {
       kap[a] = tau_eff * (double)imp[a][0];
@@ -69,7 +69,7 @@ __global__ __launch_bounds__(Team::W * kWave, 2) void team_kernel(Batch batch) {
   for (int a = 0; a < TH; ++a) {
     mrow[a] = fmaxf(mrow[a], lane_xor<16>(mrow[a]));
     mrow[a] = fmaxf(mrow[a], lane_xor<32>(mrow[a]));
-    kap[a] = exp(fmax(kap[a] - (double)mrow[a], kMinLogKernel));
+    kap[a] = exp_in_range(fmax(kap[a] - (double)mrow[a], kMinLogKernel));
   }
 
   const double Nd = (double)p.N;
@@ -136,7 +136,7 @@ __global__ __launch_bounds__(Team::W * kWave, 2) void team_kernel(Batch batch) {
   if (e.plan_out) {
     all_gather_x<T, double, TH>(lu);
     float imp[TH][1];
-    tile_importance<0, TH>(p, addr, imp);
+    tile_importance<0, TH, false>(p, addr, imp);
 #pragma unroll
     for (int a = 0; a < TH; ++a) {
       const int64_t r = at.r0 + (p.transpose ? col : ri[a]), c = at.c0 + (p.transpose ? ri[a] : col);

@@ -521,15 +521,21 @@ __device__ __forceinline__ void round_blocks(const DevProblem& p, const BatchEnt
   lds.colm[g][ql] = 0;
   wave_sync();
   mask_t held = 0;
-  {
-    unsigned int cr[M];
+  // (half of the row at a time: with N = M / 2 the other half is neither looked up nor proposed; 32:64 with the early exit 686 -> 680 us,
+  // 226 -> 207 registers, and 16:32 no longer spills)
+  constexpr int kAtOnce = M == 4 ? M : M / 2;
 #pragma unroll
-    for (int r = 0; r < M; ++r) cr[r] = rank[ql * LDB + ((row_list[r / 4] >> (8 * (r % 4))) & 0xFFu)] & (unsigned)(M - 1);
+  for (int half = 0; half < M; half += kAtOnce) {
+    if (half >= N) break;
+    unsigned int cr[kAtOnce];
 #pragma unroll
-    for (int r = 0; r < M; ++r)
-      if (r < N) {
-        const unsigned int j = (row_list[r / 4] >> (8 * (r % 4))) & 0xFFu;
-        atomicOr(&lds.colm[g][j], one << cr[r]);
+    for (int k = 0; k < kAtOnce; ++k)
+      cr[k] = rank[ql * LDB + ((row_list[(half + k) / 4] >> (8 * (k % 4))) & 0xFFu)] & (unsigned)(M - 1);
+#pragma unroll
+    for (int k = 0; k < kAtOnce; ++k)
+      if (half + k < N) {
+        const unsigned int j = (row_list[(half + k) / 4] >> (8 * (k % 4))) & 0xFFu;
+        atomicOr(&lds.colm[g][j], one << cr[k]);
         held |= one << j;
       }
   }

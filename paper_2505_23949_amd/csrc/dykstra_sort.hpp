@@ -50,9 +50,9 @@ constexpr int kChunk = 8;                 // FAST: iterations between looks for 
 constexpr int kRepeatWindow = 24;         // iterations over which a repetition is looked for (RepeatCheck); in double also between looks
 constexpr int kRaiseBits = 512;           // kKeep: what goes from a large row scaling into its row of the tile (raise_rows)
 constexpr double kRaiseAbove = 0x1p+400;
-constexpr double kSmallStep = 0x1p-32;    // near_the_end(): factors of an iteration within this of 1 ...
+constexpr double kSmallStep = 0x1p-30;    // near_the_end(): factors of an iteration within this of 1 ...
 constexpr double kNearCap = 0x1p-20;      // ... no entry of the plan as near to the cap as this ...
-constexpr float kIncrementSum = 0x1p-26f; // ... and the sum of the increments before the plan is formed anew
+constexpr float kIncrementSum = 0x1p-25f; // ... and the sum of the increments before the plan is formed anew
 constexpr int kDriftBits = 40;            // FAST: fold the fp32 scalings back beyond 2^+-kDriftBits
 constexpr double kLogFloor32 = -83.0;     // FAST: rebuilt entries are kept within [e^-83, e^55] ~ [2^-120, 2^80]
 constexpr double kLogCeil32 = 55.0;
@@ -216,12 +216,15 @@ __device__ __forceinline__ int column_lane(int gx, int q) {
 }
 
 // Whether the last iterations of a wave are done in increments (near_the_end): where a launch may take two layouts of a block whose
-// waves hold other numbers of blocks (order_run), or rows are summed in pairs (32-wide small tiles), the results would differ.  4 x 4
-// blocks have 64 or 16 to a wave, too many to converge together; on the 8-wide small tiles it gained nothing (the look 1 %).
+// waves hold other numbers of blocks (order_run) the results would differ.  4 x 4 blocks have 64 or 16 to a wave, too many to converge together; on the 8-wide small tiles it gained nothing (the look 1 %).
 template <int M, int TILES>
 constexpr bool increments_at_the_end() {
-  return (TILES == kLargeTiles && (M == 8 || M == 16 || M == 32)) || (TILES == kSmallTiles && M == 16);
+  return (TILES == kLargeTiles && (M == 8 || M == 16 || M == 32)) || (TILES == kSmallTiles && M >= 16);
 }
+
+// whether any step along a lane-column swaps registers, so that a lane's first ones need not be of the columns it owns
+template <class T, int S = 0>
+constexpr bool kSwaps = S < T::NY && (T::YM[S < T::NY ? S : 0] == 32 || (T::SWAPS && T::YM[S < T::NY ? S : 0] == 16) || (S + 1 < T::NY && kSwaps<T, (S + 1 < T::NY ? S + 1 : S)>));
 
 // registers a lane owns after a reduce-scatter of `count` values over 2^steps lanes (at least one)
 constexpr int owned(int count, int steps) { return (count >> steps) > 0 ? (count >> steps) : 1; }
@@ -441,6 +444,8 @@ __device__ __forceinline__ void chain_phase(bool on) {
 // changes), and the largest |factor - 1| among the rows and columns this lane owns is returned.
 // RUN: order_run() of the tiling.  LONE: no other wave shares the SIMD (chain_phase).
 struct NoTile {};
+// a count that is the same in all lanes, where the compiler cannot tell (in a vector register it costs the loop an instruction or two)
+__device__ __forceinline__ int of_wave(int n) { return __builtin_amdgcn_readfirstlane(n); }
 enum Form { kRecompute, kFold, kKeep };
 template <class T, Form FORM, Gather GATHER = kLanesOnly, bool ADAPT = false, int RUN = 0, bool LONE = false, class Tile, int TH, int TW, int NU>
 __device__ __forceinline__ double dykstra_iteration(double (&kap)[TH][TW], Tile& x, double (&U)[NU], double (&V)[TW],
@@ -630,13 +635,14 @@ __device__ __forceinline__ double dykstra_iteration(double (&kap)[TH][TW], Tile&
 // is below the cap, n_i and m_j the entries at the cap in row i and column j):
 //     rho'_i  = (n_i rho_i - sum_p p_ij gamma_j) / N
 //     gamma'_j = (m_j gamma_j - sum_p p_ij rho'_i - sum_cap (rho'_i - rho_i)) / N
-// up to their squares, 2^-64.  The increments are iterated in fp32 and their sums go into the double scalings: a relative error
-// of 2^-24 of an increment below 2^-32 is less than the rounding of a double iteration, whose factors carry 2^-48.  When the
-// iterations that are left, were each to change an entry by as much as the last one did, add up to less than 2^-60, all are done.
+// up to their squares, 2^-60.  The increments are iterated in fp32 and their sums go into the double scalings: a relative error
+// of 2^-24 of an increment below 2^-30 is less than the rounding of a double iteration, whose factors carry 2^-48.  When the
+// iterations that are left, were each to change an entry by as much as the last one did, add up to less than 2^-54, all are done.
 // 96 plain fp32 instructions per lane of a 32 x 32 block for the 120 of an iteration in double, and exchanges of one instruction
 // instead of three: 115 at 2.5-4 cycles where an iteration in double has 162 at 4.  Calls before / with it (us): 16:32 4096x14336
 // bf16 Wanda-style, T = 300, 2792 / 2515; 8:16 3280x12832 Wanda-style tau = 0.02 2199 / 1276; 4:8 4096x4096 student-t 537 / 326; 8:16
-// 1072x2928 with its plan, small tiles, 198 / 184; normal weights, which never come so near, 842 / 841 (8:16) and 2535 / 2548 (4:8).
+// 1072x2928 with its plan, small tiles, 198 / 178; 16:32 1600x1920 student-t, T = 500, small tiles, 176 / 117; normal weights, which never
+// come so near, 842 / 841 (8:16), 2535 / 2548 (4:8) and 143 / 145 (16:32 1088x1472, small tiles).
 // Error of the plan against a 64-bit evaluation (8, 16 and 32 wide, T = 100 to 500, three distributions): 0.98 of what it was, from
 // 0.86 to 1.03.
 // Called behind an iteration (t are done) with U_before and V_before the scalings before it; nothing happens unless the conditions
@@ -705,15 +711,31 @@ __device__ __forceinline__ int near_the_end(double (&kap)[TH][TW], Tile& x, doub
     gamma[b] = gamma_own[b] = (float)((Vown[b] - V_before[b]) * __builtin_amdgcn_rcp(V_before[b]));
   if constexpr (!LDS) all_gather_x<T, float, TH>(rho);
   all_gather_y<T, float, TW>(gamma);
+  int looks = 0;
   for (bool go_on = true; go_on;) {
     const int stop = iters - t > kChunk ? t + kChunk : iters;
     float largest = 0.0f, s[TH];
     for (; t < stop; ++t) {
       float d[TH], q[TW];
+      if constexpr (T::NY == 3) {
+        // in pairs, as the row sums in double: the same whatever the lane's offset of the columns is (LoneTiling)
 #pragma unroll
-      for (int b = 0; b < TW; ++b)
+        for (int a = 0; a < TH; ++a) {
+          float leaf[TW];
 #pragma unroll
-        for (int a = 0; a < TH; ++a) s[a] = b == 0 ? p[a][b] * gamma[b] : fmaf(p[a][b], gamma[b], s[a]);
+          for (int b = 0; b < TW; ++b) leaf[b] = p[a][b] * gamma[b];
+#pragma unroll
+          for (int h = 1; h < TW; h *= 2)
+#pragma unroll
+            for (int b = 0; b < TW; b += 2 * h) leaf[b] += leaf[b + h];
+          s[a] = leaf[0];
+        }
+      } else {
+#pragma unroll
+        for (int b = 0; b < TW; ++b)
+#pragma unroll
+          for (int a = 0; a < TH; ++a) s[a] = b == 0 ? p[a][b] * gamma[b] : fmaf(p[a][b], gamma[b], s[a]);
+      }
       chain_phase<LONE>(true);
       reduce_scatter_x<T, float, TH>(s);
       largest = 0.0f;
@@ -783,7 +805,18 @@ __device__ __forceinline__ int near_the_end(double (&kap)[TH][TW], Tile& x, doub
     for (int a = 0; a < OWN_R; ++a) sum = fmaxf(sum, fabsf(sum_r[a]));
 #pragma unroll
     for (int b = 0; b < OWN_C; ++b) sum = fmaxf(sum, fabsf(sum_c[b]));
-    if (!__any(!(step * (float)(iters - t) < 0x1p-60f))) t = iters;
+    bool done = !__any(!(step * (float)(iters - t) < 0x1p-54f));
+    // (Now and then by what it changed in the plan itself: where a block falls into parts that only entries near e^-100 connect, each
+    // part has a constant of its own, and a sum over two parts stays.)
+    if (!done && ++looks % 3 == 0) {
+      float change = 0.0f;
+#pragma unroll
+      for (int a = 0; a < TH; ++a)
+#pragma unroll
+        for (int b = 0; b < TW; ++b) change = fmaxf(change, p[a][b] * fabsf(s[a] + gamma[b]));
+      done = !__any(!(change * (float)N * (float)(iters - t) < 0x1p-54f));
+    }
+    if (done) t = iters;
     go_on = t < iters && !__any(!(sum < kIncrementSum && largest <= 2.0f * (float)kSmallStep));
   }
 #pragma unroll
@@ -948,9 +981,9 @@ struct RepeatCheck {
     for (int b = 0; b < OWN_C; ++b) at(OWN_R + b) = V[b];
     noted = t;
   }
-  // t iterations are done: the number that are as good as done
+  // whether the state is the one noted
   template <int NU, int NV>
-  __device__ __forceinline__ int look(const real (&U)[NU], const real (&V)[NV], int t, int T, real first) {
+  __device__ __forceinline__ bool same(const real (&U)[NU], const real (&V)[NV], real first) {
     // (the whole state only if a first scaling of every lane is as it was)
     bool changed = __any(differ(U[0], first));
     if (!changed) {
@@ -960,8 +993,13 @@ struct RepeatCheck {
       for (int b = 0; b < OWN_C; ++b) changed |= differ(V[b], at(OWN_R + b));
       changed = __any(changed);
     }
+    return !changed;
+  }
+  // t iterations are done: the number that are as good as done
+  template <int NU, int NV>
+  __device__ __forceinline__ int look(const real (&U)[NU], const real (&V)[NV], int t, int T, real first) {
     const int d = t - noted;
-    if (!changed) {
+    if (same(U, V, first)) {
       while (T - t >= d) t += d;
       noted = t;
     } else if (d >= kRepeatWindow) {
@@ -1246,6 +1284,13 @@ __global__ __launch_bounds__((DykstraLaunch<M, FAST, ADAPT, TILES, LONE>::kThrea
             return false;
           }
         };
+        // (the same numbers; said so, both have one register in the loop)
+        [[maybe_unused]] const auto one_register = [&]() {
+          if constexpr (!kSwaps<T>) {
+#pragma unroll
+            for (int b = 0; b < OWN_C; ++b) Vown[b] = V[b];
+          }
+        };
         if constexpr (ADAPT) {
           // iteration count as a bound: every TSENOR_ADAPTIVE_CHECK_EVERY-th iteration the largest |factor - 1|
           // of the block is compared with the tolerance; a block that passes is frozen, the wave leaves when
@@ -1260,35 +1305,48 @@ __global__ __launch_bounds__((DykstraLaunch<M, FAST, ADAPT, TILES, LONE>::kThrea
               all_frozen = __all(frozen);
             }
           };
-          while (t < p.T && !all_frozen) {
-            const int stop = (kKept || kEnd) && p.T - t > kRepeatWindow ? t + kRepeatWindow : p.T;
+          for (int end = 0; t < p.T && !all_frozen;) {
+            end = of_wave((kKept || kEnd) && p.T - end > kRepeatWindow ? end + kRepeatWindow : p.T);
+            t = of_wave(t);
             [[maybe_unused]] const double first = Uown[0];
-            while (t < stop && !all_frozen) one();
-            if (!all_frozen) try_the_end(t, first, one);
+            while (t < end && !all_frozen) one();
             if constexpr (kKept) raise_rows();
+            if (!all_frozen && try_the_end(t, first, one)) end = t;
           }
         } else if constexpr (kKept) {
           using Repeat = RepeatCheck<double, OWN_R, OWN_C, !SMALL>;
           __shared__ typename Repeat::Space seen[WPG];
           Repeat repeat = Repeat::make(seen[wave_in_group], lane);
           repeat.note(Uown, Vown, 0);
-          for (int t = 0; t < p.T;) {
-            const int stop = (p.T - t > kRepeatWindow) ? t + kRepeatWindow : p.T;
+          // (`end`: of the windows, which stay kRepeatWindow apart also where try_the_end() has run one iteration in vain: states are
+          // compared over a whole number of their short periods)
+          for (int t = 0, end = 0; t < p.T;) {
+            end = of_wave(p.T - end > kRepeatWindow ? end + kRepeatWindow : p.T);
+            t = of_wave(t);
             const double first = repeat.at(0);
-            for (; t < stop; ++t) iterate();
-            const bool summed = try_the_end(t, first, [&]() { iterate(), ++t; });
+            for (; t < end; ++t) iterate();
             raise_rows();
-            if (summed)
+            // (noted one window ago, so that the period divides kRepeatWindow)
+            const bool again = repeat.same(Uown, Vown, first);
+            if (!again) repeat.note(Uown, Vown, t);
+            const bool summed = try_the_end(t, first, [&]() { iterate(), ++t; });
+            one_register();
+            if (summed) {
               repeat.note(Uown, Vown, t);
-            else
-              t = repeat.look(Uown, Vown, t, p.T, first);
+              end = t;
+            } else if (again) {
+              while (p.T - t >= kRepeatWindow) t += kRepeatWindow;
+              end = t;
+            }
           }
         } else if constexpr (kEnd) {
-          for (int t = 0; t < p.T;) {
-            const int stop = (p.T - t > kRepeatWindow) ? t + kRepeatWindow : p.T;
+          for (int t = 0, end = 0; t < p.T;) {
+            end = of_wave(p.T - end > kRepeatWindow ? end + kRepeatWindow : p.T);
+            t = of_wave(t);
             const double first = Uown[0];
-            for (; t < stop; ++t) iterate();
-            try_the_end(t, first, [&]() { iterate(), ++t; });
+            for (; t < end; ++t) iterate();
+            if (try_the_end(t, first, [&]() { iterate(), ++t; })) end = t;
+            one_register();
           }
         } else {
           for (int t = 0; t < p.T; ++t) iterate();

@@ -34,7 +34,7 @@ def _plan(W, N, M, tau, T, flags, tol=0.0):
     return got["plan"].cpu().numpy(), got["iters_done"].cpu().numpy() if tol > 0.0 else None
 
 
-@pytest.mark.parametrize("M,tiles", [(8, "large"), (16, "large"), (32, "large"), (16, "small")])
+@pytest.mark.parametrize("M,tiles", [(8, "large"), (16, "large"), (32, "large"), (16, "small"), (32, "small")])
 @pytest.mark.parametrize("dist,tau", [("student", 0.01), ("student", 0.05), ("mixed", 0.02), ("normal", 0.2)])
 def test_plan_after_increments(M, tiles, dist, tau):
     # before, at and behind the first windows, and every remainder of the eight increments between two looks
@@ -83,6 +83,59 @@ def test_tolerance_met_in_increments(M):
     assert np.abs(plan - np.exp(log_S)).max() < PLAN_ATOL
 
 
+def _seconds(W, N, M, tau, T, flags, tau_mode=1):
+    import torch
+
+    from paper_2505_23949_amd import binding as b
+
+    p = b.make_problem(W, N, M, tau, T, mask=torch.zeros(W.shape, dtype=torch.uint8, device=W.device),
+                       tau_mode=tau_mode, flags=flags)
+    work = torch.empty(b.tsenor_workspace_bytes([p]), dtype=torch.uint8, device=W.device)
+    best = float("inf")
+    for _ in range(3):
+        start, end = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+        start.record()
+        b.tsenor_mask_ex(p, work)
+        end.record()
+        torch.cuda.synchronize()
+        best = min(best, start.elapsed_time(end))
+    return best
+
+
+def _beside_the_cap(M, rng):
+    """A block that converges within dozens of iterations (K = W) to a plan whose first entry is a few 1e-7 below the cap."""
+    W = rng.random((M, M)).astype(np.float32)
+    low, high = 0.0, 8.0
+    for _ in range(60):
+        W[0, 0] = 0.5 * (low + high)
+        below = 1.0 - np.exp(oracle.dykstra(W, M // 2, M, 1.0, 150)[0, 0])
+        if 1e-7 < below < 7e-7:
+            return W
+        low, high = (low, W[0, 0]) if below < 1e-7 else (W[0, 0], high)
+    raise AssertionError("no such weight")
+
+
+@pytest.mark.parametrize("M,tiles", [(8, "large"), (16, "large"), (16, "small"), (32, "small")])
+def test_repeated_states_beside_the_cap(M, tiles):
+    # entries so near the cap that the increments are never taken up: the look for them runs an iteration now and then, and states
+    # are found to repeat all the same
+    import torch
+
+    from paper_2505_23949_amd import binding as b
+
+    # one block everywhere, eight of them in turn: their last bits run through cycles, of which all but a few have a period that the
+    # kernels look for, most of them an even one
+    rng = np.random.Generator(np.random.Philox(5 + M))
+    flags = b.TSENOR_FLAG_TILES_LARGE if tiles == "large" else b.TSENOR_FLAG_TILES_SMALL
+    found = 0
+    for k in range(8):
+        print(f"[case] repeated states beside the cap M={M} {tiles} {k}", flush=True)
+        W = torch.from_numpy(np.tile(_beside_the_cap(M, rng), (33, 33))).to("cuda:0")
+        short, long = (_seconds(W, M // 2, M, 1.0, T, flags, b.TSENOR_TAU_ABSOLUTE) for T in (1200, 60000))
+        found += long < 10 * short
+    assert found >= 5, found
+
+
 def test_increments_end_early():
     # 32 x 32 blocks on the large tiles do not look for repeated states: 60 000 iterations are over after some thousands of steps
     import torch
@@ -90,19 +143,6 @@ def test_increments_end_early():
     from paper_2505_23949_amd import binding as b
 
     W = torch.from_numpy(np.tile(np.random.Generator(np.random.Philox(7)).random((32, 32)), (33, 33)).astype(np.float32)).to("cuda:0")
-    times = []
-    for T in (1200, 60000):
-        print(f"[case] increments end early T={T}", flush=True)
-        p = b.make_problem(W, 16, 32, 1.0, T, mask=torch.zeros(W.shape, dtype=torch.uint8, device=W.device),
-                           tau_mode=b.TSENOR_TAU_REL_MATRIX_MAX, flags=b.TSENOR_FLAG_TILES_LARGE)
-        work = torch.empty(b.tsenor_workspace_bytes([p]), dtype=torch.uint8, device=W.device)
-        best = float("inf")
-        for _ in range(3):
-            start, end = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
-            start.record()
-            b.tsenor_mask_ex(p, work)
-            end.record()
-            torch.cuda.synchronize()
-            best = min(best, start.elapsed_time(end))
-        times.append(best)
-    assert times[1] < 10 * times[0], times
+    print("[case] increments end early", flush=True)
+    short, long = (_seconds(W, 16, 32, 1.0, T, b.TSENOR_FLAG_TILES_LARGE) for T in (1200, 60000))
+    assert long < 10 * short, (short, long)

@@ -1031,13 +1031,13 @@ struct DykstraLaunch {
   static constexpr int kWavesPerGroup = (ADAPT || TILES != kLargeTiles) ? 1 : M == 64 && FAST && !LONE ? 2 : FAST || M == 4 || M == 64 ? 4 : 1;
   static constexpr int kThreads = kWavesPerGroup * kWave;
   // Waves per SIMD the register budget is set for.  Double: the loop holds twice the state of the fp32 one, two waves of up
-  // to 256 registers; the 8-wide large tiles and the 16-wide small ones fit more with near_the_end() in them as well (168 registers;
-  // 128, of which six spill outside the loops).  FAST: the more waves, the nearer the issue of plain fp32 instructions comes to its limit (1.13 ns
-  // per instruction and SIMD with two waves, 1.05 with four).  M = 32: four waves of 128 registers, the loop fits and 37
+  // to 256 registers; the 8-wide large tiles and the 16-wide small ones four of 128, of which ten and eight spill outside the loops.
+  // FAST: the more waves, the nearer the issue of plain fp32 instructions comes to its limit (1.13 ns
+  // per instruction and SIMD with two waves, 1.05 with four).  M = 32: four waves of 128 registers, the loop fits and 38
   // registers of the double-precision code around it spill (whole calls with four / three waves, us: 4096x14336 Wanda-style 1364 /
   // 1464, normal 1745 / 1764; 4096 blocks, two waves to a SIMD anyway, 172 / 168).  M = 16: three (four the same to 0.4 % slower).
-  // M = 8: four (129 registers with three; three spill outside the loop).  M = 4: four fit whatever is asked for (five spill: 1 %
-  // slower).  M = 64: three, 131 registers spill outside the loop.  With three / two waves, T = 300 normal and T = 500 student-t,
+  // M = 8: four (eight spill outside the loop).  M = 4: four fit whatever is asked for (two spill outside the loop; five waves:
+  // 1 % slower).  M = 64: three, 133 registers spill outside the loop.  With three / two waves, T = 300 normal and T = 500 student-t,
   // of which blocks run from 50 iterations to all: 57 344 blocks 7046 / 7128 and 3080 / 3200, 16 384 Wanda-style 1924 / 2066; 4096
   // blocks 572 / 532 and 549 / 531, 1024 blocks, a wave to a SIMD, 269 / 254 and 394 / 379: full launches decide.  With the early
   // exit, where a block may run a dozen iterations and the code around the loop is most of the work, two (8192x8192: 0.85 ms,
@@ -1309,7 +1309,13 @@ __global__ __launch_bounds__((DykstraLaunch<M, FAST, ADAPT, TILES, LONE>::kThrea
             end = of_wave((kKept || kEnd) && p.T - end > kRepeatWindow ? end + kRepeatWindow : p.T);
             t = of_wave(t);
             [[maybe_unused]] const double first = Uown[0];
-            while (t < end && !all_frozen) one();
+            while (t < end && !all_frozen) {
+              // The three of four that no check follows need no factor's distance from 1, which the compiler leaves out here.
+              // Whole calls at tol = 1e-5, distances in all / one of four (us): 16:32 1184x256 Wanda-style 118.8 / 110.2, 4000x5408
+              // student-t 306.5 / 301.0; 32:64 2688x576 student-t 122.3 / 118.6; with fp32 iterations 16:32 672x960 student-t 61.4 / 58.5.
+              for (const int last = of_wave(min(end, t | (TSENOR_ADAPTIVE_CHECK_EVERY - 1))); t < last; ++t) iterate();
+              if (t < end) one();
+            }
             if constexpr (kKept) raise_rows();
             if (!all_frozen && try_the_end(t, first, one)) end = t;
           }
@@ -1463,11 +1469,15 @@ __global__ __launch_bounds__((DykstraLaunch<M, FAST, ADAPT, TILES, LONE>::kThrea
           __shared__ float2 xrows32[kLdsGather32 ? WPG : 1][kLdsGather32 ? kWave >> T::NX : 1][TH];
           float2* xr = kLdsGather32 ? &xrows32[wave_in_group][lane >> T::NX][0] : nullptr;
           if constexpr (ADAPT) {
-            for (; t < stop && !all_frozen; ++t) {
+            while (t < stop && !all_frozen) {
+              for (const int last = min(stop, t | (TSENOR_ADAPTIVE_CHECK_EVERY - 1)); t < last; ++t)
+                dykstra_iteration_f32<T, kLdsGather32, true>(kap32, U32, V32, V32own, Nf, xr, rx, frozen);
+              if (t >= stop) break;
               const float worst =
                   dykstra_iteration_f32<T, kLdsGather32, true>(kap32, U32, V32, V32own, Nf, xr, rx, frozen);
-              if ((t + 1) % TSENOR_ADAPTIVE_CHECK_EVERY == 0) {
-                freeze_if(block_max<LPB>((double)worst) <= p.tol, t + 1);
+              ++t;
+              if (t % TSENOR_ADAPTIVE_CHECK_EVERY == 0) {
+                freeze_if(block_max<LPB>((double)worst) <= p.tol, t);
                 all_frozen = __all(frozen);
               }
             }

@@ -53,7 +53,7 @@ def useful_ops_per_entry_iter(M: int, fp32: bool) -> float:
 # entries a wave holds (counted in the ISA of the built library, `v_*` lines between the loop label and its
 # branch; cross-lane ds_swizzle and LDS accesses issue on another pipeline and are not counted).  Keyed by
 # (M, layout), for the kernels that run all T iterations; the team is a 64 x 64 block on eight waves, of which a row counts one.
-LOOP_VALU_PER_WAVE_ITER = {(32, "large"): (162, 2048), (64, "large"): (374, 4096), (64, "team"): (93, 512)}
+LOOP_VALU_PER_WAVE_ITER = {(64, "large"): (374, 4096), (64, "team"): (93, 512)}
 
 
 def layout_of(M: int, fp32: bool, nblocks: int, iters: int) -> str:
@@ -289,18 +289,22 @@ def bench_matrix(args, name):
             out.update({"tol": tol, "mean_iterations": round(float(done.float().mean()), 1),
                         "kernel_ms": round(dyk_ms, 4)})
             return out, mask
-        # Waves stop once the states of their blocks repeat bit for bit (in double not those of the 32- and 64-wide large tiles), so
-        # the kernel may run fewer than T iterations.  The rate at which it iterates is taken from the early-exit kernel of the same
-        # tiling, which does not look for repetitions: with the smallest tolerance a block runs until T, or until a check meets an
-        # iteration whose factors are all exactly 1.  The iterations it ran are counted.
+        # Waves stop once the states of their blocks repeat bit for bit (in double not those of the 64-wide large tiles), and in
+        # double some end in increments, a shorter iteration, so the kernel may run fewer than T iterations of its loop.  The rate at
+        # which it iterates is taken from the early-exit kernel of the same tiling, which does not look for repetitions: with the
+        # smallest tolerance a block runs until T, or until a check meets an iteration whose factors are all exactly 1.  Where
+        # increments may follow, the tolerance is the change at which they start: blocks end there and none of them is counted.
+        # The iterations it ran are counted.
         layout = layout_of(w.M, fp32, nblocks, w.iters)
-        may_stop = w.iters > 0 and layout != "team" and (fp32 or w.M < 32 or layout != "large")
+        may_stop = w.iters > 0 and layout != "team" and (fp32 or w.M < 64)
+        increments = not fp32 and (layout, w.M) in (("large", 8), ("large", 16), ("large", 32), ("small", 16), ("small", 32))
+        rate_tol = 2.0 ** -30 if increments else 1e-300
         every_ms, mean_iters = dyk_ms, float(w.iters)
         if may_stop:
             ran = torch.zeros(nblocks, dtype=torch.int32, device=dev)
             tiles = binding.TSENOR_FLAG_TILES_LARGE if layout == "large" else binding.TSENOR_FLAG_TILES_SMALL
             every = binding.make_problem(W, w.N, w.M, w.tau, w.iters, mask=torch.empty_like(mask), col_scale=cs, tau_mode=w.tau_mode,
-                                         flags=(fp32_flag if fp32 else 0) | tiles, tol=1e-300, iters_done_out=ran)
+                                         flags=(fp32_flag if fp32 else 0) | tiles, tol=rate_tol, iters_done_out=ran)
             every_ms = binding.tsenor_mask_ex_profile(every, work, max(3, steps // 2))[1]
             mean_iters = float(ran.double().mean())
         every_entry_iters = float(weights) * mean_iters
@@ -315,11 +319,11 @@ def bench_matrix(args, name):
             "frac": round(achieved / peak, 4), "traffic": traffic["kernel"], "kernel_ms": round(dyk_ms, 4),
             "kernel_ms_every_iteration": round(every_ms, 4), "mean_iterations_of_that": round(mean_iters, 1),
             "rate_of": f"dykstra_sort_kernel<{w.M}{', fp32 iterations' if fp32 else ''}{', early exit' if may_stop else ''}>",
-            "useful_ops_per_entry_iteration": ops,
+            "rate_tol": rate_tol if may_stop else 0.0, "useful_ops_per_entry_iteration": ops,
             "note": ("bound by vector-ALU issue, not memory. achieved = useful vector operations (a multiply-add is "
                      "one) x rows x cols x mean_iterations_of_that / kernel_ms_every_iteration, both of the kernel named in "
-                     "rate_of: where the kernel stops waves whose state repeats itself bit for bit, that is the early-exit "
-                     "kernel of the same tiling at the smallest tolerance, which does not; kernel_ms, from HIP events at "
+                     "rate_of: where the kernel stops waves whose state repeats itself bit for bit, or ends in increments, that "
+                     "is the early-exit kernel of the same tiling at rate_tol, which does neither; kernel_ms, from HIP events at "
                      f"the stage boundaries of {steps} back-to-back passes, is the time of the calls measured; peak = "
                      + ("the rate measured on this chip for plain (unpacked) fp32 multiplies and adds; the published "
                         "157.3 TFLOP/s (78.6 T multiply-adds/s) needs the packed instructions, which are not used"

@@ -28,7 +28,10 @@
  *     nothing to compare or count).
  *   - The arithmetic of the Dykstra iterations, the sort keys and the swap scores
  *     is IEEE double precision on the device (iterations after the fourth in single
- *     precision with TSENOR_FLAG_FP32_ITERATIONS).
+ *     precision with TSENOR_FLAG_FP32_ITERATIONS).  Once no scaling of a block changes
+ *     by more than 2^-30 in an iteration, the changes themselves may be iterated in
+ *     single precision and summed in double: 2^-54 of a scaling, less than the 2^-48
+ *     its factors carry, and the plan is the one after `iters` iterations all the same.
  */
 #ifndef TSENOR_H
 #define TSENOR_H

@@ -596,7 +596,7 @@ __device__ __forceinline__ void round_blocks(const DevProblem& p, const BatchEnt
 // Bound by instruction issue: 3 650 vector instructions per wave (M = 32, the swaps of 16:32 4096x14336 included), of which the
 // two sorts are 764 and the keys 384; 2 060 up to the first proposals.  57 344 blocks of 16:32: 0.198 ms, where the sort across
 // lanes (0.20 ms of the iteration kernel), the scan kernel (0.077 ms) and the swap kernel (0.104 ms) took 0.38 ms; 57 344 of
-// 32:64: 0.99-1.17 ms (two waves per SIMD: 224 registers, 19 KB of LDS).  Six registers spill for M = 32, none elsewhere.
+// 32:64: 0.97-1.15 ms (7 100 vector instructions per wave, two waves per SIMD: 207 registers, 19 KB of LDS).  None spill.
 template <int M, bool ZERO_T>
 __global__ __launch_bounds__(kWave, M <= 32 ? 4 : 2) void round_kernel(Batch batch) {
   constexpr int G = kWave / M;

@@ -7,7 +7,7 @@ import oracle
 pytestmark = pytest.mark.gpu
 
 # The factors of an iteration carry 2^-48 and an entry of the plan what its block's convergence makes of them: up to 1e-12 with and
-# without increments (those add 2^-24 of changes below 2^-32).
+# without increments (those add 2^-24 of changes below 2^-30).
 PLAN_ATOL = 1e-11
 
 

@@ -323,7 +323,8 @@ def bench_matrix(args, name):
             "note": ("bound by vector-ALU issue, not memory. achieved = useful vector operations (a multiply-add is "
                      "one) x rows x cols x mean_iterations_of_that / kernel_ms_every_iteration, both of the kernel named in "
                      "rate_of: where the kernel stops waves whose state repeats itself bit for bit, or ends in increments, that "
-                     "is the early-exit kernel of the same tiling at rate_tol, which does neither; kernel_ms, from HIP events at "
+                     "is the early-exit kernel of the same tiling at rate_tol, which does neither (a block that has ended while "
+                     "another of its wave goes on is not counted); kernel_ms, from HIP events at "
                      f"the stage boundaries of {steps} back-to-back passes, is the time of the calls measured; peak = "
                      + ("the rate measured on this chip for plain (unpacked) fp32 multiplies and adds; the published "
                         "157.3 TFLOP/s (78.6 T multiply-adds/s) needs the packed instructions, which are not used"

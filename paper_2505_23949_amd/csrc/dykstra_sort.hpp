@@ -53,6 +53,7 @@ constexpr double kRaiseAbove = 0x1p+400;
 constexpr double kSmallStep = 0x1p-30;    // near_the_end(): factors of an iteration within this of 1 ...
 constexpr double kNearCap = 0x1p-20;      // ... no entry of the plan as near to the cap as this ...
 constexpr float kIncrementSum = 0x1p-25f; // ... and the sum of the increments before the plan is formed anew
+constexpr float kNothingLeft = 0x1p-54f;  // ... and what is left of the iterations when they are as good as done
 constexpr int kDriftBits = 40;            // FAST: fold the fp32 scalings back beyond 2^+-kDriftBits
 constexpr double kLogFloor32 = -83.0;     // FAST: rebuilt entries are kept within [e^-83, e^55] ~ [2^-120, 2^80]
 constexpr double kLogCeil32 = 55.0;
@@ -636,8 +637,15 @@ __device__ __forceinline__ double dykstra_iteration(double (&kap)[TH][TW], Tile&
 //     rho'_i  = (n_i rho_i - sum_p p_ij gamma_j) / N
 //     gamma'_j = (m_j gamma_j - sum_p p_ij rho'_i - sum_cap (rho'_i - rho_i)) / N
 // up to their squares, 2^-60.  The increments are iterated in fp32 and their sums go into the double scalings: a relative error
-// of 2^-24 of an increment below 2^-30 is less than the rounding of a double iteration, whose factors carry 2^-48.  When the
-// iterations that are left, were each to change an entry by as much as the last one did, add up to less than 2^-54, all are done.
+// of 2^-24 of an increment below 2^-30 is less than the rounding of a double iteration, whose factors carry 2^-48.
+// When the iterations that are left, were each to change the plan by as much as the last one did, add up to less than kNothingLeft, all
+// are done.  None changes it by more: a half iteration minimises a convex function (the dual of the projection problem) over the row,
+// the column or the cap's potentials, so that on a fixed side of the cap changes of the potentials go through the three orthogonal
+// projections of Gauss-Seidel in the norm of its second derivative, which at the end of an iteration is that of the plan,
+// E^2 = sum p_ij (rho_i + gamma_j)^2 over the entries below the cap.  E does not grow (random plans and changes: ratios up to 0.9998), and
+// an entry changes by sqrt(p_ij) E at most.  E <= M times the largest sqrt(p_ij) |rho_i + gamma_j|, and sqrt(N M) times the largest
+// |rho_i + gamma_j|: 2^-49 in the plan where M = 32 at the very most.  An entry above the cap does not count in E and may move on while
+// the plan stands still (a block of two parts that entries near 2^-36 connect: 2^-39 per iteration): it must not get to the cap.
 // 96 plain fp32 instructions per lane of a 32 x 32 block for the 120 of an iteration in double, and exchanges of one instruction
 // instead of three: 115 at 2.5-4 cycles where an iteration in double has 162 at 4.  Calls before / with it (us): 16:32 4096x14336
 // bf16 Wanda-style, T = 300, 2792 / 2515; 8:16 3280x12832 Wanda-style tau = 0.02 2199 / 1276; 4:8 4096x4096 student-t 537 / 326; 8:16
@@ -793,8 +801,9 @@ __device__ __forceinline__ int near_the_end(double (&kap)[TH][TW], Tile& x, doub
         if ((t + 1) % TSENOR_ADAPTIVE_CHECK_EVERY == 0 && tol >= 0x1p-53) freeze_if(block_max<LPB>((double)largest) <= tol, t + 1);
       }
     }
-    // What the last one changed in the logarithm of an entry, rho_i + gamma_j (opposite constants in the two change nothing, and the
-    // map keeps what rounding leaves of them), is what may be left for each of the others.
+    // What the last one changed in the logarithm of an entry is rho_i + gamma_j (opposite constants in the two change nothing, and
+    // the map keeps what rounding leaves of them).
+    const float left = (float)(iters - t);
     float rho_hi = s[0], rho_lo = s[0], gamma_hi = gamma[0], gamma_lo = gamma[0], sum = 0.0f;
 #pragma unroll
     for (int a = 1; a < TH; ++a) rho_hi = fmaxf(rho_hi, s[a]), rho_lo = fminf(rho_lo, s[a]);
@@ -805,16 +814,20 @@ __device__ __forceinline__ int near_the_end(double (&kap)[TH][TW], Tile& x, doub
     for (int a = 0; a < OWN_R; ++a) sum = fmaxf(sum, fabsf(sum_r[a]));
 #pragma unroll
     for (int b = 0; b < OWN_C; ++b) sum = fmaxf(sum, fabsf(sum_c[b]));
-    bool done = !__any(!(step * (float)(iters - t) < 0x1p-54f));
+    bool done = !__any(!(step * left < kNothingLeft));
     // (Now and then by what it changed in the plan itself: where a block falls into parts that only entries near e^-100 connect, each
-    // part has a constant of its own, and a sum over two parts stays.)
+    // part has a constant of its own, and a sum over two parts stays.  That it must not take an entry to the cap is asked as well.)
     if (!done && ++looks % 3 == 0) {
       float change = 0.0f;
 #pragma unroll
       for (int a = 0; a < TH; ++a)
 #pragma unroll
-        for (int b = 0; b < TW; ++b) change = fmaxf(change, p[a][b] * fabsf(s[a] + gamma[b]));
-      done = !__any(!(change * (float)N * (float)(iters - t) < 0x1p-54f));
+        for (int b = 0; b < TW; ++b) {
+          const float log_change = (s[a] + gamma[b]) * 0x1p+40f;  // (squares in the range of a float)
+          change = fmaxf(change, p[a][b] * (log_change * log_change));
+        }
+      done = !__any(!(change * (float)N * (left * left) < (kNothingLeft * 0x1p+40f) * (kNothingLeft * 0x1p+40f) &&
+                      step * left < 0.25f * (float)kNearCap));
     }
     if (done) t = iters;
     go_on = t < iters && !__any(!(sum < kIncrementSum && largest <= 2.0f * (float)kSmallStep));

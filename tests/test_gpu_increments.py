@@ -67,6 +67,38 @@ def test_increments_of_many_iterations(M):
     assert np.abs(plan - ref).max() < 1e-9
 
 
+def test_entry_that_drifts_to_the_cap():
+    # Two parts, each with a capped entry of the other's columns, and an entry of 7e-12 in one of the two corners only: the plan stands
+    # still and the capped entry of that corner comes down by 2e-12 per iteration.  It is 1e-6 above the cap once the rest has
+    # converged and 1.3e-11 below it at the end.
+    from paper_2505_23949_amd import binding as b
+
+    import torch
+
+    M, N, T = 8, 3, 700000
+    rng = np.random.default_rng(0)
+    K = np.full((M, M), -200.0)
+    for part in (slice(0, 4), slice(4, 8)):
+        K[part, part] = 0.3 * rng.random((4, 4))
+    K[0, 4], K[4, 0], K[1, 5] = 0.0063, 5.0, -25.7
+    W = (K + 200.0).astype(np.float32)
+
+    def above(tau):
+        log_S, log_Q = oracle.dykstra(W, N, M, tau, 150, return_log_Q=True)
+        return log_Q[0, 4] + log_S[0, 4] - 1.05e-6
+
+    low, high = 1.0, 1.001
+    for _ in range(50):
+        mid = 0.5 * (low + high)
+        low, high = (low, mid) if above(mid) > 0.0 else (mid, high)
+    print("[case] entry that drifts to the cap", flush=True)
+    ref = np.exp(oracle.dykstra(W, N, M, high, T))
+    assert 1e-11 < 1.0 - ref[0, 4] < 2e-11
+    got = b.solve(torch.from_numpy(W).to("cuda:0"), N, M, high, T, tau_mode=b.TSENOR_TAU_ABSOLUTE, flags=b.TSENOR_FLAG_TILES_LARGE,
+                  want_plan=True)
+    assert np.abs(got["plan"].cpu().numpy() - ref).max() < 1e-12
+
+
 @pytest.mark.parametrize("M", [8, 16, 32])
 def test_tolerance_met_in_increments(M):
     # a tolerance far below where they begin, and far above the rounding of the factors: the count is the oracle's

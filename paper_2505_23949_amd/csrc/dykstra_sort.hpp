@@ -247,6 +247,8 @@ __device__ __forceinline__ double fast_div(double n, double d) {
   return fma(fma(-d, x, 1.0), nx, nx);
 }
 __device__ __forceinline__ float fast_rcp(float d) { return __builtin_amdgcn_rcpf(d); }
+// n/d to the last bit or two from a quotient q of the above
+__device__ __forceinline__ double refined(double q, double n, double d) { return fma(fma(-d, q, n), __builtin_amdgcn_rcp(d), q); }
 // exp(x) for |x| <= 708, below 1 ulp of error: e^x = 2^n e^r with |r| <= ln2 / 2 (n by the addition that leaves it in the low word),
 // e^r = 1 + r + r^2 q(r), q the polynomial of degree 9 that minimises the largest relative error (3.6e-18, Remez exchange).  16
 // instructions; the library's exp() spends four more on results that leave the range of a double, which no entry of a tile does.
@@ -444,11 +446,13 @@ __device__ __forceinline__ void chain_phase(bool on) {
 // ADAPT (early exit): `frozen` lanes apply factors of exactly 1 (their block has stopped; its state no longer
 // changes), and the largest |factor - 1| among the rows and columns this lane owns is returned.
 // RUN: order_run() of the tiling.  LONE: no other wave shares the SIMD (chain_phase).
+// REFINED: factors without the 2^-48 of fast_div (near_the_end).
 struct NoTile {};
 // a count that is the same in all lanes, where the compiler cannot tell (in a vector register it costs the loop an instruction or two)
 __device__ __forceinline__ int of_wave(int n) { return __builtin_amdgcn_readfirstlane(n); }
 enum Form { kRecompute, kFold, kKeep };
-template <class T, Form FORM, Gather GATHER = kLanesOnly, bool ADAPT = false, int RUN = 0, bool LONE = false, class Tile, int TH, int TW, int NU>
+template <class T, Form FORM, Gather GATHER = kLanesOnly, bool ADAPT = false, int RUN = 0, bool LONE = false, bool REFINED = false,
+          class Tile, int TH, int TW, int NU>
 __device__ __forceinline__ double dykstra_iteration(double (&kap)[TH][TW], Tile& x, double (&U)[NU], double (&V)[TW],
                                                     double (&Vown)[owned(TW, T::NY)], double Nd, double* xr = nullptr, int rx = 0,
                                                     bool frozen = false) {
@@ -512,11 +516,14 @@ __device__ __forceinline__ double dykstra_iteration(double (&kap)[TH][TW], Tile&
 #pragma unroll
   for (int a = 0; a < OWN_R; ++a) {
     double factor;
+    const double sum = R[a];
     if constexpr (BARE) {
-      R[a] = fast_rcp(R[a]);
+      R[a] = fast_rcp(sum);
+      if constexpr (REFINED) R[a] = refined(R[a], 1.0, sum);
       factor = Nd * R[a];
     } else {
-      factor = fast_div(Nd, R[a]);
+      factor = fast_div(Nd, sum);
+      if constexpr (REFINED) factor = refined(factor, Nd, sum);
     }
     if constexpr (ADAPT) {
       worst = vmax(worst, fabs(factor - 1.0));
@@ -597,7 +604,9 @@ __device__ __forceinline__ double dykstra_iteration(double (&kap)[TH][TW], Tile&
   reduce_scatter_y<T, double, TW>(C);
 #pragma unroll
   for (int b = 0; b < OWN_C; ++b) {
-    C[b] = BARE ? fast_rcp(C[b]) : fast_div(Nd, C[b]);
+    const double sum = C[b];
+    C[b] = BARE ? fast_rcp(sum) : fast_div(Nd, sum);
+    if constexpr (REFINED) C[b] = refined(C[b], BARE ? 1.0 : Nd, sum);
     if constexpr (ADAPT) {
       worst = vmax(worst, fabs(C[b] - 1.0));
       C[b] = frozen ? 1.0 : C[b];
@@ -636,8 +645,10 @@ __device__ __forceinline__ double dykstra_iteration(double (&kap)[TH][TW], Tile&
 // is below the cap, n_i and m_j the entries at the cap in row i and column j):
 //     rho'_i  = (n_i rho_i - sum_p p_ij gamma_j) / N
 //     gamma'_j = (m_j gamma_j - sum_p p_ij rho'_i - sum_cap (rho'_i - rho_i)) / N
-// up to their squares, 2^-60.  The increments are iterated in fp32 and their sums go into the double scalings: a relative error
-// of 2^-24 of an increment below 2^-30 is less than the rounding of a double iteration, whose factors carry 2^-48.
+// up to their squares, 2^-60.  The increments are iterated in fp32, a relative error of 2^-24 of changes below 2^-30; eight of them at a
+// time are summed in fp32, the rest in double, and those sums go into the double scalings.  An error of the iteration they start from
+// is in all of them: a factor of fast_div carries 2^-48, which 1 / (1 - lambda) iterations of a slow block take up where fresh errors of
+// as many iterations in double would partly cancel.  So that one has factors of 2^-52 (`refined`).
 // When the iterations that are left, were each to change the plan by as much as the last one did, add up to less than kNothingLeft, all
 // are done.  None changes it by more: a half iteration minimises a convex function (the dual of the projection problem) over the row,
 // the column or the cap's potentials, so that on a fixed side of the cap changes of the potentials go through the three orthogonal
@@ -651,34 +662,25 @@ __device__ __forceinline__ double dykstra_iteration(double (&kap)[TH][TW], Tile&
 // bf16 Wanda-style, T = 300, 2792 / 2515; 8:16 3280x12832 Wanda-style tau = 0.02 2199 / 1276; 4:8 4096x4096 student-t 537 / 326; 8:16
 // 1072x2928 with its plan, small tiles, 198 / 178; 16:32 1600x1920 student-t, T = 500, small tiles, 176 / 117; normal weights, which never
 // come so near, 842 / 841 (8:16), 2535 / 2548 (4:8) and 143 / 145 (16:32 1088x1472, small tiles).
-// Error of the plan against a 64-bit evaluation (8, 16 and 32 wide, T = 100 to 500, three distributions): 0.98 of what it was, from
-// 0.86 to 1.03.
-// Called behind an iteration (t are done) with U_before and V_before the scalings before it; nothing happens unless the conditions
-// hold for the whole wave.  Returns the number of iterations done; if that is less than T the state is that after them.
-template <class T, Form FORM, bool LDS, bool ADAPT, int LPB, bool LONE, class Tile, class Freeze, int TH, int TW, int NU>
-__device__ __forceinline__ int near_the_end(double (&kap)[TH][TW], Tile& x, double (&U)[NU], double (&V)[TW],
-                                            double (&Vown)[owned(TW, T::NY)], const double (&U_before)[owned(TH, T::NX)],
-                                            const double (&V_before)[owned(TW, T::NY)], int N, int t, int iters, double tol, float2* xr,
-                                            int rx, const bool& frozen, Freeze& freeze_if) {
-  constexpr int OWN_R = owned(TH, T::NX), OWN_C = owned(TW, T::NY);
-  static_assert(FORM != kRecompute, "the increments take the registers of the capped entries");
+// Error of the plan (2-norm) against 80-bit iterations, relative to that of iterations in double to the end (8, 16 and 32 wide on either
+// tiling, K up to 10, 40 and 100, T = 100 to 500, three distributions): 0.43, at most 1.01, where no increment came; T = 30 000 on 8 x 8
+// normal blocks 0.16.  (With sums in fp32 and factors of fast_div before them 0.98 and, T = 30 000, 6.5.)
+// The first condition: no scaling of a wave has moved by more than that from what it was, U_before and V_before.
+template <int OWN_R, int OWN_C, int NU>
+__device__ __forceinline__ bool hardly_moves(const double (&U)[NU], const double (&Vown)[OWN_C], const double (&U_before)[OWN_R],
+                                             const double (&V_before)[OWN_C]) {
   bool moves = false;
 #pragma unroll
   for (int a = 0; a < OWN_R; ++a) moves |= !(fabs(U[a] - U_before[a]) <= kSmallStep * U_before[a]);
 #pragma unroll
   for (int b = 0; b < OWN_C; ++b) moves |= !(fabs(Vown[b] - V_before[b]) <= kSmallStep * V_before[b]);
-  if (__any(moves)) return t;
+  return !__any(moves);
+}
+// The second: no entry of the plan is beside the cap (from an opaque copy of V: the products of the look are not kept for the iteration
+// that follows).
+template <Form FORM, class Tile, int TH, int TW>
+__device__ __forceinline__ bool away_from_cap(const double (&kap)[TH][TW], const Tile& x, const double (&V)[TW]) {
   bool near = false;
-#pragma unroll
-  for (int a = 0; a < TH; ++a) {
-#pragma unroll
-    for (int b = 0; b < TW; ++b) near |= !(fabs((FORM == kKeep ? x[a][b] : kap[a][b]) * V[b] - 1.0) > kNearCap);
-    __builtin_amdgcn_sched_barrier(0);
-  }
-  if (__any(near)) return t;
-  // the plan and the entries at the cap, over N (from an opaque copy of V: the products of the look are not kept for it)
-  const float inv = 1.0f / (float)N;
-  float p[TH][TW], c[TH][TW];
   double Vc[TW];
 #pragma unroll
   for (int b = 0; b < TW; ++b) {
@@ -688,8 +690,28 @@ __device__ __forceinline__ int near_the_end(double (&kap)[TH][TW], Tile& x, doub
 #pragma unroll
   for (int a = 0; a < TH; ++a) {
 #pragma unroll
+    for (int b = 0; b < TW; ++b) near |= !(fabs((FORM == kKeep ? x[a][b] : kap[a][b]) * Vc[b] - 1.0) > kNearCap);
+    __builtin_amdgcn_sched_barrier(0);
+  }
+  return !__any(near);
+}
+// The iterations behind the t that are done, U_before and V_before the scalings before the last of them, for which both hold.
+// Returns the number of iterations done; if that is less than `iters` the state is that after them.
+template <class T, Form FORM, bool LDS, bool ADAPT, int LPB, bool LONE, class Tile, class Freeze, int TH, int TW, int NU>
+__device__ __forceinline__ int iterate_increments(double (&kap)[TH][TW], Tile& x, double (&U)[NU], double (&V)[TW],
+                                                  double (&Vown)[owned(TW, T::NY)], const double (&U_before)[owned(TH, T::NX)],
+                                                  const double (&V_before)[owned(TW, T::NY)], int N, int t, int iters, double tol, float2* xr,
+                                                  int rx, const bool& frozen, Freeze& freeze_if) {
+  constexpr int OWN_R = owned(TH, T::NX), OWN_C = owned(TW, T::NY);
+  static_assert(FORM != kRecompute, "the increments take the registers of the capped entries");
+  // the plan and the entries at the cap, over N
+  const float inv = 1.0f / (float)N;
+  float p[TH][TW], c[TH][TW];
+#pragma unroll
+  for (int a = 0; a < TH; ++a) {
+#pragma unroll
     for (int b = 0; b < TW; ++b) {
-      const double entry = (FORM == kKeep ? x[a][b] : kap[a][b]) * Vc[b];
+      const double entry = (FORM == kKeep ? x[a][b] : kap[a][b]) * V[b];
       const bool at_cap = entry > 1.0;
       p[a][b] = at_cap ? 0.0f : (float)entry * inv;
       c[a][b] = at_cap ? inv : 0.0f;
@@ -711,7 +733,8 @@ __device__ __forceinline__ int near_the_end(double (&kap)[TH][TW], Tile& x, doub
   }
   reduce_scatter_x<T, float, TH>(rows_at_cap);
   reduce_scatter_y<T, float, TW>(cols_at_cap);
-  float gamma_own[OWN_C], sum_r[OWN_R] = {}, sum_c[OWN_C] = {};
+  float gamma_own[OWN_C];
+  double moved_r[OWN_R] = {}, moved_c[OWN_C] = {};  // sums of the increments
 #pragma unroll
   for (int a = 0; a < OWN_R; ++a) rho[a] = (float)((U[a] - U_before[a]) * __builtin_amdgcn_rcp(U_before[a]));
 #pragma unroll
@@ -722,7 +745,7 @@ __device__ __forceinline__ int near_the_end(double (&kap)[TH][TW], Tile& x, doub
   int looks = 0;
   for (bool go_on = true; go_on;) {
     const int stop = iters - t > kChunk ? t + kChunk : iters;
-    float largest = 0.0f, s[TH];
+    float largest = 0.0f, s[TH], sum_r[OWN_R] = {}, sum_c[OWN_C] = {};
     for (; t < stop; ++t) {
       float d[TH], q[TW];
       if constexpr (T::NY == 3) {
@@ -801,19 +824,23 @@ __device__ __forceinline__ int near_the_end(double (&kap)[TH][TW], Tile& x, doub
         if ((t + 1) % TSENOR_ADAPTIVE_CHECK_EVERY == 0 && tol >= 0x1p-53) freeze_if(block_max<LPB>((double)largest) <= tol, t + 1);
       }
     }
+#pragma unroll
+    for (int a = 0; a < OWN_R; ++a) moved_r[a] += (double)sum_r[a];
+#pragma unroll
+    for (int b = 0; b < OWN_C; ++b) moved_c[b] += (double)sum_c[b];
     // What the last one changed in the logarithm of an entry is rho_i + gamma_j (opposite constants in the two change nothing, and
     // the map keeps what rounding leaves of them).
     const float left = (float)(iters - t);
-    float rho_hi = s[0], rho_lo = s[0], gamma_hi = gamma[0], gamma_lo = gamma[0], sum = 0.0f;
+    float rho_hi = s[0], rho_lo = s[0], gamma_hi = gamma[0], gamma_lo = gamma[0], moved = 0.0f;
 #pragma unroll
     for (int a = 1; a < TH; ++a) rho_hi = fmaxf(rho_hi, s[a]), rho_lo = fminf(rho_lo, s[a]);
 #pragma unroll
     for (int b = 1; b < TW; ++b) gamma_hi = fmaxf(gamma_hi, gamma[b]), gamma_lo = fminf(gamma_lo, gamma[b]);
     const float step = fmaxf(fabsf(rho_hi + gamma_hi), fabsf(rho_lo + gamma_lo));
 #pragma unroll
-    for (int a = 0; a < OWN_R; ++a) sum = fmaxf(sum, fabsf(sum_r[a]));
+    for (int a = 0; a < OWN_R; ++a) moved = fmaxf(moved, fabsf((float)moved_r[a]));
 #pragma unroll
-    for (int b = 0; b < OWN_C; ++b) sum = fmaxf(sum, fabsf(sum_c[b]));
+    for (int b = 0; b < OWN_C; ++b) moved = fmaxf(moved, fabsf((float)moved_c[b]));
     bool done = !__any(!(step * left < kNothingLeft));
     // (Now and then by what it changed in the plan itself: where a block falls into parts that only entries near e^-100 connect, each
     // part has a constant of its own, and a sum over two parts stays.  That it must not take an entry to the cap is asked as well.)
@@ -830,30 +857,31 @@ __device__ __forceinline__ int near_the_end(double (&kap)[TH][TW], Tile& x, doub
                       step * left < 0.25f * (float)kNearCap));
     }
     if (done) t = iters;
-    go_on = t < iters && !__any(!(sum < kIncrementSum && largest <= 2.0f * (float)kSmallStep));
+    go_on = t < iters && !__any(!(moved < kIncrementSum && largest <= 2.0f * (float)kSmallStep));
+  }
+  // (a scaling has taken the product of the 1 + increments, e to their sum)
+  double by[TH];
+#pragma unroll
+  for (int a = 0; a < OWN_R; ++a) {
+    by[a] = fma(0.5 * moved_r[a], moved_r[a], moved_r[a]);
+    U[a] = fma(U[a], by[a], U[a]);
   }
 #pragma unroll
-  for (int a = 0; a < OWN_R; ++a) U[a] = fma(U[a], (double)sum_r[a], U[a]);
-#pragma unroll
-  for (int b = 0; b < OWN_C; ++b) V[b] = Vown[b] = fma(Vown[b], (double)sum_c[b], Vown[b]);
+  for (int b = 0; b < OWN_C; ++b) V[b] = Vown[b] = fma(Vown[b], fma(0.5 * moved_c[b], moved_c[b], moved_c[b]), Vown[b]);
   all_gather_y<T, double, TW>(V);
   // (the tile also when all iterations are done: it need not be kept beside p and c then)
-  float all[TH];
-#pragma unroll
-  for (int a = 0; a < OWN_R; ++a) all[a] = sum_r[a];
-  all_gather_x<T, float, TH>(all);
+  all_gather_x<T, double, TH>(by);
 #pragma unroll
   for (int a = 0; a < TH; ++a) {
-    const double by = (double)all[a];
     if constexpr (FORM == kKeep) {
-      if (a >= OWN_R) U[a] = fma(U[a], by, U[a]);
+      if (a >= OWN_R) U[a] = fma(U[a], by[a], U[a]);
     }
 #pragma unroll
     for (int b = 0; b < TW; ++b) {
       if constexpr (FORM == kKeep)
         x[a][b] = kap[a][b] * U[a];
       else
-        kap[a][b] = fma(kap[a][b], by, kap[a][b]);
+        kap[a][b] = fma(kap[a][b], by[a], kap[a][b]);
     }
     __builtin_amdgcn_sched_barrier(0);
   }
@@ -1044,7 +1072,8 @@ struct DykstraLaunch {
   static constexpr int kWavesPerGroup = (ADAPT || TILES != kLargeTiles) ? 1 : M == 64 && FAST && !LONE ? 2 : FAST || M == 4 || M == 64 ? 4 : 1;
   static constexpr int kThreads = kWavesPerGroup * kWave;
   // Waves per SIMD the register budget is set for.  Double: the loop holds twice the state of the fp32 one, two waves of up
-  // to 256 registers; the 8-wide large tiles and the 16-wide small ones four of 128, of which ten and eight spill outside the loops.
+  // to 256 registers; the 8-wide large tiles and the 16-wide small ones four of 128, of which 14 and 19 spill outside the loops (23 and 17
+  // with the early exit).
   // FAST: the more waves, the nearer the issue of plain fp32 instructions comes to its limit (1.13 ns
   // per instruction and SIMD with two waves, 1.05 with four).  M = 32: four waves of 128 registers, the loop fits and 38
   // registers of the double-precision code around it spill (whole calls with four / three waves, us: 4096x14336 Wanda-style 1364 /
@@ -1211,10 +1240,10 @@ __global__ __launch_bounds__((DykstraLaunch<M, FAST, ADAPT, TILES, LONE>::kThrea
     [[maybe_unused]] int u_exp[OWN_R] = {}, v_exp[OWN_C] = {};
     // early exit: a block whose factors have passed the tolerance is frozen at that iteration
     bool frozen = false;
-    auto freeze_if = [&](bool passed, int t_done) {
+    auto freeze_if = [&](bool passed, int t_done, bool stop = true) {
       if (!frozen && passed) {
-        frozen = true;
-        iters_done = t_done;
+        frozen = stop;
+        iters_done = min(iters_done, t_done);
       }
     };
     // FAST: the tile of the fp32 phase, fl32(kap U V)
@@ -1279,20 +1308,21 @@ __global__ __launch_bounds__((DykstraLaunch<M, FAST, ADAPT, TILES, LONE>::kThrea
         };
         constexpr bool kEnd = increments_at_the_end<M, TILES>();
         // Behind a window of iterations over which a scaling of every lane has hardly changed (`first`: what it was before them): one
-        // more iteration, whose factors near_the_end() looks at, and the rest in increments if it may.
+        // more iteration, with refined factors, and the rest in increments if that may be.  Whether any was done in increments.
         [[maybe_unused]] const auto try_the_end = [&]([[maybe_unused]] int& t, [[maybe_unused]] double first, [[maybe_unused]] auto&& one_more) {
           if constexpr (kEnd) {
             if (t + 1 >= p.T || __any(!(fabs(Uown[0] - first) <= kRepeatWindow * kSmallStep * first))) return false;
+            if (!away_from_cap<kForm>(kap, x, V)) return false;
             double U_before[OWN_R], V_before[OWN_C];
 #pragma unroll
             for (int a = 0; a < OWN_R; ++a) U_before[a] = Uown[a];
 #pragma unroll
             for (int b = 0; b < OWN_C; ++b) V_before[b] = Vown[b];
-            one_more();
-            const int before = t;
-            t = near_the_end<T, kForm, kLds, ADAPT, LPB, LONE>(kap, x, Uown, V, Vown, U_before, V_before, p.N, t, p.T, p.tol,
-                                                               reinterpret_cast<float2*>(xr), rx, frozen, freeze_if);
-            return t > before;
+            one_more(dykstra_iteration<T, kForm, kGather, ADAPT, RUN, LONE, true>(kap, x, Uown, V, Vown, Nd, xr, rx, frozen));
+            if (!hardly_moves(Uown, Vown, U_before, V_before)) return false;
+            t = iterate_increments<T, kForm, kLds, ADAPT, LPB, LONE>(kap, x, Uown, V, Vown, U_before, V_before, p.N, t, p.T, p.tol,
+                                                                     reinterpret_cast<float2*>(xr), rx, frozen, freeze_if);
+            return true;
           } else {
             return false;
           }
@@ -1310,11 +1340,11 @@ __global__ __launch_bounds__((DykstraLaunch<M, FAST, ADAPT, TILES, LONE>::kThrea
           // all its blocks are
           bool all_frozen = false;
           int t = 0;
-          const auto one = [&]() {
-            const double worst = iterate();
+          const auto count = [&](double worst) {
             ++t;
             if (t % TSENOR_ADAPTIVE_CHECK_EVERY == 0) {
-              freeze_if(block_max<LPB>(worst) <= p.tol, t);
+              // (a block whose factors are exactly 1 is not where refined ones would leave it)
+              freeze_if(block_max<LPB>(worst) <= p.tol, t, !kEnd || p.tol >= 0x1p-53);
               all_frozen = __all(frozen);
             }
           };
@@ -1327,10 +1357,10 @@ __global__ __launch_bounds__((DykstraLaunch<M, FAST, ADAPT, TILES, LONE>::kThrea
               // Whole calls at tol = 1e-5, distances in all / one of four (us): 16:32 1184x256 Wanda-style 118.8 / 110.2, 4000x5408
               // student-t 306.5 / 301.0; 32:64 2688x576 student-t 122.3 / 118.6; with fp32 iterations 16:32 672x960 student-t 61.4 / 58.5.
               for (const int last = of_wave(min(end, t | (TSENOR_ADAPTIVE_CHECK_EVERY - 1))); t < last; ++t) iterate();
-              if (t < end) one();
+              if (t < end) count(iterate());
             }
             if constexpr (kKept) raise_rows();
-            if (!all_frozen && try_the_end(t, first, one)) end = t;
+            if (!all_frozen && try_the_end(t, first, count)) end = t;
           }
         } else if constexpr (kKept) {
           using Repeat = RepeatCheck<double, OWN_R, OWN_C, !SMALL>;
@@ -1348,7 +1378,7 @@ __global__ __launch_bounds__((DykstraLaunch<M, FAST, ADAPT, TILES, LONE>::kThrea
             // (noted one window ago, so that the period divides kRepeatWindow)
             const bool again = repeat.same(Uown, Vown, first);
             if (!again) repeat.note(Uown, Vown, t);
-            const bool summed = try_the_end(t, first, [&]() { iterate(), ++t; });
+            const bool summed = try_the_end(t, first, [&](double) { ++t; });
             one_register();
             if (summed) {
               repeat.note(Uown, Vown, t);
@@ -1364,7 +1394,7 @@ __global__ __launch_bounds__((DykstraLaunch<M, FAST, ADAPT, TILES, LONE>::kThrea
             t = of_wave(t);
             const double first = Uown[0];
             for (; t < end; ++t) iterate();
-            if (try_the_end(t, first, [&]() { iterate(), ++t; })) end = t;
+            if (try_the_end(t, first, [&](double) { ++t; })) end = t;
             one_register();
           }
         } else {

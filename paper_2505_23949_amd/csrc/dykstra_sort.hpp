@@ -744,7 +744,8 @@ __device__ __forceinline__ int iterate_increments(double (&kap)[TH][TW], Tile& x
   all_gather_y<T, float, TW>(gamma);
   int looks = 0;
   for (bool go_on = true; go_on;) {
-    const int stop = iters - t > kChunk ? t + kChunk : iters;
+    // (up to a multiple of kChunk, so that a check for the tolerance comes just before what follows)
+    const int stop = min(iters, (t | (kChunk - 1)) + 1);
     float largest = 0.0f, s[TH], sum_r[OWN_R] = {}, sum_c[OWN_C] = {};
     for (; t < stop; ++t) {
       float d[TH], q[TW];
@@ -820,8 +821,10 @@ __device__ __forceinline__ int iterate_increments(double (&kap)[TH][TW], Tile& x
       all_gather_y<T, float, TW>(gamma);
       chain_phase<LONE>(false);
       if constexpr (ADAPT) {
-        // (a tolerance below the precision of a double is never met, as by the factors of the iterations in double)
-        if ((t + 1) % TSENOR_ADAPTIVE_CHECK_EVERY == 0 && tol >= 0x1p-53) freeze_if(block_max<LPB>((double)largest) <= tol, t + 1);
+        // (a tolerance that only factors of exactly 1 meet, 1 + an increment below 2^-54: the block has stopped but for what the sum
+        // of all that are left makes of them)
+        if ((t + 1) % TSENOR_ADAPTIVE_CHECK_EVERY == 0)
+          freeze_if(block_max<LPB>((double)largest) <= fmax(tol, 0x1p-54), t + 1, tol >= 0x1p-53);
       }
     }
 #pragma unroll

@@ -179,11 +179,12 @@ def test_tolerance_below_the_factors_rounding(M, tiles):
 
     W, N, tau, T = _weights(M, "normal", (8, 256 // M)), M // 2, 0.1, 500
     flags = b.TSENOR_FLAG_TILES_LARGE if tiles == "large" else b.TSENOR_FLAG_TILES_SMALL
-    for tol in (2.0**-52, 2.0**-50):
+    for tol in (1e-300, 2.0**-52, 2.0**-50):
         print(f"[case] tolerance below the factors' rounding {N}:{M} {tiles} {tol}", flush=True)
         plan, done = _plan(W, N, M, tau, T, flags, tol)
         print(f"mean {done.mean():.1f}, to the end {(done == T).mean():.3f}", flush=True)
-        assert (done == T).mean() < 0.04
+        # (one below 2^-53 is met by factors of exactly 1, which the increments of some blocks do not come down to: 0 to 0.16)
+        assert done.mean() < 300 if tol < 2.0**-53 else (done == T).mean() < 0.04
 
 
 def _seconds(W, N, M, tau, T, flags, tau_mode=1):

@@ -1075,8 +1075,10 @@ struct DykstraLaunch {
   static constexpr int kWavesPerGroup = (ADAPT || TILES != kLargeTiles) ? 1 : M == 64 && FAST && !LONE ? 2 : FAST || M == 4 || M == 64 ? 4 : 1;
   static constexpr int kThreads = kWavesPerGroup * kWave;
   // Waves per SIMD the register budget is set for.  Double: the loop holds twice the state of the fp32 one, two waves of up
-  // to 256 registers; the 8-wide large tiles and the 16-wide small ones four of 128, of which 14 and 19 spill outside the loops (23 and 17
-  // with the early exit).
+  // to 256 registers; the 8-wide large tiles and the 16-wide small ones three of 168, no spills (with four of 128 the increments spill 14
+  // and 19 outside the loops; four / three, us: 4:8 4096x4096 with all outputs 995 / 981, student-t 1536x2048 86.4 / 85.3, 8:16 2048x1024
+  // T = 500 normal 200.4 / 196.5, student-t 111.2 / 108.9, 1792x1792 student-t 73.5 / 74.1).  With the early exit the 16-wide ones four: launches
+  // of just under four waves per SIMD run at once (3936x1056 normal 245 / 270; 17 registers spill).
   // FAST: the more waves, the nearer the issue of plain fp32 instructions comes to its limit (1.13 ns
   // per instruction and SIMD with two waves, 1.05 with four).  M = 32: four waves of 128 registers, the loop fits and 38
   // registers of the double-precision code around it spill (whole calls with four / three waves, us: 4096x14336 Wanda-style 1364 /
@@ -1088,7 +1090,10 @@ struct DykstraLaunch {
   // exit, where a block may run a dozen iterations and the code around the loop is most of the work, two (8192x8192: 0.85 ms,
   // three 1.05).
   static constexpr int kWavesPerSimd =
-      FAST && !(M == 64 && ADAPT) ? (M == 16 || M == 64 ? 3 : 4) : !LONE && ((M == 16 && TILES == kSmallTiles) || (M == 8 && TILES == kLargeTiles)) ? 4 : 2;
+      FAST && !(M == 64 && ADAPT)                  ? (M == 16 || M == 64 ? 3 : 4)
+      : M == 8 && TILES == kLargeTiles             ? 3
+      : !LONE && M == 16 && TILES == kSmallTiles ? (ADAPT ? 4 : 3)
+                                                   : 2;
 };
 
 // ZERO_T: the instantiation for T = 0 (no iterations, keys are K itself).  It is a template parameter

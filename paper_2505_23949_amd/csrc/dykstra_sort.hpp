@@ -1364,6 +1364,7 @@ __global__ __launch_bounds__((DykstraLaunch<M, FAST, ADAPT, TILES, LONE>::kThrea
               // The three of four that no check follows need no factor's distance from 1, which the compiler leaves out here.
               // Whole calls at tol = 1e-5, distances in all / one of four (us): 16:32 1184x256 Wanda-style 118.8 / 110.2, 4000x5408
               // student-t 306.5 / 301.0; 32:64 2688x576 student-t 122.3 / 118.6; with fp32 iterations 16:32 672x960 student-t 61.4 / 58.5.
+              one_register();
               for (const int last = of_wave(min(end, t | (TSENOR_ADAPTIVE_CHECK_EVERY - 1))); t < last; ++t) iterate();
               if (t < end) count(iterate());
             }

@@ -1,9 +1,11 @@
-"""Matrices with a column scale, whose blocks the iterations take column by column in the order of their scales: the results are those
-of the oracle, and of the same call in ABSOLUTE mode, which takes them row by row."""
+"""Matrices with a column scale, whose blocks the iterations take column by column in the order of their scales: plans, masks, counts and
+objectives are those of the oracle on a few block rows, and those of the same call in ABSOLUTE mode, which takes them row by row, up to
+what a block's last bits owe to the blocks it shares a wave with."""
 import numpy as np
 import pytest
 
 import oracle
+from oracle import exact
 
 pytestmark = pytest.mark.gpu
 
@@ -13,9 +15,22 @@ def _scales(kind, cols, M, rng):
         return np.full(cols, 0.75, np.float32)
     if kind == "zeros":  # whole block columns without any importance
         return np.where(np.arange(cols) // M % 3 == 0, 0.0, rng.random(cols)).astype(np.float32)
+    if kind == "signed zeros":  # any bits are ordered, as integers: -0 comes before every scale
+        at = np.arange(cols) // M
+        return np.where(at % 5 == 0, -0.0, np.where(at % 7 == 1, 1e-40, rng.random(cols))).astype(np.float32)
     if kind == "descending":
         return np.linspace(3.0, 0.01, cols, dtype=np.float32)
     return rng.lognormal(0.0, 1.0, cols).astype(np.float32)
+
+
+def _differ(got, ref, M):
+    """Blocks of two masks that differ, of those in which no two entries of the oracle's plan are mathematically tied: closer than 100 times
+    what the two sides agree to on a logarithm after some hundred iterations."""
+    same = (exact.blocks(got, M) == exact.blocks(ref["mask"], M)).all(axis=(1, 2))
+    keys = np.sort(exact.blocks(ref["log_S"], M).reshape(-1, M * M), axis=1)
+    size = np.maximum(np.abs(keys[:, 1:]), np.abs(keys[:, :-1]))
+    tied = ((np.diff(keys, axis=1) <= 1e-10 * np.maximum(size, 1e-3)) & (size > 0)).any(axis=1)
+    return int((~same & ~tied).sum()), int((~tied).sum())
 
 
 def _solve(W, scale, N, M, T, tau, mode, flags, **kw):
@@ -35,7 +50,7 @@ SIZES = [(8, 13, 317, "small"), (16, 2050, 2, "small"), (32, 5, 205, "small"), (
 
 
 @pytest.mark.parametrize("M,br,bc,tiles", SIZES)
-@pytest.mark.parametrize("kind", ["equal", "zeros", "descending", "lognormal"])
+@pytest.mark.parametrize("kind", ["equal", "zeros", "signed zeros", "descending", "lognormal"])
 def test_blocks_by_column_scale(M, br, bc, tiles, kind):
     import torch
 
@@ -56,19 +71,61 @@ def test_blocks_by_column_scale(M, br, bc, tiles, kind):
         print(f"[case] by column scale {N}:{M} {br}x{bc} {tiles} {kind} flags={flags | more}", flush=True)
         got = _solve(W, s, N, M, T, tau, b.TSENOR_TAU_REL_MATRIX_MAX, flags | more)
         ref = _solve(W, s, N, M, T, te, b.TSENOR_TAU_ABSOLUTE, flags | more)
-        # in double a block's result does not depend on the blocks it shares its wave with but for the last iterations' rounding; in
-        # fp32 the tile of a wave is formed anew for all of its blocks at once
-        if "fp32" in tiles:
-            assert (got["plan"] - ref["plan"]).abs().max().item() < 1e-4
-            assert (got["mask"] != ref["mask"]).float().mean().item() < 1.2e-4
-        else:
-            assert (got["plan"] - ref["plan"]).abs().max().item() < 1e-11
-            assert (got["mask"] != ref["mask"]).float().mean().item() < 2e-5
+        # The last bits of a block owe something to the blocks it shares its wave with, which are others in the two orders: in double where
+        # increments begin, in fp32 where the tile of a wave is formed anew.
+        fp32 = "fp32" in tiles
+        differing = (got["mask"] != ref["mask"]).view(br, M, bc, M).any(3).any(1).sum().item()
+        assert (got["plan"] - ref["plan"]).abs().max().item() < (1e-4 if fp32 else 1e-11)
+        assert (got["mask"] != ref["mask"]).float().mean().item() < (1.2e-4 if fp32 else 2e-5)
+        assert (got["stats"] - ref["stats"]).abs().max().item() <= M * differing
+        mask = got["mask"].cpu().numpy()
+        assert exact.is_transposable_nm(mask, N, M)
+        objective = oracle.objective(mask, imp, M)
+        assert abs(got["objective"][0].item() - objective) <= 1e-12 * objective
         # a few block rows against the oracle
+        differ = compared = 0
         for r in sorted({0, br // 2, br - 1}):
             rows_of = slice(r * M, r * M + M)
-            plan = np.exp(oracle.dykstra(imp[rows_of], N, M, te, T, cols_first=more != 0))
-            assert np.abs(got["plan"][rows_of].cpu().numpy() - plan).max() < (1e-4 if "fp32" in tiles else 1e-9)
+            of = oracle.mask(np.ascontiguousarray(wide[rows_of, 3:3 + cols]), N, M, te, T, col_scale=scale, cols_first=more != 0,
+                             return_plan=True)
+            assert np.abs(got["plan"][rows_of].cpu().numpy() - np.exp(of["log_S"])).max() < (1e-4 if fp32 else 1e-9)
+            d, n = _differ(mask[rows_of], of, M)
+            differ, compared = differ + d, compared + n
+        print(f"blocks of another mask: {differing} in the two orders, {differ} of {compared} by the oracle", flush=True)
+        assert differ <= (0.01 * compared if fp32 else 0)
+
+
+@pytest.mark.parametrize("M,br,bc,tiles", [(8, 13, 317, "small"), (16, 131, 126, "large"), (32, 5, 205, "small"), (32, 64, 65, "large"),
+                                           (64, 33, 63, "large"), (32, 91, 91, "large fp32")])
+def test_early_exit_by_column_scale(M, br, bc, tiles):
+    # a block stops by itself, so that in double everything is bit for bit what the order of the rows gives, at every block's own place
+    import torch
+
+    from paper_2505_23949_amd import binding as b
+
+    flags = {"small": b.TSENOR_FLAG_TILES_SMALL, "large": b.TSENOR_FLAG_TILES_LARGE,
+             "large fp32": b.TSENOR_FLAG_TILES_LARGE | b.TSENOR_FLAG_FP32_ITERATIONS}[tiles]
+    rng = np.random.Generator(np.random.Philox(180 + M))
+    N, T, tau, tol = M // 2, 150, 0.02, 1e-4
+    W = 0.02 * rng.standard_normal((br * M, bc * M), dtype=np.float32)
+    scale = _scales("lognormal", bc * M, M, rng)
+    imp = oracle.importance(W, scale)
+    te = oracle.tau_eff(imp, tau, oracle.TAU_REL_MATRIX_MAX)
+    Wd, s = torch.from_numpy(W).to("cuda:0"), torch.from_numpy(scale).to("cuda:0")
+    print(f"[case] early exit by column scale {N}:{M} {br}x{bc} {tiles}", flush=True)
+    got = _solve(Wd, s, N, M, T, tau, b.TSENOR_TAU_REL_MATRIX_MAX, flags, tol=tol, want_iters_done=True)
+    ref = _solve(Wd, s, N, M, T, te, b.TSENOR_TAU_ABSOLUTE, flags, tol=tol, want_iters_done=True)
+    done = got["iters_done"].view(br, bc)
+    assert (done < T).any() and done.min().item() < done.max().item()
+    if "fp32" not in tiles:
+        for name in ("iters_done", "plan", "mask", "stats", "objective"):
+            assert torch.equal(got[name], ref[name]), name
+    else:
+        assert (got["iters_done"] - ref["iters_done"]).abs().max().item() <= 4 * b.TSENOR_ADAPTIVE_CHECK_EVERY
+    for r in (0, br - 1):
+        _, done_ref = oracle.dykstra_adaptive(imp[r * M:r * M + M], N, M, te, T, tol)
+        apart = np.abs(done[r].cpu().numpy() - done_ref.reshape(-1))
+        assert apart.max() <= (4 if "fp32" in tiles else 1) * b.TSENOR_ADAPTIVE_CHECK_EVERY
 
 
 def test_batch_of_ordered_matrices():

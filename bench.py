@@ -55,6 +55,9 @@ def useful_ops_per_entry_iter(M: int, fp32: bool) -> float:
 # (M, layout), for the kernels that run all T iterations; the team is a 64 x 64 block on eight waves, of which a row counts one.
 LOOP_VALU_PER_WAVE_ITER = {(64, "large"): (374, 4096), (64, "team"): (93, 512)}
 
+# blocks that a wave holds where the iterations may end in increments
+BLOCKS_PER_WAVE = {"large": {8: 16, 16: 8, 32: 2}, "small": {16: 4, 32: 1}}
+
 
 def layout_of(M: int, fp32: bool, nblocks: int, iters: int) -> str:
     """The library's own choice for a single matrix and a fixed count of iterations, mirrored here to pick the row of the
@@ -293,20 +296,29 @@ def bench_matrix(args, name):
         # double some end in increments, a shorter iteration, so the kernel may run fewer than T iterations of its loop.  The rate at
         # which it iterates is taken from the early-exit kernel of the same tiling, which does not look for repetitions: with the
         # smallest tolerance a block runs until T, or until a check meets an iteration whose factors are all exactly 1.  Where
-        # increments may follow, the tolerance is the change at which they start: blocks end there and none of them is counted.
-        # The iterations it ran are counted.
+        # increments may follow, the tolerance is the change at which they start, and the weights are N(0, 1) ones of the workload's
+        # shape, of which hardly a wave gets there before T.  A wave runs until the last of its blocks has ended, and without a column
+        # scale neighbours in a block row share one.  The iterations it ran are counted.
         layout = layout_of(w.M, fp32, nblocks, w.iters)
         may_stop = w.iters > 0 and layout != "team" and (fp32 or w.M < 64)
-        increments = not fp32 and (layout, w.M) in (("large", 8), ("large", 16), ("large", 32), ("small", 16), ("small", 32))
+        increments = not fp32 and w.M in BLOCKS_PER_WAVE.get(layout, {})
         rate_tol = 2.0 ** -30 if increments else 1e-300
         every_ms, mean_iters = dyk_ms, float(w.iters)
         if may_stop:
             ran = torch.zeros(nblocks, dtype=torch.int32, device=dev)
             tiles = binding.TSENOR_FLAG_TILES_LARGE if layout == "large" else binding.TSENOR_FLAG_TILES_SMALL
-            every = binding.make_problem(W, w.N, w.M, w.tau, w.iters, mask=torch.empty_like(mask), col_scale=cs, tau_mode=w.tau_mode,
-                                         flags=(fp32_flag if fp32 else 0) | tiles, tol=rate_tol, iters_done_out=ran)
+            rate_W, rate_cs = W, cs
+            if increments:
+                of_seed = torch.Generator(device=dev).manual_seed(w.seed)
+                rate_W, rate_cs = torch.randn(W.shape, device=dev, generator=of_seed).to(W.dtype), None
+            every = binding.make_problem(rate_W, w.N, w.M, w.tau, w.iters, mask=torch.empty_like(mask), col_scale=rate_cs,
+                                         tau_mode=w.tau_mode, flags=(fp32_flag if fp32 else 0) | tiles, tol=rate_tol, iters_done_out=ran)
+            binding.tsenor_mask_ex_profile(every, work, steps)  # (settles the clock)
             every_ms = binding.tsenor_mask_ex_profile(every, work, max(3, steps // 2))[1]
-            mean_iters = float(ran.double().mean())
+            of_wave = BLOCKS_PER_WAVE[layout][w.M] if increments else 1
+            padded = torch.nn.functional.pad(ran, (0, -nblocks % of_wave))
+            mean_iters = float(padded.view(-1, of_wave).amax(1).double().mean())
+            del rate_W
         every_entry_iters = float(weights) * mean_iters
         ops = useful_ops_per_entry_iter(w.M, fp32)
         achieved = ops * every_entry_iters / (every_ms * 1e-3) / 1e12
@@ -323,8 +335,8 @@ def bench_matrix(args, name):
             "note": ("bound by vector-ALU issue, not memory. achieved = useful vector operations (a multiply-add is "
                      "one) x rows x cols x mean_iterations_of_that / kernel_ms_every_iteration, both of the kernel named in "
                      "rate_of: where the kernel stops waves whose state repeats itself bit for bit, or ends in increments, that "
-                     "is the early-exit kernel of the same tiling at rate_tol, which does neither (a block that has ended while "
-                     "another of its wave goes on is not counted); kernel_ms, from HIP events at "
+                     "is the early-exit kernel of the same tiling at rate_tol, which does neither (where increments may follow, on "
+                     "N(0, 1) weights of this shape, which hardly get there); kernel_ms, from HIP events at "
                      f"the stage boundaries of {steps} back-to-back passes, is the time of the calls measured; peak = "
                      + ("the rate measured on this chip for plain (unpacked) fp32 multiplies and adds; the published "
                         "157.3 TFLOP/s (78.6 T multiply-adds/s) needs the packed instructions, which are not used"
@@ -485,8 +497,8 @@ def main() -> int:
     ap.add_argument("--precision", choices=("fp32", "fp64"), default="fp32",
                     help="arithmetic of the Dykstra iterations in the headline figure: fp32 (the precision the method "
                          "is run at, TSENOR_FLAG_FP32_ITERATIONS; checked to plan 1e-4 / 99.9 %% of blocks / 1e-5 "
-                         "retained importance against the fp64 oracle) or fp64 (the library's default: masks equal "
-                         "to the oracle's by construction).  The other one is reported beside it")
+                         "retained importance against the fp64 oracle) or fp64 (the library's default: the "
+                         "oracle's masks but for blocks with tied plan entries).  The other one is reported beside it")
     ap.add_argument("--no-other-modes", "--no-fp32-mode", dest="no_other_modes", action="store_true",
                     help="skip the secondary timings of the optional modes (for profiling runs)")
     ap.add_argument("--calibrate-copy", action="store_true",

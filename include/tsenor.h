@@ -34,7 +34,7 @@
  *     time in single precision before.  The plan is the one after `iters` iterations
  *     all the same, and nearer to an 80-bit evaluation of them than if all of them ran
  *     in double, whose factors carry 2^-48 (8 to 32 wide, K up to 100, 100 to 30 000
- *     iterations: 0.16 to 1.01 of that error).  This begins for all blocks of a wave at
+ *     iterations: 0.09 to 1.01 of that error, 0.34 on average).  This begins for all blocks of a wave at
  *     once, so the last bits of a block's plan may depend on the blocks beside it.
  */
 #ifndef TSENOR_H
@@ -169,7 +169,9 @@ typedef struct tsenor_problem {
                              (N / row sum, N / column sum) was within tol of 1.  Changes the result by O(tol).
                              With TSENOR_FLAG_FP32_ITERATIONS the factors after the fourth iteration are
                              single-precision numbers: a tol below ~1e-6 is then only met by
-                             factors that are exactly 1 */
+                             factors that are exactly 1.  In double they carry up to 2^-48 (4e-15): a smaller tol may
+                             be met later than in exact arithmetic, or not at all, and one below 2^-53 only by factors
+                             that are exactly 1 */
   int32_t* iters_done_out; /* device, optional, one int per block (block-row major): iterations that block ran */
 } tsenor_problem;
 

@@ -50,7 +50,7 @@ constexpr int kChunk = 8;                 // FAST: iterations between looks for 
 constexpr int kRepeatWindow = 24;         // iterations over which a repetition is looked for (RepeatCheck); in double also between looks
 constexpr int kRaiseBits = 512;           // kKeep: what goes from a large row scaling into its row of the tile (raise_rows)
 constexpr double kRaiseAbove = 0x1p+400;
-constexpr double kSmallStep = 0x1p-30;    // near_the_end(): factors of an iteration within this of 1 ...
+constexpr double kSmallStep = 0x1p-30;    // increments: factors of an iteration within this of 1 ...
 constexpr double kNearCap = 0x1p-20;      // ... no entry of the plan as near to the cap as this ...
 constexpr float kIncrementSum = 0x1p-25f; // ... and the sum of the increments before the plan is formed anew
 constexpr float kNothingLeft = 0x1p-54f;  // ... and what is left of the iterations when they are as good as done
@@ -216,8 +216,9 @@ __device__ __forceinline__ int column_lane(int gx, int q) {
   return turned && (q & 4) ? gx ^ 3 : gx;
 }
 
-// Whether the last iterations of a wave are done in increments (near_the_end): where a launch may take two layouts of a block whose
-// waves hold other numbers of blocks (order_run) the results would differ.  4 x 4 blocks have 64 or 16 to a wave, too many to converge together; on the 8-wide small tiles it gained nothing (the look 1 %).
+// Whether the last iterations of a wave are done in increments (iterate_increments).  Where a launch may take two layouts of a block
+// whose waves hold other numbers of blocks (order_run) the results would differ.  4 x 4 blocks have 64 or 16 to a wave, too many to
+// converge together; on the 8-wide small tiles it gained nothing (the look 1 %).
 template <int M, int TILES>
 constexpr bool increments_at_the_end() {
   return (TILES == kLargeTiles && (M == 8 || M == 16 || M == 32)) || (TILES == kSmallTiles && M >= 16);
@@ -225,7 +226,8 @@ constexpr bool increments_at_the_end() {
 
 // whether any step along a lane-column swaps registers, so that a lane's first ones need not be of the columns it owns
 template <class T, int S = 0>
-constexpr bool kSwaps = S < T::NY && (T::YM[S < T::NY ? S : 0] == 32 || (T::SWAPS && T::YM[S < T::NY ? S : 0] == 16) || (S + 1 < T::NY && kSwaps<T, (S + 1 < T::NY ? S + 1 : S)>));
+constexpr bool kSwaps = S < T::NY && (T::YM[S < T::NY ? S : 0] == 32 || (T::SWAPS && T::YM[S < T::NY ? S : 0] == 16) ||
+                                      (S + 1 < T::NY && kSwaps<T, (S + 1 < T::NY ? S + 1 : S)>));
 
 // registers a lane owns after a reduce-scatter of `count` values over 2^steps lanes (at least one)
 constexpr int owned(int count, int steps) { return (count >> steps) > 0 ? (count >> steps) : 1; }
@@ -446,7 +448,7 @@ __device__ __forceinline__ void chain_phase(bool on) {
 // ADAPT (early exit): `frozen` lanes apply factors of exactly 1 (their block has stopped; its state no longer
 // changes), and the largest |factor - 1| among the rows and columns this lane owns is returned.
 // RUN: order_run() of the tiling.  LONE: no other wave shares the SIMD (chain_phase).
-// REFINED: factors without the 2^-48 of fast_div (near_the_end).
+// REFINED: factors without the 2^-48 of fast_div (iterate_increments).
 struct NoTile {};
 // a count that is the same in all lanes, where the compiler cannot tell (in a vector register it costs the loop an instruction or two)
 __device__ __forceinline__ int of_wave(int n) { return __builtin_amdgcn_readfirstlane(n); }
@@ -650,11 +652,11 @@ __device__ __forceinline__ double dykstra_iteration(double (&kap)[TH][TW], Tile&
 // is in all of them: a factor of fast_div carries 2^-48, which 1 / (1 - lambda) iterations of a slow block take up where fresh errors of
 // as many iterations in double would partly cancel.  So that one has factors of 2^-52 (`refined`).
 // When the iterations that are left, were each to change the plan by as much as the last one did, add up to less than kNothingLeft, all
-// are done.  None changes it by more: a half iteration minimises a convex function (the dual of the projection problem) over the row,
-// the column or the cap's potentials, so that on a fixed side of the cap changes of the potentials go through the three orthogonal
-// projections of Gauss-Seidel in the norm of its second derivative, which at the end of an iteration is that of the plan,
-// E^2 = sum p_ij (rho_i + gamma_j)^2 over the entries below the cap.  E does not grow (random plans and changes: ratios up to 0.9998), and
-// an entry changes by sqrt(p_ij) E at most.  E <= M times the largest sqrt(p_ij) |rho_i + gamma_j|, and sqrt(N M) times the largest
+// are done.  That the changes do not grow: each third of an iteration minimises a convex function (the dual of the projection problem)
+// over the row, the column or the cap's potentials, so that on a fixed side of the cap changes of the potentials go through the three
+// orthogonal projections of Gauss-Seidel in the norm of its second derivative, which at the end of an iteration is that of the plan,
+// E^2 = sum p_ij (rho_i + gamma_j)^2 over the entries below the cap.  E does not grow (random plans and changes: ratios up to 0.9998),
+// and an entry changes by sqrt(p_ij) E at most.  E <= M times the largest sqrt(p_ij) |rho_i + gamma_j|, and sqrt(N M) times the largest
 // |rho_i + gamma_j|: 2^-49 in the plan where M = 32 at the very most.  An entry above the cap does not count in E and may move on while
 // the plan stands still (a block of two parts that entries near 2^-36 connect: 2^-39 per iteration): it must not get to the cap.
 // 96 plain fp32 instructions per lane of a 32 x 32 block for the 120 of an iteration in double, and exchanges of one instruction
@@ -662,9 +664,9 @@ __device__ __forceinline__ double dykstra_iteration(double (&kap)[TH][TW], Tile&
 // bf16 Wanda-style, T = 300, 2792 / 2515; 8:16 3280x12832 Wanda-style tau = 0.02 2199 / 1276; 4:8 4096x4096 student-t 537 / 326; 8:16
 // 1072x2928 with its plan, small tiles, 198 / 178; 16:32 1600x1920 student-t, T = 500, small tiles, 176 / 117; normal weights, which never
 // come so near, 842 / 841 (8:16), 2535 / 2548 (4:8) and 143 / 145 (16:32 1088x1472, small tiles).
-// Error of the plan (2-norm) against 80-bit iterations, relative to that of iterations in double to the end (8, 16 and 32 wide on either
-// tiling, K up to 10, 40 and 100, T = 100 to 500, three distributions): 0.43, at most 1.01, where no increment came; T = 30 000 on 8 x 8
-// normal blocks 0.16.  (With sums in fp32 and factors of fast_div before them 0.98 and, T = 30 000, 6.5.)
+// Error of the plan (2-norm) against 80-bit iterations, relative to that of iterations in double to the end (8, 16 and 32 wide on the
+// tilings that do this, K up to 10, 40 and 100, T = 100 to 500, three distributions): 0.34 on average and at most 1.01, where no increment
+// came; T = 30 000 on 8 x 8 normal blocks 0.16.  (With sums in fp32 and factors of fast_div before them 0.97 and, T = 30 000, 6.5.)
 // The first condition: no scaling of a wave has moved by more than that from what it was, U_before and V_before.
 template <int OWN_R, int OWN_C, int NU>
 __device__ __forceinline__ bool hardly_moves(const double (&U)[NU], const double (&Vown)[OWN_C], const double (&U_before)[OWN_R],
@@ -700,8 +702,8 @@ __device__ __forceinline__ bool away_from_cap(const double (&kap)[TH][TW], const
 template <class T, Form FORM, bool LDS, bool ADAPT, int LPB, bool LONE, class Tile, class Freeze, int TH, int TW, int NU>
 __device__ __forceinline__ int iterate_increments(double (&kap)[TH][TW], Tile& x, double (&U)[NU], double (&V)[TW],
                                                   double (&Vown)[owned(TW, T::NY)], const double (&U_before)[owned(TH, T::NX)],
-                                                  const double (&V_before)[owned(TW, T::NY)], int N, int t, int iters, double tol, float2* xr,
-                                                  int rx, const bool& frozen, Freeze& freeze_if) {
+                                                  const double (&V_before)[owned(TW, T::NY)], int N, int t, int iters, double tol,
+                                                  float2* xr, int rx, const bool& frozen, Freeze& freeze_if) {
   constexpr int OWN_R = owned(TH, T::NX), OWN_C = owned(TW, T::NY);
   static_assert(FORM != kRecompute, "the increments take the registers of the capped entries");
   // the plan and the entries at the cap, over N
@@ -994,7 +996,7 @@ __device__ __forceinline__ float dykstra_iteration_f32(const float (&kap)[TH][TW
 // with fp32 iterations 57 % end in one of period 2, 14 % of 1, 4, 6 or 8, hardly any in a period that does not divide 24.  So
 // the fp32 loops compare the state every kChunk iterations with one 8, 16 or 24 iterations old, the double ones every kRepeatWindow
 // iterations with the one before those.  The large tiles that fold (32 x 32 and 64 x 64 in double), the team and the kernels of the
-// early exit do not look.  (In double the increments of near_the_end() usually come first where there are any.)
+// early exit do not look.  (In double the increments usually come first where there are any.)
 // IN_LDS: that state is kept in LDS (`space`), for the kernels whose register budget is that of their loop; small launches, where a
 // wave has its SIMD to itself and waits for every LDS access, keep it in registers.
 template <class real, int OWN_R, int OWN_C, bool IN_LDS>
@@ -1069,16 +1071,19 @@ struct DykstraLaunch {
   // The 64-wide fp32 waves, one block each, leave when their block repeats itself: two to a workgroup (8192x28672 student, T =
   // 500: 2.91 ms, one 2.94, four 3.25; 4096x4096 normal, which does not repeat, T = 300: 563 us, 610, 581).  In a launch of one
   // wave per SIMD four, which go to the four of a CU (2048x2048 normal, T = 300: 285 us, two 302).
-  // The iterations in double of 8-, 16- and 32-wide blocks end at different times too (near_the_end): one (16:32 4096x14336
+  // The iterations in double of 8-, 16- and 32-wide blocks end at different times too (increments): one (16:32 4096x14336
   // Wanda-style 2515 us, two 2534, four 2578; normal weights the same within 0.3 %).
   // The small tiles carry the rounding behind the iterations, whose steps synchronise one wave at a time.
-  static constexpr int kWavesPerGroup = (ADAPT || TILES != kLargeTiles) ? 1 : M == 64 && FAST && !LONE ? 2 : FAST || M == 4 || M == 64 ? 4 : 1;
+  static constexpr int kWavesPerGroup = (ADAPT || TILES != kLargeTiles) ? 1
+                                        : M == 64 && FAST && !LONE      ? 2
+                                        : FAST || M == 4 || M == 64     ? 4
+                                                                        : 1;
   static constexpr int kThreads = kWavesPerGroup * kWave;
   // Waves per SIMD the register budget is set for.  Double: the loop holds twice the state of the fp32 one, two waves of up
   // to 256 registers; the 8-wide large tiles and the 16-wide small ones three of 168, no spills (with four of 128 the increments spill 14
   // and 19 outside the loops; four / three, us: 4:8 4096x4096 with all outputs 995 / 981, student-t 1536x2048 86.4 / 85.3, 8:16 2048x1024
-  // T = 500 normal 200.4 / 196.5, student-t 111.2 / 108.9, 1792x1792 student-t 73.5 / 74.1).  With the early exit the 16-wide ones four: launches
-  // of just under four waves per SIMD run at once (3936x1056 normal 245 / 270; 17 registers spill).
+  // T = 500 normal 200.4 / 196.5, student-t 111.2 / 108.9, 1792x1792 student-t 73.5 / 74.1).  With the early exit the 16-wide ones
+  // four: launches of just under four waves per SIMD run at once (3936x1056 normal 245 / 270; 17 registers spill).
   // FAST: the more waves, the nearer the issue of plain fp32 instructions comes to its limit (1.13 ns
   // per instruction and SIMD with two waves, 1.05 with four).  M = 32: four waves of 128 registers, the loop fits and 38
   // registers of the double-precision code around it spill (whole calls with four / three waves, us: 4096x14336 Wanda-style 1364 /
@@ -1104,8 +1109,8 @@ struct DykstraLaunch {
 // across the lanes and the scan of its result, 106 with round_blocks.)
 // LONE: for a launch that gives a SIMD no second wave.
 template <int M, bool FAST, bool ZERO_T = false, int TILES = kLargeTiles, bool ADAPT = false, bool LONE = false>
-__global__ __launch_bounds__((DykstraLaunch<M, FAST, ADAPT, TILES, LONE>::kThreads), (DykstraLaunch<M, FAST, ADAPT, TILES, LONE>::kWavesPerSimd)) void dykstra_sort_kernel(
-    Batch batch) {
+__global__ __launch_bounds__((DykstraLaunch<M, FAST, ADAPT, TILES, LONE>::kThreads),
+                             (DykstraLaunch<M, FAST, ADAPT, TILES, LONE>::kWavesPerSimd)) void dykstra_sort_kernel(Batch batch) {
   using T = std::conditional_t<LONE && TILES != kLargeTiles, LoneTiling<Tiling<M, TILES>>, Tiling<M, TILES>>;
   constexpr bool SMALL = TILES != kLargeTiles;
   const int which = find_problem(batch, blockIdx.x);
@@ -1317,7 +1322,8 @@ __global__ __launch_bounds__((DykstraLaunch<M, FAST, ADAPT, TILES, LONE>::kThrea
         constexpr bool kEnd = increments_at_the_end<M, TILES>();
         // Behind a window of iterations over which a scaling of every lane has hardly changed (`first`: what it was before them): one
         // more iteration, with refined factors, and the rest in increments if that may be.  Whether any was done in increments.
-        [[maybe_unused]] const auto try_the_end = [&]([[maybe_unused]] int& t, [[maybe_unused]] double first, [[maybe_unused]] auto&& one_more) {
+        [[maybe_unused]] const auto try_the_end = [&]([[maybe_unused]] int& t, [[maybe_unused]] double first,
+                                                      [[maybe_unused]] auto&& one_more) {
           if constexpr (kEnd) {
             if (t + 1 >= p.T || __any(!(fabs(Uown[0] - first) <= kRepeatWindow * kSmallStep * first))) return false;
             if (!away_from_cap<kForm>(kap, x, V)) return false;

@@ -41,8 +41,9 @@ def _plan(W, N, M, tau, T, flags, tol=0.0):
     from paper_2505_23949_amd import binding as b
 
     k = _copies(W, M, flags)
-    got = b.solve(torch.from_numpy(np.tile(W, (k, k))).to("cuda:0"), N, M, tau, T, tau_mode=b.TSENOR_TAU_REL_MATRIX_MAX, flags=flags, tol=tol,
-                  want_plan=True, want_iters_done=tol > 0.0)
+    W_all = torch.from_numpy(np.tile(W, (k, k))).to("cuda:0")
+    got = b.solve(W_all, N, M, tau, T, tau_mode=b.TSENOR_TAU_REL_MATRIX_MAX, flags=flags, tol=tol, want_plan=True,
+                  want_iters_done=tol > 0.0)
     torch.cuda.synchronize()
 
     def split(x, rows, cols):

@@ -75,8 +75,10 @@ def test_blocks_by_column_scale(M, br, bc, tiles, kind):
         # increments begin, in fp32 where the tile of a wave is formed anew.
         fp32 = "fp32" in tiles
         differing = (got["mask"] != ref["mask"]).view(br, M, bc, M).any(3).any(1).sum().item()
-        assert (got["plan"] - ref["plan"]).abs().max().item() < (1e-4 if fp32 else 1e-11)
-        assert (got["mask"] != ref["mask"]).float().mean().item() < (1.2e-4 if fp32 else 2e-5)
+        # (measured: plans within 1.1e-14 and 9e-7, every mask the same)
+        apart = (got["plan"] - ref["plan"]).abs().max().item()
+        assert apart < (1e-4 if fp32 else 1e-13)
+        assert (got["mask"] != ref["mask"]).float().mean().item() <= (1.2e-4 if fp32 else 0.0)
         assert (got["stats"] - ref["stats"]).abs().max().item() <= M * differing
         mask = got["mask"].cpu().numpy()
         assert exact.is_transposable_nm(mask, N, M)
@@ -91,7 +93,7 @@ def test_blocks_by_column_scale(M, br, bc, tiles, kind):
             assert np.abs(got["plan"][rows_of].cpu().numpy() - np.exp(of["log_S"])).max() < (1e-4 if fp32 else 1e-9)
             d, n = _differ(mask[rows_of], of, M)
             differ, compared = differ + d, compared + n
-        print(f"blocks of another mask: {differing} in the two orders, {differ} of {compared} by the oracle", flush=True)
+        print(f"plans {apart:.1e} apart, blocks of another mask: {differing} in the two orders, {differ} of {compared} by the oracle", flush=True)
         assert differ <= (0.01 * compared if fp32 else 0)
 
 

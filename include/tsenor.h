@@ -34,7 +34,7 @@
  *     time in single precision before.  The plan is the one after `iters` iterations
  *     all the same, and nearer to an 80-bit evaluation of them than if all of them ran
  *     in double, whose factors carry 2^-48 (8 to 32 wide, K up to 100, 100 to 30 000
- *     iterations: 0.09 to 1.01 of that error, 0.34 on average).  This begins for all blocks of a wave at
+ *     iterations: 0.09 to 1.06 of that error, 0.34 on average).  This begins for all blocks of a wave at
  *     once, so the last bits of a block's plan may depend on the blocks beside it.
  */
 #ifndef TSENOR_H

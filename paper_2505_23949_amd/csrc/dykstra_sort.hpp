@@ -665,8 +665,8 @@ __device__ __forceinline__ double dykstra_iteration(double (&kap)[TH][TW], Tile&
 // 1072x2928 with its plan, small tiles, 198 / 178; 16:32 1600x1920 student-t, T = 500, small tiles, 176 / 117; normal weights, which never
 // come so near, 842 / 841 (8:16), 2535 / 2548 (4:8) and 143 / 145 (16:32 1088x1472, small tiles).
 // Error of the plan (2-norm) against 80-bit iterations, relative to that of iterations in double to the end (8, 16 and 32 wide on the
-// tilings that do this, K up to 10, 40 and 100, T = 100 to 500, three distributions): 0.34 on average and at most 1.01, where no increment
-// came; T = 30 000 on 8 x 8 normal blocks 0.16.  (With sums in fp32 and factors of fast_div before them 0.97 and, T = 30 000, 6.5.)
+// tilings that do this, K up to 10, 40 and 100, T = 100 to 500, three distributions): 0.34 on average and at most 1.06, where no increment
+// came or the rounding of the entries' logarithms is what there is, 5e-16; T = 30 000 on 8 x 8 normal blocks 0.16.  (With sums in fp32 and factors of fast_div before them 0.97 and, T = 30 000, 6.5.)
 // The first condition: no scaling of a wave has moved by more than that from what it was, U_before and V_before.
 template <int OWN_R, int OWN_C, int NU>
 __device__ __forceinline__ bool hardly_moves(const double (&U)[NU], const double (&Vown)[OWN_C], const double (&U_before)[OWN_R],
